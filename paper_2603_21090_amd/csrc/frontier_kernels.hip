@@ -257,57 +257,101 @@ __global__ __launch_bounds__(256) void compact_write_kernel(Dev d) {
 // the rows whose own input row changed in the batch (flag at most thr_in) come first, grouped the same way,
 // then the others, and every tile of the window is marked: 1 when none of its rows changed.  A row's result
 // does not depend on which rows share its tile, so only the cost changes.  grid.y = list.
+//
+// A window is one workgroup (25 of them for 100,000 rows): bound by the latency of its chain, not by bytes.  A thread owns
+// sixteen consecutive positions.  The counts of four bins travel in one 64-bit word (a window's largest count
+// takes 13 of a field's 16 bits); a wave scans all groups of four at once, and one exchange of the wave totals
+// gives every thread its starting offsets: three barriers in all, where a scan of its own per bin took two barriers
+// per bin and the histogram an LDS atomic per row.
 constexpr uint32_t kBucketWindow = 4096;
 constexpr uint32_t kMaxBins = 2 * 65;                        // entry counts 0 .. k, k <= 64; changed | unchanged input
+constexpr uint32_t kMaxBinGroups = (kMaxBins + 3) / 4;
 struct BucketJob { const uint32_t* in; const uint32_t* count; uint32_t* out; uint32_t count_max; uint8_t* tile_clean; uint32_t thr_in; };
 struct BucketJobs { BucketJob j[STGN_MAX_LAYERS]; };
+// NG: groups of four bins the variant has registers for
+template <uint32_t NG>
 __global__ __launch_bounds__(256) void bucket_rows_kernel(Dev d, BucketJobs jobs) {
-  __shared__ uint32_t s[4];
-  __shared__ uint32_t s_hist[kMaxBins], s_base[kMaxBins];
+  __shared__ uint16_t s_tot[4][4 * NG];                      // per wave: rows of each bin; then the first place of its rows
   __shared__ uint32_t s_changed[kBucketWindow / 16];
   const BucketJob job = jobs.j[blockIdx.y];
   uint32_t n = job.count_max;
   if (job.count) { const uint32_t c = *job.count; n = c < n ? c : n; }
   const uint32_t w0 = blockIdx.x * kBucketWindow;
   if (w0 >= n) return;
-  const uint32_t t = threadIdx.x, p0 = w0 + t * 16u;
+  const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6, p0 = w0 + t * 16u;
   const uint32_t nbk = d.k + 1u, nb = job.tile_clean ? 2u * nbk : nbk;
-  if (t < nb) s_hist[t] = 0u;
+  const uint32_t ng = (nb + 3u) >> 2;                        // <= NG
   s_changed[t] = 0u;
-  __syncthreads();
+  // (loads are unconditional, positions past the end repeat the last row: sixteen requests leave together)
   uint32_t id[16], bin[16];
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
-    const uint32_t p = p0 + i;
-    id[i] = p < n ? (job.in ? job.in[p] : p) : 0xFFFFFFFFu;
-    uint32_t b = 0xFFFFu;                                    // no row
-    if (p < n) {
-      const uint32_t dg = d.deg[id[i]];
-      b = d.k - (dg < d.k ? dg : d.k);                       // bin 0 = full rings: longest rows first
-      if (job.tile_clean && d.flags_kept[id[i]] > job.thr_in) b += nbk;
-    }
-    bin[i] = b;
-    if (b != 0xFFFFu) atomicAdd(&s_hist[b], 1u);
+    const uint32_t p = p0 + i < n ? p0 + i : n - 1u;
+    id[i] = job.in ? job.in[p] : p;
   }
-  __syncthreads();
-  if (t == 0) {
-    uint32_t run = 0;
-    for (uint32_t b = 0; b < nb; ++b) { s_base[b] = run; run += s_hist[b]; }
-  }
-  __syncthreads();
-  for (uint32_t b = 0; b < nb; ++b) {
-    if (s_hist[b] == 0u) continue;                           // the same for every thread
-    uint32_t mine = 0;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) mine += bin[i] == b ? 1u : 0u;
-    uint32_t excl;
-    block_scan_256(mine, s, &excl);
-    uint32_t o = w0 + s_base[b] + excl;
+  for (int i = 0; i < 16; ++i) {
+    const uint32_t dg = d.deg[id[i]];
+    bin[i] = d.k - (dg < d.k ? dg : d.k);                    // bin 0 = full rings: longest rows first
+  }
+  if (job.tile_clean) {                                      // uniform
+#pragma unroll
+    for (int i = 0; i < 16; ++i) bin[i] += d.flags_kept[id[i]] > job.thr_in ? nbk : 0u;
+  }
+#pragma unroll
+  for (int i = 0; i < 16; ++i) bin[i] = p0 + i < n ? bin[i] : 0xFFFFu;   // no row
+  // rows of each bin in front of this thread's within the wave
+  uint64_t at[NG];
+#pragma unroll
+  for (uint32_t g = 0; g < NG; ++g) {
+    at[g] = 0;
+    if (g >= ng) continue;                                   // uniform
+    uint64_t mine = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) mine += (bin[i] >> 2) == g ? 1ull << (16u * (bin[i] & 3u)) : 0ull;
+    uint64_t incl = mine;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint64_t o = __shfl_up(incl, off);
+      if (lane >= (uint32_t)off) incl += o;
+    }
+    if (lane == 63u)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) s_tot[wave][4u * g + q] = (uint16_t)(incl >> (16 * q));
+    at[g] = incl - mine;
+  }
+  __syncthreads();
+  // first place of every (bin, wave) in the window: bins in order, waves in order inside a bin
+  if (wave == 0) {
+    uint32_t run = 0;
+    for (uint32_t b0 = 0; b0 < nb; b0 += 64u) {              // uniform
+      const uint32_t b = b0 + lane;
+      uint32_t c[4] = {0u, 0u, 0u, 0u};
+      if (b < nb)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) c[w] = s_tot[w][b];
+      const uint32_t all = c[0] + c[1] + c[2] + c[3], incl = wave_incl_scan(all);
+      uint32_t o = run + incl - all;
+      if (b < nb)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) { s_tot[w][b] = (uint16_t)o; o += c[w]; }
+      run += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (uint32_t g = 0; g < NG; ++g) {
+    if (g >= ng) continue;
+    uint64_t cur = at[g];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) cur += (uint64_t)s_tot[wave][4u * g + q] << (16 * q);
 #pragma unroll
     for (int i = 0; i < 16; ++i)
-      if (bin[i] == b) {
-        if (b < nbk) s_changed[(o - w0) >> 4] = 1u;          // (every writer stores the same value)
-        job.out[o++] = id[i];
+      if ((bin[i] >> 2) == g) {
+        const uint32_t sh = 16u * (bin[i] & 3u), o = (uint32_t)(cur >> sh) & 0xFFFFu;
+        cur += 1ull << sh;
+        if (bin[i] < nbk) s_changed[o >> 4] = 1u;            // (every writer stores the same value)
+        job.out[w0 + o] = id[i];
       }
   }
   if (job.tile_clean) {
@@ -358,7 +402,11 @@ void launch_bucket_rows(const Dev& d, hipStream_t s, bool all_rows) {
     }
   }
   const uint32_t blocks = (d.N + kBucketWindow - 1) / kBucketWindow;
-  hipLaunchKernelGGL(bucket_rows_kernel, dim3(blocks, nj), dim3(256), 0, s, d, jobs);
+  // registers for the usual list lengths (k up to 10 / 20 with the query cache's two halves), and for any
+  const uint32_t groups = (2u * (d.k + 1u) + 3u) / 4u;
+  if (groups <= 6u) hipLaunchKernelGGL(bucket_rows_kernel<6>, dim3(blocks, nj), dim3(256), 0, s, d, jobs);
+  else if (groups <= 11u) hipLaunchKernelGGL(bucket_rows_kernel<11>, dim3(blocks, nj), dim3(256), 0, s, d, jobs);
+  else hipLaunchKernelGGL(bucket_rows_kernel<kMaxBinGroups>, dim3(blocks, nj), dim3(256), 0, s, d, jobs);
 }
 
 bool compact_in_one(const Dev& d) { return (d.N + kFlagsPerBlock - 1) / kFlagsPerBlock <= kSmallBlocks; }

@@ -37,3 +37,26 @@ def test_rows_in_every_piece_width(d_emb):
             assert torch.equal(got.nan_to_num(nan=-3.0), want.nan_to_num(nan=-3.0)), (n, shift)
             assert bool((buf[:shift] == 7.0).all()) and bool((buf[shift + n * d_emb:] == 7.0).all()), (n, shift)
     g.close()
+
+
+@pytest.mark.parametrize("k", [1, 10, 11, 20, 21, 64])
+@pytest.mark.parametrize("d_mem", [0, 16])
+def test_regrouped_rows_equal_a_rebuild(k, d_mem):
+    """Row lists regrouped by entry count, at the list lengths on both sides of each variant of the regrouping kernel and with
+    a last window of a few rows: an incremental row is the row a rebuild computes, byte for byte, so a row dropped,
+    doubled or marked as unchanged by mistake shows."""
+    import torch
+    from paper_2603_21090_amd import binding
+    w = tiny_workload(num_nodes=36_869, num_edges=24_000, batch=2_000, k=k, d_mem=d_mem, d_node=0 if d_mem else 16, zipf_s=0.9)
+    nf = None if d_mem else np.random.default_rng(k).standard_normal((w.num_nodes, 16), dtype=np.float32)
+    g = binding.StreamTGN.from_workload(w, synth.make_weights(w), nf)
+    st = synth.EdgeStream(w)
+    ids = torch.arange(w.num_nodes, dtype=torch.int32, device="cuda")
+    for b in range(w.num_batches):
+        g.ingest_batch(*st.batch(b))
+        if b % 4 == 3:
+            rows = [g.get_embeddings(ids, layer=l) for l in range(1, w.layers + 1)]
+            g.full_rebuild()
+            for l, r in enumerate(rows):
+                assert torch.equal(r, g.get_embeddings(ids, layer=l + 1)), (b, l + 1)
+    g.close()
