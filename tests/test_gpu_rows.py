@@ -60,3 +60,32 @@ def test_regrouped_rows_equal_a_rebuild(k, d_mem):
             for l, r in enumerate(rows):
                 assert torch.equal(r, g.get_embeddings(ids, layer=l + 1)), (b, l + 1)
     g.close()
+
+
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 31, 32, 33, 41, 130])
+@pytest.mark.parametrize("aggregator", [1, 2])
+def test_aggregated_messages_of_a_hub(n, aggregator):
+    """Mean and Sum over n slots of one node in one batch, around the slots looked up ahead (32) and requested together (8),
+    against the oracle (the embedding bar of 1e-4 per row)."""
+    from oracle import oracle as orc
+    from paper_2603_21090_amd import binding
+    w = tiny_workload(num_nodes=300, num_edges=600, batch=150, aggregator=aggregator)
+    W = synth.make_weights(w)
+    o, g = orc.Oracle.from_workload(w, W), binding.StreamTGN.from_workload(w, W)
+    gen = np.random.default_rng(n)
+    hub = 17
+    for b in range(3):
+        other = gen.permutation(np.delete(np.arange(w.num_nodes), hub))[:n].astype(np.uint32)
+        side = gen.random(n) < 0.5
+        src, dst = np.where(side, hub, other).astype(np.uint32), np.where(side, other, hub).astype(np.uint32)
+        ts = 10.0 * b + np.sort(gen.random(n))
+        ef = gen.standard_normal((n, w.d_edge), dtype=np.float32)
+        assert o.ingest(src, dst, ts, ef)[0] == 0
+        g.ingest_batch(src, dst, ts, ef)
+        ref = o.embed_all()
+        ids = np.arange(w.num_nodes, dtype=np.uint32)
+        for l in range(w.layers):
+            got = g.get_embeddings(ids, layer=l + 1)
+            err = np.linalg.norm(got - ref[l], axis=1) / (np.linalg.norm(ref[l], axis=1) + 1e-30)
+            assert err.max() <= 1e-4, (b, l, err.max())
+    g.close()
