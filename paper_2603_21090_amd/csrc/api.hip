@@ -18,29 +18,6 @@ const char* const kClassNames[KC_COUNT] = {"stage_sort", "memory_update", "apply
 
 std::string g_create_error;
 
-// Scratch of the entry point that allocates nothing (stgn_predict_batch_static): the root list, the
-// roots' query times and their final-layer rows live in this array instead of the caller's workspace.
-// Every device the library runs on holds its own copy at its own address; the name below is only a
-// host-side handle, the address kernels may use is looked up once per device (static_scratch()).
-constexpr size_t kStaticScratchBytes = STGN_STATIC_SCRATCH_BYTES;
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
-constexpr int kMaxDevices = 64;
-void* g_scratch_ptr[kMaxDevices] = {};
-
-// address of the current device's copy of `scratch`; resolved once per device, with that device current
-hipError_t static_scratch(int dev, void** out) {
-  if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-  if (!g_scratch_ptr[dev]) {
-    void* p = nullptr;
-    const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
-    if (e != hipSuccess) return e;
-    if (!p) return hipErrorInvalidSymbol;
-    g_scratch_ptr[dev] = p;
-  }
-  *out = g_scratch_ptr[dev];
-  return hipSuccess;
-}
-
 struct TimedLaunch { int cls; hipEvent_t a, b; };
 
 }  // namespace
@@ -67,7 +44,6 @@ struct stgn_ctx {
   int last_par = 0;                 // state set of the batch enqueued last
   bool idle = true;                 // nothing was enqueued since the library last synchronised `stream`
   bool have_predictor = false;      // stgn_set_predictor was called
-  unsigned char* static_scratch = nullptr;   // this device's copy of the static scratch array
   std::string err;
   uint64_t host_edges = 0;          // upper bound of edges enqueued so far
   bool host_t_known = true;         // host knows the last ingested timestamp
@@ -275,9 +251,6 @@ size_t layout(const stgn_config& c, char* base, Dev* d) {
   d->dseen = c.delta_mode ? b.take<uint8_t>(N) : nullptr;
   d->dlist = c.delta_mode ? b.take<uint32_t>(N) : nullptr;
   for (uint32_t l = 0; l < c.layers; ++l) d->L[l].d_in = l == 0 ? d->d0 : c.d_emb;
-  d->pred_rows = b.take<uint32_t>(B2);
-  d->pred_tq = b.take<double>(B2);
-  d->pred_out = b.take<float>((size_t)B2 * c.d_emb);
   d->pred_src = b.take<uint32_t>(c.max_batch);
   d->pred_dst = b.take<uint32_t>(c.max_batch);
   d->pred_ts = b.take<double>(c.max_batch);
@@ -557,14 +530,8 @@ int stgn_create(const stgn_config* cfg, const stgn_weights* w, const float* node
   if (strncmp(prop.gcnArchName, "gfx950", 6) != 0)
     return fail(nullptr, STGN_E_DEVICE, std::string("built for gfx950, current device is ") + prop.gcnArchName);
 
-  void* sscratch = nullptr;
-  {
-    const hipError_t e = static_scratch(dev, &sscratch);
-    if (e != hipSuccess) return fail(nullptr, STGN_E_DEVICE, std::string("static scratch lookup: ") + hipGetErrorString(e));
-  }
   stgn_ctx* ctx = new stgn_ctx();
   ctx->cfg = *cfg;
-  ctx->static_scratch = static_cast<unsigned char*>(sscratch);
   memset(&ctx->d, 0, sizeof(Dev));
   layout(*cfg, (char*)device_workspace, &ctx->d);
   ctx->stream = (hipStream_t)hip_stream;
@@ -902,11 +869,8 @@ int stgn_predict_batch(stgn_ctx* ctx, uint32_t n, const uint32_t* src, const uin
   ctx->idle = false;
   {
     Scope t(ctx, KC_PREDICT);
-    if (at_edge_time) {
-      launch_predict_prep(d, s, n, dsrc, ddst, dts);
-      launch_layer_roots(d, s, 2 * n);
-    }
-    launch_predict_head(d, s, n, dsrc, ddst, at_edge_time, dout);
+    if (at_edge_time) launch_layer_scores(d, s, n, dsrc, ddst, dts, dout);
+    else launch_predict_head(d, s, n, dsrc, ddst, dout);
   }
   HIPCHK(ctx, hipGetLastError());
   if (!inputs_on_device) {
@@ -916,7 +880,7 @@ int stgn_predict_batch(stgn_ctx* ctx, uint32_t n, const uint32_t* src, const uin
   return STGN_OK;
 }
 
-// Device bytes of static scratch a prediction of n edges needs: the 2n roots, their query times, their rows.
+// What the limit of stgn_predict_batch_static counts for n edges: 2n root ids, query times and rows.
 static size_t static_predict_bytes(uint32_t n, uint32_t d_emb) {
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   return up((size_t)2 * n * sizeof(uint32_t)) + up((size_t)2 * n * sizeof(double)) + up((size_t)2 * n * d_emb * sizeof(float));
@@ -928,29 +892,19 @@ int stgn_predict_batch_static(stgn_ctx* ctx, uint32_t n, const uint32_t* src, co
   const stgn_config& c = ctx->cfg;
   if (!ctx->have_predictor) return fail(ctx, STGN_E_INVALID_ARG, "stgn_set_predictor has not been called");
   if (n > c.max_batch) return fail(ctx, STGN_E_BATCH_TOO_LARGE, "more edges than max_batch");
-  if (static_predict_bytes(n, c.d_emb) > kStaticScratchBytes) {
+  if (static_predict_bytes(n, c.d_emb) > STGN_STATIC_SCRATCH_BYTES) {
     char buf[160];
     snprintf(buf, sizeof buf, "%u edges of %u-wide rows need %zu bytes of static scratch, the array holds %zu",
-             n, c.d_emb, static_predict_bytes(n, c.d_emb), kStaticScratchBytes);
+             n, c.d_emb, static_predict_bytes(n, c.d_emb), (size_t)STGN_STATIC_SCRATCH_BYTES);
     return fail(ctx, STGN_E_BATCH_TOO_LARGE, buf);
   }
   if (n == 0) return STGN_OK;
   if (!src || !dst || !ts || !scores) return fail(ctx, STGN_E_INVALID_ARG, "NULL array");
-  if (!ctx->static_scratch) return fail(ctx, STGN_E_DEVICE, "static scratch was not resolved for this device");
-  // the same kernels as stgn_predict_batch, their scratch lists pointed at the static array
-  Dev d = ctx->d;
-  auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-  unsigned char* p = ctx->static_scratch;
-  d.pred_rows = reinterpret_cast<uint32_t*>(p);
-  d.pred_tq = reinterpret_cast<double*>(p + up((size_t)2 * n * sizeof(uint32_t)));
-  d.pred_out = reinterpret_cast<float*>(p + up((size_t)2 * n * sizeof(uint32_t)) + up((size_t)2 * n * sizeof(double)));
+  // the same kernels as stgn_predict_batch, on the caller's own arrays
   hipStream_t s = ctx->stream;
   ctx->idle = false;
-  if (at_edge_time) {
-    launch_predict_prep(d, s, n, src, dst, ts);
-    launch_layer_roots(d, s, 2 * n);
-  }
-  launch_predict_head(d, s, n, src, dst, at_edge_time, scores);
+  if (at_edge_time) launch_layer_scores(ctx->d, s, n, src, dst, ts, scores);
+  else launch_predict_head(ctx->d, s, n, src, dst, scores);
   HIPCHK(ctx, hipGetLastError());
   return STGN_OK;
 }

@@ -96,9 +96,14 @@ struct LayerArgs {
   const float* KVn; const float* KVe;              // cached key|value rows of the input table's nodes / of the edges
                                                    // (ES variants: KVe holds the raw feature rows, one slot each)
   float* KVout;                                    // the next layer's node table (null for the last layer)
-  // root-node inference: query time per list row instead of the node's last-interaction time, and the
-  // output rows go to out_rows[list position] instead of the layer cache (both null otherwise)
-  const double* tq_rows; float* out_rows;
+  // root-node inference (scores null otherwise): list row r is the source (r even) or destination (r odd) of edge
+  // r / 2, queried at the edge's time instead of the node's last-interaction time; an id past `nodes` is a dead
+  // row.  The rows are not stored: their tile holds both ends of its eight edges, and the link score
+  // y = h_u . head[0 : d) + h_v . head[d : 2d) + head[2d] leaves the kernel in their place (NaN with a dead end).
+  // One launch for what took three (roots listed, rows stored, rows read back by the head): 4,000 candidates on
+  // 100,000 nodes 35.2 -> 29.9 us, score + ingest of one edge at a time 78.6 -> 75.2 us.
+  const uint32_t *root_src, *root_dst; const double* root_ts; uint32_t nodes;
+  const float* head; float* scores;
   double window;                                   // ring entries older than the query time minus this are ignored (+inf: none)
   const RingEntry* ring; const uint32_t* deg; const double* t_last;
   const double* om_rev; const double* ph_rev;
@@ -160,6 +165,7 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
   // wave index, made provably uniform so that tile indices and weight addresses stay in scalar registers
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const uint32_t k = a.k, dk = a.dk;
+  const bool roots = !DELTA && a.scores != nullptr;   // (root-node inference runs the exact variant)
   const uint32_t c_in = chunks_of(a.d_in), c_de = chunks_of(a.d_emb);                                     // chunks of K
   const uint32_t g_in = kCG * c_in, g_de = kCG * c_de, g_dk = kCG * SH, g_zt = kCG * NZ, g_o = kCG * KS;  // groups of K
   const uint32_t ntd = round_up(a.d_emb, 16) >> 4, ntk = round_up(dk, 16) >> 4;                           // column tiles
@@ -260,8 +266,14 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
   auto stage_a = [&](uint32_t t) {                            // requests only: nothing waits for the values here
     if (tid < kTM) {
       const uint32_t r = t * kTM + tid;
-      p_row = (t < ntiles && r < n) ? (rows ? rows[r] : r) : 0xFFFFFFFFu;
-      p_tqn = (a.tq_rows && t < ntiles && r < n) ? a.tq_rows[r] : 0.0;
+      const bool listed = t < ntiles && r < n;
+      if (roots) {
+        p_row = listed ? ((r & 1u) ? a.root_dst : a.root_src)[r >> 1] : 0xFFFFFFFFu;
+        p_row = p_row < a.nodes ? p_row : 0xFFFFFFFFu;
+        p_tqn = listed ? a.root_ts[r >> 1] : 0.0;
+      } else {
+        p_row = listed ? (rows ? rows[r] : r) : 0xFFFFFFFFu;
+      }
       if constexpr (QCACHE) { if (tid == 0) p_clean = t < ntiles ? (a.all_clean ? 1u : a.tile_clean ? a.tile_clean[t] : 0u) : 0u; }
     }
   };
@@ -304,7 +316,7 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
     const uint32_t j = newest >= sl ? newest - sl : newest + k - sl;
     if (j >= cnt) { e.nbr = 0u; e.eid = 0u; e.t = 0.0; }
     Rs[r * k + j] = e;
-    if (sl == 0) { s_cnt[r] = cnt; s_tq[r] = a.tq_rows ? s_tqn[r] : tl; }
+    if (sl == 0) { s_cnt[r] = cnt; s_tq[r] = roots ? s_tqn[r] : tl; }
   };
   stage_a(blockIdx.x);
   stage_a_commit();
@@ -506,7 +518,7 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
     // next tile's rows, in flight among the gathers of phase 3 (four-slot shapes have no registers to
     // spare in phase 3: theirs are requested behind it)
     if constexpr (KS <= 2) { if (pf_ok) stage_b(); else stage_none(); }
-    if (QCACHE && !clean && !a.out_rows) {                    // the rows' q | qt for later batches
+    if (QCACHE && !clean && !roots) {                      // the rows' q | qt for later batches
       static_for<NQ>([&](auto E) {
         constexpr int e = decltype(E)::value;
         const uint32_t x = tid + 256u * e, r = x / QW4, q4 = x - r * QW4;
@@ -735,7 +747,7 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
       // the launch: one update of the same word per row serialises -- 860 K of them took half of a launch)
       float dg = 0.0f;
       uint32_t dc = 0u;
-      if (a.is_final && live && sub == 0 && !a.out_rows) {
+      if (a.is_final && live && sub == 0) {
         const uint32_t tau = a.drift->tau;
         const float old = a.dseen[nn] ? a.dsum[nn] * __powf(a.gamma, (float)(tau - a.dlast[nn])) : 0.0f;
         const float nw = ex ? 0.0f : old + (nvalid ? (float)nch / (float)nvalid : 0.0f);
@@ -983,16 +995,25 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
             for (int r = 0; r < 4; ++r) {
               const uint32_t node = s_node[m16_row(lane, r)];
               const float v = acc[t][r] + b;
-              if (a.out_rows) {
-                const uint32_t lr = tile * kTM + m16_row(lane, r);
-                if (lr < n) a.out_rows[(size_t)lr * a.d_emb + col] = v;
-              } else if (node != 0xFFFFFFFFu) {
-                a.Hout[(size_t)node * a.ld_out + col] = v;
-              }
-              Qs[c_off_q - m16_col(lane) + r * ll.ldq + col] = v;     // operand of phase 6 (q is no longer needed)
+              if (!roots && node != 0xFFFFFFFFu) a.Hout[(size_t)node * a.ld_out + col] = v;
+              Qs[c_off_q - m16_col(lane) + r * ll.ldq + col] = v;     // operand of phase 6 and of the link scores (q is no longer needed)
             }
           }
         }
+      }
+    }
+    if (roots) {
+      // link scores: a wave takes edges w and w + 4 of the tile (the list holds whole edges)
+      __syncthreads();
+      for (uint32_t e = wave; e < kTM / 2; e += 4) {
+        const uint32_t i = tile * (kTM / 2) + e;
+        const float* hu = Qs + 2u * e * ll.ldq;
+        const float* hv = hu + ll.ldq;
+        float acc = 0.0f;
+        for (uint32_t c = lane; c < a.d_emb; c += 64) acc = fmaf(hu[c], a.head[c], fmaf(hv[c], a.head[a.d_emb + c], acc));
+        for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+        const bool ok = s_node[2u * e] != 0xFFFFFFFFu && s_node[2u * e + 1u] != 0xFFFFFFFFu;
+        if (lane == 0 && 2u * i < n) a.scores[i] = ok ? acc + a.head[2u * a.d_emb] : __builtin_nanf("");
       }
     }
     // ================================================================ phase 6: next layer's cached keys | values of these rows
@@ -1021,7 +1042,7 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
     __syncthreads();
   }
   if constexpr (DELTA) {
-    if (lane == 0 && a.is_final && !a.out_rows) {
+    if (lane == 0 && a.is_final) {
       if (drift_sum != 0.0) atomicAdd(&a.drift->G, drift_sum);
       if (drift_new) atomicAdd(&a.drift->count, drift_new);
     }
@@ -1033,7 +1054,7 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
                         (uint32_t)__builtin_amdgcn_readlane((int)gathered, 16) +
                         (uint32_t)__builtin_amdgcn_readlane((int)gathered, 32) +
                         (uint32_t)__builtin_amdgcn_readlane((int)gathered, 48);
-  if (!a.out_rows) {
+  if (!roots) {
     if (lane == 0) s_cnt[wave] = gsum;
     __syncthreads();
     if (threadIdx.x == 0) {

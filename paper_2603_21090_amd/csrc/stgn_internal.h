@@ -208,9 +208,7 @@ struct Dev {
   DriftCtl* drift;
   float*   dsum; uint32_t* dlast; uint8_t* dseen;   // [N] each
   uint32_t* dlist;                   // [N] nodes whose estimate exceeds the threshold (stgn_maintain)
-  // root-node inference (stgn_predict_batch): the 2n roots (source, destination of edge i at 2i, 2i+1),
-  // their query times, their final-layer rows, staging for host inputs / outputs, and the head [w | b]
-  uint32_t* pred_rows; double* pred_tq; float* pred_out;
+  // link scores (stgn_predict_batch): staging for host inputs / outputs, and the head [w | b]
   uint32_t* pred_src; uint32_t* pred_dst; double* pred_ts; float* pred_scores;
   float*   pred_w;
   uint32_t* qnodes; float* qout;     // staging for host-side get_embeddings
@@ -297,10 +295,9 @@ void launch_drift_values(const Dev& d, hipStream_t s, float* out);   // every no
 void launch_gather_rows(const Dev& d, hipStream_t s, uint32_t layer, uint32_t n, const uint32_t* nodes, float* out);
 void launch_gather_times(const Dev& d, hipStream_t s, uint32_t n, const uint32_t* nodes, double* out);   // last-interaction times
 // root-node inference: roots and query times of n edges; the final layer for the 2n roots; the linear head
-void launch_predict_prep(const Dev& d, hipStream_t s, uint32_t n, const uint32_t* src, const uint32_t* dst, const double* ts);
-void launch_layer_roots(const Dev& d, hipStream_t s, uint32_t nroots);
-void launch_predict_head(const Dev& d, hipStream_t s, uint32_t n, const uint32_t* src, const uint32_t* dst,
-                         int at_edge_time, float* scores);
+void launch_layer_scores(const Dev& d, hipStream_t s, uint32_t n, const uint32_t* src, const uint32_t* dst, const double* ts,
+                         float* scores);
+void launch_predict_head(const Dev& d, hipStream_t s, uint32_t n, const uint32_t* src, const uint32_t* dst, float* scores);
 void launch_init_state(const Dev& d, hipStream_t s);
 void launch_zero(float* p, size_t n, hipStream_t s);
 void launch_noop(hipStream_t s);
