@@ -126,3 +126,22 @@ def test_scores_at_edge_time_around_a_tile(d_emb):
     got = g.predict_batch(bad_s, bad_d, ts, at_edge_time=True)
     assert torch.isnan(got[7:9]).all() and torch.equal(got[:7], all_[:7]) and torch.equal(got[9:], all_[9:])
     g.close()
+
+
+@pytest.mark.parametrize("d_emb", [7, 100])
+def test_rows_to_host_arrays(d_emb):
+    """Host lists on both sides of the pinned block (1 MiB of ids and rows), against the device call."""
+    import torch
+    from paper_2603_21090_amd import binding
+    w = tiny_workload(d_emb=d_emb, heads=1, num_nodes=300, num_edges=900, batch=300)
+    g = binding.StreamTGN.from_workload(w, synth.make_weights(w))
+    st = synth.EdgeStream(w)
+    for b in range(w.num_batches):
+        g.ingest_batch(*st.batch(b))
+    gen = np.random.default_rng(d_emb)
+    edge = ((1 << 20) - 16) // (4 + 4 * d_emb)
+    for n in (1, 3, 333, edge - 1, edge, edge + 1, 2 * edge + 5):
+        ids = gen.integers(0, w.num_nodes, n).astype(np.uint32)
+        want = g.get_embeddings(torch.from_numpy(ids.astype(np.int32)).cuda()).cpu().numpy()
+        assert np.array_equal(g.get_embeddings(ids), want), n
+    g.close()
