@@ -155,7 +155,7 @@ void launch_layer(const Dev& d, hipStream_t s, uint32_t layer, const uint32_t* r
 void launch_layer_scores(const Dev& d, hipStream_t s, uint32_t n, const uint32_t* src, const uint32_t* dst, const double* ts,
                          float* scores) {
   LaunchArgs a = make_args(d, d.layers - 1);
-  a.delta = false;                                            // root rows are computed at their own times, from nothing cached
+  a.roots = true;                                             // (computed at their own times, from nothing cached)
   a.k.tile_clean = nullptr;                                   // the cached rows are current, hence every root's q and qt
   a.k.all_clean = a.k.QC ? 1u : 0u;
   a.k.root_src = src; a.k.root_dst = dst; a.k.root_ts = ts; a.k.nodes = d.N;
@@ -298,8 +298,8 @@ int setup_embed_attributes(const Dev& d) {
     a.set_attr = true;
     go_heads(a);
     if (a.err != hipSuccess) return -1;
-    if (a.delta) {                                                // the exact variant serves the root rows
-      a.delta = false;
+    if (l + 1 == d.layers) {                                      // the final layer's root rows
+      a.roots = true;
       go_heads(a);
       if (a.err != hipSuccess) return -1;
     }

@@ -96,7 +96,7 @@ struct LayerArgs {
   const float* KVn; const float* KVe;              // cached key|value rows of the input table's nodes / of the edges
                                                    // (ES variants: KVe holds the raw feature rows, one slot each)
   float* KVout;                                    // the next layer's node table (null for the last layer)
-  // root-node inference (scores null otherwise): list row r is the source (r even) or destination (r odd) of edge
+  // root-node inference (read by the ROOTS variants only): list row r is the source (r even) or destination (r odd) of edge
   // r / 2, queried at the edge's time instead of the node's last-interaction time; an id past `nodes` is a dead
   // row.  The rows are not stored: their tile holds both ends of its eight edges, and the link score
   // y = h_u . head[0 : d) + h_v . head[d : 2d) + head[2d] leaves the kernel in their place (NaN with a dead end).
@@ -141,15 +141,20 @@ struct GatherBuf {
 // W_V,h[time | edge]), and the cached rows hold the node parts alone.
 // DELTA: the approximate mode of Sec. 3.3 "Stage 4" (attention cache, delta update of changed entries).
 // QCACHE: the query cache is in use (rows may read q and qt back, rows that project store theirs).
-template <int KS, int NT, int ES, int H, int JC, int WGS, bool DELTA, bool QCACHE>
+// ROOTS: root-node inference (LayerArgs::root_src and on).  A variant of its own and not a test at run time: the seven
+// places that differ cost every streamed launch registers it does not have.  Two heads of one slot, two time slots, raw
+// edge rows, query cache: 11 spilled vector and 119 spilled scalar registers with the test, 2 and 92 without; a
+// layer launch of 1.3 million nodes (k = 20, batches of 2,000) 436 us with it, 398 without.
+template <int KS, int NT, int ES, int H, int JC, int WGS, bool DELTA, bool QCACHE, bool ROOTS>
 __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows,
                                                          const uint32_t* count_ptr, uint32_t count_max) {
   extern __shared__ __align__(16) float lds[];
   __shared__ uint32_t s_node[kTM], s_cnt[kTM], s_next[kTM], s_ex[kTM], s_cleann;
-  __shared__ double s_tq[kTM], s_tqn[kTM];
+  __shared__ double s_tq[kTM], s_tqn[ROOTS ? kTM : 1u];
   __shared__ __align__(16) double s_om[NT * kSlot], s_ph[NT * kSlot];
   static_assert(KS % H == 0, "whole slots per head");
   static_assert(!(DELTA && ES), "the delta mode keeps projected edge rows");
+  static_assert(!(DELTA && ROOTS), "root rows are computed exactly");
   constexpr int SH = KS / H;                  // slots per head
   constexpr int NZ = NT + ES;                 // slots of z
   constexpr uint32_t Ztp = NZ * kSlot;        // floats of one head's qt / pb vector
@@ -165,7 +170,6 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
   // wave index, made provably uniform so that tile indices and weight addresses stay in scalar registers
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const uint32_t k = a.k, dk = a.dk;
-  const bool roots = !DELTA && a.scores != nullptr;   // (root-node inference runs the exact variant)
   const uint32_t c_in = chunks_of(a.d_in), c_de = chunks_of(a.d_emb);                                     // chunks of K
   const uint32_t g_in = kCG * c_in, g_de = kCG * c_de, g_dk = kCG * SH, g_zt = kCG * NZ, g_o = kCG * KS;  // groups of K
   const uint32_t ntd = round_up(a.d_emb, 16) >> 4, ntk = round_up(dk, 16) >> 4;                           // column tiles
@@ -267,7 +271,7 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
     if (tid < kTM) {
       const uint32_t r = t * kTM + tid;
       const bool listed = t < ntiles && r < n;
-      if (roots) {
+      if constexpr (ROOTS) {
         p_row = listed ? ((r & 1u) ? a.root_dst : a.root_src)[r >> 1] : 0xFFFFFFFFu;
         p_row = p_row < a.nodes ? p_row : 0xFFFFFFFFu;
         p_tqn = listed ? a.root_ts[r >> 1] : 0.0;
@@ -278,7 +282,10 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
     }
   };
   auto stage_a_commit = [&]() {
-    if (tid < kTM) { s_next[tid] = p_row; s_tqn[tid] = p_tqn; }
+    if (tid < kTM) {
+      s_next[tid] = p_row;
+      if constexpr (ROOTS) s_tqn[tid] = p_tqn;
+    }
     if constexpr (QCACHE) { if (tid == 0) s_cleann = p_clean; }
   };
   auto stage_b = [&]() {
@@ -316,7 +323,7 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
     const uint32_t j = newest >= sl ? newest - sl : newest + k - sl;
     if (j >= cnt) { e.nbr = 0u; e.eid = 0u; e.t = 0.0; }
     Rs[r * k + j] = e;
-    if (sl == 0) { s_cnt[r] = cnt; s_tq[r] = roots ? s_tqn[r] : tl; }
+    if (sl == 0) { s_cnt[r] = cnt; s_tq[r] = ROOTS ? s_tqn[ROOTS ? r : 0u] : tl; }
   };
   stage_a(blockIdx.x);
   stage_a_commit();
@@ -518,7 +525,7 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
     // next tile's rows, in flight among the gathers of phase 3 (four-slot shapes have no registers to
     // spare in phase 3: theirs are requested behind it)
     if constexpr (KS <= 2) { if (pf_ok) stage_b(); else stage_none(); }
-    if (QCACHE && !clean && !roots) {                      // the rows' q | qt for later batches
+    if (QCACHE && !ROOTS && !clean) {                        // the rows' q | qt for later batches
       static_for<NQ>([&](auto E) {
         constexpr int e = decltype(E)::value;
         const uint32_t x = tid + 256u * e, r = x / QW4, q4 = x - r * QW4;
@@ -995,14 +1002,14 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
             for (int r = 0; r < 4; ++r) {
               const uint32_t node = s_node[m16_row(lane, r)];
               const float v = acc[t][r] + b;
-              if (!roots && node != 0xFFFFFFFFu) a.Hout[(size_t)node * a.ld_out + col] = v;
+              if (!ROOTS && node != 0xFFFFFFFFu) a.Hout[(size_t)node * a.ld_out + col] = v;
               Qs[c_off_q - m16_col(lane) + r * ll.ldq + col] = v;     // operand of phase 6 and of the link scores (q is no longer needed)
             }
           }
         }
       }
     }
-    if (roots) {
+    if constexpr (ROOTS) {
       // link scores: a wave takes edges w and w + 4 of the tile (the list holds whole edges)
       __syncthreads();
       for (uint32_t e = wave; e < kTM / 2; e += 4) {
@@ -1017,7 +1024,7 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
       }
     }
     // ================================================================ phase 6: next layer's cached keys | values of these rows
-    if (a.KVout) {
+    if (!ROOTS && a.KVout) {
       constexpr uint32_t ntkv = 8u * KS;                      // column tiles of a cached row; a wave takes tiles w + 8 i, w + 8 i + 4
       Ops16<2> ok;
       load_b16(a.WKVnext + (size_t)wave * g_de * kGrpFloats, 0, ok.b[0]);
@@ -1054,7 +1061,7 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
                         (uint32_t)__builtin_amdgcn_readlane((int)gathered, 16) +
                         (uint32_t)__builtin_amdgcn_readlane((int)gathered, 32) +
                         (uint32_t)__builtin_amdgcn_readlane((int)gathered, 48);
-  if (!roots) {
+  if constexpr (!ROOTS) {
     if (lane == 0) s_cnt[wave] = gsum;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -1072,14 +1079,15 @@ struct LaunchArgs {
   uint32_t ks, nt, heads;
   bool es;                          // raw edge rows (never together with delta)
   bool delta;                       // the delta-mode variant of the kernel
+  bool roots;                       // the root-node variant (the exact one also in delta mode)
   uint32_t num_cu;                  // compute units of the device
   bool set_attr; size_t lds; hipError_t err;
   int query_wgs; uint32_t wgs;      // query_wgs: only report the workgroups per CU of the variant in `wgs`
 };
 
-template <int KS, int NT, int ES, int H, int JC, int WGS, bool DELTA, bool QCACHE>
+template <int KS, int NT, int ES, int H, int JC, int WGS, bool DELTA, bool QCACHE, bool ROOTS>
 void go_k(LaunchArgs& a) {
-  auto kern = layer_kernel<KS, NT, ES, H, JC, WGS, DELTA, QCACHE>;
+  auto kern = layer_kernel<KS, NT, ES, H, JC, WGS, DELTA, QCACHE, ROOTS>;
   if (a.query_wgs) { a.wgs = WGS; return; }
   if (a.set_attr) {
     // never lowered: other layers of this context and other contexts of the process may launch the same variant
@@ -1101,15 +1109,21 @@ void go_k(LaunchArgs& a) {
   hipLaunchKernelGGL(kern, dim3((uint32_t)blocks), dim3(256), a.lds, a.s, a.k, a.rows, a.cp, a.cm);
 }
 
-template <int KS, int NT, int H, int JC, int WGS>
-void go(LaunchArgs& a) {
-  if (a.delta) { go_k<KS, NT, 0, H, 1, WGS, true, false>(a); return; }
+template <int KS, int NT, int H, int JC, int WGS, bool ROOTS>
+void go_exact(LaunchArgs& a) {
   if (a.es) {
-    if (a.k.QC) go_k<KS, NT, 1, H, JC, WGS, false, true>(a); else go_k<KS, NT, 1, H, JC, WGS, false, false>(a);
+    if (a.k.QC) go_k<KS, NT, 1, H, JC, WGS, false, true, ROOTS>(a); else go_k<KS, NT, 1, H, JC, WGS, false, false, ROOTS>(a);
     return;
   }
-  if (a.k.QC) { go_k<KS, NT, 0, H, JC, WGS, false, true>(a); return; }
-  go_k<KS, NT, 0, H, JC, WGS, false, false>(a);
+  if (a.k.QC) { go_k<KS, NT, 0, H, JC, WGS, false, true, ROOTS>(a); return; }
+  go_k<KS, NT, 0, H, JC, WGS, false, false, ROOTS>(a);
+}
+
+template <int KS, int NT, int H, int JC, int WGS>
+void go(LaunchArgs& a) {
+  if (a.roots) go_exact<KS, NT, H, JC, WGS, true>(a);
+  else if (a.delta) go_k<KS, NT, 0, H, 1, WGS, true, false, false>(a);
+  else go_exact<KS, NT, H, JC, WGS, false>(a);
 }
 
 // Ring entries per chunk and workgroups per CU are bounded by registers: two chunks of JC * 4 KS
