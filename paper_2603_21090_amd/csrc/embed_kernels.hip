@@ -17,10 +17,11 @@ using layer_impl::LayerArgs;
 // checked on the host) yields a row of NaN instead of a read outside the table.
 //
 // A copy, bound by HBM for long lists and by the launch for short ones.  A workgroup takes `per` consecutive list
-// positions (grid = list / per) and its threads stride over their pieces of V floats; four pieces per thread are
+// positions (and again `per`, a grid further on, when the list outgrows the largest grid) and its threads stride over their pieces of V floats; four pieces per thread are
 // requested before the first is stored, and the (row, piece) pair advances by additions.  One million rows of 100
 // floats: 184 us = 4.9 TB/s, the rate of a large copy (one float per thread and a 64-bit division each: 284 us).
 // Results are stored past the caches: nothing here reads them again, and the tables keep their place.
+constexpr uint32_t kGatherBlocks = 1u << 16;
 template <int V> struct Piece;
 template <> struct Piece<4> { typedef float type __attribute__((ext_vector_type(4))); };
 template <> struct Piece<2> { typedef float type __attribute__((ext_vector_type(2))); };
@@ -32,31 +33,33 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(Table T, uint32_t N, u
   using P = typename Piece<V>::type;
   constexpr int U = 4;
   const uint32_t q = width / V;                               // pieces per row
-  const uint32_t i0 = blockIdx.x * per, rows = min(per, n - i0), tot = rows * q;
   const uint32_t dr = 256u / q, dc = 256u - dr * q;
-  const uint32_t* ids = nodes + i0;
-  P* dst = reinterpret_cast<P*>(out) + (size_t)i0 * q;
-  uint32_t x = threadIdx.x, r = x / q, c = x - r * q;
-  while (x < tot) {
-    P v[U];
-    uint32_t id[U], rr[U], cc[U];
+  for (uint64_t i0 = (uint64_t)blockIdx.x * per; i0 < n; i0 += (uint64_t)gridDim.x * per) {   // (uniform)
+    const uint32_t rows = (uint32_t)min((uint64_t)per, n - i0), tot = rows * q;
+    const uint32_t* ids = nodes + i0;
+    P* dst = reinterpret_cast<P*>(out) + (size_t)i0 * q;
+    uint32_t x = threadIdx.x, r = x / q, c = x - r * q;
+    while (x < tot) {
+      P v[U];
+      uint32_t id[U], rr[U], cc[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      rr[u] = r < rows ? r : rows - 1u;                       // (pieces past the end repeat the last row and are not stored)
-      cc[u] = c;
-      id[u] = ids[rr[u]];
-      c += dc; r += dr;
-      if (c >= q) { c -= q; ++r; }
+      for (int u = 0; u < U; ++u) {
+        rr[u] = r < rows ? r : rows - 1u;                     // (pieces past the end repeat the last row and are not stored)
+        cc[u] = c;
+        id[u] = ids[rr[u]];
+        c += dc; r += dr;
+        if (c >= q) { c -= q; ++r; }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        v[u] = *reinterpret_cast<const P*>(T.base + (size_t)(id[u] < N ? id[u] : 0u) * T.ld + V * cc[u]);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const P nan = (P)(__builtin_nanf(""));
+        if (x + 256u * u < tot) __builtin_nontemporal_store(id[u] < N ? v[u] : nan, dst + x + 256u * u);
+      }
+      x += 256u * U;
     }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      v[u] = *reinterpret_cast<const P*>(T.base + (size_t)(id[u] < N ? id[u] : 0u) * T.ld + V * cc[u]);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const P nan = (P)(__builtin_nanf(""));
-      if (x + 256u * u < tot) __builtin_nontemporal_store(id[u] < N ? v[u] : nan, dst + x + 256u * u);
-    }
-    x += 256u * U;
   }
 }
 
@@ -179,7 +182,8 @@ void launch_gather_rows(const Dev& d, hipStream_t s, uint32_t layer, uint32_t n,
   const uint32_t fill = n / 2048u;
   if (per > fill) per = fill;
   if (per < 8) per = 8;
-  const uint32_t blocks = (n + per - 1) / per;
+  // a launch may hold 2^24 workgroups of 256 threads: the grid stops far below that and far above what fills the chip
+  const uint32_t blocks = (uint32_t)std::min<uint64_t>(((uint64_t)n + per - 1) / per, kGatherBlocks);
   const Table& T = d.H[layer];
   if (v == 4) hipLaunchKernelGGL(gather_rows_kernel<4>, dim3(blocks), dim3(256), 0, s, T, d.N, width, n, per, nodes, out);
   else if (v == 2) hipLaunchKernelGGL(gather_rows_kernel<2>, dim3(blocks), dim3(256), 0, s, T, d.N, width, n, per, nodes, out);

@@ -39,6 +39,34 @@ def test_rows_in_every_piece_width(d_emb):
     g.close()
 
 
+@pytest.mark.parametrize("d_emb,n,shift", [(252, 8 * 65_536 + 3, 1), (252, 4 * 8 * 65_536, 1), (1, 2 ** 32 - 5, 0)])
+def test_lists_longer_than_the_largest_grid(d_emb, n, shift):
+    """Eight rows per workgroup and 65,536 workgroups, by three rows and several times over; and a list whose length and the
+    rows of a workgroup do not add up in 32 bits (34 GB of ids and results)."""
+    import torch
+    from paper_2603_21090_amd import binding
+    w = tiny_workload(d_emb=d_emb, heads=1, num_nodes=300, num_edges=900, batch=300)
+    g = binding.StreamTGN.from_workload(w, synth.make_weights(w))
+    st = synth.EdgeStream(w)
+    for b in range(w.num_batches):
+        g.ingest_batch(*st.batch(b))
+    table = g.get_embeddings(torch.arange(w.num_nodes, dtype=torch.int32, device="cuda"))
+    step = (1 << 26) // d_emb
+    ids = torch.empty(n, dtype=torch.int32, device="cuda")
+    for lo in range(0, n, step):
+        ids[lo:lo + step].random_(0, w.num_nodes)
+    buf = torch.full((n * d_emb + 2,), 7.0, device="cuda")
+    rc = g._L.stgn_get_embeddings(g._h, 0, n, C.c_void_p(ids.data_ptr()), C.c_void_p(buf.data_ptr() + 4 * shift), 1)
+    assert rc == 0 and g.sync() == 0
+    got = buf[shift:shift + n * d_emb].view(n, d_emb)
+    for lo in range(0, n, step):
+        assert torch.equal(got[lo:lo + step], table[ids[lo:lo + step].long()]), lo
+    assert bool((buf[:shift] == 7.0).all()) and bool((buf[shift + n * d_emb:] == 7.0).all())
+    g.close()
+    del ids, buf, got
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("k", [1, 10, 11, 20, 21, 64])
 @pytest.mark.parametrize("d_mem", [0, 16])
 def test_regrouped_rows_equal_a_rebuild(k, d_mem):
