@@ -933,7 +933,7 @@ int stgn_get_embeddings(stgn_ctx* ctx, uint32_t layer, uint32_t n, const uint32_
   if (on_device) {
     ctx->idle = false;
     Scope t(ctx, KC_GATHER);
-    launch_gather_rows(d, ctx->stream, layer, n, nodes, out);
+    HIPCHK(ctx, launch_gather_rows(d, ctx->stream, layer, n, nodes, out));
     return STGN_OK;
   }
   for (uint32_t i = 0; i < n; ++i)
@@ -944,9 +944,8 @@ int stgn_get_embeddings(stgn_ctx* ctx, uint32_t layer, uint32_t n, const uint32_
   if ((size_t)n * 4 + 16 + (size_t)n * c.d_emb * 4 <= kRowIoBytes) {
     const size_t o_rows = ((size_t)n * 4 + 15) & ~(size_t)15;
     memcpy(ctx->row_io, nodes, (size_t)n * 4);
-    launch_gather_rows(d, ctx->stream, layer, n, reinterpret_cast<const uint32_t*>(ctx->row_io),
-                       reinterpret_cast<float*>(ctx->row_io + o_rows));
-    HIPCHK(ctx, hipGetLastError());
+    HIPCHK(ctx, launch_gather_rows(d, ctx->stream, layer, n, reinterpret_cast<const uint32_t*>(ctx->row_io),
+                                   reinterpret_cast<float*>(ctx->row_io + o_rows)));
     const int rc = sync_and_poll(ctx);
     if (rc != STGN_E_DEVICE) memcpy(out, ctx->row_io + o_rows, (size_t)n * c.d_emb * 4);
     return rc;
@@ -954,7 +953,7 @@ int stgn_get_embeddings(stgn_ctx* ctx, uint32_t layer, uint32_t n, const uint32_
   for (uint32_t lo = 0; lo < n; lo += d.q_cap) {
     const uint32_t m = std::min(d.q_cap, n - lo);
     HIPCHK(ctx, hipMemcpyAsync(d.qnodes, nodes + lo, (size_t)m * 4, hipMemcpyHostToDevice, ctx->stream));
-    launch_gather_rows(d, ctx->stream, layer, m, d.qnodes, d.qout);
+    HIPCHK(ctx, launch_gather_rows(d, ctx->stream, layer, m, d.qnodes, d.qout));
     HIPCHK(ctx, hipMemcpyAsync(out + (size_t)lo * c.d_emb, d.qout, (size_t)m * c.d_emb * 4, hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
   }
@@ -1036,7 +1035,7 @@ int stgn_get_memory(stgn_ctx* ctx, uint32_t n, const uint32_t* nodes, float* mem
       const uint32_t m = std::min(d.q_cap, n - lo);
       rowbuf.resize((size_t)m * d.d0);
       HIPCHK(ctx, hipMemcpyAsync(d.qnodes, nodes + lo, (size_t)m * 4, hipMemcpyHostToDevice, ctx->stream));
-      launch_gather_rows(d, ctx->stream, 0, m, d.qnodes, d.qout);
+      HIPCHK(ctx, launch_gather_rows(d, ctx->stream, 0, m, d.qnodes, d.qout));
       HIPCHK(ctx, hipMemcpyAsync(rowbuf.data(), d.qout, rowbuf.size() * 4, hipMemcpyDeviceToHost, ctx->stream));
       HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
       for (uint32_t i = 0; i < m; ++i)

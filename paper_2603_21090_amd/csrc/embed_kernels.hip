@@ -171,8 +171,8 @@ void launch_predict_head(const Dev& d, hipStream_t s, uint32_t n, const uint32_t
   hipLaunchKernelGGL(predict_head_kernel, dim3((n + 3) / 4), dim3(256), 0, s, d, n, src, dst, scores);
 }
 
-void launch_gather_rows(const Dev& d, hipStream_t s, uint32_t layer, uint32_t n, const uint32_t* nodes, float* out) {
-  const uint32_t width = layer == 0 ? d.d0 : d.d_emb;
+hipError_t launch_gather_rows(const Dev& d, hipStream_t s, uint32_t layer, uint32_t n, const uint32_t* nodes, float* out) {
+  uint32_t width = layer == 0 ? d.d0 : d.d_emb;
   // 16-byte pieces where the width and the caller's buffer allow (table rows are aligned to 256 bytes), else 8, else 4
   const uintptr_t at = reinterpret_cast<uintptr_t>(out);
   const int v = width % 4 == 0 && at % 16 == 0 ? 4 : width % 2 == 0 && at % 8 == 0 ? 2 : 1;
@@ -184,10 +184,11 @@ void launch_gather_rows(const Dev& d, hipStream_t s, uint32_t layer, uint32_t n,
   if (per < 8) per = 8;
   // a launch may hold 2^24 workgroups of 256 threads: the grid stops far below that and far above what fills the chip
   const uint32_t blocks = (uint32_t)std::min<uint64_t>(((uint64_t)n + per - 1) / per, kGatherBlocks);
-  const Table& T = d.H[layer];
-  if (v == 4) hipLaunchKernelGGL(gather_rows_kernel<4>, dim3(blocks), dim3(256), 0, s, T, d.N, width, n, per, nodes, out);
-  else if (v == 2) hipLaunchKernelGGL(gather_rows_kernel<2>, dim3(blocks), dim3(256), 0, s, T, d.N, width, n, per, nodes, out);
-  else hipLaunchKernelGGL(gather_rows_kernel<1>, dim3(blocks), dim3(256), 0, s, T, d.N, width, n, per, nodes, out);
+  Table T = d.H[layer];
+  uint32_t N = d.N;
+  void* args[] = {&T, &N, &width, &n, &per, &nodes, &out};
+  const auto kern = v == 4 ? gather_rows_kernel<4> : v == 2 ? gather_rows_kernel<2> : gather_rows_kernel<1>;
+  return hipLaunchKernel(reinterpret_cast<const void*>(kern), dim3(blocks), dim3(256), args, 0, s);
 }
 
 void launch_gather_times(const Dev& d, hipStream_t s, uint32_t n, const uint32_t* nodes, double* out) {

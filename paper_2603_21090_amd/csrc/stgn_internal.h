@@ -292,7 +292,8 @@ void launch_layer(const Dev& d, hipStream_t s, uint32_t layer, const uint32_t* r
 void launch_drift_reset(const Dev& d, hipStream_t s);
 void launch_drift_list(const Dev& d, hipStream_t s, float threshold);
 void launch_drift_values(const Dev& d, hipStream_t s, float* out);   // every node's decayed estimate, [N]
-void launch_gather_rows(const Dev& d, hipStream_t s, uint32_t layer, uint32_t n, const uint32_t* nodes, float* out);
+// (returns the launch's own status: no error that an earlier call left behind is taken for it, or lost)
+hipError_t launch_gather_rows(const Dev& d, hipStream_t s, uint32_t layer, uint32_t n, const uint32_t* nodes, float* out);
 void launch_gather_times(const Dev& d, hipStream_t s, uint32_t n, const uint32_t* nodes, double* out);   // last-interaction times
 // root-node inference: roots and query times of n edges; the final layer for the 2n roots; the linear head
 void launch_layer_scores(const Dev& d, hipStream_t s, uint32_t n, const uint32_t* src, const uint32_t* dst, const double* ts,

@@ -173,3 +173,28 @@ def test_rows_to_host_arrays(d_emb):
         want = g.get_embeddings(torch.from_numpy(ids.astype(np.int32)).cuda()).cpu().numpy()
         assert np.array_equal(g.get_embeddings(ids), want), n
     g.close()
+
+
+def test_rows_despite_an_error_left_behind():
+    """An error that an earlier call of the program left with the runtime is not this call's: rows to a host array (short list and
+    long) and to the device come as they do without it."""
+    import torch
+    from paper_2603_21090_amd import binding
+    w = tiny_workload(num_nodes=300, num_edges=900, batch=300)
+    g = binding.StreamTGN.from_workload(w, synth.make_weights(w))
+    st = synth.EdgeStream(w)
+    for b in range(w.num_batches):
+        g.ingest_batch(*st.batch(b))
+    long_ = (1 << 20) // (4 * w.d_emb) + 1
+    for n in (5, long_):
+        ids = np.arange(n, dtype=np.uint32) % w.num_nodes
+        dev = torch.from_numpy(ids.astype(np.int32)).cuda()
+        want = g.get_embeddings(dev).cpu().numpy()
+        host, rows = np.empty((n, w.d_emb), dtype=np.float32), torch.empty((n, w.d_emb), device="cuda")
+        for out, nodes, on_device in ((host.ctypes.data, ids.ctypes.data, 0), (rows.data_ptr(), dev.data_ptr(), 1)):
+            assert g._L.hipSetDevice(4096) != 0 and g._L.hipPeekAtLastError() != 0
+            rc = g._L.stgn_get_embeddings(g._h, 0, n, C.c_void_p(nodes), C.c_void_p(out), on_device)
+            g._L.hipGetLastError()
+            assert rc == 0, (n, on_device, g.last_error())
+        assert np.array_equal(host, want) and np.array_equal(rows.cpu().numpy(), want)
+    g.close()
