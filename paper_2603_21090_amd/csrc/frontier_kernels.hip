@@ -264,8 +264,10 @@ __global__ __launch_bounds__(256) void compact_write_kernel(Dev d) {
 // gives every thread its starting offsets: three barriers in all, where a scan of its own per bin took two barriers
 // per bin and the histogram an LDS atomic per row.
 constexpr uint32_t kBucketWindow = 4096;
-constexpr uint32_t kMaxBins = 2 * 65;                        // entry counts 0 .. k, k <= 64; changed | unchanged input
+// entry counts 0 .. k: twice (changed | unchanged input) where the query cache is in use, which takes k <= 32; once, k <= 64
+constexpr uint32_t kMaxBins = 2 * 33;
 constexpr uint32_t kMaxBinGroups = (kMaxBins + 3) / 4;
+static_assert(kMaxBins >= 65, "lists without the cache's halves fit as well");
 struct BucketJob { const uint32_t* in; const uint32_t* count; uint32_t* out; uint32_t count_max; uint8_t* tile_clean; uint32_t thr_in; };
 struct BucketJobs { BucketJob j[STGN_MAX_LAYERS]; };
 // NG: groups of four bins the variant has registers for
@@ -402,8 +404,11 @@ void launch_bucket_rows(const Dev& d, hipStream_t s, bool all_rows) {
     }
   }
   const uint32_t blocks = (d.N + kBucketWindow - 1) / kBucketWindow;
-  // registers for the usual list lengths (k up to 10 / 20 with the query cache's two halves), and for any
-  const uint32_t groups = (2u * (d.k + 1u) + 3u) / 4u;
+  // a variant's registers and its unrolled bodies grow with its bins: k up to 11, 21 and 32 with the query cache's two halves,
+  // up to 23, 43 and 64 without them (rebuilds, the delta mode)
+  uint32_t halves = 1u;
+  for (uint32_t j = 0; j < nj; ++j) if (jobs.j[j].tile_clean) halves = 2u;
+  const uint32_t groups = (halves * (d.k + 1u) + 3u) / 4u;
   if (groups <= 6u) hipLaunchKernelGGL(bucket_rows_kernel<6>, dim3(blocks, nj), dim3(256), 0, s, d, jobs);
   else if (groups <= 11u) hipLaunchKernelGGL(bucket_rows_kernel<11>, dim3(blocks, nj), dim3(256), 0, s, d, jobs);
   else hipLaunchKernelGGL(bucket_rows_kernel<kMaxBinGroups>, dim3(blocks, nj), dim3(256), 0, s, d, jobs);

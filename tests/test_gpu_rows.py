@@ -67,12 +67,13 @@ def test_lists_longer_than_the_largest_grid(d_emb, n, shift):
     torch.cuda.empty_cache()
 
 
-@pytest.mark.parametrize("k", [1, 10, 11, 20, 21, 64])
+@pytest.mark.parametrize("k", [1, 10, 11, 12, 20, 21, 22, 23, 24, 32, 33, 43, 44, 64])
 @pytest.mark.parametrize("d_mem", [0, 16])
 def test_regrouped_rows_equal_a_rebuild(k, d_mem):
-    """Row lists regrouped by entry count, at the list lengths on both sides of each variant of the regrouping kernel and with
-    a last window of a few rows: an incremental row is the row a rebuild computes, byte for byte, so a row dropped,
-    doubled or marked as unchanged by mistake shows."""
+    """Row lists regrouped by entry count, at the list lengths on both sides of each variant of the regrouping kernel (11 | 12
+    and 21 | 22 where the query cache doubles the bins, up to 32; 23 | 24 for a rebuild's list and 43 | 44 past the cache)
+    and with a last window of a few rows: an incremental row is the row a rebuild computes, byte for byte, so a row
+    dropped, doubled or marked as unchanged by mistake shows."""
     import torch
     from paper_2603_21090_amd import binding
     w = tiny_workload(num_nodes=36_869, num_edges=24_000, batch=2_000, k=k, d_mem=d_mem, d_node=0 if d_mem else 16, zipf_s=0.9)
