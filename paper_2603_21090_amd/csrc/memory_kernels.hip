@@ -22,6 +22,7 @@ constexpr uint32_t kWaves = kThreads / 64;
 // slots a thread requests together
 constexpr uint32_t kMeanPre = kThreads / kRows;
 constexpr uint32_t kMeanU = 8;
+template <uint32_t U> struct Together { static constexpr uint32_t value = U; };
 
 __device__ inline float sigmoidf_(float x) { return 1.0f / (1.0f + expf(-x)); }
 
@@ -126,6 +127,9 @@ __global__ __launch_bounds__(kThreads) void memory_update_kernel(Dev d, const ui
       // slots: taken one at a time, a tile with a hub was a chain of 3 latencies per slot, 151 us of a launch for 500
       // edges.  The first kMeanPre slots of every row are resolved at once, one per thread, and the values are
       // requested kMeanU at a time and added in slot order: 105 us beside the layer kernel, batch 319 -> 278 us.
+      // Most rows of a batch hold one slot: theirs is requested alone, since seven repeated cosines and loads per
+      // column cost a launch of 1,000 such rows 38.8 us where one at a time took 35.1 (31.6 now; two slots 43.5 one at a
+      // time, 40.0 now; eight 97, 41).
       // They lie where the message and gate tiles are written later (at least 16 x 60 + 64 floats behind off_m; ids
       // far below 2^31 are finite as floats, which the padding of those tiles has to be).
       static_assert(kRows * kMeanPre * sizeof(uint2) <= (kRows * 3 * (kGrpK + 4) + 4 * kGrpK) * sizeof(float), "fits the smallest tiles");
@@ -147,42 +151,47 @@ __global__ __launch_bounds__(kThreads) void memory_update_kernel(Dev d, const ui
             val = H0.base[(size_t)s_self[r] * H0.ld + col];
           } else {
             const uint32_t n = s_n[r];
-            float acc = 0.0f;
-            for (uint32_t j0 = 0; j0 < n; j0 += kMeanU) {
-              // (places past the row's slots repeat its last one and are not added)
-              uint2 oi[kMeanU];
-              if (j0 < kMeanPre) {
+            auto sum = [&](auto together) {                  // U slots requested together
+              constexpr uint32_t U = decltype(together)::value;
+              float acc = 0.0f;
+              for (uint32_t j0 = 0; j0 < n; j0 += U) {
+                // (places past the row's slots repeat its last one and are not added)
+                uint2 oi[U];
+                if (j0 < kMeanPre) {
 #pragma unroll
-                for (uint32_t u = 0; u < kMeanU; ++u) oi[u] = s_pre[r * kMeanPre + (j0 + u < n ? j0 + u : n - 1u)];
-              } else {
+                  for (uint32_t u = 0; u < U; ++u) oi[u] = s_pre[r * kMeanPre + (j0 + u < n ? j0 + u : n - 1u)];
+                } else {
 #pragma unroll
-                for (uint32_t u = 0; u < kMeanU; ++u) oi[u].y = d.slot_sorted[s_seg[r] + (j0 + u < n ? j0 + u : n - 1u)];
+                  for (uint32_t u = 0; u < U; ++u) oi[u].y = d.slot_sorted[s_seg[r] + (j0 + u < n ? j0 + u : n - 1u)];
 #pragma unroll
-                for (uint32_t u = 0; u < kMeanU; ++u) {
-                  const uint32_t i = oi[u].y >> 1;
-                  oi[u] = make_uint2((oi[u].y & 1) ? src[i] : dst[i], i);
+                  for (uint32_t u = 0; u < U; ++u) {
+                    const uint32_t i = oi[u].y >> 1;
+                    oi[u] = make_uint2((oi[u].y & 1) ? src[i] : dst[i], i);
+                  }
                 }
-              }
-              float v[kMeanU];
-              if (col < 2 * dm + de) {
+                float v[U];
+                if (col < 2 * dm + de) {
 #pragma unroll
-                for (uint32_t u = 0; u < kMeanU; ++u) {
-                  const float* p = col < 2 * dm ? H0.base + (size_t)oi[u].x * H0.ld + (col - dm)
-                                                : ef + (size_t)oi[u].y * de + (col - 2 * dm);
-                  v[u] = *p;
+                  for (uint32_t u = 0; u < U; ++u) {
+                    const float* p = col < 2 * dm ? H0.base + (size_t)oi[u].x * H0.ld + (col - dm)
+                                                  : ef + (size_t)oi[u].y * de + (col - 2 * dm);
+                    v[u] = *p;
+                  }
+                } else {
+                  const uint32_t q = col - 2 * dm - de;
+                  const double om = d.om_rev[q], ph = d.ph_rev[q];
+                  double te[U];
+#pragma unroll
+                  for (uint32_t u = 0; u < U; ++u) te[u] = ts[oi[u].y];
+#pragma unroll
+                  for (uint32_t u = 0; u < U; ++u) v[u] = cos_rev64(om * (te[u] - s_tl[r]) + ph);
                 }
-              } else {
-                const uint32_t q = col - 2 * dm - de;
-                const double om = d.om_rev[q], ph = d.ph_rev[q];
-                double te[kMeanU];
 #pragma unroll
-                for (uint32_t u = 0; u < kMeanU; ++u) te[u] = ts[oi[u].y];
-#pragma unroll
-                for (uint32_t u = 0; u < kMeanU; ++u) v[u] = cos_rev64(om * (te[u] - s_tl[r]) + ph);
+                for (uint32_t u = 0; u < U; ++u) acc += j0 + u < n ? v[u] : 0.0f;
               }
-#pragma unroll
-              for (uint32_t u = 0; u < kMeanU; ++u) acc += j0 + u < n ? v[u] : 0.0f;
-            }
+              return acc;
+            };
+            const float acc = n == 1u ? sum(Together<1>{}) : sum(Together<kMeanU>{});
             val = acc / (float)n;
           }
         }

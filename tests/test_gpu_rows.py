@@ -120,6 +120,32 @@ def test_aggregated_messages_of_a_hub(n, aggregator):
     g.close()
 
 
+def test_rows_of_one_slot_do_the_work_of_one():
+    """Mean over 1,000 rows: with one slot a row takes one cosine and one load per column, with eight it takes eight.  The launches
+    were 31 and 41 us; 38 and 40 when every row went through eight places, 35 and 97 one slot at a time."""
+    import torch
+    from paper_2603_21090_amd import binding
+    rows, best = 1_000, {}
+    for slots in (1, 8):
+        n = rows * slots // 2
+        w = tiny_workload(num_nodes=60_000, num_edges=200_000, batch=n, k=10, layers=1, d_mem=100, d_edge=172, d_time=100,
+                          d_emb=100, d_msg=100, aggregator=1)
+        g = binding.StreamTGN.from_workload(w, synth.make_weights(w), max_edges=24 * n)
+        gen, us = np.random.default_rng(slots), []
+        for b in range(24):
+            ends = np.repeat(gen.permutation(w.num_nodes)[:rows].astype(np.int32), slots)
+            batch = (ends[:n], ends[n:], b + np.sort(gen.random(n)), gen.standard_normal((n, w.d_edge), dtype=np.float32))
+            batch = [torch.from_numpy(x.copy()).cuda() for x in batch]
+            torch.cuda.synchronize()
+            g.kernel_times(enable=True, reset=True)
+            g.ingest_batch(*batch)
+            g.sync()
+            us.append(g.kernel_times(enable=False, reset=True)["memory_update"]["usec"])
+        best[slots] = min(us)
+        g.close()
+    assert best[1] <= 0.87 * best[8], best
+
+
 @pytest.mark.parametrize("d_emb", [1, 62, 100, 252])
 def test_scores_at_edge_time_around_a_tile(d_emb):
     """A tile of the layer kernel holds eight edges: calls of other sizes give the same scores byte for byte, an id past the node
