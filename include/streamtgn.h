@@ -216,14 +216,14 @@ int stgn_set_predictor(stgn_ctx *ctx, const float *w, float b);
  * src, dst, ts, scores: [n], all on the host (inputs_on_device = 0; synchronises) or all on the
  * device (1; asynchronous on hip_stream).  n <= max_batch.  Needs stgn_set_predictor.  Host
  * inputs with an id >= num_nodes return STGN_E_NODE_OUT_OF_RANGE; device inputs give that edge
- * the score NaN.  Changes no state. */
+ * the score NaN.  scores may lie over ts, or begin where src or dst begins.  Changes no state. */
 int stgn_predict_batch(stgn_ctx *ctx, uint32_t n, const uint32_t *src, const uint32_t *dst,
                        const double *ts, int at_edge_time, int inputs_on_device, float *scores);
 
 /* stgn_predict_batch for callers that cannot allocate (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc): device inputs and outputs only, asynchronous on hip_stream,
- * and no allocation of any kind inside the call, nor any scratch: the kernels read the caller's arrays and
- * write the scores.  The size of a call is bounded as if the 2n roots, their query times and their rows
+ * and no allocation of any kind inside the call: the kernels read the caller's arrays (a copy of ts in the
+ * workspace where scores lies over it) and write the scores.  The size of a call is bounded as if the 2n roots, their query times and their rows
  * were kept in STGN_STATIC_SCRATCH_BYTES: n edges of d_emb-wide rows count 2n (4 + 8 + 4 d_emb) bytes (each of
  * the three lists rounded up to 256); a larger n returns STGN_E_BATCH_TOO_LARGE and enqueues nothing.
  * Same results as stgn_predict_batch with inputs_on_device = 1. */

@@ -853,6 +853,17 @@ int stgn_set_predictor(stgn_ctx* ctx, const float* w, float b) {
   return STGN_OK;
 }
 
+// Scores may lie over the call's own times.  A workgroup writes the scores of edges [8 t, 8 t + 8) over the times of
+// [4 t, 4 t + 4), which another one may not have read yet: then the kernel reads a copy of the times.  (Over the ids a
+// workgroup only writes where it alone reads, and it reads first.)
+static hipError_t times_clear_of_scores(const Dev& d, hipStream_t s, uint32_t n, const float* scores, const double** ts) {
+  const uintptr_t w = reinterpret_cast<uintptr_t>(scores), r = reinterpret_cast<uintptr_t>(*ts);
+  if (w >= r + (size_t)n * sizeof(double) || r >= w + (size_t)n * sizeof(float)) return hipSuccess;
+  const hipError_t e = hipMemcpyAsync(d.pred_ts, *ts, (size_t)n * sizeof(double), hipMemcpyDefault, s);
+  *ts = d.pred_ts;
+  return e;
+}
+
 int stgn_predict_batch(stgn_ctx* ctx, uint32_t n, const uint32_t* src, const uint32_t* dst, const double* ts,
                        int at_edge_time, int inputs_on_device, float* scores) {
   if (!ctx) return STGN_E_INVALID_ARG;
@@ -875,6 +886,7 @@ int stgn_predict_batch(stgn_ctx* ctx, uint32_t n, const uint32_t* src, const uin
     dsrc = d.pred_src; ddst = d.pred_dst; dts = d.pred_ts; dout = d.pred_scores;
   }
   ctx->idle = false;
+  if (at_edge_time) HIPCHK(ctx, times_clear_of_scores(d, s, n, dout, &dts));
   {
     Scope t(ctx, KC_PREDICT);
     if (at_edge_time) launch_layer_scores(d, s, n, dsrc, ddst, dts, dout);
@@ -911,6 +923,7 @@ int stgn_predict_batch_static(stgn_ctx* ctx, uint32_t n, const uint32_t* src, co
   // the same kernels as stgn_predict_batch, on the caller's own arrays
   hipStream_t s = ctx->stream;
   ctx->idle = false;
+  if (at_edge_time) HIPCHK(ctx, times_clear_of_scores(ctx->d, s, n, scores, &ts));
   if (at_edge_time) launch_layer_scores(ctx->d, s, n, src, dst, ts, scores);
   else launch_predict_head(ctx->d, s, n, src, dst, scores);
   HIPCHK(ctx, hipGetLastError());

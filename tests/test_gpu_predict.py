@@ -126,3 +126,42 @@ def test_predict_argument_errors_and_dead_rows(binding):
         assert np.isnan(got[3]) and np.array_equal(np.delete(got, 3), np.delete(ref, 3))
     g.sync()
     g.close()
+
+
+@pytest.mark.parametrize("entry", ["stgn_predict_batch", "stgn_predict_batch_static"])
+def test_scores_over_the_calls_own_arrays(binding, entry):
+    """Results placed over the times (from the start, in the middle, across either end) or over the ids of the same call, with far
+    more edges than workgroups hold at once: the scores of a call whose arrays are apart."""
+    import ctypes as C
+    import torch
+    w = tiny_workload(num_nodes=2_000, num_edges=9_000, batch=4_501, layers=1)
+    st = synth.EdgeStream(w)
+    g = binding.StreamTGN.from_workload(w, synth.make_weights(w))
+    g.set_predictor(np.random.default_rng(4).standard_normal(2 * w.d_emb).astype(np.float32), 0.5)
+    g.ingest_batch(*st.batch(0))
+    s, d, t, _ = st.batch(1)
+    n = len(s)
+    assert n > 4_000
+    sd, dd, td = (torch.from_numpy(x).cuda() for x in (s.astype(np.int32), d.astype(np.int32), t))
+
+    def score(at_edge_time, src, dst, ts, out):
+        torch.cuda.synchronize()
+        args = [C.c_void_p(p) for p in (src, dst, ts)] + [at_edge_time] + [1] * (entry == "stgn_predict_batch")
+        assert getattr(g._L, entry)(g._h, n, *args, C.c_void_p(out)) == 0 and g.sync() == 0
+    for mode in (0, 1):
+        want = torch.empty(n, device="cuda")
+        score(mode, sd.data_ptr(), dd.data_ptr(), td.data_ptr(), want.data_ptr())
+        assert bool(torch.isfinite(want).all())
+        for shift in (-5, -1, 0, 1, n // 2, n, n + 3, 2 * n - 1):    # floats between the first time and the first score
+            buf = torch.zeros(4 * n + 16, device="cuda")
+            at = 6                                                  # (times on 8-byte addresses)
+            buf[at:at + 2 * n] = td.view(torch.float32)
+            score(mode, sd.data_ptr(), dd.data_ptr(), buf.data_ptr() + 4 * at, buf.data_ptr() + 4 * (at + shift))
+            assert torch.equal(buf[at + shift:at + shift + n], want), (mode, shift)
+        over = sd.clone()
+        score(mode, over.data_ptr(), dd.data_ptr(), td.data_ptr(), over.data_ptr())
+        assert torch.equal(over.view(torch.float32), want), mode
+        over = dd.clone()
+        score(mode, sd.data_ptr(), over.data_ptr(), td.data_ptr(), over.data_ptr())
+        assert torch.equal(over.view(torch.float32), want), mode
+    g.close()
