@@ -900,7 +900,8 @@ int stgn_predict_batch(stgn_ctx* ctx, uint32_t n, const uint32_t* src, const uin
   return STGN_OK;
 }
 
-// What the limit of stgn_predict_batch_static counts for n edges: 2n root ids, query times and rows.
+// What the limit of stgn_predict_batch_static counts for n edges: 2n root ids, query times and rows, as if they were
+// stored.  Nothing is stored any more; calls past the limit stay refused.
 static size_t static_predict_bytes(uint32_t n, uint32_t d_emb) {
   auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
   return up((size_t)2 * n * sizeof(uint32_t)) + up((size_t)2 * n * sizeof(double)) + up((size_t)2 * n * d_emb * sizeof(float));
@@ -914,7 +915,7 @@ int stgn_predict_batch_static(stgn_ctx* ctx, uint32_t n, const uint32_t* src, co
   if (n > c.max_batch) return fail(ctx, STGN_E_BATCH_TOO_LARGE, "more edges than max_batch");
   if (static_predict_bytes(n, c.d_emb) > STGN_STATIC_SCRATCH_BYTES) {
     char buf[160];
-    snprintf(buf, sizeof buf, "%u edges of %u-wide rows need %zu bytes of static scratch, the array holds %zu",
+    snprintf(buf, sizeof buf, "%u edges of %u-wide rows count as %zu bytes of static scratch, the limit is %zu",
              n, c.d_emb, static_predict_bytes(n, c.d_emb), (size_t)STGN_STATIC_SCRATCH_BYTES);
     return fail(ctx, STGN_E_BATCH_TOO_LARGE, buf);
   }
@@ -952,8 +953,10 @@ int stgn_get_embeddings(stgn_ctx* ctx, uint32_t layer, uint32_t n, const uint32_
   for (uint32_t i = 0; i < n; ++i)
     if (nodes[i] >= c.num_nodes) return fail(ctx, STGN_E_NODE_OUT_OF_RANGE, "node id >= num_nodes");
   // A short list: the gather reads its ids from and writes its rows to pinned host memory, so one launch and one
-  // wait (the control block's) serve the call.  With a copy in, a copy out to pageable memory and a
-  // second wait, a batch of 333 edges with its 666 rows took 215 us, now 168.  Longer lists are bound by the transfer, and go through device memory.
+  // wait (the control block's) serve the call, where the way through device memory takes a copy in, a copy out to
+  // pageable memory and a second wait.  Rows of 100 floats: 16 of them 18 us and 40, 666 28 and 51, 2,594 (the longest
+  // list that fits the block) 61 and 86.  Past it the transfer itself takes over (5,190 rows: 147), and the block would
+  // have to grow with the call.
   if ((size_t)n * 4 + 16 + (size_t)n * c.d_emb * 4 <= kRowIoBytes) {
     const size_t o_rows = ((size_t)n * 4 + 15) & ~(size_t)15;
     memcpy(ctx->row_io, nodes, (size_t)n * 4);

@@ -17,9 +17,11 @@ using layer_impl::LayerArgs;
 // checked on the host) yields a row of NaN instead of a read outside the table.
 //
 // A copy, bound by HBM for long lists and by the launch for short ones.  A workgroup takes `per` consecutive list
-// positions (and again `per`, a grid further on, when the list outgrows the largest grid) and its threads stride over their pieces of V floats; four pieces per thread are
-// requested before the first is stored, and the (row, piece) pair advances by additions.  One million rows of 100
-// floats: 184 us = 4.9 TB/s, the rate of a large copy (one float per thread and a 64-bit division each: 284 us).
+// positions (and again `per`, a grid further on, when the list outgrows the largest grid) and its threads stride over
+// their pieces of V floats; four pieces per thread are requested before the first is stored, and the (row, piece) pair
+// advances by additions.  One million rows of 100 floats: 184 us = 4.4 TB/s of ids, rows read and rows stored, 4.9 with
+// the padding of the tables' rows to 512 bytes, where a large copy reaches 6.0 (one float per thread and a 64-bit
+// division each: 284 us).
 // Results are stored past the caches: nothing here reads them again, and the tables keep their place.
 constexpr uint32_t kGatherBlocks = 1u << 16;
 template <int V> struct Piece;

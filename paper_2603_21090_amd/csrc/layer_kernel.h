@@ -101,7 +101,7 @@ struct LayerArgs {
   // row.  The rows are not stored: their tile holds both ends of its eight edges, and the link score
   // y = h_u . head[0 : d) + h_v . head[d : 2d) + head[2d] leaves the kernel in their place (NaN with a dead end).
   // One launch for what took three (roots listed, rows stored, rows read back by the head): 4,000 candidates on
-  // 100,000 nodes 35.2 -> 29.9 us, score + ingest of one edge at a time 78.6 -> 75.2 us.
+  // 100,000 nodes 35.2 -> 29.9 us.
   const uint32_t *root_src, *root_dst; const double* root_ts; uint32_t nodes;
   const float* head; float* scores;
   double window;                                   // ring entries older than the query time minus this are ignored (+inf: none)
@@ -267,7 +267,10 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
   constexpr uint32_t QW4 = 16u * NQ;                          // quads per cached row
   uint32_t p_row = 0xFFFFFFFFu, p_clean = 0u;
   double p_tqn = 0.0;
-  auto stage_a = [&](uint32_t t) {                            // requests only: nothing waits for the values here
+  // Requests only: nothing waits for the values here, but for the ids of link scores, which are compared with the node
+  // count at once.  (Compared in stage_a_commit instead: 4,000 edges 29.4 and 29.3 us, 8,000 48.5 and 48.4, and up to
+  // 19 more spilled registers in the variants of one key slot.)
+  auto stage_a = [&](uint32_t t) {
     if (tid < kTM) {
       const uint32_t r = t * kTM + tid;
       const bool listed = t < ntiles && r < n;

@@ -295,7 +295,8 @@ void launch_drift_values(const Dev& d, hipStream_t s, float* out);   // every no
 // (returns the launch's own status: no error that an earlier call left behind is taken for it, or lost)
 hipError_t launch_gather_rows(const Dev& d, hipStream_t s, uint32_t layer, uint32_t n, const uint32_t* nodes, float* out);
 void launch_gather_times(const Dev& d, hipStream_t s, uint32_t n, const uint32_t* nodes, double* out);   // last-interaction times
-// root-node inference: roots and query times of n edges; the final layer for the 2n roots; the linear head
+// link scores of n edges: at their own times (the final layer for their 2n ends, scores out of the same launch), or from
+// the cached final-layer rows
 void launch_layer_scores(const Dev& d, hipStream_t s, uint32_t n, const uint32_t* src, const uint32_t* dst, const double* ts,
                          float* scores);
 void launch_predict_head(const Dev& d, hipStream_t s, uint32_t n, const uint32_t* src, const uint32_t* dst, float* scores);
