@@ -1,11 +1,13 @@
-"""The prediction entry point that allocates nothing (static device scratch) against the ordinary one:
-same kernels, so the scores must agree bit for bit -- on two calls in a row, the second with a smaller
-input, so that whatever the first call left in the shared scratch array would show."""
+"""The prediction entry point that allocates nothing, against the CPU oracle (the bar of tests/test_gpu_predict.py) and bit for
+bit against the ordinary entry point, which launches the same kernels -- on two calls in a row, the second with a smaller
+input; and the size limit it has always had."""
 import numpy as np
 import pytest
 
+from oracle import oracle as orc
 from paper_2603_21090_amd import synth
 from tests.helpers import tiny_workload
+from tests.test_gpu_predict import score_bound
 
 pytestmark = pytest.mark.gpu
 
@@ -28,10 +30,13 @@ def test_static_scratch_prediction_matches_the_ordinary_entry_point(binding, kw)
     import torch
     w = tiny_workload(num_nodes=200, num_edges=2400, batch=120, zipf_s=1.0, **kw)
     st = synth.EdgeStream(w)
-    g = binding.StreamTGN.from_workload(w, synth.make_weights(w), synth.node_features(w))
+    W, nf = synth.make_weights(w), synth.node_features(w)
+    o, g = orc.Oracle.from_workload(w, W, nf), binding.StreamTGN.from_workload(w, W, nf)
     rng = np.random.default_rng(9)
-    g.set_predictor((rng.standard_normal(2 * w.d_emb) / np.sqrt(w.d_emb)).astype(np.float32), 0.125)
+    wp = (rng.standard_normal(2 * w.d_emb) / np.sqrt(w.d_emb)).astype(np.float32)
+    g.set_predictor(wp, 0.125)
     for b in range(12):
+        assert o.ingest(*st.batch(b))[0] == 0
         g.ingest_batch(*st.batch(b))
     g.sync()
 
@@ -51,6 +56,9 @@ def test_static_scratch_prediction_matches_the_ordinary_entry_point(binding, kw)
             want, got = want.cpu().numpy(), got.cpu().numpy()
             assert np.isfinite(want).all()
             assert np.array_equal(got, want), f"mode {mode}, n {len(want)}: worst {np.abs(got - want).max():.3e}"
+            s, d, t = (a.cpu().numpy() for a in args)
+            ref = o.predict(s.astype(np.uint32), d.astype(np.uint32), t, wp, 0.125, at_edge_time=mode)
+            assert (np.abs(got - ref) <= score_bound(o, w, wp, s, d)).all(), f"mode {mode}, n {len(ref)}: worst {np.abs(got - ref).max():.3e}"
     # an id past the node count scores NaN, as in the ordinary call; the others are unaffected
     s, d, t = dev(14, 50)
     s2 = s.clone(); s2[7] = w.num_nodes + 5
@@ -62,7 +70,7 @@ def test_static_scratch_prediction_matches_the_ordinary_entry_point(binding, kw)
 
 
 def test_static_scratch_limit_is_enforced(binding):
-    """More roots than the static array holds: a clear error, nothing enqueued."""
+    """More edges than the limit counts for (2 n root ids, query times and rows in 4 MiB): a clear error, nothing enqueued."""
     import torch
     w = tiny_workload(num_nodes=64, num_edges=256, batch=64, layers=1, d_mem=8, d_edge=4, d_time=8, d_emb=256, d_msg=8,
                       heads=4, k=2)
