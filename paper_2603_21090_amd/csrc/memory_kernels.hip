@@ -124,9 +124,9 @@ __global__ __launch_bounds__(kThreads) void memory_update_kernel(Dev d, const ui
       // message is mean(x) W_msg + b_msg and the sum is the slot count times that.  The node's own
       // memory is the same in every one of its inputs and is staged as it is.
       // A slot is three dependent reads (slot, partner, the partner's row), and a hub owns a tenth of a batch's
-      // slots: taken one at a time, a tile with a hub was a chain of 3 latencies per slot, 151 us of a launch for 500
+      // slots: taken one at a time, a tile with a hub was a chain of 3 latencies per slot, 162 us of a launch for 500
       // edges.  The first kMeanPre slots of every row are resolved at once, one per thread, and the values are
-      // requested kMeanU at a time and added in slot order: 105 us beside the layer kernel, batch 319 -> 278 us.
+      // requested kMeanU at a time and added in slot order: 120 us (both beside the layer kernel), batch 314 -> 275 us.
       // Most rows of a batch hold one slot: theirs is requested alone, since seven repeated cosines and loads per
       // column cost a launch of 1,000 such rows 38.8 us where one at a time took 35.1 (31.6 now; two slots 43.5 one at a
       // time, 40.0 now; eight 97, 41).
