@@ -10,11 +10,12 @@
 // Edge features of at most one 64-float slot are not cached at all (ES variants): the raw row rides with the
 // time encoding, z_j = [phi_j | e_j] in place of phi_j and W[time | edge] in place of W[time] above, and the
 // cached rows hold the node terms alone.
-// A workgroup of four waves owns 16 target rows and runs its phases without leaving the CU:
+// A workgroup of eight waves (four: rows of one slot, delta mode) owns 16 target rows and runs its phases without
+// leaving the CU:
 //   1. q  = h_v W_Q(node block) + phi(0) W_Q(time block)                           (MFMA 16x16x4)
 //   2. qt_h = q_h W_K,h[time]^T, kept in LDS                                        (MFMA)
 //   3. gather the cached rows of the ring entries, time encodings, scores, softmax, weighted sums;
-//      one wave serves four rows, 16 lanes x float4 per 64-float slot                (HBM / vector ALU)
+//      a row is served by one 16-lane group per key slot, lane x float4               (HBM / vector ALU)
 //   4. o_h += pb_h W_V,h[time]                                                       (MFMA)
 //   5. h_v' = [o_1 | .. | o_H] W_O + b_O, written into the layer cache               (MFMA)
 //   6. unless this is the last layer: the row's own cached keys|values for the next layer,
@@ -127,13 +128,43 @@ struct LayerArgs {
   DriftCtl* drift; float* dsum; uint32_t* dlast; uint8_t* dseen;
 };
 
-// cached rows (node and edge, keys and values) of one chunk of JC ring entries, one float4 per lane and slot;
-// ES: the edge's raw feature row (one slot) instead of its cached row
-template <int JC, int KS, int ES>
+// One 16-lane group's share of the cached rows of JC ring entries, one float4 per lane and piece: the neighbour's key slot
+// and value slot, the edge's likewise (ES: the edge's raw feature row, one slot, instead), and the entry's time.
+template <int JC, int ES>
 struct GatherBuf {
-  float4 n[JC][2 * KS];
-  float4 e[JC][ES ? 1 : 2 * KS];
+  float4 nk[JC], nv[JC];
+  float4 e[JC][ES ? 1 : 2];
+  double t[JC];
 };
+
+// exchanges between the 16-lane groups of a wave: {groups 0 and 2, groups 1 and 3} of x, each in both groups of its pair;
+// {lanes 0 - 31, lanes 32 - 63} of x, each in both halves
+struct Two { float lo, hi; };
+__device__ inline Two both_of_pair(float x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, x), false, false);
+  return {__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1])};
+}
+__device__ inline Two both_halves(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, x), false, false);
+  return {__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1])};
+}
+
+// what the compiler may not move across a wave's own LDS traffic (the LDS serves one wave's requests in order)
+__device__ inline void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Waves of a workgroup.  Rows of two and four key slots: eight waves of at most 128 registers, two workgroups per CU;
+// rows of one slot and the delta mode: four.  What bounds the kernel is the latency of a tile's dependent phases, so what
+// counts is waves in flight and work per wave.  With one 16-lane group per row (all slots of all heads in one lane) a wave
+// needed 240 registers, eight waves fitted a CU, and the time parameters and qt went through LDS once per entry; with
+// a group per slot it needs 117 - 128, sixteen fit, and the entry loop reads nothing from LDS but the ring
+// record.  Layer launches before and after: 100,000 nodes, d_edge 172, 197 -> 173 us; 1,000,000 nodes, d_edge 100,
+// 1,087 -> 971 and (query cache) 1,054 -> 1,012; 1,300,000 nodes, raw edge rows, k = 20, 1,053 -> 973; four
+// heads of 32, 20,000 nodes, 110 -> 75; 10,000 nodes, one tile per workgroup, 33 -> 31.
+__host__ __device__ constexpr int layer_waves(int ks, bool delta) { return delta || ks == 1 ? 4 : 8; }
 
 // KS key slots in total (heads x slots per head), NT time slots; JC ring entries fetched together.
 // ES = 1: raw edge rows.  The vector z_j = [phi(dt_j) | f_j] of NZ = NT + 1 slots takes the place of phi(dt_j)
@@ -141,16 +172,22 @@ struct GatherBuf {
 // W_V,h[time | edge]), and the cached rows hold the node parts alone.
 // DELTA: the approximate mode of Sec. 3.3 "Stage 4" (attention cache, delta update of changed entries).
 // QCACHE: the query cache is in use (rows may read q and qt back, rows that project store theirs).
-// ROOTS: root-node inference (LayerArgs::root_src and on).  A variant of its own and not a test at run time: the seven
-// places that differ cost every streamed launch registers it does not have.  Two heads of one slot, two time slots, raw
-// edge rows, query cache: 11 spilled vector and 119 spilled scalar registers with the test, 2 and 92 without; a
-// layer launch of 1.3 million nodes (k = 20, batches of 2,000) 436 us with it, 398 without.
+// ROOTS: root-node inference (LayerArgs::root_src and on).  A variant of its own and not a test at run time: the
+// places that differ would cost every streamed launch registers.
 template <int KS, int NT, int ES, int H, int JC, int WGS, bool DELTA, bool QCACHE, bool ROOTS>
-__global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows,
-                                                         const uint32_t* count_ptr, uint32_t count_max) {
+__global__ __launch_bounds__(64 * layer_waves(KS, DELTA), WGS * layer_waves(KS, DELTA) / 4)
+void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t* count_ptr, uint32_t count_max) {
   extern __shared__ __align__(16) float lds[];
-  __shared__ uint32_t s_node[kTM], s_cnt[kTM], s_next[kTM], s_ex[kTM], s_cleann;
-  __shared__ double s_tq[kTM], s_tqn[ROOTS ? kTM : 1u];
+  constexpr int NW = layer_waves(KS, DELTA);  // waves
+  constexpr uint32_t TH = 64u * NW;           // threads
+  constexpr int NTL = 8 / NW;                 // column tiles a wave multiplies together in the dense phases
+  constexpr int RPW = (int)kTM / NW;          // rows a wave serves
+  constexpr uint32_t LS = 64u / RPW;          // lanes per row while the rows are staged
+  constexpr int NI = NTL;                     // ring slots and input quads per lane that are fetched a tile ahead
+  constexpr int GPR = DELTA ? 1 : KS;         // 16-lane groups per row in phase 3: one per key slot
+  constexpr int RPP = 4 / GPR;                // rows a wave works on at a time there
+  constexpr int PASSES = RPW / RPP;
+  __shared__ uint32_t s_node[2][kTM], s_sum[NW];
   __shared__ __align__(16) double s_om[NT * kSlot], s_ph[NT * kSlot];
   static_assert(KS % H == 0, "whole slots per head");
   static_assert(!(DELTA && ES), "the delta mode keeps projected edge rows");
@@ -163,10 +200,11 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
   uint32_t n = count_max;
   if (count_ptr) { const uint32_t c = *count_ptr; n = c < count_max ? c : count_max; }
   const uint32_t ntiles = (n + kTM - 1) / kTM;
-  // Per-lane indices and everything derived from them are re-derived at the top of every tile from an
-  // opaque copy of the thread index: otherwise the compiler hoists dozens of loop-invariant address
-  // registers out of the persistent tile loop and keeps them alive (or spilled) across all phases.
-  uint32_t tid = threadIdx.x, lane = tid & 63u, sub = lane & 15u, grp = lane >> 4;
+  if (blockIdx.x >= ntiles) return;           // (a workgroup's first tile is the one of its index)
+  // The lane index and everything derived from it are derived anew at the top of every tile and of its phases, from
+  // the lane counter and behind the compiler's back: otherwise it hoists dozens of loop-invariant address registers out
+  // of the persistent tile loop and keeps them alive (or spilled) across all phases.
+  uint32_t lane, sub, grp;
   // wave index, made provably uniform so that tile indices and weight addresses stay in scalar registers
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const uint32_t k = a.k, dk = a.dk;
@@ -176,48 +214,41 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
   constexpr uint32_t ntz = Ztp >> 4;                                                                       // tiles of a qt vector
   const uint32_t nzt_t = (a.d_time + 15u) >> 4, nzt = nzt_t + (ES ? (a.d_edge + 15u) >> 4 : 0u);           // ... that hold valid columns
   const LayerLds ll = layer_lds(a.d_in, H, KS, NZ, k, DELTA);
-  float* Xs = lds;                            // input rows (phases 0-1), then head outputs (phases 3-5)
-  float* Qs = lds + ll.off_q;                 // q (phases 1-3), then the output rows (phases 5-6)
+  float* Xs = lds;                            // input rows (phases 0-1), later the output rows (phases 5-6) ...
+  float* Qs = lds + ll.off_q;                 // q (phases 1-3), then head outputs (phases 3-5) ... or the other way round
   float* Zs = lds + ll.off_z;                 // qt (phases 2-3), then pb (phases 3-4)
   RingEntry* Rs = reinterpret_cast<RingEntry*>(lds + ll.off_r);   // [row][j], j = 0 the most recent entry
-  using ZBuf = GatherBuf<JC, KS, ES>;
+  using ZBuf = GatherBuf<JC, ES>;
 
-  // ---- per-lane constants
   // time-encoding parameters (omega, phase in revolutions) live in LDS, zero past d_time
-  for (uint32_t q = threadIdx.x; q < NT * kSlot; q += 256) {
+  for (uint32_t q = threadIdx.x; q < NT * kSlot; q += TH) {
     s_om[q] = q < a.d_time ? a.om_rev[q] : 0.0;
     s_ph[q] = q < a.d_time ? a.ph_rev[q] : 0.0;
   }
   // operand padding (columns nobody writes) must be finite: clear the tiles once
-  for (uint32_t x = threadIdx.x; x < ll.off_r; x += 256) lds[x] = 0.0f;
-  uint32_t gathered = 0;
+  for (uint32_t x = threadIdx.x; x < ll.off_r; x += TH) lds[x] = 0.0f;
+  uint32_t gathered = 0;                      // ring entries of this wave's rows
   double drift_sum = 0.0;                     // delta mode: this wave's share of the drift estimator's sum and member count
   uint32_t drift_new = 0;
-  uint32_t a_x, a_q, a_z, c_off_x, c_off_q, c_off_z;
   auto derive_lane = [&]() {
-    asm volatile("" : "+v"(tid));
-    lane = tid & 63u; sub = lane & 15u; grp = lane >> 4;
-    a_x = (lane & 15u) * ll.ldx + 4u * (lane >> 4);
-    a_q = (lane & 15u) * ll.ldq + 4u * (lane >> 4);
-    a_z = (lane & 15u) * ll.ldz + 4u * (lane >> 4);
-    c_off_x = (4u * (lane >> 4)) * ll.ldx + (lane & 15u);
-    c_off_q = (4u * (lane >> 4)) * ll.ldq + (lane & 15u);
-    c_off_z = (4u * (lane >> 4)) * ll.ldz + (lane & 15u);
+    uint32_t x;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(x));
+    lane = x; sub = x & 15u; grp = x >> 4;
   };
   derive_lane();
 
-  // ---- phase-2 work units: (head, pair of valid qt column tiles); wave w owns units w, w + 4, ...
-  // Lane i of `udesc` holds the description of the wave's i-th unit (head, first tile, whether a
-  // second tile follows), worked out once; inside the tile loop a unit costs one cross-lane read.
-  const uint32_t npr = (nzt + 1u) >> 1, nunits2 = H * npr;
-  const uint32_t nu2 = wave < nunits2 ? (nunits2 - wave + 3u) >> 2 : 0u;     // units of this wave
+  // ---- phase-2 work units: (head, NTL valid qt column tiles); wave w owns units w, w + NW, ...
+  // Lane i of `udesc` holds the description of the wave's i-th unit (head, first tile, second tile, whether there is a
+  // second one), worked out once; inside the tile loop a unit costs one cross-lane read.
+  const uint32_t npr = (nzt + NTL - 1u) / NTL, nunits2 = H * npr;
+  const uint32_t nu2 = wave < nunits2 ? (nunits2 - wave + (NW - 1u)) / NW : 0u;     // units of this wave
   struct Unit2 { uint32_t h, t0, t1; bool two; };
   uint32_t udesc = 0;
   if (lane < nu2) {
     // the i-th valid tile: time tiles first, then (raw edge rows) the tiles of slot NT
     auto vt = [&](uint32_t i) { return i < nzt_t ? i : 4u * NT + (i - nzt_t); };
-    const uint32_t x = wave + 4u * lane, h = x / npr, i0 = 2u * (x - h * npr);
-    const uint32_t two = i0 + 1u < nzt ? 1u : 0u;
+    const uint32_t x = wave + NW * lane, h = x / npr, i0 = NTL * (x - h * npr);
+    const uint32_t two = NTL == 2 && i0 + 1u < nzt ? 1u : 0u;
     udesc = h | (vt(i0) << 8) | (vt(i0 + two) << 16) | (two << 24);
   }
   auto decode2 = [&](uint32_t i) {
@@ -227,117 +258,97 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
     return u;
   };
   auto wkt = [&](uint32_t h, uint32_t t) { return a.WKT + (size_t)(h * ntz + t) * g_dk * kGrpFloats; };
-  auto store2 = [&](const Unit2& u, const floatx4 (&acc)[2]) {
-    float* zp = Zs + u.h * Ztp + c_off_z;
+  auto request2 = [&](const Unit2& u, Ops16<NTL>& o) {
+    load_b16(wkt(u.h, u.t0), 0, o.b[0], lane);
+    if constexpr (NTL == 2) load_b16(wkt(u.h, u.t1), 0, o.b[1], lane);
+  };
+  auto store2 = [&](const Unit2& u, const floatx4 (&acc)[NTL]) {
+    float* zp = Zs + u.h * Ztp + m16_row(lane, 0) * ll.ldz + m16_col(lane);
 #pragma unroll
     for (int r = 0; r < 4; ++r) zp[u.t0 * 16 + r * ll.ldz] = acc[0][r];
-    if (u.two) {
+    if constexpr (NTL == 2) {
+      if (u.two) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) zp[u.t1 * 16 + r * ll.ldz] = acc[1][r];
+        for (int r = 0; r < 4; ++r) zp[u.t1 * 16 + r * ll.ldz] = acc[1][r];
+      }
     }
   };
-  // ---- phase-4 work units: (head, pair of head-output column tiles)
-  const uint32_t np4 = (ntk + 1u) >> 1, nunits4 = H * np4;
-  // ---- phases 1 and 5: column tiles nt and nt + 4 of the d_emb outputs form a unit; the bias values of
+  // ---- phase-4 work units: (head, NTL head-output column tiles)
+  const uint32_t np4 = (ntk + NTL - 1u) / NTL, nunits4 = H * np4;
+  // ---- phases 1 and 5: column tiles nt (and nt + 4) of the d_emb outputs form a unit; the bias values of
   // a wave's first unit stay in registers (further units, d_emb > 128, read theirs when they get there)
-  float cq_r[2], bo_r[2];
+  float cq_r[NTL], bo_r[NTL];
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const uint32_t col = (wave + 4 * t) * 16 + m16_col(lane);
+  for (int t = 0; t < NTL; ++t) {
+    const uint32_t col = (wave + NW * t) * 16 + m16_col(lane);
     cq_r[t] = col < a.d_emb ? a.cQ[col] : 0.0f;
     bo_r[t] = col < a.d_emb ? a.bO[col] : 0.0f;
   }
+  // column tile of a product's t-th operand: past the end the unit's first tile again (its result is not stored)
+  auto tile_b = [&](const float* W, uint32_t nt, int t, uint32_t limit, uint32_t groups) {
+    const uint32_t x = nt + NW * t < limit ? nt + NW * t : nt;
+    return W + (size_t)x * groups * kGrpFloats;
+  };
   __syncthreads();
 
-  // ---- staging of a tile, one tile ahead.  Stage A requests the tile's row ids (ahead of phase 1) and
-  // puts them into s_next once they are there (end of phase 2); stage B (issued with the first gathers of
-  // phase 3, whose waits cover it: a later wait for a weight chunk would stall on it, loads return in
-  // order) fetches, into registers, this thread's
-  // share of the rows' ring slots, degrees, query times and own input rows; the tile's phase 0 then
-  // only moves registers into LDS.  A workgroup strides over many tiles, so all but its first tile
-  // start without waiting for memory.  Shapes whose share does not fit two items per thread stage
-  // inside phase 0 instead.
+  // ---- staging of a tile, one tile ahead, every wave its own rows: lane -> (row lane / LS of the wave's, item lane % LS).
+  // Stage A requests the rows' ids (ahead of phase 1).  Stage B (issued with the first gathers of phase 3, whose waits
+  // cover it: a later wait for a weight chunk would stall on it, loads return in order) fetches, into registers, the
+  // lane's share of the rows' ring slots, degrees, query times and own input rows; the tile's phase 0 then only moves
+  // registers into LDS.  A workgroup strides over many tiles, so all but its first tile start without waiting for
+  // memory.  Shapes whose share does not fit the registers stage inside phase 0 instead.
   const uint32_t qpr = round_up(a.d_in, kGrpK) >> 2;          // 16-byte quads per staged input row
   const bool pf_ok = kTM * k <= 512u && kTM * qpr <= 512u;
-  RingEntry p_ring[2];
-  uint32_t p_deg[2];
-  double p_tl[2];
-  float4 p_x[2];                                              // own input rows (not fetched for a tile that reads q | qt back)
-  constexpr int NQ = KS + H * NZ;                             // quads per thread of a tile's cached q | qt rows
-  constexpr uint32_t QW4 = 16u * NQ;                          // quads per cached row
+  RingEntry p_ring[NI];
+  uint32_t p_deg = 0;
+  double p_tl = 0.0;
+  float4 p_x[NI];                                             // own input rows (not fetched for a tile that reads q | qt back)
+  constexpr uint32_t kQC = kSlot * (KS + H * NZ);             // floats per cached q | qt row
   uint32_t p_row = 0xFFFFFFFFu, p_clean = 0u;
   double p_tqn = 0.0;
-  // Requests only: nothing waits for the values here, but for the ids of link scores, which are compared with the node
-  // count at once.  (Compared in stage_a_commit instead: 4,000 edges 29.4 and 29.3 us, 8,000 48.5 and 48.4, and up to
-  // 19 more spilled registers in the variants of one key slot.)
+  // (requests only, but for the ids of link scores, which are compared with the node count at once)
   auto stage_a = [&](uint32_t t) {
-    if (tid < kTM) {
-      const uint32_t r = t * kTM + tid;
-      const bool listed = t < ntiles && r < n;
-      if constexpr (ROOTS) {
-        p_row = listed ? ((r & 1u) ? a.root_dst : a.root_src)[r >> 1] : 0xFFFFFFFFu;
-        p_row = p_row < a.nodes ? p_row : 0xFFFFFFFFu;
-        p_tqn = listed ? a.root_ts[r >> 1] : 0.0;
-      } else {
-        p_row = listed ? (rows ? rows[r] : r) : 0xFFFFFFFFu;
-      }
-      if constexpr (QCACHE) { if (tid == 0) p_clean = t < ntiles ? (a.all_clean ? 1u : a.tile_clean ? a.tile_clean[t] : 0u) : 0u; }
+    const uint32_t r = t * kTM + wave * RPW + lane / LS;
+    const bool listed = t < ntiles && r < n;
+    const uint32_t rc = listed ? r : 0u;
+    if constexpr (ROOTS) {
+      p_row = ((rc & 1u) ? a.root_dst : a.root_src)[rc >> 1];
+      p_row = listed && p_row < a.nodes ? p_row : 0xFFFFFFFFu;
+      p_tqn = a.root_ts[rc >> 1];
+    } else {
+      p_row = rows ? rows[rc] : rc;
+      p_row = listed ? p_row : 0xFFFFFFFFu;
     }
-  };
-  auto stage_a_commit = [&]() {
-    if (tid < kTM) {
-      s_next[tid] = p_row;
-      if constexpr (ROOTS) s_tqn[tid] = p_tqn;
-    }
-    if constexpr (QCACHE) { if (tid == 0) s_cleann = p_clean; }
+    if constexpr (QCACHE) p_clean = t < ntiles ? (a.all_clean ? 1u : a.tile_clean ? a.tile_clean[t] : 0u) : 0u;
   };
   auto stage_b = [&]() {
-    const bool cl = QCACHE && __builtin_amdgcn_readfirstlane((int)s_cleann) != 0;
+    const bool cl = QCACHE && __builtin_amdgcn_readfirstlane((int)p_clean) != 0;
+    const uint32_t it = lane % LS;
+    const size_t nn = p_row != 0xFFFFFFFFu ? p_row : 0u;
+    p_deg = a.deg[nn];
+    p_tl = ROOTS ? p_tqn : a.t_last[nn];
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const uint32_t x = tid + 256u * e;
-      {
-        const uint32_t xc = x < kTM * k ? x : 0u;
-        const uint32_t r = xc / k, sl = xc - r * k;
-        const uint32_t node = s_next[r];
-        const uint32_t nn = node != 0xFFFFFFFFu ? node : 0u;
-        p_ring[e] = a.ring[(size_t)nn * k + sl];
-        p_deg[e] = a.deg[nn];
-        p_tl[e] = a.t_last[nn];
-      }
-      if (!cl) {
-        const uint32_t xc = x < kTM * qpr ? x : 0u;
-        const uint32_t r = xc / qpr, q = xc - r * qpr;
-        const uint32_t node = s_next[r];
-        // columns past d_in are row padding of the table (zero)
-        p_x[e] = *reinterpret_cast<const float4*>(a.Hin + (size_t)(node != 0xFFFFFFFFu ? node : 0u) * a.ld_in + 4u * q);
-      } else {
-        p_x[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-      }
+    for (int e = 0; e < NI; ++e) {
+      const uint32_t sl = it + LS * e;
+      p_ring[e] = a.ring[nn * k + (sl < k ? sl : 0u)];
+    }
+#pragma unroll
+    for (int e = 0; e < NI; ++e) {
+      const uint32_t q = it + LS * e;
+      // columns past d_in are row padding of the table (zero)
+      if (!cl) p_x[e] = *reinterpret_cast<const float4*>(a.Hin + nn * a.ld_in + 4u * (q < qpr ? q : 0u));
+      else p_x[e] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
   };
-  // the record of adjacency position p sits in ring slot p mod k; with the row's degree known, slot
-  // sl holds the j-th most recent entry, j = (newest - sl) mod k; places past the row's entry count
-  // name node 0 / edge 0 (finite cached rows whose weight in every sum is zero)
-  auto place_ring = [&](uint32_t r, uint32_t sl, bool live, RingEntry e, uint32_t dg_in, double tl) {
-    const uint32_t dg = live ? dg_in : 0u;
-    const uint32_t cnt = dg < k ? dg : k;
-    const uint32_t newest = dg ? (dg - 1u) % k : 0u;
-    const uint32_t j = newest >= sl ? newest - sl : newest + k - sl;
-    if (j >= cnt) { e.nbr = 0u; e.eid = 0u; e.t = 0.0; }
-    Rs[r * k + j] = e;
-    if (sl == 0) { s_cnt[r] = cnt; s_tq[r] = ROOTS ? s_tqn[ROOTS ? r : 0u] : tl; }
-  };
-  stage_a(blockIdx.x);
-  stage_a_commit();
-  __syncthreads();
   auto stage_none = [&]() {                                   // keeps the registers defined on every path
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      p_ring[e].nbr = 0u; p_ring[e].eid = 0u; p_ring[e].t = 0.0; p_deg[e] = 0u; p_tl[e] = 0.0;
+    for (int e = 0; e < NI; ++e) {
+      p_ring[e].nbr = 0u; p_ring[e].eid = 0u; p_ring[e].t = 0.0;
+      p_x[e] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
-    p_x[0] = p_x[1] = make_float4(0.f, 0.f, 0.f, 0.f);
+    p_deg = 0u; p_tl = 0.0;
   };
+  stage_a(blockIdx.x);
   if (pf_ok) stage_b(); else stage_none();
 
   // Round i gives workgroup b the tile i G + (b + 37 i) mod G (G workgroups): every round is a permutation of
@@ -346,141 +357,158 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
   // the same workgroups every long tile.
   const uint32_t G = gridDim.x;
   auto tile_of = [&](uint32_t i) { return i * G + (blockIdx.x + 37u * i) % G; };
-  for (uint32_t round = 0;; ++round) {
-    const uint32_t tile = tile_of(round);
-    if (tile >= ntiles) break;                                // wave-uniform; only in a workgroup's last round
+  // A tile ends with a barrier only where its output rows are read back from LDS.  Otherwise a wave goes on to its next
+  // tile while others still read this tile's head outputs; tiles that read q | qt back then alternate between the
+  // two places for the head outputs, and all others have barriers ahead of what overwrites them.
+  const bool end_barrier = ROOTS || DELTA || a.KVout != nullptr;
+  bool o_in_x = false;                                        // the previous tile's head outputs lie in Xs
+  // One tile.  CLEAN: every row of it has its q and qt in the query cache.  Two copies of the body and not tests inside
+  // one: merged, the query cache's variants spilled 29 to 51 registers, and a spilled prefetch is waited for.
+  auto work_tile = [&](auto CLEAN, const uint32_t tile, const uint32_t round) __attribute__((always_inline)) {
+    constexpr bool clean = decltype(CLEAN)::value;
     derive_lane();
-    // every row of the tile has its q and qt in the query cache (set by the staging of a tile ago; uniform)
-    const bool clean = QCACHE && __builtin_amdgcn_readfirstlane((int)s_cleann) != 0;
+    uint32_t* nodes_s = s_node[round & 1u];
+    if (!clean && o_in_x) __syncthreads();
+    o_in_x = clean && !end_barrier && !o_in_x;
+    float* const Os = o_in_x ? Xs : Qs;                       // head outputs
+    float* const Hs = o_in_x ? Qs : Xs;                       // output rows
+    const uint32_t ldo = o_in_x ? ll.ldx : ll.ldq, ldh = o_in_x ? ll.ldq : ll.ldx;
     // ================================================================ phase 0: stage the tile
-    Ops16<2> oq;                                              // first weight chunk of this wave's first unit
+    Ops16<NTL> oq;                                            // first weight chunk of this wave's first unit
     const uint32_t w1 = wave < ntd ? wave : 0u;              // loads are unconditional (clamped), products are not
-    if (!clean) {
-      load_b16(a.WQ + (size_t)w1 * g_in * kGrpFloats, 0, oq.b[0]);
-      load_b16(a.WQ + (size_t)(w1 + 4 < ntd ? w1 + 4 : w1) * g_in * kGrpFloats, 0, oq.b[1]);
+    if constexpr (!clean) {
+#pragma unroll
+      for (int t = 0; t < NTL; ++t) load_b16(tile_b(a.WQ, w1, t, ntd, g_in), 0, oq.b[t], lane);
     }
-    if (tid < kTM) {
-      s_node[tid] = s_next[tid];
-      if constexpr (DELTA) {
-        // exact recomputation for endpoints of the batch (query time and entries moved), for rows whose own
-        // input row changed (every score moves), and whenever the caller asks for it
-        const uint32_t node = s_next[tid];
-        const uint32_t fl = node != 0xFFFFFFFFu ? a.flags[node] : 0u;
-        s_ex[tid] = (a.force_exact || fl == 1u || (fl != 0u && fl <= a.thr_in)) ? 1u : 0u;
-      }
+    const uint32_t node_s = p_row;                            // this lane's row while staging
+    const bool live_s = node_s != 0xFFFFFFFFu;
+    const uint32_t local_s = wave * RPW + lane / LS, it = lane % LS;
+    if (it == 0u) nodes_s[local_s] = node_s;
+    bool ex = false;
+    if constexpr (DELTA) {
+      // exact recomputation for endpoints of the batch (query time and entries moved), for rows whose own
+      // input row changed (every score moves), and whenever the caller asks for it
+      const uint32_t fl = live_s ? a.flags[node_s] : 0u;
+      ex = a.force_exact || fl == 1u || (fl != 0u && fl <= a.thr_in);
     }
+    uint32_t cnt_s, newest;
+    double tq_s;
+    auto row_facts = [&](uint32_t dg_in, double tl) {
+      const uint32_t dg = live_s ? dg_in : 0u;
+      cnt_s = dg < k ? dg : k;
+      newest = dg ? (dg - 1u) % k : 0u;
+      tq_s = tl;
+    };
+    // the record of adjacency position p sits in ring slot p mod k; with the row's degree known, slot
+    // sl holds the j-th most recent entry, j = (newest - sl) mod k; places past the row's entry count
+    // name node 0 / edge 0 (finite cached rows whose weight in every sum is zero)
+    auto place_ring = [&](uint32_t sl, RingEntry e) {
+      const uint32_t j = newest >= sl ? newest - sl : newest + k - sl;
+      if (j >= cnt_s) { e.nbr = 0u; e.eid = 0u; e.t = 0.0; }
+      Rs[local_s * k + j] = e;
+    };
+    auto place_x = [&](uint32_t q, float4 v) {
+      if (!live_s) v = make_float4(0.f, 0.f, 0.f, 0.f);
+      *reinterpret_cast<float4*>(Xs + local_s * ll.ldx + 4u * q) = v;
+    };
     if (pf_ok) {
       // everything was fetched a tile ago: registers -> LDS
+      row_facts(p_deg, p_tl);
 #pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        const uint32_t x = tid + 256u * e;
-        if (x < kTM * k) {
-          const uint32_t r = x / k, sl = x - r * k;
-          place_ring(r, sl, s_next[r] != 0xFFFFFFFFu, p_ring[e], p_deg[e], p_tl[e]);
-        }
-        if (!clean && x < kTM * qpr) {
-          const uint32_t r = x / qpr, q = x - r * qpr;
-          const float4 v = s_next[r] != 0xFFFFFFFFu ? p_x[e] : make_float4(0.f, 0.f, 0.f, 0.f);
-          *reinterpret_cast<float4*>(Xs + r * ll.ldx + 4u * q) = v;
-        }
+      for (int e = 0; e < NI; ++e) if (it + LS * e < k) place_ring(it + LS * e, p_ring[e]);
+      if constexpr (!clean) {
+#pragma unroll
+        for (int e = 0; e < NI; ++e) if (it + LS * e < qpr) place_x(it + LS * e, p_x[e]);
       }
+    } else {
+      const size_t nn = live_s ? node_s : 0u;
+      row_facts(a.deg[nn], ROOTS ? p_tqn : a.t_last[nn]);
+      for (uint32_t sl = it; sl < k; sl += LS) place_ring(sl, a.ring[nn * k + sl]);
+      if constexpr (!clean)
+        for (uint32_t q = it; q < qpr; q += LS) place_x(q, *reinterpret_cast<const float4*>(a.Hin + nn * a.ld_in + 4u * q));
     }
-    __syncthreads();
-    if (!pf_ok) {
-      // thread (row, slot) fetches its slot without waiting for the row's degree (both loads leave together)
-      for (uint32_t x = tid; x < kTM * k; x += 256) {
-        const uint32_t r = x / k, sl = x - r * k;
-        const uint32_t node = s_node[r];
-        const bool live = node != 0xFFFFFFFFu;
-        const uint32_t nn = live ? node : 0u;
-        place_ring(r, sl, live, a.ring[(size_t)nn * k + sl], a.deg[nn], a.t_last[nn]);
-      }
-      const uint32_t total = kTM * qpr;
-      for (uint32_t x0 = tid; x0 < total; x0 += 512u) {
-        float4 v[2];
-        uint32_t rr[2], cc[2];
-        bool ok[2];
+    wave_lds_fence();
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          uint32_t x = x0 + 256u * e;
-          ok[e] = x < total;
-          x = ok[e] ? x : 0u;
-          const uint32_t r = x / qpr, q = x - r * qpr;
-          const uint32_t node = s_node[r];
-          rr[e] = r; cc[e] = 4u * q;
-          const bool live = node != 0xFFFFFFFFu;
-          // columns past d_in are row padding of the table (zero)
-          v[e] = *reinterpret_cast<const float4*>(a.Hin + (size_t)(live ? node : 0u) * a.ld_in + 4u * q);
-          if (!live) v[e] = make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-#pragma unroll
-        for (int e = 0; e < 2; ++e)
-          if (ok[e]) *reinterpret_cast<float4*>(Xs + rr[e] * ll.ldx + cc[e]) = v[e];
-      }
-      __syncthreads();
-    }
+    for (int r = 0; r < RPW; ++r) gathered += (uint32_t)__builtin_amdgcn_readlane((int)cnt_s, r * (int)LS);
     stage_a(tile_of(round + 1u));                            // row ids of this workgroup's next tile
-    // ---- this lane group's row: entry count, query time, ring records; the first chunk of cached
-    // rows is requested now and arrives while the projections below run
-    const uint32_t local = wave * 4u + grp;
-    const uint32_t cnt = s_cnt[local];
-    const double tq = s_tq[local];
-    const RingEntry* rrow = Rs + local * k;
-    gathered += cnt;
-    uint32_t cmax = (uint32_t)__builtin_amdgcn_readlane((int)cnt, 0);
-    cmax = max(cmax, (uint32_t)__builtin_amdgcn_readlane((int)cnt, 16));
-    cmax = max(cmax, (uint32_t)__builtin_amdgcn_readlane((int)cnt, 32));
-    cmax = max(cmax, (uint32_t)__builtin_amdgcn_readlane((int)cnt, 48));
-    const uint32_t nchunk3 = (cmax + JC - 1) / JC;
-    auto gather = [&](uint32_t c, ZBuf& zb) {
+    // ---- phase 3's rows: pass p works on rows p RPP .. p RPP + RPP - 1 of the wave's, GPR groups of 16 lanes each,
+    // group g on key slot g.  With one pass a lane's row is the one it staged, else the pass has one row.
+    static_assert(PASSES == 1 || RPP == 1, "a pass is either all rows of the wave or one of them");
+    const uint32_t g = GPR == 1 ? 0u : grp % GPR;             // this lane's key slot,
+    const uint32_t head = g / SH, sg = g - head * SH;         // its head and its place among the head's slots
+    auto row_of = [&](int p) { return PASSES == 1 ? local_s : wave * RPW + (uint32_t)p; };
+    auto node_of = [&](int p) { return PASSES == 1 ? node_s : (uint32_t)__builtin_amdgcn_readlane((int)node_s, p * (int)LS); };
+    auto cnt_of = [&](int p) { return PASSES == 1 ? cnt_s : (uint32_t)__builtin_amdgcn_readlane((int)cnt_s, p * (int)LS); };
+    auto tq_of = [&](int p) {
+      if constexpr (PASSES == 1) return tq_s;
+      const uint64_t u = __builtin_bit_cast(uint64_t, tq_s);
+      const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, p * (int)LS);
+      const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), p * (int)LS);
+      return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+    };
+    auto cmax_of = [&](int p) {
+      uint32_t m = (uint32_t)__builtin_amdgcn_readlane((int)cnt_s, p * RPP * (int)LS);
+#pragma unroll
+      for (int r = 1; r < RPP; ++r) m = max(m, (uint32_t)__builtin_amdgcn_readlane((int)cnt_s, (p * RPP + r) * (int)LS));
+      return m;
+    };
+    auto gather = [&](int p, uint32_t c, ZBuf& zb) {
+      const RingEntry* rrow = Rs + row_of(p) * k;
 #pragma unroll
       for (int jc = 0; jc < JC; ++jc) {
         const uint32_t j = c * JC + jc;
         const RingEntry e = rrow[j < k ? j : k - 1u];
-        const float* nrow = a.KVn + (size_t)e.nbr * a.ld_kv + 4u * sub;
-        const float* erow = a.KVe + (size_t)e.eid * a.ld_kve + 4u * sub;
-#pragma unroll
-        for (int s = 0; s < 2 * KS; ++s) {
-          zb.n[jc][s] = *reinterpret_cast<const float4*>(nrow + s * kSlot);
-          if constexpr (!ES) zb.e[jc][s] = *reinterpret_cast<const float4*>(erow + s * kSlot);
+        const float* nrow = a.KVn + (size_t)e.nbr * (2u * kSlot * KS) + kSlot * g + 4u * sub;
+        zb.nk[jc] = *reinterpret_cast<const float4*>(nrow);
+        zb.nv[jc] = *reinterpret_cast<const float4*>(nrow + kSlot * KS);
+        if constexpr (ES) {
+          zb.e[jc][0] = *reinterpret_cast<const float4*>(a.KVe + (size_t)e.eid * kSlot + 4u * sub);
+        } else {
+          const float* erow = a.KVe + (size_t)e.eid * a.ld_kve + kSlot * g + 4u * sub;
+          zb.e[jc][0] = *reinterpret_cast<const float4*>(erow);
+          zb.e[jc][1] = *reinterpret_cast<const float4*>(erow + kSlot * KS);
         }
-        if constexpr (ES) zb.e[jc][0] = *reinterpret_cast<const float4*>(erow);
+        zb.t[jc] = e.t;
       }
     };
-    ZBuf z0;
-    if (clean) {
-      // the rows' q and qt from the query cache, requested together with the first gather (whose wait at
-      // the start of phase 3 is there in any case), then into their tiles
-      float4 qv[NQ];
-      static_for<NQ>([&](auto E) {
-        constexpr int e = decltype(E)::value;
-        const uint32_t x = tid + 256u * e, r = x / QW4, q4 = x - r * QW4;
-        const uint32_t node = s_node[r];
-        qv[e] = *reinterpret_cast<const float4*>(a.QC + (size_t)(node != 0xFFFFFFFFu ? node : 0u) * (4u * QW4) + 4u * q4);
-      });
-      if constexpr (!DELTA) gather(0, z0);
-      static_for<NQ>([&](auto E) {
-        constexpr int e = decltype(E)::value;
-        const uint32_t x = tid + 256u * e, r = x / QW4, q4 = x - r * QW4;
-        const float4 v = s_node[r] != 0xFFFFFFFFu ? qv[e] : make_float4(0.f, 0.f, 0.f, 0.f);
-        float* dst = q4 < 16u * KS ? Qs + r * ll.ldq + 4u * q4 : Zs + r * ll.ldz + 4u * (q4 - 16u * KS);
-        *reinterpret_cast<float4*>(dst) = v;
+    // z slots a lane works with: all of them when a head is one slot (every head needs them all); shared out over the
+    // head's slots otherwise, slot t to the lanes of key slot t mod SH
+    constexpr int NZL = SH == 1 ? NZ : (NZ + SH - 1) / SH;
+    ZBuf z0[PASSES];
+    float4 qk[PASSES], qt[PASSES][NZL];                       // this lane's share of the row's q and qt vectors
+    if constexpr (clean) {
+      // the rows' q and qt from the query cache, each lane what it needs, requested together with the first gather
+      static_for<PASSES>([&](auto P) {
+        constexpr int p = decltype(P)::value;
+        const uint32_t node = node_of(p);
+        const float* qrow = a.QC + (size_t)(node != 0xFFFFFFFFu ? node : 0u) * kQC + 4u * sub;
+        qk[p] = *reinterpret_cast<const float4*>(qrow + kSlot * g);
+#pragma unroll
+        for (int i = 0; i < NZL; ++i) {
+          const uint32_t t = SH == 1 ? (uint32_t)i : sg + SH * i;
+          qt[p][i] = *reinterpret_cast<const float4*>(qrow + kSlot * KS + head * Ztp + (t < NZ ? t : 0u) * kSlot);
+        }
+        gather(p, 0, z0[p]);
       });
     } else {
-    if constexpr (!DELTA) gather(0, z0);
+    __syncthreads();
     // ================================================================ phase 1: q = x W_Q + c_Q
     for (uint32_t nt = wave; nt < ntd; nt += 8) {
-      const bool two = nt + 4 < ntd;
-      const float* const Bt[2] = {a.WQ + (size_t)nt * g_in * kGrpFloats, a.WQ + (size_t)(two ? nt + 4 : nt) * g_in * kGrpFloats};
-      floatx4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-      if (nt != wave) { load_b16(Bt[0], 0, oq.b[0]); load_b16(Bt[1], 0, oq.b[1]); }
-      mfma16_gemm_pre<2>(Xs + a_x, c_in, Bt, acc, oq);
+      const float* Bt[NTL];
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const uint32_t col = (nt + 4 * t) * 16 + m16_col(lane);
-        if ((t == 0 || two) && col < a.d_emb) {
+      for (int t = 0; t < NTL; ++t) Bt[t] = tile_b(a.WQ, nt, t, ntd, g_in);
+      floatx4 acc[NTL] = {};
+      if (nt != wave) {
+#pragma unroll
+        for (int t = 0; t < NTL; ++t) load_b16(Bt[t], 0, oq.b[t], lane);
+      }
+      mfma16_gemm_pre<NTL>(Xs + a16_off(lane, ll.ldx), c_in, Bt, acc, oq, lane);
+#pragma unroll
+      for (int t = 0; t < NTL; ++t) {
+        const uint32_t col = (nt + NW * t) * 16 + m16_col(lane);
+        if (nt + NW * t < ntd && col < a.d_emb) {
           const float cq = nt == wave ? cq_r[t] : a.cQ[col];
-          const uint32_t h = col / dk;
+          const uint32_t h = H == 1 ? 0u : H == 2 ? (col >= dk ? 1u : 0u) : (col >= dk ? 1u : 0u) + (col >= 2u * dk ? 1u : 0u) + (col >= 3u * dk ? 1u : 0u);
           float* qp = Qs + m16_row(lane, 0) * ll.ldq + h * (SH * kSlot) + (col - h * dk);
 #pragma unroll
           for (int r = 0; r < 4; ++r) qp[r * ll.ldq] = acc[t][r] + cq;
@@ -489,54 +517,60 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
     }
     // ================================================================ phase 2: qt_h = q_h W_K,h[time]^T
     {
-      Ops16<2> o2;
+      Ops16<NTL> o2;
       Unit2 ua = decode2(0);                                  // weights of the first unit are requested
-      load_b16(wkt(ua.h, ua.t0), 0, o2.b[0]);                 // ahead of the barrier (unit 0 of an idle wave: head 0, tile 0)
-      load_b16(wkt(ua.h, ua.t1), 0, o2.b[1]);
+      request2(ua, o2);                                       // ahead of the barrier (unit 0 of an idle wave: head 0, tile 0)
       __syncthreads();
+      const float* qa = Qs + a16_off(lane, ll.ldq);
       if constexpr (SH == 1) {
         // one chunk per unit: the operands of the next unit are in flight during this unit's products
-        load_a16(Qs + ua.h * kSlot + a_q, 0, o2.a);
-        if (nu2) pingpong_peeled<Ops16<2>>(
+        load_a16(qa + ua.h * kSlot, 0, o2.a);
+        if (nu2) pingpong_peeled<Ops16<NTL>>(
             nu2, o2,
-            [&](uint32_t i, Ops16<2>& o) {
+            [&](uint32_t i, Ops16<NTL>& o) {
               const Unit2 u = decode2(i);
-              load_a16(Qs + u.h * kSlot + a_q, 0, o.a);
-              load_b16(wkt(u.h, u.t0), 0, o.b[0]);
-              load_b16(wkt(u.h, u.t1), 0, o.b[1]);
+              load_a16(qa + u.h * kSlot, 0, o.a);
+              request2(u, o);
             },
-            [&](uint32_t i, const Ops16<2>& o) {
+            [&](uint32_t i, const Ops16<NTL>& o) {
               const Unit2 u = decode2(i);
-              floatx4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-              mfma16_chunk<2>(o, acc);
+              floatx4 acc[NTL] = {};
+              mfma16_chunk<NTL>(o, acc);
               store2(u, acc);
             });
       } else {
         for (uint32_t i = 0; i < nu2; ++i) {
           ua = decode2(i);
-          const float* const Bt[2] = {wkt(ua.h, ua.t0), wkt(ua.h, ua.t1)};
-          floatx4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-          if (i) { load_b16(Bt[0], 0, o2.b[0]); load_b16(Bt[1], 0, o2.b[1]); }
-          mfma16_gemm_pre<2>(Qs + ua.h * (SH * kSlot) + a_q, SH, Bt, acc, o2);
+          const float* Bt[NTL];
+          Bt[0] = wkt(ua.h, ua.t0);
+          if constexpr (NTL == 2) Bt[1] = wkt(ua.h, ua.t1);
+          floatx4 acc[NTL] = {};
+          if (i) request2(ua, o2);
+          mfma16_gemm_pre<NTL>(qa + ua.h * (SH * kSlot), SH, Bt, acc, o2, lane);
           store2(ua, acc);
         }
       }
     }
-    }  // q and qt: read back, or projected
-    stage_a_commit();                                         // requested ahead of the loads waited for above: here by now
+    if constexpr (!DELTA) static_for<PASSES>([&](auto P) { gather(decltype(P)::value, 0, z0[decltype(P)::value]); });
     __syncthreads();
-    // next tile's rows, in flight among the gathers of phase 3 (four-slot shapes have no registers to
-    // spare in phase 3: theirs are requested behind it)
-    if constexpr (KS <= 2) { if (pf_ok) stage_b(); else stage_none(); }
-    if (QCACHE && !ROOTS && !clean) {                        // the rows' q | qt for later batches
-      static_for<NQ>([&](auto E) {
-        constexpr int e = decltype(E)::value;
-        const uint32_t x = tid + 256u * e, r = x / QW4, q4 = x - r * QW4;
-        const uint32_t node = s_node[r];
-        const float* src = q4 < 16u * KS ? Qs + r * ll.ldq + 4u * q4 : Zs + r * ll.ldz + 4u * (q4 - 16u * KS);
-        if (node != 0xFFFFFFFFu) *reinterpret_cast<float4*>(a.QC + (size_t)node * (4u * QW4) + 4u * q4) = *reinterpret_cast<const float4*>(src);
-      });
-      __syncthreads();                                        // phase 3 puts pb where qt is: not before every thread has read its share
+    }  // q and qt: read back, or projected
+    if constexpr (!DELTA) {
+      if constexpr (!clean) {
+        static_for<PASSES>([&](auto P) {
+          constexpr int p = decltype(P)::value;
+          const uint32_t node = node_of(p), local = row_of(p);
+          qk[p] = *reinterpret_cast<const float4*>(Qs + local * ll.ldq + kSlot * g + 4u * sub);
+          float* qrow = QCACHE ? a.QC + (size_t)node * kQC + 4u * sub : nullptr;
+          const bool keep = QCACHE && !ROOTS && node != 0xFFFFFFFFu;           // the rows' q | qt for later batches
+          if (keep) *reinterpret_cast<float4*>(qrow + kSlot * g) = qk[p];
+#pragma unroll
+          for (int i = 0; i < NZL; ++i) {
+            const uint32_t t = SH == 1 ? (uint32_t)i : sg + SH * i, at = head * Ztp + (t < NZ ? t : 0u) * kSlot;
+            qt[p][i] = *reinterpret_cast<const float4*>(Zs + local * ll.ldz + at + 4u * sub);
+            if (keep && t < NZ) *reinterpret_cast<float4*>(qrow + kSlot * KS + at) = qt[p][i];
+          }
+        });
+      }
     }
     // ================================================================ phase 3: gather + attention
     // The time encodings are not masked per entry: a column past d_time has omega = phase = 0 and comes out as
@@ -558,10 +592,11 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
       // weight e_new / Z', sums corrected by (new weight x new value) - (old weight x old value); the
       // other entries keep the weight they have (Eq. delta_embedding, "updated neighbours").
       float* Sc = lds + ll.off_sc;
-      const uint32_t node = s_node[local];
-      const bool live = node != 0xFFFFFFFFu;
+      const uint32_t local = local_s, node = node_s, cnt = cnt_s, cmax = cmax_of(0);
+      const double tq = tq_s;
+      const RingEntry* rrow = Rs + local * k;
+      const bool live = live_s;
       const uint32_t nn = live ? node : 0u;
-      const bool ex = s_ex[local] != 0u;
       float* acS = a.ac_S + (size_t)nn * (kSlot * KS) + 4u * sub;
       float* acP = a.ac_P + (size_t)nn * (kSlot * NT * H) + 4u * sub;
       float* acZM = a.ac_ZM + (size_t)nn * (2 * H);
@@ -569,9 +604,7 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
       for (uint32_t j = sub; j < cnt; j += 16)
 #pragma unroll
         for (int h = 0; h < H; ++h) Sc[(local * k + j) * H + h] = -INFINITY;
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      wave_lds_fence();
       float4 accv[KS], accp[H][NT];
       float mref[H], lrun[H];                                 // exact row: running reference and denominator; delta row: m and Z
 #pragma unroll
@@ -721,9 +754,7 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
         pingpong_clamped<DBuf>(n_items, b0, fetch, work);
       }
       // ---- the row's sums: normalised by the denominator after an exact recomputation, as they stand after a delta update
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      wave_lds_fence();
 #pragma unroll
       for (int h = 0; h < H; ++h) {
         const float inv = ex ? (lrun[h] > 0.0f ? 1.0f / lrun[h] : 0.0f) : 1.0f;
@@ -731,7 +762,7 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
         for (int s = h * SH; s < (h + 1) * SH; ++s) {
           float4 o = accv[s];
           o.x *= inv; o.y *= inv; o.z *= inv; o.w *= inv;
-          *reinterpret_cast<float4*>(Xs + local * ll.ldx + s * kSlot + 4u * sub) = o;
+          *reinterpret_cast<float4*>(Qs + local * ll.ldq + s * kSlot + 4u * sub) = o;
           if (live) *reinterpret_cast<float4*>(acS + s * kSlot) = o;
         }
 #pragma unroll
@@ -771,285 +802,268 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
                    (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int(dg), 48));
       drift_new += (uint32_t)__builtin_amdgcn_readlane((int)dc, 0) + (uint32_t)__builtin_amdgcn_readlane((int)dc, 16) +
                    (uint32_t)__builtin_amdgcn_readlane((int)dc, 32) + (uint32_t)__builtin_amdgcn_readlane((int)dc, 48);
-    } else
-    {
-      float4 accv[KS], accp[H][NZ];
+    } else {
+      // ---- exact mode.  A row is served by one 16-lane group per key slot: a lane holds four columns of one slot of one
+      // head, so sums, query and gathered rows take a quarter to a half of the registers that a group per row would need,
+      // and all of q and qt and the time parameters stay in registers through the entry loop.  The time encodings,
+      // which every head needs, are worked out once per row: each group evaluates its share of the columns and the groups
+      // exchange them (SH = 1), or the slots of z are shared out over a head's slots (SH > 1).
+      constexpr int CP = SH == 1 ? 4 * NT / KS : 4;           // cosines a lane evaluates per entry
+      double om[CP], ph[CP];
+      {
+        const uint32_t i0 = SH == 1 ? g * CP : 4u * (sg < NT ? sg : 0u);   // first (slot, column of the quad) = (i0 / 4, i0 % 4)
+        const uint32_t at = (i0 >> 2) * kSlot + 4u * sub + (i0 & 3u);
 #pragma unroll
-      for (int s = 0; s < KS; ++s) accv[s] = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int c = 0; c < CP; ++c) {
+          om[c] = s_om[at + (c & 3) + (c >> 2) * kSlot];
+          ph[c] = s_ph[at + (c & 3) + (c >> 2) * kSlot];
+        }
+      }
+      static_for<PASSES>([&](auto P) {
+      constexpr int p = decltype(P)::value;
+      const uint32_t local = row_of(p), cnt = cnt_of(p), cmax = cmax_of(p);
+      const double tq = tq_of(p);
+      const uint32_t nchunk3 = (cmax + JC - 1) / JC;
+      float4 accv = make_float4(0.f, 0.f, 0.f, 0.f), accp[NZL];
 #pragma unroll
-      for (int h = 0; h < H; ++h)
-#pragma unroll
-        for (int t = 0; t < NZ; ++t) accp[h][t] = make_float4(0.f, 0.f, 0.f, 0.f);
-      float mref[H], lrun[H];
-#pragma unroll
-      for (int h = 0; h < H; ++h) { mref[h] = -INFINITY; lrun[h] = 0.0f; }
-      // this lane's share of the row's q and qt vectors stays in registers for the whole phase
-      float4 qk[KS];
-#pragma unroll
-      for (int s = 0; s < KS; ++s) qk[s] = *reinterpret_cast<const float4*>(Qs + local * ll.ldq + s * kSlot + 4u * sub);
-      const float* zq = Zs + local * ll.ldz + 4u * sub;       // qt of head h, time slot t: + h Ztp + 64 t (read per chunk)
+      for (int i = 0; i < NZL; ++i) accp[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      float mref = -INFINITY, lrun = 0.0f;
       auto attend = [&](uint32_t c, const ZBuf& zb) {
-        // time encodings of the chunk's entries (computed for every lane, then masked: no branches)
-        float4 zt[JC][NZ];
+        float4 zt[JC][NZL];
+        float sc[JC];
         bool vj[JC];
-        double2 om[NT][2], ph[NT][2];
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            om[t][q] = *reinterpret_cast<const double2*>(s_om + t * kSlot + 4u * sub + 2 * q);
-            ph[t][q] = *reinterpret_cast<const double2*>(s_ph + t * kSlot + 4u * sub + 2 * q);
-          }
 #pragma unroll
         for (int jc = 0; jc < JC; ++jc) {
-          const uint32_t j = c * JC + jc;
-          const double dt = tq - rrow[j < k ? j : k - 1u].t;
-          vj[jc] = j < cnt && dt <= a.window;          // inside the temporal window [tq - T_w, tq] (Sec. 3.3.2)
+          const double dt = tq - zb.t[jc];
+          vj[jc] = c * JC + jc < cnt && dt <= a.window;       // inside the temporal window [tq - T_w, tq] (Sec. 3.3.2)
+          float cs[CP], all[4 * NT];
 #pragma unroll
-          for (int t = 0; t < NT; ++t) {
-            const float c0 = cos_rev(om[t][0].x * dt + ph[t][0].x), c1 = cos_rev(om[t][0].y * dt + ph[t][0].y);
-            const float c2 = cos_rev(om[t][1].x * dt + ph[t][1].x), c3 = cos_rev(om[t][1].y * dt + ph[t][1].y);
-            // columns past d_time come out as cos(0) = 1 and need no mask: qt is exactly zero there (zero
-            // weight columns), and what they add to pb meets zero weight rows in phase 4
-            zt[jc][t] = make_float4(c0, c1, c2, c3);
-          }
-          if constexpr (ES) zt[jc][NT] = zb.e[jc][0];
-        }
-        // scores: q . (cached node keys + cached edge keys) + qt . phi  (raw edge rows: q . node keys + qt . z)
-        float sc[JC][H];
+          for (int i = 0; i < CP; ++i) cs[i] = cos_rev(__builtin_fma(om[i], dt, ph[i]));
+          if constexpr (SH == 1) {
 #pragma unroll
-        for (int h = 0; h < H; ++h) {
-#pragma unroll
-          for (int jc = 0; jc < JC; ++jc) {
-            float p = 0.0f;
-#pragma unroll
-            for (int s = h * SH; s < (h + 1) * SH; ++s) {
-              float4 kk = zb.n[jc][s];
-              if constexpr (!ES) {
-                kk.x += zb.e[jc][s].x; kk.y += zb.e[jc][s].y; kk.z += zb.e[jc][s].z; kk.w += zb.e[jc][s].w;
+            for (int i = 0; i < CP; ++i) {
+              if constexpr (KS == 1) {
+                all[i] = cs[i];
+              } else if constexpr (KS == 2) {
+                const Two w = both_of_pair(cs[i]);
+                all[i] = w.lo; all[CP + i] = w.hi;
+              } else {
+                const Two w = both_of_pair(cs[i]);
+                const Two lo = both_halves(w.lo), hi = both_halves(w.hi);
+                all[i] = lo.lo; all[CP + i] = hi.lo; all[2 * CP + i] = lo.hi; all[3 * CP + i] = hi.hi;
               }
-              p = dot4(qk[s], kk, p);
             }
 #pragma unroll
-            for (int t = 0; t < NZ; ++t) p = dot4(*reinterpret_cast<const float4*>(zq + h * Ztp + t * kSlot), zt[jc][t], p);
-            const float tsum = row16_sum(p);
-            sc[jc][h] = vj[jc] ? tsum : -INFINITY;
+            for (int t = 0; t < NT; ++t) zt[jc][t] = make_float4(all[4 * t], all[4 * t + 1], all[4 * t + 2], all[4 * t + 3]);
+            if constexpr (ES) zt[jc][NT] = zb.e[jc][0];
+          } else {
+            // (SH >= NT: time slots come first in a lane's share)
+            const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int i = 0; i < NZL; ++i) {
+              const uint32_t t = sg + SH * i;
+              zt[jc][i] = i == 0 && t < NT ? make_float4(cs[0], cs[1], cs[2], cs[3]) : ES && t == NT ? zb.e[jc][0] : zero;
+            }
           }
+          // score: q . (cached node keys + cached edge keys) + qt . phi  (raw edge rows: q . node keys + qt . z)
+          float4 kk = zb.nk[jc];
+          if constexpr (!ES) { kk.x += zb.e[jc][0].x; kk.y += zb.e[jc][0].y; kk.z += zb.e[jc][0].z; kk.w += zb.e[jc][0].w; }
+          float s = dot4(qk[p], kk, 0.0f);
+#pragma unroll
+          for (int i = 0; i < NZL; ++i) s = dot4(qt[p][i], zt[jc][i], s);
+          s = row16_sum(s);
+          if constexpr (SH >= 2) { const Two w = both_of_pair(s); s = w.lo + w.hi; }
+          if constexpr (SH == 4) { const Two w = both_halves(s); s = w.lo + w.hi; }
+          sc[jc] = vj[jc] ? s : -INFINITY;
         }
         // softmax against a reference score that only moves when a score exceeds it by a wide
         // margin (any reference gives the same quotient; the margin keeps exp() in range)
-        bool need = false;
-        float smax[H];
+        float smax = sc[0];
 #pragma unroll
-        for (int h = 0; h < H; ++h) {
-          smax[h] = sc[0][h];
+        for (int jc = 1; jc < JC; ++jc) smax = fmaxf(smax, sc[jc]);
+        const bool mv = smax > mref + 30.0f;
+        if (__any(mv)) {
+          const float mnew = mv ? smax : mref;
+          const float scale = mv ? __expf(mref - mnew) : 1.0f;            // exp(-inf) = 0 on the first move
+          lrun *= scale;
+          accv.x *= scale; accv.y *= scale; accv.z *= scale; accv.w *= scale;
 #pragma unroll
-          for (int jc = 1; jc < JC; ++jc) smax[h] = fmaxf(smax[h], sc[jc][h]);
-          need = need || smax[h] > mref[h] + 30.0f;
-        }
-        if (__any(need)) {
-#pragma unroll
-          for (int h = 0; h < H; ++h) {
-            const bool mv = smax[h] > mref[h] + 30.0f;
-            const float mnew = mv ? smax[h] : mref[h];
-            const float scale = mv ? __expf(mref[h] - mnew) : 1.0f;     // exp(-inf) = 0 on the first move
-            lrun[h] *= scale;
-#pragma unroll
-            for (int s = h * SH; s < (h + 1) * SH; ++s) {
-              accv[s].x *= scale; accv[s].y *= scale; accv[s].z *= scale; accv[s].w *= scale;
-            }
-#pragma unroll
-            for (int t = 0; t < NZ; ++t) {
-              accp[h][t].x *= scale; accp[h][t].y *= scale; accp[h][t].z *= scale; accp[h][t].w *= scale;
-            }
-            mref[h] = mnew;
+          for (int i = 0; i < NZL; ++i) {
+            accp[i].x *= scale; accp[i].y *= scale; accp[i].z *= scale; accp[i].w *= scale;
           }
+          mref = mnew;
         }
 #pragma unroll
-        for (int h = 0; h < H; ++h) {
+        for (int jc = 0; jc < JC; ++jc) {
+          const float w = vj[jc] ? __expf(sc[jc] - mref) : 0.0f;
+          lrun += w;
+          float4 vv = zb.nv[jc];
+          if constexpr (!ES) { vv.x += zb.e[jc][1].x; vv.y += zb.e[jc][1].y; vv.z += zb.e[jc][1].z; vv.w += zb.e[jc][1].w; }
+          accv.x = fmaf(w, vv.x, accv.x); accv.y = fmaf(w, vv.y, accv.y);
+          accv.z = fmaf(w, vv.z, accv.z); accv.w = fmaf(w, vv.w, accv.w);
 #pragma unroll
-          for (int jc = 0; jc < JC; ++jc) {
-            const float p = vj[jc] ? __expf(sc[jc][h] - mref[h]) : 0.0f;
-            lrun[h] += p;
-#pragma unroll
-            for (int s = h * SH; s < (h + 1) * SH; ++s) {
-              float4 vv = zb.n[jc][KS + s];
-              if constexpr (!ES) {
-                const float4 ve = zb.e[jc][KS + s];
-                vv.x += ve.x; vv.y += ve.y; vv.z += ve.z; vv.w += ve.w;
-              }
-              accv[s].x = fmaf(p, vv.x, accv[s].x);
-              accv[s].y = fmaf(p, vv.y, accv[s].y);
-              accv[s].z = fmaf(p, vv.z, accv[s].z);
-              accv[s].w = fmaf(p, vv.w, accv[s].w);
-            }
-#pragma unroll
-            for (int t = 0; t < NZ; ++t) {
-              const float4 zv = zt[jc][t];
-              accp[h][t].x = fmaf(p, zv.x, accp[h][t].x);
-              accp[h][t].y = fmaf(p, zv.y, accp[h][t].y);
-              accp[h][t].z = fmaf(p, zv.z, accp[h][t].z);
-              accp[h][t].w = fmaf(p, zv.w, accp[h][t].w);
-            }
+          for (int i = 0; i < NZL; ++i) {
+            accp[i].x = fmaf(w, zt[jc][i].x, accp[i].x); accp[i].y = fmaf(w, zt[jc][i].y, accp[i].y);
+            accp[i].z = fmaf(w, zt[jc][i].z, accp[i].z); accp[i].w = fmaf(w, zt[jc][i].w, accp[i].w);
           }
         }
       };
-      if (nchunk3) pingpong_clamped<ZBuf>(nchunk3, z0, gather, attend);
+      if (nchunk3) pingpong_clamped<ZBuf>(nchunk3, z0[p], [&](uint32_t c, ZBuf& zb) { gather(p, c, zb); }, attend);
       // the cached-value part of the head outputs goes into the O tile (padded-head layout; the
       // padding lanes hold exact zeros), pb overwrites qt (each lane owns its float4s)
+      const float inv = lrun > 0.0f ? 1.0f / lrun : 0.0f;     // no entry, or none inside the window: b_O alone
+      accv.x *= inv; accv.y *= inv; accv.z *= inv; accv.w *= inv;
+      *reinterpret_cast<float4*>(Os + local * ldo + kSlot * g + 4u * sub) = accv;
 #pragma unroll
-      for (int h = 0; h < H; ++h) {
-        const float inv = lrun[h] > 0.0f ? 1.0f / lrun[h] : 0.0f;    // no entry, or none inside the window: b_O alone
-#pragma unroll
-        for (int s = h * SH; s < (h + 1) * SH; ++s) {
-          float4 o = accv[s];
-          o.x *= inv; o.y *= inv; o.z *= inv; o.w *= inv;
-          *reinterpret_cast<float4*>(Xs + local * ll.ldx + s * kSlot + 4u * sub) = o;
-        }
-#pragma unroll
-        for (int t = 0; t < NZ; ++t) {
-          float4 o = accp[h][t];
-          o.x *= inv; o.y *= inv; o.z *= inv; o.w *= inv;
-          if (t < NT) clear_past_d_time(o, t);                 // (a raw edge row's padding is zero, and so are its sums)
-          *reinterpret_cast<float4*>(Zs + local * ll.ldz + h * Ztp + t * kSlot + 4u * sub) = o;
-        }
+      for (int i = 0; i < NZL; ++i) {
+        const uint32_t t = SH == 1 ? (uint32_t)i : sg + SH * i;
+        float4 o = accp[i];
+        o.x *= inv; o.y *= inv; o.z *= inv; o.w *= inv;
+        if (t < NT) clear_past_d_time(o, t);                   // (a raw edge row's padding is zero, and so are its sums)
+        if (t < NZ) *reinterpret_cast<float4*>(Zs + local * ll.ldz + head * Ztp + t * kSlot + 4u * sub) = o;
       }
+      });
     }
     // ================================================================ phase 4: o_h += pb_h W_V,h[time | raw edge]
+    derive_lane();
     {
-      // K runs over the slots of z, one chunk per slot; the operands of the next slot are in flight
-      // during the current one.  The weights of the first slot are requested ahead of the barrier.
-      Ops16<2> ov[2];
-      uint32_t x = wave;
+      // K runs over the slots of z, one chunk per slot.  Every weight chunk of the wave's first unit is requested ahead
+      // of the barrier: one memory latency for the unit, most of it spent waiting for the slowest wave of phase 3
+      // anyway.  Further units request theirs when they get there.
       auto wv = [&](uint32_t h, uint32_t nt) { return a.WV + (size_t)(h * ntk + nt) * g_zt * kGrpFloats; };
-      uint32_t h4 = 0, n0 = 0, n1 = 0;
-      bool two4 = false;
-      auto decode4 = [&](uint32_t xx) {
-        h4 = xx / np4;
-        n0 = 2u * (xx - h4 * np4);
-        two4 = n0 + 1u < ntk;
-        n1 = two4 ? n0 + 1u : n0;
+      uint32_t x = wave < nunits4 ? wave : nunits4 - 1u;
+      Upfront16<NTL, NZ> u4;
+      auto request4 = [&]() {
+        const uint32_t h4 = x / np4, n0 = NTL * (x - h4 * np4);
+        const float* Bt[NTL];
+#pragma unroll
+        for (int t = 0; t < NTL; ++t) Bt[t] = wv(h4, n0 + t < ntk ? n0 + t : n0);
+        u4.request(Bt, NZ, lane);
       };
-      decode4(x < nunits4 ? x : nunits4 - 1u);
-      // every weight chunk of the wave's first unit is requested ahead of the barrier: one memory latency
-      // for the unit, most of it spent waiting for the slowest wave of phase 3 anyway
-      Upfront16<2, NZ> u4;
-      {
-        const float* const B4[2] = {wv(h4, n0), wv(h4, n1)};
-        u4.request(B4, NZ);
-      }
+      request4();
+      // the next tile's rows travel during the dense phases, behind the weights this phase waits for (ahead of the entry
+      // loop they would take registers from it)
+      if (pf_ok) stage_b(); else stage_none();
       __syncthreads();
-      if constexpr (KS > 2) { if (pf_ok) stage_b(); else stage_none(); }
-      for (; x < nunits4; x += 4) {
-        floatx4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-        if (x == wave) {
-          u4.multiply(Zs + h4 * Ztp + a_z, NZ, acc);
-        } else {
-          decode4(x);
-          load_b16(wv(h4, n0), 0, ov[0].b[0]);
-          load_b16(wv(h4, n1), 0, ov[0].b[1]);
-          const float* Ap = Zs + h4 * Ztp + a_z;
-          const float* B0 = wv(h4, n0);
-          const float* B1 = wv(h4, n1);
-          load_a16(Ap, 0, ov[0].a);
+      if (wave < nunits4) {
+        for (;;) {
+          const uint32_t h4 = x / np4, n0 = NTL * (x - h4 * np4);
+          floatx4 acc[NTL] = {};
+          u4.multiply(Zs + h4 * Ztp + a16_off(lane, ll.ldz), NZ, acc);
 #pragma unroll
-          for (int c = 0; c < NZ; ++c) {
-            if (c + 1 < NZ) {
-              load_a16(Ap, (c + 1) * kCG, ov[(c + 1) & 1].a);
-              load_b16(B0, (c + 1) * kCG, ov[(c + 1) & 1].b[0]);
-              load_b16(B1, (c + 1) * kCG, ov[(c + 1) & 1].b[1]);
+          for (int t = 0; t < NTL; ++t) {
+            const uint32_t col = (n0 + t) * 16 + m16_col(lane);
+            if (n0 + t < ntk && col < dk) {
+              float* op = Os + m16_row(lane, 0) * ldo + h4 * (SH * kSlot) + col;    // one lane per (row, column)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) op[r * ldo] += acc[t][r];
             }
-            __builtin_amdgcn_sched_barrier(0);      // requests stay ahead of the products they overlap
-            mfma16_chunk<2>(ov[c & 1], acc);
-            __builtin_amdgcn_sched_barrier(0);
           }
-        }
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          const uint32_t col = (t ? n1 : n0) * 16 + m16_col(lane);
-          if ((t == 0 || two4) && col < dk) {
-            float* op = Xs + c_off_x - m16_col(lane) + h4 * (SH * kSlot) + col;    // one lane per (row, column)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) op[r * ll.ldx] += acc[t][r];
-          }
+          x += NW;
+          if (x >= nunits4) break;
+          request4();
         }
       }
     }
     // ================================================================ phase 5: h' = o W_O + b_O
+    derive_lane();
     {
-      Ops16<2> oo;
-      constexpr int U5 = KS <= 2 ? KS : 1;                    // weight chunks of the first unit requested up front
-      Upfront16<2, U5> u5;
+      constexpr bool kUp = KS * NTL <= 4;                     // all weight chunks of the first unit requested up front
+      Ops16<NTL> oo;
+      Upfront16<NTL, kUp ? KS : 1> u5;
       {
-        const float* const B5[2] = {a.WO + (size_t)w1 * g_o * kGrpFloats, a.WO + (size_t)(w1 + 4 < ntd ? w1 + 4 : w1) * g_o * kGrpFloats};
-        if constexpr (KS <= 2) u5.request(B5, KS);
-        else { load_b16(B5[0], 0, oo.b[0]); load_b16(B5[1], 0, oo.b[1]); }
+        const float* Bt[NTL];
+#pragma unroll
+        for (int t = 0; t < NTL; ++t) Bt[t] = tile_b(a.WO, w1, t, ntd, g_o);
+        if constexpr (kUp) u5.request(Bt, KS, lane);
+        else {
+#pragma unroll
+          for (int t = 0; t < NTL; ++t) load_b16(Bt[t], 0, oo.b[t], lane);
+        }
       }
       __syncthreads();
       for (uint32_t nt = wave; nt < ntd; nt += 8) {
-        const bool two = nt + 4 < ntd;
-        const float* const Bt[2] = {a.WO + (size_t)nt * g_o * kGrpFloats, a.WO + (size_t)(two ? nt + 4 : nt) * g_o * kGrpFloats};
-        floatx4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-        if (KS <= 2 && nt == wave) {
-          u5.multiply(Xs + a_x, KS, acc);
+        const float* Bt[NTL];
+#pragma unroll
+        for (int t = 0; t < NTL; ++t) Bt[t] = tile_b(a.WO, nt, t, ntd, g_o);
+        floatx4 acc[NTL] = {};
+        if (kUp && nt == wave) {
+          u5.multiply(Os + a16_off(lane, ldo), KS, acc);
         } else {
-          if (nt != wave) { load_b16(Bt[0], 0, oo.b[0]); load_b16(Bt[1], 0, oo.b[1]); }
-          mfma16_gemm_pre<2>(Xs + a_x, KS, Bt, acc, oo);
+          if (nt != wave) {
+#pragma unroll
+            for (int t = 0; t < NTL; ++t) load_b16(Bt[t], 0, oo.b[t], lane);
+          }
+          mfma16_gemm_pre<NTL>(Os + a16_off(lane, ldo), KS, Bt, acc, oo, lane);
         }
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          const uint32_t col = (nt + 4 * t) * 16 + m16_col(lane);
-          if ((t == 0 || two) && col < a.d_emb) {
+        for (int t = 0; t < NTL; ++t) {
+          const uint32_t col = (nt + NW * t) * 16 + m16_col(lane);
+          if (nt + NW * t < ntd && col < a.d_emb) {
             const float b = nt == wave ? bo_r[t] : a.bO[col];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-              const uint32_t node = s_node[m16_row(lane, r)];
+              const uint32_t node = nodes_s[m16_row(lane, r)];
               const float v = acc[t][r] + b;
               if (!ROOTS && node != 0xFFFFFFFFu) a.Hout[(size_t)node * a.ld_out + col] = v;
-              Qs[c_off_q - m16_col(lane) + r * ll.ldq + col] = v;     // operand of phase 6 and of the link scores (q is no longer needed)
+              if (end_barrier) Hs[m16_row(lane, r) * ldh + col] = v;     // operand of phase 6 and of the link scores
             }
           }
         }
       }
     }
     if constexpr (ROOTS) {
-      // link scores: a wave takes edges w and w + 4 of the tile (the list holds whole edges)
+      // link scores: a wave takes edges w and on of the tile (the list holds whole edges)
       __syncthreads();
-      for (uint32_t e = wave; e < kTM / 2; e += 4) {
+      for (uint32_t e = wave; e < kTM / 2; e += NW) {
         const uint32_t i = tile * (kTM / 2) + e;
-        const float* hu = Qs + 2u * e * ll.ldq;
-        const float* hv = hu + ll.ldq;
+        const float* hu = Hs + 2u * e * ldh;
+        const float* hv = hu + ldh;
         float acc = 0.0f;
         for (uint32_t c = lane; c < a.d_emb; c += 64) acc = fmaf(hu[c], a.head[c], fmaf(hv[c], a.head[a.d_emb + c], acc));
         for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-        const bool ok = s_node[2u * e] != 0xFFFFFFFFu && s_node[2u * e + 1u] != 0xFFFFFFFFu;
+        const bool ok = nodes_s[2u * e] != 0xFFFFFFFFu && nodes_s[2u * e + 1u] != 0xFFFFFFFFu;
         if (lane == 0 && 2u * i < n) a.scores[i] = ok ? acc + a.head[2u * a.d_emb] : __builtin_nanf("");
       }
     }
     // ================================================================ phase 6: next layer's cached keys | values of these rows
     if (!ROOTS && a.KVout) {
-      constexpr uint32_t ntkv = 8u * KS;                      // column tiles of a cached row; a wave takes tiles w + 8 i, w + 8 i + 4
-      Ops16<2> ok;
-      load_b16(a.WKVnext + (size_t)wave * g_de * kGrpFloats, 0, ok.b[0]);
-      load_b16(a.WKVnext + (size_t)(wave + 4) * g_de * kGrpFloats, 0, ok.b[1]);
+      constexpr uint32_t ntkv = 8u * KS;                      // column tiles of a cached row; a wave takes tiles w + 8 i (and w + 8 i + 4)
+      Ops16<NTL> ok;
+#pragma unroll
+      for (int t = 0; t < NTL; ++t) load_b16(tile_b(a.WKVnext, wave, t, ntkv, g_de), 0, ok.b[t], lane);
       __syncthreads();
       for (uint32_t nt = wave; nt < ntkv; nt += 8) {
-        const float* const Bt[2] = {a.WKVnext + (size_t)nt * g_de * kGrpFloats, a.WKVnext + (size_t)(nt + 4) * g_de * kGrpFloats};
-        floatx4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-        if (nt != wave) { load_b16(Bt[0], 0, ok.b[0]); load_b16(Bt[1], 0, ok.b[1]); }
-        mfma16_gemm_pre<2>(Qs + a_q, c_de, Bt, acc, ok);
+        const float* Bt[NTL];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          const uint32_t col = (nt + 4 * t) * 16 + m16_col(lane);   // every column is written: padding columns get exact zeros
+        for (int t = 0; t < NTL; ++t) Bt[t] = tile_b(a.WKVnext, nt, t, ntkv, g_de);
+        floatx4 acc[NTL] = {};
+        if (nt != wave) {
+#pragma unroll
+          for (int t = 0; t < NTL; ++t) load_b16(Bt[t], 0, ok.b[t], lane);
+        }
+        mfma16_gemm_pre<NTL>(Hs + a16_off(lane, ldh), c_de, Bt, acc, ok, lane);
+#pragma unroll
+        for (int t = 0; t < NTL; ++t) {
+          const uint32_t col = (nt + NW * t) * 16 + m16_col(lane);   // every column is written: padding columns get exact zeros
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            const uint32_t node = s_node[m16_row(lane, r)];
+            const uint32_t node = nodes_s[m16_row(lane, r)];
             if (node != 0xFFFFFFFFu) a.KVout[(size_t)node * a.ld_kv + col] = acc[t][r];
           }
         }
       }
     }
-    __syncthreads();
+    if (end_barrier) __syncthreads();
+  };
+  for (uint32_t round = 0;; ++round) {
+    const uint32_t tile = tile_of(round);
+    if (tile >= ntiles) break;                                // wave-uniform; only in a workgroup's last round
+    // (set by the staging of a tile ago; uniform)
+    if constexpr (QCACHE) {
+      if (__builtin_amdgcn_readfirstlane((int)p_clean) != 0) { work_tile(std::true_type{}, tile, round); continue; }
+    }
+    work_tile(std::false_type{}, tile, round);
   }
   if constexpr (DELTA) {
     if (lane == 0 && a.is_final) {
@@ -1060,15 +1074,13 @@ __global__ __launch_bounds__(256, WGS) void layer_kernel(LayerArgs a, const uint
   // statistics: the workgroup's count goes into the slot of its index with a plain update (launches
   // on one stream follow each other, and no other workgroup of a launch has this index); thousands of
   // same-address atomic updates at the end of a launch were measured to cost a third of its duration
-  const uint32_t gsum = (uint32_t)__builtin_amdgcn_readlane((int)gathered, 0) +
-                        (uint32_t)__builtin_amdgcn_readlane((int)gathered, 16) +
-                        (uint32_t)__builtin_amdgcn_readlane((int)gathered, 32) +
-                        (uint32_t)__builtin_amdgcn_readlane((int)gathered, 48);
   if constexpr (!ROOTS) {
-    if (lane == 0) s_cnt[wave] = gsum;
+    if (lane == 0) s_sum[wave] = gathered;
     __syncthreads();
     if (threadIdx.x == 0) {
-      const uint32_t tot = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
+      uint32_t tot = 0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) tot += s_sum[w];
       if (tot) a.gathered_slots[blockIdx.x] += tot;
       if (blockIdx.x == 0 && n) a.ctrl->tot_rows += n;
     }
@@ -1109,7 +1121,7 @@ void go_k(LaunchArgs& a) {
   if (cap > kStatSlots) cap = kStatSlots;                              // staging one tile ahead
   if (blocks > cap) blocks = cap;
   if (blocks < 1) blocks = 1;
-  hipLaunchKernelGGL(kern, dim3((uint32_t)blocks), dim3(256), a.lds, a.s, a.k, a.rows, a.cp, a.cm);
+  hipLaunchKernelGGL(kern, dim3((uint32_t)blocks), dim3(64 * layer_waves(KS, DELTA)), a.lds, a.s, a.k, a.rows, a.cp, a.cm);
 }
 
 template <int KS, int NT, int H, int JC, int WGS, bool ROOTS>
