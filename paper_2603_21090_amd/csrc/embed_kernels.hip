@@ -105,6 +105,7 @@ LaunchArgs make_args(const Dev& d, uint32_t layer) {
   k.WKVnext = layer + 1 < d.layers ? d.L[layer + 1].WKVn : nullptr;
   k.ring = d.ring; k.deg = d.deg; k.t_last = d.t_last;
   k.om_rev = d.om_rev; k.ph_rev = d.ph_rev; k.ctrl = d.ctrl; k.gathered_slots = d.gathered_slots;
+  k.sp = L.sp; k.iKVnext = layer + 1 < d.layers ? d.L[layer + 1].iKVn : 0.0f;
   k.WQ = L.WQn; k.cQ = L.cQ; k.WKT = L.WKT; k.WV = L.WV; k.WO = L.WO; k.bO = L.bO;
   k.ld_in = d.H[layer].ld; k.ld_out = d.H[layer + 1].ld; k.ld_kv = d.ld_kv; k.ld_kve = d.KVE[layer].ld;
   k.window = d.window;
@@ -151,7 +152,8 @@ void launch_layer(const Dev& d, hipStream_t s, uint32_t layer, const uint32_t* r
                   bool force_exact) {
   LaunchArgs a = make_args(d, layer);
   a.k.force_exact = force_exact ? 1u : 0u;
-  if (force_exact) a.k.tile_clean = nullptr;                   // every row projects its query again (and refreshes the cache)
+  if (force_exact) a.k.tile_clean = nullptr;                   // every row projects its query again (and refreshes the cache):
+                                                               // the variant that reads nothing back
   a.s = s; a.rows = rows; a.cp = cp; a.cm = cm; a.set_attr = false;
   go_heads(a);
 }
@@ -161,8 +163,6 @@ void launch_layer_scores(const Dev& d, hipStream_t s, uint32_t n, const uint32_t
                          float* scores) {
   LaunchArgs a = make_args(d, d.layers - 1);
   a.roots = true;                                             // (computed at their own times, from nothing cached)
-  a.k.tile_clean = nullptr;                                   // the cached rows are current, hence every root's q and qt
-  a.k.all_clean = a.k.QC ? 1u : 0u;
   a.k.root_src = src; a.k.root_dst = dst; a.k.root_ts = ts; a.k.nodes = d.N;
   a.k.head = d.pred_w; a.k.scores = scores;
   a.s = s; a.rows = nullptr; a.cp = nullptr; a.cm = 2 * n; a.set_attr = false;

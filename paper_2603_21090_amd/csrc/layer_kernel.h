@@ -12,21 +12,31 @@
 // cached rows hold the node terms alone.
 // A workgroup of eight waves (four: rows of one slot, delta mode) owns 16 target rows and runs its phases without
 // leaving the CU:
-//   1. q  = h_v W_Q(node block) + phi(0) W_Q(time block)                           (MFMA 16x16x4)
-//   2. qt_h = q_h W_K,h[time]^T, kept in LDS                                        (MFMA)
+//   1. q  = h_v W_Q(node block) + phi(0) W_Q(time block)                           (MFMA 16x16x32, split operands)
+//   2. qt_h = q_h W_K,h[time]^T                                                     (MFMA)
 //   3. gather the cached rows of the ring entries, time encodings, scores, softmax, weighted sums;
 //      a row is served by one 16-lane group per key slot, lane x float4               (HBM / vector ALU)
 //   4. o_h += pb_h W_V,h[time]                                                       (MFMA)
 //   5. h_v' = [o_1 | .. | o_H] W_O + b_O, written into the layer cache               (MFMA)
 //   6. unless this is the last layer: the row's own cached keys|values for the next layer,
 //      h_v' [W_K | W_V](node rows of layer l + 1)                                     (MFMA)
-// Weights stream from L2 (group-major packing, see mfma16.h); several workgroups per CU overlap one's
-// gather with another's products.
+// Weights stream from L2, each phase's requested a phase ahead; several workgroups per CU overlap one's gather with
+// another's products.
+//
+// The products of phases 1, 2, 4, 5 and 6 take their fp32 operands as pairs of f16 (split16.h): a fifth of the matrix
+// cycles of the fp32 instructions, which had been 30 to 47 % of a launch and stood in line with everything else in it.  Layer launches
+// before and after: 1,000,000 nodes, d_edge 100, 1,017 -> 815 us and (query cache) 942 -> 793; 1,300,000 nodes, raw edge
+// rows, k = 20, 973 -> 817; 100,000 nodes, d_edge 172, 182 -> 151 and 182 -> 159; a rebuild of 200,000 nodes 583 + 403 -> 460 + 324;
+// 10,000 nodes 32 + 37 -> 26 + 32.  Errors of whole layer-2 tables against 64 bits (2-norm / largest over root mean square),
+// fp32 products -> split: d 100, d_edge 172, two heads 2.8e-7 / 2.7e-6 -> 2.5e-7 / 1.9e-6; raw edge rows, k = 20 2.2e-7 /
+// 2.4e-6 -> 1.4e-7 / 9.7e-7; four heads of 32 1.1e-7 / 1.0e-6 -> 7.2e-8 / 5.0e-7; one head of 64 1.2e-7 / 1.1e-6 ->
+// 1.0e-7 / 8.3e-7; one head of 100 1.2e-7 / 1.6e-6 -> 8.4e-8 / 6.9e-7.
 #pragma once
 #include <mutex>
 #include <type_traits>
 #include "stgn_internal.h"
 #include "mfma16.h"
+#include "split16.h"
 
 namespace stgn {
 
@@ -79,13 +89,13 @@ struct LayerLds {
 // fall into distinct banks.  ks = key slots (heads * slots per head), nz = slots of z = [phi | raw edge row].
 __host__ __device__ inline LayerLds layer_lds(uint32_t d_in, uint32_t heads, uint32_t ks, uint32_t nz, uint32_t k, bool delta) {
   LayerLds l;
-  const uint32_t wx = round_up(d_in, kGrpK), wo = kSlot * ks;
+  const uint32_t wx = round_up(d_in, 16u), wo = kSlot * ks;
   l.ldx = (wx > wo ? wx : wo) + 4;                // the input tile and the head-output tile share storage
   l.ldq = wo + 4;                                 // q in the padded-head layout, later the output rows h'
   l.ldz = heads * kSlot * nz + 4;
   l.off_q = kTM * l.ldx;
   l.off_z = l.off_q + kTM * l.ldq;
-  l.off_r = l.off_z + kTM * l.ldz + 4 * kGrpK;    // operand reads may run one chunk past the last row
+  l.off_r = l.off_z + kTM * l.ldz + 64u;    // operand reads may run one chunk past the last row
   l.off_sc = l.off_r + kTM * k * 4;               // the ring records of the tile's rows, 16 bytes each
   l.total = l.off_sc + (delta ? kTM * k * heads : 0u);       // delta mode: the scores of a row's entries until its weights are known
   return l;
@@ -110,14 +120,14 @@ struct LayerArgs {
   const double* om_rev; const double* ph_rev;
   Ctrl* ctrl;
   uint64_t* gathered_slots;                        // statistic: ring entries gathered, one plain counter per workgroup index
-  const float *WQ, *cQ, *WKT, *WV, *WO, *bO, *WKVnext;   // matrices group-major (mfma16.h)
+  const float *WQ, *cQ, *WKT, *WV, *WO, *bO, *WKVnext;   // matrices in the packing of split16.h
+  SplitParams sp; float iKVnext;                   // their inverse scales and the bounds (LayerDev)
   uint32_t ld_in, ld_out, ld_kv, ld_kve;           // ld_kve = 0 without edge features (every edge reads one zero row)
   uint32_t k, d_in, d_emb, dk, d_time, d_edge;
-  // query cache (both null: off): this layer's cached q | qt rows, [node][64 (KS + H NZ)], and per tile of the
-  // row list whether every row's input row is unchanged (then q and qt are read back, not projected); a
-  // launch that must recompute everything passes tile_clean = null and still refreshes QC
+  // query cache (null: off): this layer's cached q | qt rows, [node][64 (KS + H NZ)], and per tile of the row list whether
+  // every row's input row is unchanged (then q and qt are read back, not projected); a launch that must recompute everything
+  // takes the variant without the cache, which still refreshes QC.  Link scores read every root's row back: nothing changed.
   float* QC; const uint8_t* tile_clean;
-  uint32_t all_clean;                              // every listed row reads q | qt back (root-node inference: nothing changed)
   // delta mode (read by the delta variant only): the batch's dirty flags and the highest flag whose owner's
   // input row of this layer changed (a row at or below it, or an endpoint, is recomputed exactly; an entry whose
   // neighbour is at or below it is a changed entry); the attention cache of this layer; the drift estimator
@@ -160,7 +170,7 @@ __device__ inline void wave_lds_fence() {
 // rows of one slot and the delta mode: four.  What bounds the kernel is the latency of a tile's dependent phases, so what
 // counts is waves in flight and work per wave.  With one 16-lane group per row (all slots of all heads in one lane) a wave
 // needed 240 registers, eight waves fitted a CU, and the time parameters and qt went through LDS once per entry; with
-// a group per slot it needs 117 - 128, sixteen fit, and the entry loop reads nothing from LDS but the ring
+// a group per slot it needs 111 - 128, sixteen fit, and the entry loop reads nothing from LDS but the ring
 // record.  Layer launches before and after: 100,000 nodes, d_edge 172, 197 -> 173 us; 1,000,000 nodes, d_edge 100,
 // 1,087 -> 971 and (query cache) 1,054 -> 1,012; 1,300,000 nodes, raw edge rows, k = 20, 1,053 -> 973; four
 // heads of 32, 20,000 nodes, 110 -> 75; 10,000 nodes, one tile per workgroup, 33 -> 31.
@@ -171,7 +181,7 @@ __host__ __device__ constexpr int layer_waves(int ks, bool delta) { return delta
 // in the re-associated time products (scores: (W_K,h[time | edge] q_h) . z_j; values: (sum_j a_j z_j)
 // W_V,h[time | edge]), and the cached rows hold the node parts alone.
 // DELTA: the approximate mode of Sec. 3.3 "Stage 4" (attention cache, delta update of changed entries).
-// QCACHE: the query cache is in use (rows may read q and qt back, rows that project store theirs).
+// QCACHE: rows may read q and qt back from the query cache.
 // ROOTS: root-node inference (LayerArgs::root_src and on).  A variant of its own and not a test at run time: the
 // places that differ would cost every streamed launch registers.
 template <int KS, int NT, int ES, int H, int JC, int WGS, bool DELTA, bool QCACHE, bool ROOTS>
@@ -188,6 +198,9 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   constexpr int RPP = 4 / GPR;                // rows a wave works on at a time there
   constexpr int PASSES = RPW / RPP;
   __shared__ uint32_t s_node[2][kTM], s_sum[NW];
+  // the rows' scales (split16.h): of the input rows, of q, of pb per head, of the output rows, and of the head outputs
+  // (these held twice, by tile parity: a wave may be at the next tile's while another still reads this one's)
+  __shared__ __align__(16) float s_sx[kTM], s_sq[kTM], s_sz[H][kTM], s_sh[kTM], s_so[2][kTM];
   __shared__ __align__(16) double s_om[NT * kSlot], s_ph[NT * kSlot];
   static_assert(KS % H == 0, "whole slots per head");
   static_assert(!(DELTA && ES), "the delta mode keeps projected edge rows");
@@ -208,8 +221,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   // wave index, made provably uniform so that tile indices and weight addresses stay in scalar registers
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const uint32_t k = a.k, dk = a.dk;
-  const uint32_t c_in = chunks_of(a.d_in), c_de = chunks_of(a.d_emb);                                     // chunks of K
-  const uint32_t g_in = kCG * c_in, g_de = kCG * c_de, g_dk = kCG * SH, g_zt = kCG * NZ, g_o = kCG * KS;  // groups of K
+  const uint32_t c_in = chunks64(a.d_in), c_de = chunks64(a.d_emb);                                       // chunks of K
   const uint32_t ntd = round_up(a.d_emb, 16) >> 4, ntk = round_up(dk, 16) >> 4;                           // column tiles
   constexpr uint32_t ntz = Ztp >> 4;                                                                       // tiles of a qt vector
   const uint32_t nzt_t = (a.d_time + 15u) >> 4, nzt = nzt_t + (ES ? (a.d_edge + 15u) >> 4 : 0u);           // ... that hold valid columns
@@ -230,6 +242,14 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   uint32_t gathered = 0;                      // ring entries of this wave's rows
   double drift_sum = 0.0;                     // delta mode: this wave's share of the drift estimator's sum and member count
   uint32_t drift_new = 0;
+  // Arguments that a phase needs once a tile: fetched from the argument block there (a scalar load that the phase's products
+  // cover), not held, or spilled, through the tile loop.
+  typedef const __attribute__((address_space(4))) LayerArgs* ArgBlock;
+  auto args = [&]() {
+    ArgBlock p = (ArgBlock)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+  };
   auto derive_lane = [&]() {
     uint32_t x;
     asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(x));
@@ -244,112 +264,178 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   const uint32_t nu2 = wave < nunits2 ? (nunits2 - wave + (NW - 1u)) / NW : 0u;     // units of this wave
   struct Unit2 { uint32_t h, t0, t1; bool two; };
   uint32_t udesc = 0;
-  if (lane < nu2) {
+  auto describe2 = [&]() {
     // the i-th valid tile: time tiles first, then (raw edge rows) the tiles of slot NT
     auto vt = [&](uint32_t i) { return i < nzt_t ? i : 4u * NT + (i - nzt_t); };
-    const uint32_t x = wave + NW * lane, h = x / npr, i0 = NTL * (x - h * npr);
+    const uint32_t x = wave + NW * (lane < nu2 ? lane : 0u), h = x / npr, i0 = NTL * (x - h * npr);
     const uint32_t two = NTL == 2 && i0 + 1u < nzt ? 1u : 0u;
-    udesc = h | (vt(i0) << 8) | (vt(i0 + two) << 16) | (two << 24);
-  }
+    udesc = nu2 ? h | (vt(i0) << 8) | (vt(i0 + two) << 16) | (two << 24) : 0u;
+  };
+  describe2();
   auto decode2 = [&](uint32_t i) {
     const uint32_t dsc = (uint32_t)__builtin_amdgcn_readlane((int)udesc, (int)i);
     Unit2 u;
     u.h = dsc & 0xFFu; u.t0 = (dsc >> 8) & 0xFFu; u.t1 = (dsc >> 16) & 0xFFu; u.two = (dsc >> 24) != 0u;
     return u;
   };
-  auto wkt = [&](uint32_t h, uint32_t t) { return a.WKT + (size_t)(h * ntz + t) * g_dk * kGrpFloats; };
-  auto request2 = [&](const Unit2& u, Ops16<NTL>& o) {
-    load_b16(wkt(u.h, u.t0), 0, o.b[0], lane);
-    if constexpr (NTL == 2) load_b16(wkt(u.h, u.t1), 0, o.b[1], lane);
+  auto wkt = [&](uint32_t h, uint32_t t) { return a.WKT + (size_t)(h * ntz + t) * SH * kChunkFloats; };
+  auto request2 = [&](const Unit2& u, OpsS<NTL>& o) {
+    load_b64(wkt(u.h, u.t0), 0, o.b[0], lane);
+    if constexpr (NTL == 2) load_b64(wkt(u.h, u.t1), 0, o.b[1], lane);
   };
-  auto store2 = [&](const Unit2& u, const floatx4 (&acc)[NTL]) {
-    float* zp = Zs + u.h * Ztp + m16_row(lane, 0) * ll.ldz + m16_col(lane);
+  // four rows' factors that take a product back to scale: the matrix's inverse scale and the rows'
+  auto unscale = [&](const float* rows_s, float inv_w, float (&f)[4]) {
+    const float4 v = *reinterpret_cast<const float4*>(rows_s + s16_row(lane, 0));
+    f[0] = inv_pow2(v.x) * inv_w; f[1] = inv_pow2(v.y) * inv_w; f[2] = inv_pow2(v.z) * inv_w; f[3] = inv_pow2(v.w) * inv_w;
+  };
+  auto store2 = [&](const Unit2& u, const AccS<NTL>& acc, float iKT) {
+    float* zp = Zs + u.h * Ztp + s16_row(lane, 0) * ll.ldz + s16_col(lane);
+    float f[4];
+    unscale(s_sq, iKT, f);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) zp[u.t0 * 16 + r * ll.ldz] = acc[0][r];
+    for (int r = 0; r < 4; ++r) zp[u.t0 * 16 + r * ll.ldz] = acc_value(acc, 0, r) * f[r];
     if constexpr (NTL == 2) {
       if (u.two) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) zp[u.t1 * 16 + r * ll.ldz] = acc[1][r];
+        for (int r = 0; r < 4; ++r) zp[u.t1 * 16 + r * ll.ldz] = acc_value(acc, 1, r) * f[r];
       }
     }
   };
   // ---- phase-4 work units: (head, NTL head-output column tiles)
-  const uint32_t np4 = (ntk + NTL - 1u) / NTL, nunits4 = H * np4;
-  // ---- phases 1 and 5: column tiles nt (and nt + 4) of the d_emb outputs form a unit; the bias values of
-  // a wave's first unit stay in registers (further units, d_emb > 128, read theirs when they get there)
-  float cq_r[NTL], bo_r[NTL];
-#pragma unroll
-  for (int t = 0; t < NTL; ++t) {
-    const uint32_t col = (wave + NW * t) * 16 + m16_col(lane);
-    cq_r[t] = col < a.d_emb ? a.cQ[col] : 0.0f;
-    bo_r[t] = col < a.d_emb ? a.bO[col] : 0.0f;
-  }
+  constexpr int N4 = KS == 1 ? 1 : NTL;       // (one slot: at most as many tiles as waves)
+  const uint32_t np4 = (ntk + N4 - 1u) / N4, nunits4 = H * np4;
+  // ---- phases 1 and 5: column tiles nt (and nt + 4) of the d_emb outputs form a unit
   // column tile of a product's t-th operand: past the end the unit's first tile again (its result is not stored)
-  auto tile_b = [&](const float* W, uint32_t nt, int t, uint32_t limit, uint32_t groups) {
+  auto tile_b = [&](const float* W, uint32_t nt, int t, uint32_t limit, uint32_t chunks) {
     const uint32_t x = nt + NW * t < limit ? nt + NW * t : nt;
-    return W + (size_t)x * groups * kGrpFloats;
+    return W + (size_t)x * chunks * kChunkFloats;
   };
   __syncthreads();
 
   // ---- staging of a tile, one tile ahead, every wave its own rows: lane -> (row lane / LS of the wave's, item lane % LS).
-  // Stage A requests the rows' ids (ahead of phase 1).  Stage B (issued with the first gathers of phase 3, whose waits
-  // cover it: a later wait for a weight chunk would stall on it, loads return in order) fetches, into registers, the
-  // lane's share of the rows' ring slots, degrees, query times and own input rows; the tile's phase 0 then only moves
-  // registers into LDS.  A workgroup strides over many tiles, so all but its first tile start without waiting for
-  // memory.  Shapes whose share does not fit the registers stage inside phase 0 instead.
-  const uint32_t qpr = round_up(a.d_in, kGrpK) >> 2;          // 16-byte quads per staged input row
-  const bool pf_ok = kTM * k <= 512u && kTM * qpr <= 512u;
+  // While a tile is worked on, the next one is made ready in steps, each behind requests that are waited for earlier
+  // (loads return in order): stage A requests the rows' ids at the top of the tile; stage B, behind the entry loop and
+  // the weights of phases 4 and 5, the lane's share of the rows' ring slots, degrees, query times and own input rows;
+  // `commit`, between phases 4 and 5, moves those into LDS (the ring records and input tile of this tile are no longer
+  // needed); and where q and qt are read back, they and the first gather are requested right behind it, so that phase 5
+  // hides them.  All but a workgroup's first tile start without waiting for memory.  Shapes whose share does not
+  // fit the registers fetch it inside `commit` instead.
+  const uint32_t qpr = round_up(a.d_in, 16u) >> 2;          // 16-byte quads per staged input row
+  const bool pf_ok = QCACHE || (kTM * k <= 512u && kTM * qpr <= 512u);   // (the query cache is kept for such shapes only)
   RingEntry p_ring[NI];
   uint32_t p_deg = 0;
   double p_tl = 0.0;
-  float4 p_x[NI];                                             // own input rows (not fetched for a tile that reads q | qt back)
+  float4 p_x[NI];                                             // own input rows (one address for all while q | qt are read back)
   constexpr uint32_t kQC = kSlot * (KS + H * NZ);             // floats per cached q | qt row
   uint32_t p_row = 0xFFFFFFFFu, p_clean = 0u;
   double p_tqn = 0.0;
-  // (requests only, but for the ids of link scores, which are compared with the node count at once)
   auto stage_a = [&](uint32_t t) {
     const uint32_t r = t * kTM + wave * RPW + lane / LS;
-    const bool listed = t < ntiles && r < n;
-    const uint32_t rc = listed ? r : 0u;
+    const uint32_t rc = r < n ? r : n - 1u;                   // (past the list: its last row, dropped in stage B)
     if constexpr (ROOTS) {
       p_row = ((rc & 1u) ? a.root_dst : a.root_src)[rc >> 1];
-      p_row = listed && p_row < a.nodes ? p_row : 0xFFFFFFFFu;
       p_tqn = a.root_ts[rc >> 1];
     } else {
       p_row = rows ? rows[rc] : rc;
-      p_row = listed ? p_row : 0xFFFFFFFFu;
     }
-    if constexpr (QCACHE) p_clean = t < ntiles ? (a.all_clean ? 1u : a.tile_clean ? a.tile_clean[t] : 0u) : 0u;
+    if constexpr (QCACHE && !ROOTS) {                         // (a byte of a word that no lane has to hold: scalar)
+      const uint32_t tc = t < ntiles ? t : ntiles - 1u;
+      typedef const __attribute__((address_space(4))) uint32_t* ScalarWords;
+      p_clean = (((ScalarWords)(uintptr_t)a.tile_clean)[tc >> 2] >> (8u * (tc & 3u))) & 0xFFu;
+    }
   };
-  auto stage_b = [&]() {
-    const bool cl = QCACHE && __builtin_amdgcn_readfirstlane((int)p_clean) != 0;
+  // (requests without conditions: behind a branch the compiler would wait for more than it needs to)
+  auto stage_b = [&](uint32_t t) {
+    const bool cl = QCACHE && (ROOTS || p_clean != 0u);
     const uint32_t it = lane % LS;
+    const ArgBlock ab = args();
+    if (t * kTM + wave * RPW + lane / LS >= n || (ROOTS && p_row >= a.nodes)) p_row = 0xFFFFFFFFu;
     const size_t nn = p_row != 0xFFFFFFFFu ? p_row : 0u;
-    p_deg = a.deg[nn];
-    p_tl = ROOTS ? p_tqn : a.t_last[nn];
+    p_deg = ab->deg[nn];
+    p_tl = ROOTS ? p_tqn : ab->t_last[nn];
 #pragma unroll
     for (int e = 0; e < NI; ++e) {
       const uint32_t sl = it + LS * e;
-      p_ring[e] = a.ring[nn * k + (sl < k ? sl : 0u)];
+      p_ring[e] = ab->ring[nn * k + (sl < k ? sl : 0u)];
     }
 #pragma unroll
     for (int e = 0; e < NI; ++e) {
       const uint32_t q = it + LS * e;
       // columns past d_in are row padding of the table (zero)
-      if (!cl) p_x[e] = *reinterpret_cast<const float4*>(a.Hin + nn * a.ld_in + 4u * (q < qpr ? q : 0u));
-      else p_x[e] = make_float4(0.f, 0.f, 0.f, 0.f);
+      p_x[e] = *reinterpret_cast<const float4*>(ab->Hin + (cl ? 0u : nn * ab->ld_in + 4u * (q < qpr ? q : 0u)));
     }
   };
-  auto stage_none = [&]() {                                   // keeps the registers defined on every path
+  // the staged tile's rows: id, entry count and query time of this lane's row
+  uint32_t node_s = 0xFFFFFFFFu, cnt_s = 0u;
+  double tq_s = 0.0;
+  // Input rows into Xs, split, each row under the scale of its largest magnitude; q's scale follows from a bound.  Columns up to
+  // the end of the last chunk are written (zero past d_in): what else lies there need not be a number.
+  const uint32_t qpz = min(16u * c_in, (ll.ldx - 4u) >> 2);
+  auto row_max = [&](float m) {                               // over the lanes that stage a row (LS = 16 or 32)
+    m = fmaxf(m, dpp_mov<0xB1>(m)); m = fmaxf(m, dpp_mov<0x4E>(m)); m = fmaxf(m, dpp_mov<0x141>(m)); m = fmaxf(m, dpp_mov<0x140>(m));
+    if constexpr (LS == 32u) { const Two w = both_of_pair(m); m = fmaxf(w.lo, w.hi); }
+    return m;
+  };
+  auto max4 = [](const float4& v) { return fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))); };
+  auto row_scales = [&](float m) {
+    const ArgBlock ab = args();
+    const float bQ = ab->sp.bQ, bcQ = ab->sp.bcQ;
+    m = row_max(m);
+    const uint32_t local = wave * RPW + lane / LS;
+    const float sx = pow2_scale(m);
+    if (lane % LS == 0u) { s_sx[local] = sx; s_sq[local] = pow2_scale(fmaf(m, bQ, bcQ)); }
+    return sx;
+  };
+  auto place_x = [&](uint32_t q, float4 v, float sx) {
+    if (q >= qpr || node_s == 0xFFFFFFFFu) v = make_float4(0.f, 0.f, 0.f, 0.f);
+    split_store4(Xs + (wave * RPW + lane / LS) * ll.ldx, 4u * q, v, sx);
+  };
+  auto commit_x = [&](bool staged) {
+    const uint32_t it = lane % LS;
+    if (staged) {
+      float m = 0.0f;
 #pragma unroll
-    for (int e = 0; e < NI; ++e) {
-      p_ring[e].nbr = 0u; p_ring[e].eid = 0u; p_ring[e].t = 0.0;
-      p_x[e] = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int e = 0; e < NI; ++e) m = fmaxf(m, it + LS * e < qpr ? max4(p_x[e]) : 0.0f);
+      const float sx = row_scales(m);
+#pragma unroll
+      for (int e = 0; e < NI; ++e) if (it + LS * e < qpz) place_x(it + LS * e, p_x[e], sx);
+    } else {
+      const float* xr = a.Hin + (size_t)(node_s != 0xFFFFFFFFu ? node_s : 0u) * a.ld_in;
+      float m = 0.0f;
+      for (uint32_t q = it; q < qpr; q += LS) m = fmaxf(m, max4(*reinterpret_cast<const float4*>(xr + 4u * q)));
+      const float sx = row_scales(m);
+      for (uint32_t q = it; q < qpz; q += LS) place_x(q, *reinterpret_cast<const float4*>(xr + 4u * (q < qpr ? q : 0u)), sx);
     }
-    p_deg = 0u; p_tl = 0.0;
   };
-  stage_a(blockIdx.x);
-  if (pf_ok) stage_b(); else stage_none();
+  auto commit = [&](uint32_t round) {
+    const uint32_t local = wave * RPW + lane / LS, it = lane % LS;
+    node_s = p_row;
+    const bool live = node_s != 0xFFFFFFFFu;
+    const size_t nn = live ? node_s : 0u;
+    const uint32_t dg0 = pf_ok ? p_deg : a.deg[nn];
+    tq_s = pf_ok || ROOTS ? p_tl : a.t_last[nn];
+    const uint32_t dg = live ? dg0 : 0u;
+    cnt_s = dg < k ? dg : k;
+    const uint32_t newest = dg ? (dg - 1u) % k : 0u;
+    // the record of adjacency position p sits in ring slot p mod k; with the row's degree known, slot
+    // sl holds the j-th most recent entry, j = (newest - sl) mod k; places past the row's entry count
+    // name node 0 / edge 0 (finite cached rows whose weight in every sum is zero)
+    auto place_ring = [&](uint32_t sl, RingEntry e) {
+      const uint32_t j = newest >= sl ? newest - sl : newest + k - sl;
+      if (j >= cnt_s) { e.nbr = 0u; e.eid = 0u; e.t = 0.0; }
+      Rs[local * k + j] = e;
+    };
+    if (it == 0u) s_node[round & 1u][local] = node_s;
+    if (pf_ok) {
+#pragma unroll
+      for (int e = 0; e < NI; ++e) if (it + LS * e < k) place_ring(it + LS * e, p_ring[e]);
+    } else {
+      for (uint32_t sl = it; sl < k; sl += LS) place_ring(sl, a.ring[nn * k + sl]);
+    }
+    wave_lds_fence();
+#pragma unroll
+    for (int r = 0; r < RPW; ++r) gathered += (uint32_t)__builtin_amdgcn_readlane((int)cnt_s, r * (int)LS);
+  };
 
   // Round i gives workgroup b the tile i G + (b + 37 i) mod G (G workgroups): every round is a permutation of
   // its G tiles, and a workgroup's position inside the round moves from round to round.  The row list may
@@ -357,33 +443,116 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   // the same workgroups every long tile.
   const uint32_t G = gridDim.x;
   auto tile_of = [&](uint32_t i) { return i * G + (blockIdx.x + 37u * i) % G; };
-  // A tile ends with a barrier only where its output rows are read back from LDS.  Otherwise a wave goes on to its next
-  // tile while others still read this tile's head outputs; tiles that read q | qt back then alternate between the
-  // two places for the head outputs, and all others have barriers ahead of what overwrites them.
-  const bool end_barrier = ROOTS || DELTA || a.KVout != nullptr;
-  bool o_in_x = false;                                        // the previous tile's head outputs lie in Xs
+
+  // ---- phase 3's rows: pass p works on rows p RPP .. p RPP + RPP - 1 of the wave's, GPR groups of 16 lanes each,
+  // group g on key slot g.  With one pass a lane's row is the one it staged, else the pass has one row.
+  static_assert(PASSES == 1 || RPP == 1, "a pass is either all rows of the wave or one of them");
+  uint32_t g = 0, head = 0, sg = 0;                           // this lane's key slot, its head and its place among the head's slots
+  auto derive_slot = [&]() { g = GPR == 1 ? 0u : grp % GPR; head = g / SH; sg = g - head * SH; };
+  auto row_of = [&](int p) { return wave * RPW + (PASSES == 1 ? lane / LS : (uint32_t)p); };
+  auto node_of = [&](int p) { return PASSES == 1 ? node_s : (uint32_t)__builtin_amdgcn_readlane((int)node_s, p * (int)LS); };
+  auto cnt_of = [&](int p) { return PASSES == 1 ? cnt_s : (uint32_t)__builtin_amdgcn_readlane((int)cnt_s, p * (int)LS); };
+  auto tq_of = [&](int p) {
+    if constexpr (PASSES == 1) return tq_s;
+    const uint64_t u = __builtin_bit_cast(uint64_t, tq_s);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, p * (int)LS);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), p * (int)LS);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+  };
+  auto cmax_of = [&](int p) {
+    uint32_t m = (uint32_t)__builtin_amdgcn_readlane((int)cnt_s, p * RPP * (int)LS);
+#pragma unroll
+    for (int r = 1; r < RPP; ++r) m = max(m, (uint32_t)__builtin_amdgcn_readlane((int)cnt_s, (p * RPP + r) * (int)LS));
+    return m;
+  };
+  auto gather = [&](int p, uint32_t c, ZBuf& zb) {
+    const RingEntry* rrow = Rs + row_of(p) * k;
+#pragma unroll
+    for (int jc = 0; jc < JC; ++jc) {
+      const uint32_t j = c * JC + jc;
+      const RingEntry e = rrow[j < k ? j : k - 1u];
+      const float* nrow = a.KVn + (size_t)e.nbr * (2u * kSlot * KS) + kSlot * g + 4u * sub;
+      zb.nk[jc] = *reinterpret_cast<const float4*>(nrow);
+      zb.nv[jc] = *reinterpret_cast<const float4*>(nrow + kSlot * KS);
+      if constexpr (ES) {
+        zb.e[jc][0] = *reinterpret_cast<const float4*>(a.KVe + (size_t)e.eid * kSlot + 4u * sub);
+      } else {
+        const float* erow = a.KVe + (size_t)e.eid * a.ld_kve + kSlot * g + 4u * sub;
+        zb.e[jc][0] = *reinterpret_cast<const float4*>(erow);
+        zb.e[jc][1] = *reinterpret_cast<const float4*>(erow + kSlot * KS);
+      }
+      zb.t[jc] = e.t;
+    }
+  };
+  // z slots a lane works with: all of them when a head is one slot (every head needs them all); shared out over the
+  // head's slots otherwise, slot t to the lanes of key slot t mod SH
+  constexpr int NZL = SH == 1 ? NZ : (NZ + SH - 1) / SH;
+  ZBuf z0[PASSES];                                            // the first gather
+  float4 qk[PASSES], qt[PASSES][NZL];                         // this lane's share of the row's q and qt vectors
+  auto request_first = [&](auto P) { gather(decltype(P)::value, 0, z0[decltype(P)::value]); };
+  // the pass's q and qt from the query cache, each lane what it needs, and its first gather
+  auto request_back = [&](auto P) {
+    constexpr int p = decltype(P)::value;
+    const uint32_t node = node_of(p);
+    const float* qrow = a.QC + (size_t)(node != 0xFFFFFFFFu ? node : 0u) * kQC + 4u * sub;
+    qk[p] = *reinterpret_cast<const float4*>(qrow + kSlot * g);
+#pragma unroll
+    for (int i = 0; i < NZL; ++i) {
+      const uint32_t t = SH == 1 ? (uint32_t)i : sg + SH * i;
+      qt[p][i] = *reinterpret_cast<const float4*>(qrow + kSlot * KS + head * Ztp + (t < NZ ? t : 0u) * kSlot);
+    }
+    request_first(P);
+  };
+  constexpr std::integral_constant<int, 0> kPass0{};
+
+  // Weights of phases 1 and 2: the first units' chunks, requested together.
+  const uint32_t w1 = wave < ntd ? wave : 0u;                // loads are unconditional (clamped), products are not
+  constexpr int C1 = KS == 1 && !DELTA ? 1 : 2;               // chunks of W_Q requested up front
+  Upfront<NTL, C1> u1;
+  float c1v[NTL];                                             // this lane's c_Q of the first unit
+  constexpr int U2 = SH == 1 ? 2 : 1;                         // phase 2's units requested up front
+  OpsS<NTL> o2[U2];
+  auto request12 = [&]() {
+    const float* const wq = args()->WQ;
+    const float* B1[NTL];
+#pragma unroll
+    for (int t = 0; t < NTL; ++t) B1[t] = tile_b(wq, w1, t, ntd, c_in);
+    u1.request(B1, c_in, lane);
+#pragma unroll
+    for (int t = 0; t < NTL; ++t) { const uint32_t col = (w1 + NW * t) * 16 + s16_col(lane); c1v[t] = a.cQ[col < a.d_emb ? col : 0u]; }
+#pragma unroll
+    for (int i = 0; i < U2; ++i) request2(decode2((uint32_t)i < nu2 ? i : 0u), o2[i]);   // (an idle wave: head 0, tile 0)
+  };
+
+  // the first tile
+  stage_a(blockIdx.x);
+  stage_b(blockIdx.x);
+  commit(0u);
+  commit_x(pf_ok);
+  derive_slot();
+  if constexpr (QCACHE) request_back(kPass0); else request12();
+  __syncthreads();
+
+  // What separates a tile's uses of the LDS from the next tile's.  Ring records: a wave reads only its own rows'.  Xs holds the
+  // input rows (phase 1), then the cached-value part of the head outputs (read in phase 4), and takes the next tile's
+  // input rows behind the barrier in front of phase 5.  Qs holds q, then the whole head outputs (phase 5): a projecting tile has a
+  // barrier ahead of its phase 1, a tile that reads q back writes Qs behind its first barrier.  Zs holds qt, pb, then the output
+  // rows (phase 6, link scores): projecting tiles have two barriers ahead of their qt, and where tiles may read theirs back, a
+  // tile that stored output rows there ends with one.
+  const bool kv = !ROOTS && a.KVout != nullptr, rows_in_lds = ROOTS || kv;
+  constexpr bool kRowsInZ = H * NZ >= KS;                     // (wide heads of few time slots: Zs is narrower than a row, they take Xs)
+  float* const Hs = kRowsInZ ? Zs : Xs;                       // output rows
+  const uint32_t ldh = kRowsInZ ? ll.ldz : ll.ldx;
   // One tile.  CLEAN: every row of it has its q and qt in the query cache.  Two copies of the body and not tests inside
   // one: merged, the query cache's variants spilled 29 to 51 registers, and a spilled prefetch is waited for.
   auto work_tile = [&](auto CLEAN, const uint32_t tile, const uint32_t round) __attribute__((always_inline)) {
     constexpr bool clean = decltype(CLEAN)::value;
     derive_lane();
-    uint32_t* nodes_s = s_node[round & 1u];
-    if (!clean && o_in_x) __syncthreads();
-    o_in_x = clean && !end_barrier && !o_in_x;
-    float* const Os = o_in_x ? Xs : Qs;                       // head outputs
-    float* const Hs = o_in_x ? Qs : Xs;                       // output rows
-    const uint32_t ldo = o_in_x ? ll.ldx : ll.ldq, ldh = o_in_x ? ll.ldq : ll.ldx;
-    // ================================================================ phase 0: stage the tile
-    Ops16<NTL> oq;                                            // first weight chunk of this wave's first unit
-    const uint32_t w1 = wave < ntd ? wave : 0u;              // loads are unconditional (clamped), products are not
-    if constexpr (!clean) {
-#pragma unroll
-      for (int t = 0; t < NTL; ++t) load_b16(tile_b(a.WQ, w1, t, ntd, g_in), 0, oq.b[t], lane);
-    }
-    const uint32_t node_s = p_row;                            // this lane's row while staging
+    derive_slot();
+    const uint32_t* nodes_s = s_node[round & 1u];
+    const uint32_t par = round & 1u;
+    const uint32_t local_s = wave * RPW + lane / LS;
     const bool live_s = node_s != 0xFFFFFFFFu;
-    const uint32_t local_s = wave * RPW + lane / LS, it = lane % LS;
-    if (it == 0u) nodes_s[local_s] = node_s;
     bool ex = false;
     if constexpr (DELTA) {
       // exact recomputation for endpoints of the batch (query time and entries moved), for rows whose own
@@ -391,198 +560,131 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
       const uint32_t fl = live_s ? a.flags[node_s] : 0u;
       ex = a.force_exact || fl == 1u || (fl != 0u && fl <= a.thr_in);
     }
-    uint32_t cnt_s, newest;
-    double tq_s;
-    auto row_facts = [&](uint32_t dg_in, double tl) {
-      const uint32_t dg = live_s ? dg_in : 0u;
-      cnt_s = dg < k ? dg : k;
-      newest = dg ? (dg - 1u) % k : 0u;
-      tq_s = tl;
-    };
-    // the record of adjacency position p sits in ring slot p mod k; with the row's degree known, slot
-    // sl holds the j-th most recent entry, j = (newest - sl) mod k; places past the row's entry count
-    // name node 0 / edge 0 (finite cached rows whose weight in every sum is zero)
-    auto place_ring = [&](uint32_t sl, RingEntry e) {
-      const uint32_t j = newest >= sl ? newest - sl : newest + k - sl;
-      if (j >= cnt_s) { e.nbr = 0u; e.eid = 0u; e.t = 0.0; }
-      Rs[local_s * k + j] = e;
-    };
-    auto place_x = [&](uint32_t q, float4 v) {
-      if (!live_s) v = make_float4(0.f, 0.f, 0.f, 0.f);
-      *reinterpret_cast<float4*>(Xs + local_s * ll.ldx + 4u * q) = v;
-    };
-    if (pf_ok) {
-      // everything was fetched a tile ago: registers -> LDS
-      row_facts(p_deg, p_tl);
-#pragma unroll
-      for (int e = 0; e < NI; ++e) if (it + LS * e < k) place_ring(it + LS * e, p_ring[e]);
-      if constexpr (!clean) {
-#pragma unroll
-        for (int e = 0; e < NI; ++e) if (it + LS * e < qpr) place_x(it + LS * e, p_x[e]);
-      }
-    } else {
-      const size_t nn = live_s ? node_s : 0u;
-      row_facts(a.deg[nn], ROOTS ? p_tqn : a.t_last[nn]);
-      for (uint32_t sl = it; sl < k; sl += LS) place_ring(sl, a.ring[nn * k + sl]);
-      if constexpr (!clean)
-        for (uint32_t q = it; q < qpr; q += LS) place_x(q, *reinterpret_cast<const float4*>(a.Hin + nn * a.ld_in + 4u * q));
-    }
-    wave_lds_fence();
-#pragma unroll
-    for (int r = 0; r < RPW; ++r) gathered += (uint32_t)__builtin_amdgcn_readlane((int)cnt_s, r * (int)LS);
-    stage_a(tile_of(round + 1u));                            // row ids of this workgroup's next tile
-    // ---- phase 3's rows: pass p works on rows p RPP .. p RPP + RPP - 1 of the wave's, GPR groups of 16 lanes each,
-    // group g on key slot g.  With one pass a lane's row is the one it staged, else the pass has one row.
-    static_assert(PASSES == 1 || RPP == 1, "a pass is either all rows of the wave or one of them");
-    const uint32_t g = GPR == 1 ? 0u : grp % GPR;             // this lane's key slot,
-    const uint32_t head = g / SH, sg = g - head * SH;         // its head and its place among the head's slots
-    auto row_of = [&](int p) { return PASSES == 1 ? local_s : wave * RPW + (uint32_t)p; };
-    auto node_of = [&](int p) { return PASSES == 1 ? node_s : (uint32_t)__builtin_amdgcn_readlane((int)node_s, p * (int)LS); };
-    auto cnt_of = [&](int p) { return PASSES == 1 ? cnt_s : (uint32_t)__builtin_amdgcn_readlane((int)cnt_s, p * (int)LS); };
-    auto tq_of = [&](int p) {
-      if constexpr (PASSES == 1) return tq_s;
-      const uint64_t u = __builtin_bit_cast(uint64_t, tq_s);
-      const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, p * (int)LS);
-      const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), p * (int)LS);
-      return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
-    };
-    auto cmax_of = [&](int p) {
-      uint32_t m = (uint32_t)__builtin_amdgcn_readlane((int)cnt_s, p * RPP * (int)LS);
-#pragma unroll
-      for (int r = 1; r < RPP; ++r) m = max(m, (uint32_t)__builtin_amdgcn_readlane((int)cnt_s, (p * RPP + r) * (int)LS));
-      return m;
-    };
-    auto gather = [&](int p, uint32_t c, ZBuf& zb) {
-      const RingEntry* rrow = Rs + row_of(p) * k;
-#pragma unroll
-      for (int jc = 0; jc < JC; ++jc) {
-        const uint32_t j = c * JC + jc;
-        const RingEntry e = rrow[j < k ? j : k - 1u];
-        const float* nrow = a.KVn + (size_t)e.nbr * (2u * kSlot * KS) + kSlot * g + 4u * sub;
-        zb.nk[jc] = *reinterpret_cast<const float4*>(nrow);
-        zb.nv[jc] = *reinterpret_cast<const float4*>(nrow + kSlot * KS);
-        if constexpr (ES) {
-          zb.e[jc][0] = *reinterpret_cast<const float4*>(a.KVe + (size_t)e.eid * kSlot + 4u * sub);
-        } else {
-          const float* erow = a.KVe + (size_t)e.eid * a.ld_kve + kSlot * g + 4u * sub;
-          zb.e[jc][0] = *reinterpret_cast<const float4*>(erow);
-          zb.e[jc][1] = *reinterpret_cast<const float4*>(erow + kSlot * KS);
-        }
-        zb.t[jc] = e.t;
-      }
-    };
-    // z slots a lane works with: all of them when a head is one slot (every head needs them all); shared out over the
-    // head's slots otherwise, slot t to the lanes of key slot t mod SH
-    constexpr int NZL = SH == 1 ? NZ : (NZ + SH - 1) / SH;
-    ZBuf z0[PASSES];
-    float4 qk[PASSES], qt[PASSES][NZL];                       // this lane's share of the row's q and qt vectors
     if constexpr (clean) {
-      // the rows' q and qt from the query cache, each lane what it needs, requested together with the first gather
-      static_for<PASSES>([&](auto P) {
-        constexpr int p = decltype(P)::value;
-        const uint32_t node = node_of(p);
-        const float* qrow = a.QC + (size_t)(node != 0xFFFFFFFFu ? node : 0u) * kQC + 4u * sub;
-        qk[p] = *reinterpret_cast<const float4*>(qrow + kSlot * g);
-#pragma unroll
-        for (int i = 0; i < NZL; ++i) {
-          const uint32_t t = SH == 1 ? (uint32_t)i : sg + SH * i;
-          qt[p][i] = *reinterpret_cast<const float4*>(qrow + kSlot * KS + head * Ztp + (t < NZ ? t : 0u) * kSlot);
-        }
-        gather(p, 0, z0[p]);
-      });
+      if constexpr (PASSES == 2) request_back(std::integral_constant<int, 1>{});
+      stage_a(tile_of(round + 1u));                          // row ids of this workgroup's next tile
     } else {
-    __syncthreads();
     // ================================================================ phase 1: q = x W_Q + c_Q
-    for (uint32_t nt = wave; nt < ntd; nt += 8) {
-      const float* Bt[NTL];
-#pragma unroll
-      for (int t = 0; t < NTL; ++t) Bt[t] = tile_b(a.WQ, nt, t, ntd, g_in);
-      floatx4 acc[NTL] = {};
-      if (nt != wave) {
-#pragma unroll
-        for (int t = 0; t < NTL; ++t) load_b16(Bt[t], 0, oq.b[t], lane);
-      }
-      mfma16_gemm_pre<NTL>(Xs + a16_off(lane, ll.ldx), c_in, Bt, acc, oq, lane);
+    if constexpr (QCACHE) describe2();                        // (one register less through the other tiles)
+    if constexpr (QCACHE) request12();                        // (otherwise requested ahead of the previous tile's stores)
+    stage_a(tile_of(round + 1u));
+    if (!kRowsInZ && rows_in_lds && round) {                  // (the previous tile had its output rows where the input rows go)
+      __syncthreads();
+      commit_x(false);
+    }
+    __syncthreads();                                          // input rows there, the previous tile's head outputs read
+    const float iQ = args()->sp.iQ;
+    auto store1 = [&](uint32_t nt, const AccS<NTL>& acc) {
+      float f[4];
+      unscale(s_sx, iQ, f);
+      const float4 sq = *reinterpret_cast<const float4*>(s_sq + s16_row(lane, 0));
+      const float sqv[4] = {sq.x, sq.y, sq.z, sq.w};
 #pragma unroll
       for (int t = 0; t < NTL; ++t) {
-        const uint32_t col = (nt + NW * t) * 16 + m16_col(lane);
+        const uint32_t col = (nt + NW * t) * 16 + s16_col(lane);
         if (nt + NW * t < ntd && col < a.d_emb) {
-          const float cq = nt == wave ? cq_r[t] : a.cQ[col];
+          const float cq = nt == wave ? c1v[t] : a.cQ[col];
           const uint32_t h = H == 1 ? 0u : H == 2 ? (col >= dk ? 1u : 0u) : (col >= dk ? 1u : 0u) + (col >= 2u * dk ? 1u : 0u) + (col >= 3u * dk ? 1u : 0u);
-          float* qp = Qs + m16_row(lane, 0) * ll.ldq + h * (SH * kSlot) + (col - h * dk);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) qp[r * ll.ldq] = acc[t][r] + cq;
+          for (int r = 0; r < 4; ++r)
+            split_store1(Qs + s16_row(lane, r) * ll.ldq, h * (SH * kSlot) + (col - h * dk), fmaf(acc_value(acc, t, r), f[r], cq), sqv[r]);
         }
       }
+    };
+    if (wave < ntd) {
+      const float* B1[NTL];
+#pragma unroll
+      for (int t = 0; t < NTL; ++t) B1[t] = tile_b(a.WQ, w1, t, ntd, c_in);
+      AccS<NTL> acc;
+      u1.multiply(Xs + s16_off(lane, ll.ldx), c_in, B1, acc, lane);
+      store1(wave, acc);
     }
+    for (uint32_t nt = wave + 8; nt < ntd; nt += 8) {
+      const float* Bt[NTL];
+#pragma unroll
+      for (int t = 0; t < NTL; ++t) Bt[t] = tile_b(a.WQ, nt, t, ntd, c_in);
+      AccS<NTL> acc;
+      mfma_lean<NTL>(Xs + s16_off(lane, ll.ldx), 0u, c_in, Bt, acc, lane);
+      store1(nt, acc);
+    }
+    __syncthreads();
     // ================================================================ phase 2: qt_h = q_h W_K,h[time]^T
     {
-      Ops16<NTL> o2;
-      Unit2 ua = decode2(0);                                  // weights of the first unit are requested
-      request2(ua, o2);                                       // ahead of the barrier (unit 0 of an idle wave: head 0, tile 0)
-      __syncthreads();
-      const float* qa = Qs + a16_off(lane, ll.ldq);
-      if constexpr (SH == 1) {
-        // one chunk per unit: the operands of the next unit are in flight during this unit's products
-        load_a16(qa + ua.h * kSlot, 0, o2.a);
-        if (nu2) pingpong_peeled<Ops16<NTL>>(
-            nu2, o2,
-            [&](uint32_t i, Ops16<NTL>& o) {
-              const Unit2 u = decode2(i);
-              load_a16(qa + u.h * kSlot, 0, o.a);
-              request2(u, o);
-            },
-            [&](uint32_t i, const Ops16<NTL>& o) {
-              const Unit2 u = decode2(i);
-              floatx4 acc[NTL] = {};
-              mfma16_chunk<NTL>(o, acc);
-              store2(u, acc);
-            });
+      const float* qa = Qs + s16_off(lane, ll.ldq);
+      const float iKT = args()->sp.iKT;
+      auto products2 = [&](uint32_t i, OpsS<NTL>& o) {
+        const Unit2 u = decode2(i);
+        AccS<NTL> acc;
+        const float* qh = qa + u.h * (SH * kSlot);
+        load_a64(qh, 0, o.a);
+        mfma_chunk<NTL>(o.a, o.b, acc);
+        if constexpr (SH > 1) {
+          const float* Bt[NTL];
+          Bt[0] = wkt(u.h, u.t0);
+          if constexpr (NTL == 2) Bt[1] = wkt(u.h, u.t1);
+          mfma_lean<NTL>(qh, 1u, SH, Bt, acc, lane);
+        }
+        store2(u, acc, iKT);
+      };
+      if constexpr (U2 == 2) {
+        for (uint32_t i = 0; i < nu2; i += 2) {
+          products2(i, o2[0]);
+          if (i + 2 < nu2) request2(decode2(i + 2), o2[0]);
+          if (i + 1 < nu2) {
+            products2(i + 1, o2[1]);
+            if (i + 3 < nu2) request2(decode2(i + 3), o2[1]);
+          }
+        }
       } else {
         for (uint32_t i = 0; i < nu2; ++i) {
-          ua = decode2(i);
-          const float* Bt[NTL];
-          Bt[0] = wkt(ua.h, ua.t0);
-          if constexpr (NTL == 2) Bt[1] = wkt(ua.h, ua.t1);
-          floatx4 acc[NTL] = {};
-          if (i) request2(ua, o2);
-          mfma16_gemm_pre<NTL>(qa + ua.h * (SH * kSlot), SH, Bt, acc, o2, lane);
-          store2(ua, acc);
+          products2(i, o2[0]);
+          if (i + 1 < nu2) request2(decode2(i + 1), o2[0]);
         }
       }
     }
-    if constexpr (!DELTA) static_for<PASSES>([&](auto P) { gather(decltype(P)::value, 0, z0[decltype(P)::value]); });
+    if constexpr (!DELTA) static_for<PASSES>(request_first);
     __syncthreads();
     }  // q and qt: read back, or projected
-    if constexpr (!DELTA) {
-      if constexpr (!clean) {
-        static_for<PASSES>([&](auto P) {
-          constexpr int p = decltype(P)::value;
-          const uint32_t node = node_of(p), local = row_of(p);
-          qk[p] = *reinterpret_cast<const float4*>(Qs + local * ll.ldq + kSlot * g + 4u * sub);
-          float* qrow = QCACHE ? a.QC + (size_t)node * kQC + 4u * sub : nullptr;
-          const bool keep = QCACHE && !ROOTS && node != 0xFFFFFFFFu;           // the rows' q | qt for later batches
-          if (keep) *reinterpret_cast<float4*>(qrow + kSlot * g) = qk[p];
-#pragma unroll
-          for (int i = 0; i < NZL; ++i) {
-            const uint32_t t = SH == 1 ? (uint32_t)i : sg + SH * i, at = head * Ztp + (t < NZ ? t : 0u) * kSlot;
-            qt[p][i] = *reinterpret_cast<const float4*>(Zs + local * ll.ldz + at + 4u * sub);
-            if (keep && t < NZ) *reinterpret_cast<float4*>(qrow + kSlot * KS + at) = qt[p][i];
-          }
-        });
-      }
-    }
-    // ================================================================ phase 3: gather + attention
     // The time encodings are not masked per entry: a column past d_time has omega = phase = 0 and comes out as
-    // cos(0) = 1.  In the scores it meets an exact zero of qt (zero weight columns; tiles phase 2 does not
-    // write hold what the previous tile's pb left there, hence the zeros written here), and its share of pb
-    // is cleared once per row, when pb goes into its tile.
+    // cos(0) = 1.  In the scores it meets an exact zero of qt and in phase 4 one of pb: both are cleared there once
+    // per row.
     auto clear_past_d_time = [&](float4& o, int t) {
       const uint32_t c0 = (uint32_t)t * kSlot + 4u * sub;
       o.x = c0 < a.d_time ? o.x : 0.0f;
       o.y = c0 + 1u < a.d_time ? o.y : 0.0f;
       o.z = c0 + 2u < a.d_time ? o.z : 0.0f;
       o.w = c0 + 3u < a.d_time ? o.w : 0.0f;
+    };
+    if constexpr (!DELTA) {
+      if constexpr (!clean) {
+        static_for<PASSES>([&](auto P) {
+          constexpr int p = decltype(P)::value;
+          const uint32_t node = node_of(p), local = row_of(p);
+          qk[p] = split_load4(Qs + local * ll.ldq, kSlot * g + 4u * sub, inv_pow2(s_sq[local]));
+          float* qrow = a.QC + (size_t)node * kQC + 4u * sub;
+          const bool keep = !ROOTS && a.QC && node != 0xFFFFFFFFu;             // the rows' q | qt for later batches
+          if (keep) *reinterpret_cast<float4*>(qrow + kSlot * g) = qk[p];
+#pragma unroll
+          for (int i = 0; i < NZL; ++i) {
+            const uint32_t t = SH == 1 ? (uint32_t)i : sg + SH * i, at = head * Ztp + (t < NZ ? t : 0u) * kSlot;
+            qt[p][i] = *reinterpret_cast<const float4*>(Zs + local * ll.ldz + at + 4u * sub);
+            if (t < NT) clear_past_d_time(qt[p][i], t);
+            if (keep && t < NZ) *reinterpret_cast<float4*>(qrow + kSlot * KS + at) = qt[p][i];
+          }
+        });
+      }
+    }
+    // ================================================================ phase 3: gather + attention
+    auto group_max = [&](float m) {                           // over a 16-lane group
+      m = fmaxf(m, dpp_mov<0xB1>(m)); m = fmaxf(m, dpp_mov<0x4E>(m)); m = fmaxf(m, dpp_mov<0x141>(m));
+      return fmaxf(m, dpp_mov<0x140>(m));
+    };
+    // scales of the head outputs and of the output rows, from bounds: the largest cached-value part plus what pb can add
+    auto output_scales = [&](uint32_t local, float m_o, float m_z, bool writer) {
+      const ArgBlock ab = args();
+      const float bV = ab->sp.bV, bO = ab->sp.bO, bbO = ab->sp.bbO;
+      const float bo = fmaf(m_z, bV, m_o);
+      if (writer) { s_so[par][local] = pow2_scale(bo); s_sh[local] = pow2_scale(fmaf(bo, bO, bbO)); }
     };
     if constexpr (DELTA) {
       // ---- delta mode.  An exact row runs the same online softmax as the exact mode and leaves its attention
@@ -619,8 +721,16 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
       }
       float4 qk[KS];
 #pragma unroll
-      for (int s = 0; s < KS; ++s) qk[s] = *reinterpret_cast<const float4*>(Qs + local * ll.ldq + s * kSlot + 4u * sub);
-      const float* zq = Zs + local * ll.ldz + 4u * sub;
+      for (int s = 0; s < KS; ++s) qk[s] = split_load4(Qs + local * ll.ldq, s * kSlot + 4u * sub, inv_pow2(s_sq[local]));
+      float* zq = Zs + local * ll.ldz + 4u * sub;
+#pragma unroll
+      for (int h = 0; h < H; ++h)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          float4 o = *reinterpret_cast<float4*>(zq + h * Ztp + t * kSlot);
+          clear_past_d_time(o, t);
+          *reinterpret_cast<float4*>(zq + h * Ztp + t * kSlot) = o;
+        }
       uint32_t nch = 0, nvalid = 0;
       const bool any_delta = __any(!ex);                      // (exact rows take every entry: no flags needed)
       struct DBuf { float4 n[2 * KS], e[2 * KS]; uint32_t j; };
@@ -755,6 +865,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
       }
       // ---- the row's sums: normalised by the denominator after an exact recomputation, as they stand after a delta update
       wave_lds_fence();
+      float m_o = 0.0f, m_z = 0.0f;                           // largest head output of the row (cached part), largest pb of any head
 #pragma unroll
       for (int h = 0; h < H; ++h) {
         const float inv = ex ? (lrun[h] > 0.0f ? 1.0f / lrun[h] : 0.0f) : 1.0f;
@@ -762,17 +873,25 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
         for (int s = h * SH; s < (h + 1) * SH; ++s) {
           float4 o = accv[s];
           o.x *= inv; o.y *= inv; o.z *= inv; o.w *= inv;
-          *reinterpret_cast<float4*>(Qs + local * ll.ldq + s * kSlot + 4u * sub) = o;
+          *reinterpret_cast<float4*>(Xs + local * ll.ldx + s * kSlot + 4u * sub) = o;
+          m_o = fmaxf(m_o, max4(o));
           if (live) *reinterpret_cast<float4*>(acS + s * kSlot) = o;
         }
+        float mz = 0.0f;
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-          float4 o = accp[h][t];
+          float4& o = accp[h][t];
           o.x *= inv; o.y *= inv; o.z *= inv; o.w *= inv;
           clear_past_d_time(o, t);
-          *reinterpret_cast<float4*>(Zs + local * ll.ldz + h * Ztp + t * kSlot + 4u * sub) = o;
+          mz = fmaxf(mz, max4(o));
           if (live) *reinterpret_cast<float4*>(acP + (h * NT + t) * kSlot) = o;
         }
+        mz = row_max(mz);
+        m_z = fmaxf(m_z, mz);
+        const float sz = pow2_scale(mz);
+        if (sub == 0) s_sz[h][local] = sz;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) split_store4(Zs + local * ll.ldz, h * Ztp + t * kSlot + 4u * sub, accp[h][t], sz);
         if (live && sub == 0) { acZM[2 * h] = lrun[h]; acZM[2 * h + 1] = mref[h]; }
         if (ex && live)
           for (uint32_t j = sub; j < cnt; j += 16) {          // the weights in effect after the exact recomputation
@@ -782,6 +901,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
             w[2 * h + 1] = lrun[h] > 0.0f ? __expf(sj - mref[h]) * inv : 0.0f;
           }
       }
+      output_scales(local, row_max(m_o), m_z, sub == 0);
       // ---- drift estimator (Sec. 3.5), final layer: an exact recomputation restarts the node's estimate, a
       // delta update adds the changed fraction of its entries to the decayed estimate
       // (the changes of the sum and of the member count are collected per wave and added once, at the end of
@@ -909,108 +1029,157 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
         }
       };
       if (nchunk3) pingpong_clamped<ZBuf>(nchunk3, z0[p], [&](uint32_t c, ZBuf& zb) { gather(p, c, zb); }, attend);
-      // the cached-value part of the head outputs goes into the O tile (padded-head layout; the
-      // padding lanes hold exact zeros), pb overwrites qt (each lane owns its float4s)
+      // the cached-value part of the head outputs goes into Xs (padded-head layout; the padding lanes hold exact
+      // zeros), pb, split, where qt is (each lane owns its columns)
+      wave_lds_fence();                                       // (a lane's split columns share their bytes with its neighbour's qt)
       const float inv = lrun > 0.0f ? 1.0f / lrun : 0.0f;     // no entry, or none inside the window: b_O alone
       accv.x *= inv; accv.y *= inv; accv.z *= inv; accv.w *= inv;
-      *reinterpret_cast<float4*>(Os + local * ldo + kSlot * g + 4u * sub) = accv;
+      *reinterpret_cast<float4*>(Xs + local * ll.ldx + kSlot * g + 4u * sub) = accv;
+      float m_o = group_max(max4(accv)), m_z = 0.0f;
 #pragma unroll
       for (int i = 0; i < NZL; ++i) {
         const uint32_t t = SH == 1 ? (uint32_t)i : sg + SH * i;
-        float4 o = accp[i];
+        float4& o = accp[i];
         o.x *= inv; o.y *= inv; o.z *= inv; o.w *= inv;
         if (t < NT) clear_past_d_time(o, t);                   // (a raw edge row's padding is zero, and so are its sums)
-        if (t < NZ) *reinterpret_cast<float4*>(Zs + local * ll.ldz + head * Ztp + t * kSlot + 4u * sub) = o;
+        m_z = fmaxf(m_z, max4(o));
       }
+      m_z = group_max(m_z);
+      if constexpr (SH >= 2) { const Two w = both_of_pair(m_z); m_z = fmaxf(w.lo, w.hi); }
+      if constexpr (SH == 4) { const Two w = both_halves(m_z); m_z = fmaxf(w.lo, w.hi); }
+      const float sz = pow2_scale(m_z);                       // of the head's pb
+      if (sub == 0u && sg == 0u) s_sz[head][local] = sz;
+#pragma unroll
+      for (int i = 0; i < NZL; ++i) {
+        const uint32_t t = SH == 1 ? (uint32_t)i : sg + SH * i;
+        if (t < NZ) split_store4(Zs + local * ll.ldz, head * Ztp + t * kSlot + 4u * sub, accp[i], sz);
+      }
+      if constexpr (KS >= 2) { const Two w = both_of_pair(m_o), v = both_of_pair(m_z); m_o = fmaxf(w.lo, w.hi); m_z = fmaxf(v.lo, v.hi); }
+      if constexpr (KS == 4) { const Two w = both_halves(m_o), v = both_halves(m_z); m_o = fmaxf(w.lo, w.hi); m_z = fmaxf(v.lo, v.hi); }
+      output_scales(local, m_o, m_z, sub == 0u && g == 0u);
       });
     }
     // ================================================================ phase 4: o_h += pb_h W_V,h[time | raw edge]
+    // K runs over the slots of z, one chunk per slot.  The weights of this phase and of the next are requested ahead of its
+    // barrier, and behind them the next tile's rows.
     derive_lane();
-    {
-      // K runs over the slots of z, one chunk per slot.  Every weight chunk of the wave's first unit is requested ahead
-      // of the barrier: one memory latency for the unit, most of it spent waiting for the slowest wave of phase 3
-      // anyway.  Further units request theirs when they get there.
-      auto wv = [&](uint32_t h, uint32_t nt) { return a.WV + (size_t)(h * ntk + nt) * g_zt * kGrpFloats; };
-      uint32_t x = wave < nunits4 ? wave : nunits4 - 1u;
-      Upfront16<NTL, NZ> u4;
-      auto request4 = [&]() {
-        const uint32_t h4 = x / np4, n0 = NTL * (x - h4 * np4);
-        const float* Bt[NTL];
+    auto wv = [&](uint32_t h, uint32_t nt) { return a.WV + (size_t)(h * ntk + nt) * NZ * kChunkFloats; };
+    uint32_t x4 = wave < nunits4 ? wave : nunits4 - 1u;
+    Upfront<N4, NZ> u4;
+    const float* B4[N4];
+    auto request4 = [&]() {
+      const uint32_t h4 = x4 / np4, n0 = N4 * (x4 - h4 * np4);
 #pragma unroll
-        for (int t = 0; t < NTL; ++t) Bt[t] = wv(h4, n0 + t < ntk ? n0 + t : n0);
-        u4.request(Bt, NZ, lane);
-      };
-      request4();
-      // the next tile's rows travel during the dense phases, behind the weights this phase waits for (ahead of the entry
-      // loop they would take registers from it)
-      if (pf_ok) stage_b(); else stage_none();
-      __syncthreads();
-      if (wave < nunits4) {
-        for (;;) {
-          const uint32_t h4 = x / np4, n0 = NTL * (x - h4 * np4);
-          floatx4 acc[NTL] = {};
-          u4.multiply(Zs + h4 * Ztp + a16_off(lane, ll.ldz), NZ, acc);
+      for (int t = 0; t < N4; ++t) B4[t] = wv(h4, n0 + t < ntk ? n0 + t : n0);
+      u4.request(B4, NZ, lane);
+    };
+    constexpr int U5 = NTL == 1 ? (KS < 2 ? KS : 2) : KS <= 2 ? KS : 1;   // chunks of W_O requested up front
+    Upfront<NTL, U5> u5;
+    const float* B5[NTL];
 #pragma unroll
-          for (int t = 0; t < NTL; ++t) {
-            const uint32_t col = (n0 + t) * 16 + m16_col(lane);
-            if (n0 + t < ntk && col < dk) {
-              float* op = Os + m16_row(lane, 0) * ldo + h4 * (SH * kSlot) + col;    // one lane per (row, column)
+    for (int t = 0; t < NTL; ++t) B5[t] = tile_b(a.WO, w1, t, ntd, KS);
+    float b5v[NTL];                                           // this lane's bias of the first unit
+    auto request5 = [&]() {
+      u5.request(B5, KS, lane);
 #pragma unroll
-              for (int r = 0; r < 4; ++r) op[r * ldo] += acc[t][r];
+      for (int t = 0; t < NTL; ++t) { const uint32_t col = (w1 + NW * t) * 16 + s16_col(lane); b5v[t] = a.bO[col < a.d_emb ? col : 0u]; }
+    };
+    request4();
+    stage_b(tile_of(round + 1u));
+    __syncthreads();
+    const float iV = args()->sp.iV;
+    if (wave < nunits4) {
+      const float4 so = *reinterpret_cast<const float4*>(s_so[par] + s16_row(lane, 0));
+      const float sov[4] = {so.x, so.y, so.z, so.w};
+      for (;;) {
+        const uint32_t h4 = x4 / np4, n0 = N4 * (x4 - h4 * np4);
+        AccS<N4> acc;
+        u4.multiply(Zs + h4 * Ztp + s16_off(lane, ll.ldz), NZ, B4, acc, lane);
+        float f[4];
+        unscale(s_sz[h4], iV, f);
+#pragma unroll
+        for (int t = 0; t < N4; ++t) {
+          const uint32_t col = (n0 + t) * 16 + s16_col(lane);
+          if (n0 + t < ntk && col < dk) {
+            const uint32_t at = h4 * (SH * kSlot) + col;      // one lane per (row, column)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const uint32_t row = s16_row(lane, r);
+              split_store1(Qs + row * ll.ldq, at, fmaf(acc_value(acc, t, r), f[r], Xs[row * ll.ldx + at]), sov[r]);
             }
           }
-          x += NW;
-          if (x >= nunits4) break;
-          request4();
         }
+        x4 += NW;
+        if (x4 >= nunits4) break;
+        request4();
       }
     }
     // ================================================================ phase 5: h' = o W_O + b_O
     derive_lane();
-    {
-      constexpr bool kUp = KS * NTL <= 4;                     // all weight chunks of the first unit requested up front
-      Ops16<NTL> oo;
-      Upfront16<NTL, kUp ? KS : 1> u5;
-      {
-        const float* Bt[NTL];
+    request5();
+    commit(round + 1u);
+    if constexpr (QCACHE) { derive_slot(); request_back(kPass0); }           // (a tile that projects does not use them)
+    __syncthreads();
+    if (kRowsInZ || !rows_in_lds) {                           // the next tile's input rows, if it projects
+      if (!QCACHE || (!ROOTS && p_clean == 0u)) commit_x(pf_ok);
+    }
+    // a load behind a store waits for it: the first units' results stay in registers until everything that the following
+    // phases read has been requested
+    const float iO = args()->sp.iO;
+    auto bias5 = [&](uint32_t nt, const AccS<NTL>& acc, floatx4 (&o)[NTL]) {
+      float f[4];
+      unscale(s_so[par], iO, f);
+      const float4 sh = *reinterpret_cast<const float4*>(s_sh + s16_row(lane, 0));
+      const float shv[4] = {sh.x, sh.y, sh.z, sh.w};
 #pragma unroll
-        for (int t = 0; t < NTL; ++t) Bt[t] = tile_b(a.WO, w1, t, ntd, g_o);
-        if constexpr (kUp) u5.request(Bt, KS, lane);
-        else {
+      for (int t = 0; t < NTL; ++t) {
+        const uint32_t col = (nt + NW * t) * 16 + s16_col(lane);
+        const float b = nt == wave ? b5v[t] : a.bO[col < a.d_emb ? col : 0u];
 #pragma unroll
-          for (int t = 0; t < NTL; ++t) load_b16(Bt[t], 0, oo.b[t], lane);
+        for (int r = 0; r < 4; ++r) {
+          o[t][r] = fmaf(acc_value(acc, t, r), f[r], b);
+          if (rows_in_lds && nt + NW * t < ntd && col < a.d_emb) {          // for the link scores; operand of phase 6
+            if constexpr (ROOTS) Hs[s16_row(lane, r) * ldh + col] = o[t][r];
+            else split_store1(Hs + s16_row(lane, r) * ldh, col, o[t][r], shv[r]);
+          }
         }
       }
-      __syncthreads();
-      for (uint32_t nt = wave; nt < ntd; nt += 8) {
-        const float* Bt[NTL];
-#pragma unroll
-        for (int t = 0; t < NTL; ++t) Bt[t] = tile_b(a.WO, nt, t, ntd, g_o);
-        floatx4 acc[NTL] = {};
-        if (kUp && nt == wave) {
-          u5.multiply(Os + a16_off(lane, ldo), KS, acc);
-        } else {
-          if (nt != wave) {
-#pragma unroll
-            for (int t = 0; t < NTL; ++t) load_b16(Bt[t], 0, oo.b[t], lane);
-          }
-          mfma16_gemm_pre<NTL>(Os + a16_off(lane, ldo), KS, Bt, acc, oo, lane);
-        }
+    };
+    auto store5 = [&](uint32_t nt, const floatx4 (&acc)[NTL]) {
+      if constexpr (!ROOTS) {
+        float* const hout = args()->Hout;
 #pragma unroll
         for (int t = 0; t < NTL; ++t) {
-          const uint32_t col = (nt + NW * t) * 16 + m16_col(lane);
+          const uint32_t col = (nt + NW * t) * 16 + s16_col(lane);
           if (nt + NW * t < ntd && col < a.d_emb) {
-            const float b = nt == wave ? bo_r[t] : a.bO[col];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-              const uint32_t node = nodes_s[m16_row(lane, r)];
-              const float v = acc[t][r] + b;
-              if (!ROOTS && node != 0xFFFFFFFFu) a.Hout[(size_t)node * a.ld_out + col] = v;
-              if (end_barrier) Hs[m16_row(lane, r) * ldh + col] = v;     // operand of phase 6 and of the link scores
+              const uint32_t node = nodes_s[s16_row(lane, r)];
+              if (node != 0xFFFFFFFFu) hout[(size_t)node * a.ld_out + col] = acc[t][r];
             }
           }
         }
       }
+    };
+    floatx4 out5[NTL] = {};
+    if (wave < ntd) {
+      AccS<NTL> acc;
+      u5.multiply(Qs + s16_off(lane, ll.ldq), KS, B5, acc, lane);
+      bias5(wave, acc, out5);
+    }
+    for (uint32_t nt = wave + 8; nt < ntd; nt += 8) {
+      const float* Bt[NTL];
+#pragma unroll
+      for (int t = 0; t < NTL; ++t) Bt[t] = tile_b(a.WO, nt, t, ntd, KS);
+      AccS<NTL> acc;
+      floatx4 o[NTL];
+      mfma_lean<NTL>(Qs + s16_off(lane, ll.ldq), 0u, KS, Bt, acc, lane);
+      bias5(nt, acc, o);
+      store5(nt, o);
+    }
+    if (!kRowsInZ && kv) {                                    // (Xs: what lies past the output row need not be a number)
+      const uint32_t w = 64u * c_de - a.d_emb;
+      for (uint32_t x = threadIdx.x; x < kTM * w; x += TH) split_store1(Xs + (x / w) * ll.ldx, a.d_emb + x % w, 0.0f, 1.0f);
     }
     if constexpr (ROOTS) {
       // link scores: a wave takes edges w and on of the tile (the list holds whole edges)
@@ -1027,43 +1196,77 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
       }
     }
     // ================================================================ phase 6: next layer's cached keys | values of these rows
-    if (!ROOTS && a.KVout) {
-      constexpr uint32_t ntkv = 8u * KS;                      // column tiles of a cached row; a wave takes tiles w + 8 i (and w + 8 i + 4)
-      Ops16<NTL> ok;
+    // A wave takes column tiles w, w + NW, ... of a cached row.  The second tile's chunks follow the first's into the same
+    // registers.
+    constexpr uint32_t ntkv = 8u * KS;
+    auto store6 = [&](uint32_t nt, const floatx4& acc) {
+      float* const kvout = args()->KVout;
+      const uint32_t col = nt * 16 + s16_col(lane);           // every column is written: padding columns get exact zeros
 #pragma unroll
-      for (int t = 0; t < NTL; ++t) load_b16(tile_b(a.WKVnext, wave, t, ntkv, g_de), 0, ok.b[t], lane);
+      for (int r = 0; r < 4; ++r) {
+        const uint32_t node = nodes_s[s16_row(lane, r)];
+        if (node != 0xFFFFFFFFu) kvout[(size_t)node * (2u * kSlot * KS) + col] = acc[r];
+      }
+    };
+    floatx4 out6[2] = {};
+    if (kv) {
+      const float* const wkv0 = args()->WKVnext;
+      auto wkv = [&](uint32_t nt) { return wkv0 + (size_t)nt * c_de * kChunkFloats; };
+      const float* Ha = Hs + s16_off(lane, ldh);
+      const uint32_t c1 = c_de > 1 ? 1u : 0u;
+      float4 b6[2][1][4];
+      load_b64(wkv(wave), 0, b6[0][0], lane);
+      load_b64(wkv(wave), c1, b6[1][0], lane);
       __syncthreads();
-      for (uint32_t nt = wave; nt < ntkv; nt += 8) {
-        const float* Bt[NTL];
+      float f[4];
+      unscale(s_sh, args()->iKVnext, f);
+      AccS<1> acc[2];
+      auto chunk6 = [&](uint32_t ch, const float4 (&b)[1][4], AccS<1>& ac) {
+        float4 x[4];
+        load_a64(Ha, ch, x);
+        mfma_chunk<1>(x, b, ac);
+      };
+      auto value6 = [&](const AccS<1>& ac) {
+        floatx4 v;
 #pragma unroll
-        for (int t = 0; t < NTL; ++t) Bt[t] = tile_b(a.WKVnext, nt, t, ntkv, g_de);
-        floatx4 acc[NTL] = {};
-        if (nt != wave) {
+        for (int r = 0; r < 4; ++r) v[r] = acc_value(ac, 0, r) * f[r];
+        return v;
+      };
+      chunk6(0, b6[0], acc[0]);
+      load_b64(wkv(wave + NW), 0, b6[0][0], lane);
+      if (c1) chunk6(1, b6[1], acc[0]);
+      load_b64(wkv(wave + NW), c1, b6[1][0], lane);
+      chunk6(0, b6[0], acc[1]);
+      if (c1) chunk6(1, b6[1], acc[1]);
 #pragma unroll
-          for (int t = 0; t < NTL; ++t) load_b16(Bt[t], 0, ok.b[t], lane);
-        }
-        mfma16_gemm_pre<NTL>(Hs + a16_off(lane, ldh), c_de, Bt, acc, ok, lane);
-#pragma unroll
-        for (int t = 0; t < NTL; ++t) {
-          const uint32_t col = (nt + NW * t) * 16 + m16_col(lane);   // every column is written: padding columns get exact zeros
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const uint32_t node = nodes_s[m16_row(lane, r)];
-            if (node != 0xFFFFFFFFu) a.KVout[(size_t)node * a.ld_kv + col] = acc[t][r];
-          }
-        }
+      for (int t = 0; t < 2; ++t) {
+        const float* const Bt[1] = {wkv(wave + NW * t)};
+        mfma_lean<1>(Ha, 2u, c_de, Bt, acc[t], lane);
+        out6[t] = value6(acc[t]);
+      }
+      for (uint32_t nt = wave + 2 * NW; nt < ntkv; nt += NW) {
+        const float* const Bt[1] = {wkv(nt)};
+        AccS<1> ac;
+        mfma_lean<1>(Ha, 0u, c_de, Bt, ac, lane);
+        store6(nt, value6(ac));
       }
     }
-    if (end_barrier) __syncthreads();
+    if constexpr (!QCACHE) request12();                       // the next tile's
+    if (wave < ntd) store5(wave, out5);
+    if (kv) {
+      store6(wave, out6[0]);
+      store6(wave + NW, out6[1]);
+    }
+    if (QCACHE && rows_in_lds) __syncthreads();
   };
   for (uint32_t round = 0;; ++round) {
     const uint32_t tile = tile_of(round);
     if (tile >= ntiles) break;                                // wave-uniform; only in a workgroup's last round
     // (set by the staging of a tile ago; uniform)
     if constexpr (QCACHE) {
-      if (__builtin_amdgcn_readfirstlane((int)p_clean) != 0) { work_tile(std::true_type{}, tile, round); continue; }
+      if (ROOTS || p_clean != 0u) { work_tile(std::true_type{}, tile, round); continue; }
     }
-    work_tile(std::false_type{}, tile, round);
+    if constexpr (!(QCACHE && ROOTS)) work_tile(std::false_type{}, tile, round);
   }
   if constexpr (DELTA) {
     if (lane == 0 && a.is_final) {
@@ -1127,10 +1330,10 @@ void go_k(LaunchArgs& a) {
 template <int KS, int NT, int H, int JC, int WGS, bool ROOTS>
 void go_exact(LaunchArgs& a) {
   if (a.es) {
-    if (a.k.QC) go_k<KS, NT, 1, H, JC, WGS, false, true, ROOTS>(a); else go_k<KS, NT, 1, H, JC, WGS, false, false, ROOTS>(a);
+    if (a.k.tile_clean) go_k<KS, NT, 1, H, JC, WGS, false, true, ROOTS>(a); else go_k<KS, NT, 1, H, JC, WGS, false, false, ROOTS>(a);
     return;
   }
-  if (a.k.QC) { go_k<KS, NT, 0, H, JC, WGS, false, true, ROOTS>(a); return; }
+  if (a.k.tile_clean) { go_k<KS, NT, 0, H, JC, WGS, false, true, ROOTS>(a); return; }
   go_k<KS, NT, 0, H, JC, WGS, false, false, ROOTS>(a);
 }
 

@@ -38,7 +38,6 @@ __device__ inline uint32_t m16_row(uint32_t lane, uint32_t r) { return 4u * (lan
 __device__ inline uint32_t m16_col(uint32_t lane) { return lane & 15u; }
 
 // per-lane element offset into an A tile in LDS with stride lda
-__device__ inline uint32_t a16_off(uint32_t lane, uint32_t lda) { return (lane & 15u) * lda + 4u * (lane >> 4); }
 __device__ inline uint32_t a16_lane_off(uint32_t lda) {
   const uint32_t lane = threadIdx.x & 63u;
   return (lane & 15u) * lda + 4u * (lane >> 4);
@@ -59,18 +58,11 @@ __device__ inline void load_a16(const float* Ap, uint32_t g0, float4 (&a)[kCG]) 
   for (int c = 0; c < kCG; ++c) a[c] = *reinterpret_cast<const float4*>(Ap + kGrpK * (g0 + c));
 }
 
-// B operands of groups [g0, g0 + kCG) of the column tile whose group 0 is Bt (wave-uniform).  The lane is an argument so
-// that a caller with a long loop can pass an opaque copy of it: from threadIdx.x alone the compiler computes one 64-bit
-// address per lane and matrix ahead of the loop and keeps (or spills) them all; with it a load takes its matrix's address
-// from scalar registers and 16 lane as the offset.
-__device__ inline void load_b16(const float* __restrict__ Bt, uint32_t g0, float4 (&b)[kCG], uint32_t lane) {
-  const char* p = reinterpret_cast<const char*>(Bt) + (size_t)g0 * 1024u;
-  const uint32_t off = lane * 16u;
-#pragma unroll
-  for (int c = 0; c < kCG; ++c) b[c] = *reinterpret_cast<const float4*>(p + c * 1024 + off);
-}
+// B operands of groups [g0, g0 + kCG) of the column tile whose group 0 is Bt (wave-uniform).
 __device__ inline void load_b16(const float* __restrict__ Bt, uint32_t g0, float4 (&b)[kCG]) {
-  load_b16(Bt, g0, b, threadIdx.x & 63u);
+  const float4* p = reinterpret_cast<const float4*>(Bt) + (size_t)g0 * 64u + (threadIdx.x & 63u);
+#pragma unroll
+  for (int c = 0; c < kCG; ++c) b[c] = p[c * 64];
 }
 
 template <int U, int NTL>
@@ -160,22 +152,16 @@ __device__ __forceinline__ void pingpong_clamped(uint32_t n, Buf& P, LoadF load,
 // already in P.b -- callers request them ahead of the barrier that makes A valid.
 template <int NTL>
 __device__ __forceinline__ void mfma16_gemm_pre(const float* Ap, uint32_t nchunks, const float* const (&Bt)[NTL],
-                                                floatx4 (&acc)[NTL], Ops16<NTL>& P, uint32_t lane) {
+                                                floatx4 (&acc)[NTL], Ops16<NTL>& P) {
   load_a16(Ap, 0, P.a);
   pingpong_peeled<Ops16<NTL>>(
       nchunks, P,
       [&](uint32_t ch, Ops16<NTL>& o) {
         load_a16(Ap, ch * kCG, o.a);
 #pragma unroll
-        for (int t = 0; t < NTL; ++t) load_b16(Bt[t], ch * kCG, o.b[t], lane);
+        for (int t = 0; t < NTL; ++t) load_b16(Bt[t], ch * kCG, o.b[t]);
       },
       [&](uint32_t, const Ops16<NTL>& o) { mfma16_chunk<NTL>(o, acc); });
-}
-
-template <int NTL>
-__device__ __forceinline__ void mfma16_gemm_pre(const float* Ap, uint32_t nchunks, const float* const (&Bt)[NTL],
-                                                floatx4 (&acc)[NTL], Ops16<NTL>& P) {
-  mfma16_gemm_pre<NTL>(Ap, nchunks, Bt, acc, P, threadIdx.x & 63u);
 }
 
 template <int NTL>
@@ -195,13 +181,12 @@ template <int NTL, int MAXC>
 struct Upfront16 {
   float4 b[MAXC][NTL][kCG];
   // requests are unconditional: chunks past the end repeat the last one and are never multiplied
-  __device__ __forceinline__ void request(const float* const (&Bt)[NTL], uint32_t nchunks) { request(Bt, nchunks, threadIdx.x & 63u); }
-  __device__ __forceinline__ void request(const float* const (&Bt)[NTL], uint32_t nchunks, uint32_t lane) {
+  __device__ __forceinline__ void request(const float* const (&Bt)[NTL], uint32_t nchunks) {
 #pragma unroll
     for (int ch = 0; ch < MAXC; ++ch) {
       const uint32_t c = (uint32_t)ch < nchunks ? (uint32_t)ch : nchunks - 1u;
 #pragma unroll
-      for (int t = 0; t < NTL; ++t) load_b16(Bt[t], c * kCG, b[ch][t], lane);
+      for (int t = 0; t < NTL; ++t) load_b16(Bt[t], c * kCG, b[ch][t]);
     }
   }
   __device__ __forceinline__ void multiply(const float* Ap, uint32_t nchunks, floatx4 (&acc)[NTL]) {
