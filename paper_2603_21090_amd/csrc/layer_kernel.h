@@ -58,6 +58,27 @@ __device__ inline float row16_sum(float x) {
   return x;
 }
 
+// largest of each 16-lane row's magnitudes (every lane of a row receives it): as integers, whose order is theirs, with
+// no quieting of NaNs between the steps (a NaN comes out as the largest)
+template <int CTRL>
+__device__ inline uint32_t dpp_max(uint32_t x) {
+  return max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, false));
+}
+__device__ inline float row16_max(float m) {
+  uint32_t x = __builtin_bit_cast(uint32_t, m);
+  x = dpp_max<0xB1>(x); x = dpp_max<0x4E>(x); x = dpp_max<0x141>(x); x = dpp_max<0x140>(x);
+  return __builtin_bit_cast(float, x);
+}
+__device__ inline float bits_max(float a, float b) {
+  return __builtin_bit_cast(float, max(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b)));
+}
+
+// 1 / x to about half a unit in the last place, 0 for 0 (x >= 0)
+__device__ inline float reciprocal(float x) {
+  const float r = __builtin_amdgcn_rcpf(x);
+  return x > 0.0f ? fmaf(fmaf(-x, r, 1.0f), r, r) : 0.0f;
+}
+
 // cos(2 pi frac(x)) with the argument reduced in fp64: timestamps reach 1e7 and beyond
 __device__ inline float cos_rev(double x) {
   const double f = __builtin_amdgcn_fract(x);
@@ -229,7 +250,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   float* Xs = lds;                            // input rows (phases 0-1), later the output rows (phases 5-6) ...
   float* Qs = lds + ll.off_q;                 // q (phases 1-3), then head outputs (phases 3-5) ... or the other way round
   float* Zs = lds + ll.off_z;                 // qt (phases 2-3), then pb (phases 3-4)
-  RingEntry* Rs = reinterpret_cast<RingEntry*>(lds + ll.off_r);   // [row][j], j = 0 the most recent entry
+  RingEntry* Rs = reinterpret_cast<RingEntry*>(__builtin_assume_aligned(lds + ll.off_r, 16));   // [row][j], j = 0 the most recent entry
   using ZBuf = GatherBuf<JC, ES>;
 
   // time-encoding parameters (omega, phase in revolutions) live in LDS, zero past d_time
@@ -372,8 +393,8 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   // the end of the last chunk are written (zero past d_in): what else lies there need not be a number.
   const uint32_t qpz = min(16u * c_in, (ll.ldx - 4u) >> 2);
   auto row_max = [&](float m) {                               // over the lanes that stage a row (LS = 16 or 32)
-    m = fmaxf(m, dpp_mov<0xB1>(m)); m = fmaxf(m, dpp_mov<0x4E>(m)); m = fmaxf(m, dpp_mov<0x141>(m)); m = fmaxf(m, dpp_mov<0x140>(m));
-    if constexpr (LS == 32u) { const Two w = both_of_pair(m); m = fmaxf(w.lo, w.hi); }
+    m = row16_max(m);
+    if constexpr (LS == 32u) { const Two w = both_of_pair(m); m = bits_max(w.lo, w.hi); }
     return m;
   };
   auto max4 = [](const float4& v) { return fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))); };
@@ -441,8 +462,14 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   // its G tiles, and a workgroup's position inside the round moves from round to round.  The row list may
   // be regrouped by entry count in windows of 256 tiles (long rows first), so a fixed position would hand
   // the same workgroups every long tile.
-  const uint32_t G = gridDim.x;
-  auto tile_of = [&](uint32_t i) { return i * G + (blockIdx.x + 37u * i) % G; };
+  const uint32_t G = gridDim.x, step37 = 37u % G;
+  uint32_t tile_base = 0, tile_pos = blockIdx.x, next_tile = blockIdx.x;
+  auto advance = [&]() {                                      // next_tile: this workgroup's tile of the next round
+    tile_base += G;
+    tile_pos += step37;
+    if (tile_pos >= G) tile_pos -= G;
+    next_tile = tile_base + tile_pos;
+  };
 
   // ---- phase 3's rows: pass p works on rows p RPP .. p RPP + RPP - 1 of the wave's, GPR groups of 16 lanes each,
   // group g on key slot g.  With one pass a lane's row is the one it staged, else the pass has one row.
@@ -470,7 +497,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
 #pragma unroll
     for (int jc = 0; jc < JC; ++jc) {
       const uint32_t j = c * JC + jc;
-      const RingEntry e = rrow[j < k ? j : k - 1u];
+      const RingEntry e = rrow[JC == 1 || j < k ? j : k - 1u];   // (a chunk of one never runs past the longest row's entries, but for a wave without any: the record of place 0)
       const float* nrow = a.KVn + (size_t)e.nbr * (2u * kSlot * KS) + kSlot * g + 4u * sub;
       zb.nk[jc] = *reinterpret_cast<const float4*>(nrow);
       zb.nv[jc] = *reinterpret_cast<const float4*>(nrow + kSlot * KS);
@@ -562,12 +589,12 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     }
     if constexpr (clean) {
       if constexpr (PASSES == 2) request_back(std::integral_constant<int, 1>{});
-      stage_a(tile_of(round + 1u));                          // row ids of this workgroup's next tile
+      stage_a(next_tile);                          // row ids of this workgroup's next tile
     } else {
     // ================================================================ phase 1: q = x W_Q + c_Q
     if constexpr (QCACHE) describe2();                        // (one register less through the other tiles)
     if constexpr (QCACHE) request12();                        // (otherwise requested ahead of the previous tile's stores)
-    stage_a(tile_of(round + 1u));
+    stage_a(next_tile);
     if (!kRowsInZ && rows_in_lds && round) {                  // (the previous tile had its output rows where the input rows go)
       __syncthreads();
       commit_x(false);
@@ -648,12 +675,13 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     // The time encodings are not masked per entry: a column past d_time has omega = phase = 0 and comes out as
     // cos(0) = 1.  In the scores it meets an exact zero of qt and in phase 4 one of pb: both are cleared there once
     // per row.
-    auto clear_past_d_time = [&](float4& o, int t) {
-      const uint32_t c0 = (uint32_t)t * kSlot + 4u * sub;
-      o.x = c0 < a.d_time ? o.x : 0.0f;
-      o.y = c0 + 1u < a.d_time ? o.y : 0.0f;
-      o.z = c0 + 2u < a.d_time ? o.z : 0.0f;
-      o.w = c0 + 3u < a.d_time ? o.w : 0.0f;
+    // (the last time slot's alone: d_time > 64 (NT - 1))
+    auto clear_past_d_time = [&](float4& o, uint32_t t) {
+      const uint32_t c0 = (NT - 1) * kSlot + 4u * sub, end = t == NT - 1 ? a.d_time : 0xFFFFFFFFu;
+      o.x = c0 < end ? o.x : 0.0f;
+      o.y = c0 + 1u < end ? o.y : 0.0f;
+      o.z = c0 + 2u < end ? o.z : 0.0f;
+      o.w = c0 + 3u < end ? o.w : 0.0f;
     };
     if constexpr (!DELTA) {
       if constexpr (!clean) {
@@ -668,17 +696,13 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
           for (int i = 0; i < NZL; ++i) {
             const uint32_t t = SH == 1 ? (uint32_t)i : sg + SH * i, at = head * Ztp + (t < NZ ? t : 0u) * kSlot;
             qt[p][i] = *reinterpret_cast<const float4*>(Zs + local * ll.ldz + at + 4u * sub);
-            if (t < NT) clear_past_d_time(qt[p][i], t);
+            if (SH > 1 || i == NT - 1) clear_past_d_time(qt[p][i], t);
             if (keep && t < NZ) *reinterpret_cast<float4*>(qrow + kSlot * KS + at) = qt[p][i];
           }
         });
       }
     }
     // ================================================================ phase 3: gather + attention
-    auto group_max = [&](float m) {                           // over a 16-lane group
-      m = fmaxf(m, dpp_mov<0xB1>(m)); m = fmaxf(m, dpp_mov<0x4E>(m)); m = fmaxf(m, dpp_mov<0x141>(m));
-      return fmaxf(m, dpp_mov<0x140>(m));
-    };
     // scales of the head outputs and of the output rows, from bounds: the largest cached-value part plus what pb can add
     auto output_scales = [&](uint32_t local, float m_o, float m_z, bool writer) {
       const ArgBlock ab = args();
@@ -724,13 +748,12 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
       for (int s = 0; s < KS; ++s) qk[s] = split_load4(Qs + local * ll.ldq, s * kSlot + 4u * sub, inv_pow2(s_sq[local]));
       float* zq = Zs + local * ll.ldz + 4u * sub;
 #pragma unroll
-      for (int h = 0; h < H; ++h)
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          float4 o = *reinterpret_cast<float4*>(zq + h * Ztp + t * kSlot);
-          clear_past_d_time(o, t);
-          *reinterpret_cast<float4*>(zq + h * Ztp + t * kSlot) = o;
-        }
+      for (int h = 0; h < H; ++h) {
+        float4* o = reinterpret_cast<float4*>(zq + h * Ztp + (NT - 1) * kSlot);
+        float4 v = *o;
+        clear_past_d_time(v, NT - 1);
+        *o = v;
+      }
       uint32_t nch = 0, nvalid = 0;
       const bool any_delta = __any(!ex);                      // (exact rows take every entry: no flags needed)
       struct DBuf { float4 n[2 * KS], e[2 * KS]; uint32_t j; };
@@ -868,7 +891,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
       float m_o = 0.0f, m_z = 0.0f;                           // largest head output of the row (cached part), largest pb of any head
 #pragma unroll
       for (int h = 0; h < H; ++h) {
-        const float inv = ex ? (lrun[h] > 0.0f ? 1.0f / lrun[h] : 0.0f) : 1.0f;
+        const float inv = ex ? reciprocal(lrun[h]) : 1.0f;
 #pragma unroll
         for (int s = h * SH; s < (h + 1) * SH; ++s) {
           float4 o = accv[s];
@@ -882,7 +905,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
         for (int t = 0; t < NT; ++t) {
           float4& o = accp[h][t];
           o.x *= inv; o.y *= inv; o.z *= inv; o.w *= inv;
-          clear_past_d_time(o, t);
+          if (t == NT - 1) clear_past_d_time(o, t);
           mz = fmaxf(mz, max4(o));
           if (live) *reinterpret_cast<float4*>(acP + (h * NT + t) * kSlot) = o;
         }
@@ -1032,21 +1055,21 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
       // the cached-value part of the head outputs goes into Xs (padded-head layout; the padding lanes hold exact
       // zeros), pb, split, where qt is (each lane owns its columns)
       wave_lds_fence();                                       // (a lane's split columns share their bytes with its neighbour's qt)
-      const float inv = lrun > 0.0f ? 1.0f / lrun : 0.0f;     // no entry, or none inside the window: b_O alone
+      const float inv = reciprocal(lrun);                     // no entry, or none inside the window: b_O alone
       accv.x *= inv; accv.y *= inv; accv.z *= inv; accv.w *= inv;
       *reinterpret_cast<float4*>(Xs + local * ll.ldx + kSlot * g + 4u * sub) = accv;
-      float m_o = group_max(max4(accv)), m_z = 0.0f;
+      float m_o = row16_max(max4(accv)), m_z = 0.0f;
 #pragma unroll
       for (int i = 0; i < NZL; ++i) {
         const uint32_t t = SH == 1 ? (uint32_t)i : sg + SH * i;
         float4& o = accp[i];
         o.x *= inv; o.y *= inv; o.z *= inv; o.w *= inv;
-        if (t < NT) clear_past_d_time(o, t);                   // (a raw edge row's padding is zero, and so are its sums)
+        if (SH > 1 || i == NT - 1) clear_past_d_time(o, t);    // (a raw edge row's padding is zero, and so are its sums)
         m_z = fmaxf(m_z, max4(o));
       }
-      m_z = group_max(m_z);
-      if constexpr (SH >= 2) { const Two w = both_of_pair(m_z); m_z = fmaxf(w.lo, w.hi); }
-      if constexpr (SH == 4) { const Two w = both_halves(m_z); m_z = fmaxf(w.lo, w.hi); }
+      m_z = row16_max(m_z);
+      if constexpr (SH >= 2) { const Two w = both_of_pair(m_z); m_z = bits_max(w.lo, w.hi); }
+      if constexpr (SH == 4) { const Two w = both_halves(m_z); m_z = bits_max(w.lo, w.hi); }
       const float sz = pow2_scale(m_z);                       // of the head's pb
       if (sub == 0u && sg == 0u) s_sz[head][local] = sz;
 #pragma unroll
@@ -1054,8 +1077,8 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
         const uint32_t t = SH == 1 ? (uint32_t)i : sg + SH * i;
         if (t < NZ) split_store4(Zs + local * ll.ldz, head * Ztp + t * kSlot + 4u * sub, accp[i], sz);
       }
-      if constexpr (KS >= 2) { const Two w = both_of_pair(m_o), v = both_of_pair(m_z); m_o = fmaxf(w.lo, w.hi); m_z = fmaxf(v.lo, v.hi); }
-      if constexpr (KS == 4) { const Two w = both_halves(m_o), v = both_halves(m_z); m_o = fmaxf(w.lo, w.hi); m_z = fmaxf(v.lo, v.hi); }
+      if constexpr (KS >= 2) { const Two w = both_of_pair(m_o), v = both_of_pair(m_z); m_o = bits_max(w.lo, w.hi); m_z = bits_max(v.lo, v.hi); }
+      if constexpr (KS == 4) { const Two w = both_halves(m_o), v = both_halves(m_z); m_o = bits_max(w.lo, w.hi); m_z = bits_max(v.lo, v.hi); }
       output_scales(local, m_o, m_z, sub == 0u && g == 0u);
       });
     }
@@ -1067,8 +1090,9 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     uint32_t x4 = wave < nunits4 ? wave : nunits4 - 1u;
     Upfront<N4, NZ> u4;
     const float* B4[N4];
+    auto head4 = [&]() { return H == 1 ? 0u : H == 2 ? (x4 >= np4 ? 1u : 0u) : (x4 >= np4 ? 1u : 0u) + (x4 >= 2u * np4 ? 1u : 0u) + (x4 >= 3u * np4 ? 1u : 0u); };
     auto request4 = [&]() {
-      const uint32_t h4 = x4 / np4, n0 = N4 * (x4 - h4 * np4);
+      const uint32_t h4 = head4(), n0 = N4 * (x4 - h4 * np4);
 #pragma unroll
       for (int t = 0; t < N4; ++t) B4[t] = wv(h4, n0 + t < ntk ? n0 + t : n0);
       u4.request(B4, NZ, lane);
@@ -1085,14 +1109,14 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
       for (int t = 0; t < NTL; ++t) { const uint32_t col = (w1 + NW * t) * 16 + s16_col(lane); b5v[t] = a.bO[col < a.d_emb ? col : 0u]; }
     };
     request4();
-    stage_b(tile_of(round + 1u));
+    stage_b(next_tile);
     __syncthreads();
     const float iV = args()->sp.iV;
     if (wave < nunits4) {
       const float4 so = *reinterpret_cast<const float4*>(s_so[par] + s16_row(lane, 0));
       const float sov[4] = {so.x, so.y, so.z, so.w};
       for (;;) {
-        const uint32_t h4 = x4 / np4, n0 = N4 * (x4 - h4 * np4);
+        const uint32_t h4 = head4(), n0 = N4 * (x4 - h4 * np4);
         AccS<N4> acc;
         u4.multiply(Zs + h4 * Ztp + s16_off(lane, ll.ldz), NZ, B4, acc, lane);
         float f[4];
@@ -1260,8 +1284,9 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     if (QCACHE && rows_in_lds) __syncthreads();
   };
   for (uint32_t round = 0;; ++round) {
-    const uint32_t tile = tile_of(round);
+    const uint32_t tile = next_tile;
     if (tile >= ntiles) break;                                // wave-uniform; only in a workgroup's last round
+    advance();
     // (set by the staging of a tile ago; uniform)
     if constexpr (QCACHE) {
       if (ROOTS || p_clean != 0u) { work_tile(std::true_type{}, tile, round); continue; }

@@ -44,24 +44,29 @@ __device__ inline float pow2_scale(float bound) {
 }
 __device__ inline float inv_pow2(float s) { return __builtin_bit_cast(float, 0x7F000000u - __builtin_bit_cast(uint32_t, s)); }
 
-__device__ inline void split1(float a, float s, _Float16& h, _Float16& l) {
-  const float x = a * s;
-  h = (_Float16)x;
-  l = (_Float16)((x - (float)h) * kLoScale);
+// Pairs of elements through the mixed-precision multiply-add: h = f16(a s), r = a s - h (exact), l = f16(2048 r), three
+// instructions an element with the packing done by them (conversions, a subtraction and a multiplication each took six
+// and a pack).  In the halves of `hi` and `lo`: element 0 low, element 1 high.
+__device__ inline void split2(float a0, float a1, float s, uint32_t& hi, uint32_t& lo) {
+  float r0, r1;
+  const float k = kLoScale;
+  asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(hi) : "v"(a0), "v"(s));
+  asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(hi) : "v"(a1), "v"(s));
+  asm("v_fma_mix_f32 %0, %1, %2, -%3 op_sel_hi:[0,0,1]" : "=v"(r0) : "v"(a0), "v"(s), "v"(hi));
+  asm("v_fma_mix_f32 %0, %1, %2, -%3 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "=v"(r1) : "v"(a1), "v"(s), "v"(hi));
+  asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(lo) : "v"(r0), "s"(k));
+  asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(lo) : "v"(r1), "s"(k));
 }
 
 // four consecutive columns (the first a multiple of four) of a row in LDS that starts at `row`
 __device__ inline float* split_at(float* row, uint32_t col) { return row + (col & ~7u) + ((col & 4u) >> 1); }
 __device__ inline void split_store4(float* row, uint32_t col, const float4& v, float s) {
-  halfx4 h, l;
-  _Float16 x, y;
-  split1(v.x, s, x, y); h[0] = x; l[0] = y;
-  split1(v.y, s, x, y); h[1] = x; l[1] = y;
-  split1(v.z, s, x, y); h[2] = x; l[2] = y;
-  split1(v.w, s, x, y); h[3] = x; l[3] = y;
+  uint2 h, l;
+  split2(v.x, v.y, s, h.x, l.x);
+  split2(v.z, v.w, s, h.y, l.y);
   float* p = split_at(row, col);
-  *reinterpret_cast<halfx4*>(p) = h;
-  *reinterpret_cast<halfx4*>(p + 4) = l;
+  *reinterpret_cast<uint2*>(p) = h;
+  *reinterpret_cast<uint2*>(p + 4) = l;
 }
 __device__ inline float4 split_load4(const float* row, uint32_t col, float inv) {
   const float* p = split_at(const_cast<float*>(row), col);
@@ -72,11 +77,15 @@ __device__ inline float4 split_load4(const float* row, uint32_t col, float inv) 
 }
 // one element
 __device__ inline void split_store1(float* row, uint32_t col, float v, float s) {
-  _Float16 h, l;
-  split1(v, s, h, l);
-  _Float16* p = reinterpret_cast<_Float16*>(row + (col & ~7u)) + (col & 7u);
-  p[0] = h;
-  p[8] = l;
+  uint32_t h, l;
+  float r;
+  const float k = kLoScale;
+  asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(h) : "v"(v), "v"(s));
+  asm("v_fma_mix_f32 %0, %1, %2, -%3 op_sel_hi:[0,0,1]" : "=v"(r) : "v"(v), "v"(s), "v"(h));
+  asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(l) : "v"(r), "s"(k));
+  uint16_t* p = reinterpret_cast<uint16_t*>(row + (col & ~7u)) + (col & 7u);
+  p[0] = (uint16_t)h;
+  p[8] = (uint16_t)l;
 }
 
 // per-lane offset (floats) into an A tile in LDS with rows of lda floats
