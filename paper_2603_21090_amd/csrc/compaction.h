@@ -34,23 +34,25 @@ __device__ inline uint32_t block_scan_256(uint32_t v, uint32_t* s, uint32_t* exc
 constexpr uint32_t kFlagsPerThread = 16;
 constexpr uint32_t kFlagsPerBlock = 256 * kFlagsPerThread;
 
+// Four flags at once: a flag is at most STGN_MAX_LAYERS + 1, so adding 127 - v to a byte carries into its top bit, and no
+// further, exactly when the byte exceeds v.  (A byte at a time, a workgroup that counts a hundred thousand flags spent
+// 27 us on it, the whole of the apply launch it rides in.)
+constexpr uint32_t kTopBits = 0x80808080u;
+static_assert(STGN_MAX_LAYERS + 1 < 127, "flags leave the top bit of their byte free");
+__device__ inline uint32_t over(uint32_t w, uint32_t v) { return (w + (127u - v) * 0x01010101u) & kTopBits; }   // bytes > v (v <= 127)
+// bytes of w in [1, thr], one top bit each (thr of 127 and above: no upper limit)
+__device__ inline uint32_t word_upto(uint32_t w, uint32_t thr) { return over(w, 0u) & ~(thr < 127u ? over(w, thr) : 0u); }
+__device__ inline uint32_t count_upto(const uint4 m, uint32_t thr) {
+  return (uint32_t)(__popc(word_upto(m.x, thr)) + __popc(word_upto(m.y, thr)) + __popc(word_upto(m.z, thr)) + __popc(word_upto(m.w, thr)));
+}
 // bit j set iff byte j of the 16 flags lies in [1, thr]
 __device__ inline uint32_t bytes_upto(const uint4 m, uint32_t thr) {
-  uint32_t bits = 0;
-  const uint32_t w[4] = {m.x, m.y, m.z, m.w};
-  for (int q = 0; q < 4; ++q)
-    for (int j = 0; j < 4; ++j) {
-      const uint32_t f = (w[q] >> (8 * j)) & 0xFFu;
-      if (f != 0u && f <= thr) bits |= 1u << (4 * q + j);
-    }
-  return bits;
+  auto nibble = [](uint32_t top) { return ((top >> 7) * 0x01020408u) >> 24 & 0xFu; };   // top bits of the four bytes, side by side
+  return nibble(word_upto(m.x, thr)) | nibble(word_upto(m.y, thr)) << 4 | nibble(word_upto(m.z, thr)) << 8 | nibble(word_upto(m.w, thr)) << 12;
 }
 __device__ inline uint32_t bytes_equal(const uint4 m, uint32_t value) {
-  uint32_t n = 0;
-  const uint32_t w[4] = {m.x, m.y, m.z, m.w};
-  for (int q = 0; q < 4; ++q)
-    for (int j = 0; j < 4; ++j) n += ((w[q] >> (8 * j)) & 0xFFu) == value ? 1u : 0u;
-  return n;
+  const uint32_t v = value * 0x01010101u;
+  return 16u - (uint32_t)(__popc(over(m.x ^ v, 0u)) + __popc(over(m.y ^ v, 0u)) + __popc(over(m.z ^ v, 0u)) + __popc(over(m.w ^ v, 0u)));
 }
 
 // list 0 is A (every non-zero flag); list 1 + l is R[l] for the layers that need their own list.
@@ -107,15 +109,25 @@ __device__ inline void compact_small_block(const Dev& d, uint32_t last_value, ui
 #pragma unroll
   for (uint32_t i = 0; i <= STGN_MAX_LAYERS; ++i) eq[i] = 0u;
   const bool last_block = bid == nblk - 1;
-  for (uint32_t b = 0; b < bid; ++b) {
-    const uint4 pm = *reinterpret_cast<const uint4*>(d.mark + b * kFlagsPerBlock + t * kFlagsPerThread);
+  // (eight blocks' flags are requested together: the last workgroups of a large array would wait for each)
+  for (uint32_t b0 = 0; b0 < bid; b0 += 8u) {
+    uint4 pm[8];
 #pragma unroll
-    for (uint32_t list = 0; list <= STGN_MAX_LAYERS; ++list)
-      if (list < nl) part[list] += (uint32_t)__popc(bytes_upto(pm, thr[list]));
-    if (last_block) {
+    for (uint32_t i = 0; i < 8u; ++i) {
+      const uint32_t b = b0 + i < bid ? b0 + i : bid - 1u;
+      pm[i] = *reinterpret_cast<const uint4*>(d.mark + b * kFlagsPerBlock + t * kFlagsPerThread);
+    }
 #pragma unroll
-      for (uint32_t i = 0; i <= STGN_MAX_LAYERS; ++i)
-        if (i + 2u <= last_value) eq[i] += bytes_equal(pm, i + 2u);
+    for (uint32_t i = 0; i < 8u; ++i) {
+      if (b0 + i >= bid) break;                                          // uniform
+#pragma unroll
+      for (uint32_t list = 0; list <= STGN_MAX_LAYERS; ++list)
+        if (list < nl) part[list] += count_upto(pm[i], thr[list]);
+      if (last_block) {
+#pragma unroll
+        for (uint32_t h = 0; h <= STGN_MAX_LAYERS; ++h)
+          if (h + 2u <= last_value) eq[h] += bytes_equal(pm[i], h + 2u);
+      }
     }
   }
   uint4 m = make_uint4(0u, 0u, 0u, 0u);
