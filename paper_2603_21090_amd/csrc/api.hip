@@ -380,8 +380,7 @@ int pack_parameters(stgn_ctx* ctx, const stgn_weights* w) {
         (rc = upload(ctx, d.br, vec(w->b_r, c.d_mem))) || (rc = upload(ctx, d.bh, vec(w->b_h, c.d_mem))))
       return rc;
   }
-  // attention weights feed the layer kernel's split products (split16.h), but for what projects the cached rows outside
-  // it: the first layer's node rows and the edge rows, which are group-major (see tiled_size).
+  // attention weights feed split products (split16.h).
   // Row z of W_K / W_V belongs to the node block (z < d_in), the edge block or the time block of the
   // attention input; column h dk + cc to head h.  In a cached row and in the head-output tile head h
   // starts at float 64 sh h (padded-head layout).
@@ -425,27 +424,24 @@ int pack_parameters(stgn_ctx* ctx, const stgn_weights* w) {
         for (uint32_t col = 0; col < c.d_emb; ++col)
           mO.put(h * hp + cc, col, WOs[(size_t)(h * dk + cc) * c.d_emb + col]);
     // node and edge rows of [W_K | W_V] in the cached-row layout: keys in floats [0, 64 ks), values behind
-    std::vector<float> WKVn(tiled_size(L.d_in, d.ld_kv), 0.0f);
-    SplitMatrix mKV(L.d_in, d.ld_kv);
-    std::vector<float> WKVe(c.d_edge && !d.es ? tiled_size(c.d_edge, d.ld_kv) : 0, 0.0f);
+    SplitMatrix mKV(L.d_in, d.ld_kv), mKVe(d.es ? 0u : c.d_edge, d.ld_kv);
     for (uint32_t h = 0; h < c.heads; ++h)
       for (uint32_t cc = 0; cc < dk; ++cc) {
         const uint32_t kc = h * hp + cc, vc = kSlot * d.ks + h * hp + cc;
         const size_t wc = (size_t)h * dk + cc;
         for (uint32_t i = 0; i < L.d_in; ++i) {
-          put_tiled(WKVn, L.d_in, i, kc, WK[(size_t)i * c.d_emb + wc]);
-          put_tiled(WKVn, L.d_in, i, vc, WV[(size_t)i * c.d_emb + wc]);
           mKV.put(i, kc, WK[(size_t)i * c.d_emb + wc]);
           mKV.put(i, vc, WV[(size_t)i * c.d_emb + wc]);
         }
         for (uint32_t i = 0; i < (d.es ? 0u : c.d_edge); ++i) {
-          put_tiled(WKVe, c.d_edge, i, kc, WK[(size_t)(e0 + i) * c.d_emb + wc]);
-          put_tiled(WKVe, c.d_edge, i, vc, WV[(size_t)(e0 + i) * c.d_emb + wc]);
+          mKVe.put(i, kc, WK[(size_t)(e0 + i) * c.d_emb + wc]);
+          mKVe.put(i, vc, WV[(size_t)(e0 + i) * c.d_emb + wc]);
         }
       }
-    std::vector<float> WQn, WKT, WVp, WO;
+    std::vector<float> WQn, WKT, WVp, WO, WKVn, WKVe;
     L.sp.iQ = mQ.pack(WQn); L.sp.iKT = mKT.pack(WKT); L.sp.iV = mV.pack(WVp); L.sp.iO = mO.pack(WO);
-    if (l) L.iKVn = mKV.pack(WKVn);
+    L.iKVn = mKV.pack(WKVn);
+    if (mKVe.K) L.iKVe = mKVe.pack(WKVe);
     auto largest = [](const float* p, uint32_t n) { float m = 0.0f; for (uint32_t i = 0; i < n; ++i) m = std::max(m, std::fabs(p[i])); return m; };
     L.sp.bQ = (float)mQ.column_sum(); L.sp.bcQ = largest(cQ.data(), c.d_emb);
     L.sp.bV = (float)mV.column_sum();

@@ -5,6 +5,7 @@
 // (adjacency append, in-place memory write-back).
 #include "stgn_internal.h"
 #include "mfma16.h"
+#include "split16.h"
 #include "compaction.h"
 #include "placement.h"
 
@@ -161,83 +162,122 @@ __device__ inline uint64_t log_addr(const Dev& d, uint32_t node, uint32_t pos) {
 //       KVE[l][e] = feat_e [W_K | W_V](edge rows of layer l) for the batch's edges e (not with raw edge rows:
 //       those are copied by the appending workgroups of the launch);
 //   all_nodes (initial state, full rebuild):  KV[0][v] for every node.
-// One workgroup (four waves) per 16 rows and 128 of the 128 ks output columns: the rows go through
-// LDS as the A operand, wave w computes the column tiles w and w + 4 of the workgroup's column group
-// (these launches are small and latency-bound: more, shorter workgroups finish sooner).  `bid` / `nblk`
-// are the workgroup's index and count among the workgroups that project.
+// One workgroup (four waves) per 16 rows and 128 of the 128 ks output columns: the rows go through LDS as the A operand of
+// split products (split16.h), wave w computes the column tiles w and w + 4 of the workgroup's column group (these
+// launches are small and latency-bound: more, shorter workgroups finish sooner).  For all nodes an item is RT tiles of
+// rows and takes every column group in turn: a tile streams 64 KB of weights a group from L2, which is what
+// bounds one tile at a time (200,000 nodes, d 100, two groups: 206 us with fp32 products and one tile, 123 with four).
+// `bid` / `nblk` are the workgroup's index and count among the workgroups that project.
 constexpr uint32_t kProjRows = 16;
-__device__ void project_rows(const Dev& d, const float* __restrict__ ef, uint32_t all_nodes, uint32_t bid, uint32_t nblk,
-                             float* lds) {
+template <int RT>
+__device__ void project_rows(const Dev& d, const float* __restrict__ ef, bool all_nodes, uint32_t bid, uint32_t nblk, float* lds) {
+  __shared__ __align__(16) float s_scale[RT * kProjRows];
+  constexpr uint32_t kRows = RT * kProjRows;
+  constexpr int kHeld = RT > 1 ? 2 : 4;                       // 64-column pieces of a row held in registers between its maximum and its split
   const BatchCtl* c = d.bc;
   const uint32_t nD = all_nodes ? d.N : (d.d_mem ? c->nD : 0u);
   const uint32_t nE = (all_nodes || !d.d_edge || d.es) ? 0u : c->n_edges;
-  const uint64_t E0 = c->E_base;
-  const uint32_t tD = (nD + kProjRows - 1) / kProjRows, tE = (nE + kProjRows - 1) / kProjRows;
-  // work items: (row tile, column group); for all nodes one item per row tile, which takes every column group
-  // in turn (the rows are staged once, with 16-byte loads)
+  const uint64_t E0 = all_nodes ? 0u : c->E_base;
+  const uint32_t tD = (nD + kRows - 1) / kRows, tE = (nE + kRows - 1) / kRows;
+  // work items: (row tile, column group); for all nodes one item per row tile
   const uint32_t groups_per_item = all_nodes ? d.ks : 1u;
   const uint32_t ntiles = (tD + d.layers * tE) * (all_nodes ? 1u : d.ks);
-  const uint32_t kmax = d.d0 > d.d_edge ? d.d0 : d.d_edge;
-  const uint32_t lda = round_up(kmax, kGrpK) + 4;
-  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t kmax = all_nodes || d.d0 > d.d_edge ? d.d0 : d.d_edge;
+  const uint32_t lda = round_up(kmax, kChunkK) + 4;
+  const uint32_t lane = threadIdx.x & 63u, sub = threadIdx.x & 15u, r16 = threadIdx.x >> 4;
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const uint32_t a_off = a16_lane_off(lda);
-  // operand padding must be finite: clear the tile once (one chunk of slack behind the last row)
-  for (uint32_t x = threadIdx.x; x < kProjRows * lda + 4 * kGrpK; x += 256) lds[x] = 0.0f;
-  __syncthreads();
+  // 16-byte reads of a row's pieces, where every row starts on such a boundary
+  const bool ef_quads = d.d_edge % 4u == 0u && (reinterpret_cast<uintptr_t>(ef) & 15u) == 0u, mem_quads = d.d_mem % 4u == 0u;
+  struct Weights { float4 b[2][4]; };
   for (uint32_t item = bid; item < ntiles; item += nblk) {
     const uint32_t tile = all_nodes ? item : item / d.ks;
     uint32_t nt = all_nodes ? wave : wave + 8u * (item - tile * d.ks);
     const bool node_job = tile < tD;
     const uint32_t layer = node_job ? 0u : (tile - tD) / tE;
-    const uint32_t r0 = (node_job ? tile : (tile - tD) - layer * tE) * kProjRows;
+    const uint32_t r0 = (node_job ? tile : (tile - tD) - layer * tE) * kRows;
     const uint32_t nrows = node_job ? nD : nE;
     const uint32_t K = node_job ? d.d0 : d.d_edge;
     const float* W = node_job ? d.L[0].WKVn : d.L[layer].WKVe;
+    const float inv_w = node_job ? d.L[0].iKVn : d.L[layer].iKVe;
     float* out = node_job ? d.KV[0].base : d.KVE[layer].base;
-    const uint32_t ck = chunks_of(K), gk = kCG * ck;
-    Ops16<2> P;                                               // first weight chunk, requested ahead of the staging
-    load_b16(W + (size_t)nt * gk * kGrpFloats, 0, P.b[0]);
-    load_b16(W + (size_t)(nt + 4) * gk * kGrpFloats, 0, P.b[1]);
-    // stage the rows (columns K .. lda keep zeros or finite leftovers of a wider job: they meet zero weights).
+    const uint32_t ck = chunks64(K);
+    Weights P;                                                // first weight chunk, requested ahead of the staging
+    load_b64(W + (size_t)nt * ck * kChunkFloats, 0, P.b[0], lane);
+    load_b64(W + (size_t)(nt + 4) * ck * kChunkFloats, 0, P.b[1], lane);
+    // Sixteen lanes stage a row, lane `sub` the columns 64 i + 4 sub .. + 3, up to the end of the last chunk (zero past K).
     // A batch endpoint's new memory is read from the batch's scratch rows: the write-back into the
     // memory table runs in the same launch.
-    if (all_nodes) {
-      // whole table rows (stride and row padding are multiples of four floats; padding columns are zero)
-      const uint32_t q4 = round_up(K, 4u) >> 2;
-      for (uint32_t x = threadIdx.x; x < kProjRows * q4; x += 256) {
-        const uint32_t r = x / q4, q = x - r * q4;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      const uint32_t r = rt * kProjRows + r16, row = r0 + r;
+      const bool live = row < nrows;
+      const size_t rc = live ? row : 0u;
+      const uint32_t node = !node_job || all_nodes ? (uint32_t)rc : d.D[rc];
+      const float* table = d.H[0].base + (size_t)node * d.H[0].ld;          // (row padding is zero)
+      auto piece = [&](uint32_t i) {
+        const uint32_t col = kChunkK * i + 4u * sub;
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (r0 + r < nrows) v = *reinterpret_cast<const float4*>(d.H[0].base + (size_t)(r0 + r) * d.H[0].ld + 4u * q);
-        *reinterpret_cast<float4*>(lds + r * lda + 4u * q) = v;
-      }
-    } else
-    for (uint32_t x = threadIdx.x; x < kProjRows * K; x += 256) {
-      const uint32_t r = x / K, col = x - r * K;
-      float v = 0.0f;
-      if (r0 + r < nrows) {
-        if (!node_job) v = ef[(size_t)(r0 + r) * d.d_edge + col];
-        else if (all_nodes) v = d.H[0].base[(size_t)(r0 + r) * d.H[0].ld + col];
-        else if (col < d.d_mem) v = d.mem_new[(size_t)(r0 + r) * d.d_mem + col];
-        else v = d.H[0].base[(size_t)d.D[r0 + r] * d.H[0].ld + col];
-      }
-      lds[r * lda + col] = v;
+        if (!live || col >= K) return v;
+        const float* src;
+        bool quads;
+        if (!node_job) { src = ef + rc * d.d_edge + col; quads = ef_quads; }
+        else if (all_nodes || (mem_quads && col >= d.d_mem)) { src = table + col; quads = true; }
+        else if (col + 4u <= d.d_mem) { src = d.mem_new + rc * d.d_mem + col; quads = mem_quads; }
+        else {                                                              // memory ends inside the piece
+          float e[4];
+          for (uint32_t q = 0; q < 4u; ++q)
+            e[q] = col + q < d.d_mem ? d.mem_new[rc * d.d_mem + col + q] : col + q < K ? table[col + q] : 0.0f;
+          return make_float4(e[0], e[1], e[2], e[3]);
+        }
+        if (quads) return *reinterpret_cast<const float4*>(src);
+        v.x = src[0];
+        if (col + 1u < K) v.y = src[1];
+        if (col + 2u < K) v.z = src[2];
+        if (col + 3u < K) v.w = src[3];
+        return v;
+      };
+      float4 v[kHeld];
+      float m = 0.0f;
+#pragma unroll
+      for (int i = 0; i < kHeld; ++i) { v[i] = piece(i); m = fmaxf(m, max4(v[i])); }
+      for (uint32_t i = kHeld; i < ck; ++i) m = fmaxf(m, max4(piece(i)));
+      const float s = pow2_scale(row16_max(m));
+      if (sub == 0u) s_scale[r] = s;
+      float* lrow = lds + r * lda;
+#pragma unroll
+      for (int i = 0; i < kHeld; ++i) if ((uint32_t)i < ck) split_store4(lrow, kChunkK * i + 4u * sub, v[i], s);
+      for (uint32_t i = kHeld; i < ck; ++i) split_store4(lrow, kChunkK * i + 4u * sub, piece(i), s);
     }
     __syncthreads();
     for (uint32_t cg = 0; cg < groups_per_item; ++cg, nt += 8u) {
-      const float* const Bt[2] = {W + (size_t)nt * gk * kGrpFloats, W + (size_t)(nt + 4) * gk * kGrpFloats};
-      if (cg) { load_b16(Bt[0], 0, P.b[0]); load_b16(Bt[1], 0, P.b[1]); }
-      floatx4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-      mfma16_gemm_pre<2>(lds + a_off, ck, Bt, acc, P);
+      const float* const Bt[2] = {W + (size_t)nt * ck * kChunkFloats, W + (size_t)(nt + 4) * ck * kChunkFloats};
+      if (cg) { load_b64(Bt[0], 0, P.b[0], lane); load_b64(Bt[1], 0, P.b[1], lane); }
+      AccS<2> acc[RT];
+      pingpong_peeled<Weights>(
+          ck, P,
+          [&](uint32_t ch, Weights& o) { load_b64(Bt[0], ch, o.b[0], lane); load_b64(Bt[1], ch, o.b[1], lane); },
+          [&](uint32_t ch, const Weights& o) {
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const uint32_t col = (nt + 4 * t) * 16 + m16_col(lane);     // every column is written: padding columns get exact zeros
+            for (int rt = 0; rt < RT; ++rt) {
+              float4 a[4];
+              load_a64(lds + rt * kProjRows * lda + s16_off(lane, lda), ch, a);
+              mfma_chunk<2>(a, o.b, acc[rt]);
+            }
+          });
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const uint32_t row = r0 + m16_row(lane, r);
-          if (row < nrows) {
-            const size_t orow = node_job ? (size_t)(all_nodes ? row : d.D[row]) : (size_t)(E0 + row);
-            out[orow * d.ld_kv + col] = acc[t][r];
+      for (int rt = 0; rt < RT; ++rt) {
+        const float4 sc = *reinterpret_cast<const float4*>(s_scale + rt * kProjRows + s16_row(lane, 0));
+        const float f[4] = {inv_pow2(sc.x) * inv_w, inv_pow2(sc.y) * inv_w, inv_pow2(sc.z) * inv_w, inv_pow2(sc.w) * inv_w};
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          const uint32_t col = (nt + 4 * t) * 16 + s16_col(lane);           // every column is written: padding columns get exact zeros
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const uint32_t row = r0 + rt * kProjRows + s16_row(lane, r);
+            if (row < nrows) {
+              const size_t orow = node_job ? (size_t)(all_nodes ? row : d.D[row]) : (size_t)(E0 + row);
+              out[orow * d.ld_kv + col] = acc_value(acc[rt], t, r) * f[r];
+            }
           }
         }
       }
@@ -246,14 +286,15 @@ __device__ void project_rows(const Dev& d, const float* __restrict__ ef, uint32_
   }
 }
 
-size_t project_lds(const Dev& d) {
-  const uint32_t kmax = d.d0 > d.d_edge ? d.d0 : d.d_edge;
-  return ((size_t)kProjRows * (round_up(kmax, kGrpK) + 4) + 4 * kGrpK) * sizeof(float);
-}
+size_t project_lds(uint32_t tiles, uint32_t kmax) { return (size_t)tiles * kProjRows * (round_up(kmax, kChunkK) + 4) * sizeof(float); }
+size_t project_lds(const Dev& d) { return project_lds(1u, d.d0 > d.d_edge ? d.d0 : d.d_edge); }
+// row tiles per item for all nodes: four while their rows stay in registers between maximum and split
+int project_tiles(const Dev& d) { return d.d0 <= 2u * kChunkK ? 4 : 1; }
 
+template <int RT>
 __global__ __launch_bounds__(256) void project_nodes_kernel(Dev d) {
   extern __shared__ __align__(16) float lds[];
-  project_rows(d, nullptr, 1u, blockIdx.x, gridDim.x, lds);
+  project_rows<RT>(d, nullptr, true, blockIdx.x, gridDim.x, lds);
 }
 
 // The first `proj_blocks` workgroups compute the batch's cached key|value rows (project_rows: the
@@ -283,7 +324,7 @@ __global__ __launch_bounds__(256) void apply_kernel(Dev d, const uint32_t* __res
   }
   if (c->skip) return;
   if (blockIdx.x < proj_blocks) {
-    project_rows(d, ef, 0u, blockIdx.x, proj_blocks, lds);
+    project_rows<1>(d, ef, false, blockIdx.x, proj_blocks, lds);
     return;
   }
   const uint32_t n = c->n_edges, nD = c->nD;
@@ -397,10 +438,12 @@ void launch_apply(const Dev& d, hipStream_t s, const uint32_t* src, const uint32
 }
 
 void launch_project_nodes(const Dev& d, hipStream_t s) {
-  uint64_t blocks = (uint64_t)((d.N + kProjRows - 1) / kProjRows);
+  const uint32_t tiles = (uint32_t)project_tiles(d), rows = tiles * kProjRows;
+  uint64_t blocks = (uint64_t)((d.N + rows - 1) / rows);
   const uint32_t cap = 8u * (d.num_cu ? d.num_cu : 256u);
   if (blocks > cap) blocks = cap;
-  hipLaunchKernelGGL(project_nodes_kernel, dim3((uint32_t)blocks), dim3(256), project_lds(d), s, d);
+  if (tiles == 4) hipLaunchKernelGGL(project_nodes_kernel<4>, dim3((uint32_t)blocks), dim3(256), project_lds(tiles, d.d0), s, d);
+  else hipLaunchKernelGGL(project_nodes_kernel<1>, dim3((uint32_t)blocks), dim3(256), project_lds(tiles, d.d0), s, d);
 }
 
 void launch_init_state(const Dev& d, hipStream_t s) {
@@ -420,8 +463,9 @@ int setup_ingest_attributes(const Dev& d) {
   if (project_lds(d) + 1024 > kMaxLds) return -1;
   if (hipFuncSetAttribute((const void*)apply_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                           (int)project_lds(d)) != hipSuccess) return -1;
-  return hipFuncSetAttribute((const void*)project_nodes_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)project_lds(d)) == hipSuccess ? 0 : -1;
+  const void* nodes = project_tiles(d) == 4 ? (const void*)project_nodes_kernel<4> : (const void*)project_nodes_kernel<1>;
+  return hipFuncSetAttribute(nodes, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)project_lds((uint32_t)project_tiles(d), d.d0)) == hipSuccess ? 0 : -1;
 }
 
 }  // namespace stgn

@@ -58,21 +58,6 @@ __device__ inline float row16_sum(float x) {
   return x;
 }
 
-// largest of each 16-lane row's magnitudes (every lane of a row receives it): as integers, whose order is theirs, with
-// no quieting of NaNs between the steps (a NaN comes out as the largest)
-template <int CTRL>
-__device__ inline uint32_t dpp_max(uint32_t x) {
-  return max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, false));
-}
-__device__ inline float row16_max(float m) {
-  uint32_t x = __builtin_bit_cast(uint32_t, m);
-  x = dpp_max<0xB1>(x); x = dpp_max<0x4E>(x); x = dpp_max<0x141>(x); x = dpp_max<0x140>(x);
-  return __builtin_bit_cast(float, x);
-}
-__device__ inline float bits_max(float a, float b) {
-  return __builtin_bit_cast(float, max(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b)));
-}
-
 // 1 / x to about half a unit in the last place, 0 for 0 (x >= 0)
 __device__ inline float reciprocal(float x) {
   const float r = __builtin_amdgcn_rcpf(x);
@@ -397,7 +382,6 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     if constexpr (LS == 32u) { const Two w = both_of_pair(m); m = bits_max(w.lo, w.hi); }
     return m;
   };
-  auto max4 = [](const float4& v) { return fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))); };
   auto row_scales = [&](float m) {
     const ArgBlock ab = args();
     const float bQ = ab->sp.bQ, bcQ = ab->sp.bcQ;

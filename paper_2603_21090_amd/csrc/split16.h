@@ -44,6 +44,23 @@ __device__ inline float pow2_scale(float bound) {
 }
 __device__ inline float inv_pow2(float s) { return __builtin_bit_cast(float, 0x7F000000u - __builtin_bit_cast(uint32_t, s)); }
 
+// largest of each 16-lane row's magnitudes (every lane of a row receives it): as integers, whose order is theirs, with
+// no quieting of NaNs between the steps (a NaN comes out as the largest)
+template <int CTRL>
+__device__ inline uint32_t dpp_max(uint32_t x) {
+  return max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, false));
+}
+__device__ inline float row16_max(float m) {
+  uint32_t x = __builtin_bit_cast(uint32_t, m);
+  x = dpp_max<0xB1>(x); x = dpp_max<0x4E>(x); x = dpp_max<0x141>(x); x = dpp_max<0x140>(x);
+  return __builtin_bit_cast(float, x);
+}
+__device__ inline float bits_max(float a, float b) {
+  return __builtin_bit_cast(float, max(__builtin_bit_cast(uint32_t, a), __builtin_bit_cast(uint32_t, b)));
+}
+
+__device__ inline float max4(const float4& v) { return fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))); }
+
 // Pairs of elements through the mixed-precision multiply-add: h = f16(a s), r = a s - h (exact), l = f16(2048 r), three
 // instructions an element with the packing done by them (conversions, a subtraction and a multiplication each took six
 // and a pack).  In the halves of `hi` and `lo`: element 0 low, element 1 high.

@@ -83,8 +83,7 @@ struct Table {
   uint32_t ld;
 };
 
-// Packed parameters of one attention layer (device pointers; WQn, WKT, WV, WO and, past the first layer, WKVn in the split
-// packing of split16.h, the rest group-major).
+// Packed parameters of one attention layer (device pointers; matrices in the packing of split16.h).
 //
 // Keys and values are linear in the attention input z_j = [h_{u_j} | e_j | phi(dt)], so they split by
 // input block (paper Eq. attn_detail):  K_j = h_{u_j} W_K[node rows] + e_j W_K[edge rows] + phi W_K[time rows].
@@ -116,7 +115,7 @@ struct SplitParams {
 };
 struct LayerDev {
   SplitParams sp;
-  float iKVn;                    // inverse scale of WKVn where it is split (layers past the first)
+  float iKVn, iKVe;              // inverse scales of WKVn and WKVe
   uint32_t d_in;                 // input width
   const float* WQn;              // [d_in x d_emb]            node block of W_Q / sqrt(dk)
   const float* cQ;               // [d_emb]                   phi(0) * (time block of W_Q) / sqrt(dk)

@@ -98,3 +98,32 @@ def test_queries_read_back_over_several_tiles(binding, kw):
     for l in (1, 2):
         assert np.array_equal(streamed[l - 1], g.get_embeddings(every, layer=l)), f"layer {l}"
     g.close()
+
+
+@pytest.mark.parametrize("kw", [
+    dict(d_mem=30, d_node=7, d_edge=70),            # memory ends inside a 16-byte piece, rows of no whole pieces
+    dict(d_mem=32, d_node=100, d_edge=300),         # five chunks: the row is read again between maximum and split
+    dict(d_mem=0, d_node=130, d_edge=257),          # node rows too long for four tiles an item
+    dict(d_mem=64, d_node=0, d_edge=65),
+])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_projected_rows(binding, kw, shift):
+    """Cached key|value rows of nodes and edges at the edges of their staging, with features that start on a 16-byte boundary
+    and off it."""
+    import torch
+    w = tiny_workload(num_nodes=200, num_edges=900, batch=90, layers=2, k=5, d_time=20, d_emb=40, d_msg=20, **kw)
+    W, nf, st = synth.make_weights(w), synth.node_features(w), synth.EdgeStream(w)
+    o, g = orc.Oracle.from_workload(w, W, nf), binding.StreamTGN.from_workload(w, W, nf)
+    for i in range(w.num_batches):
+        s, d, t, ef = st.batch(i)
+        assert o.ingest(s, d, t, ef)[0] == 0
+        room = torch.zeros(ef.size + shift, device="cuda")
+        room[shift:] = torch.from_numpy(ef.reshape(-1)).cuda()
+        g.ingest_batch(torch.from_numpy(s.astype(np.int32)).cuda(), torch.from_numpy(d.astype(np.int32)).cuda(),
+                       torch.from_numpy(t).cuda(), room[shift:].view(ef.shape))
+    every, ref = np.arange(w.num_nodes, dtype=np.uint32), o.embed_all()
+    streamed = [g.get_embeddings(every, layer=l) for l in (1, 2)]
+    g.full_rebuild()
+    for l in (1, 2):
+        assert rows_close(streamed[l - 1], ref[l - 1], 1e-4).all() and np.array_equal(streamed[l - 1], g.get_embeddings(every, layer=l))
+    g.close()
