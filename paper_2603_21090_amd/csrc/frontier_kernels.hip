@@ -258,12 +258,15 @@ __global__ __launch_bounds__(256) void compact_write_kernel(Dev d) {
 // then the others, and every tile of the window is marked: 1 when none of its rows changed.  A row's result
 // does not depend on which rows share its tile, so only the cost changes.  grid.y = list.
 //
-// A window is one workgroup (25 of them for 100,000 rows): bound by the latency of its chain, not by bytes.  A thread owns
-// sixteen consecutive positions.  The counts of four bins travel in one 64-bit word (a window's largest count
+// A window is one workgroup (25 of them for 100,000 rows): bound by the latency of its chain and by the instructions of its few
+// waves, not by bytes, hence sixteen waves.  A thread owns four consecutive positions (sixteen, in four
+// waves, took 15.3 us for the two lists of 100,000 nodes where this takes 11.1, and 26 for 1,300,000 where this takes 17.7).  The counts of four bins travel in one 64-bit word (a window's largest count
 // takes 13 of a field's 16 bits); a wave scans all groups of four at once, and one exchange of the wave totals
 // gives every thread its starting offsets: three barriers in all, where a scan of its own per bin took two barriers
 // per bin and the histogram an LDS atomic per row.
 constexpr uint32_t kBucketWindow = 4096;
+constexpr uint32_t kBucketThreads = 1024, kBucketWaves = kBucketThreads / 64;
+constexpr int kBucketItems = kBucketWindow / kBucketThreads;   // positions per thread
 // entry counts 0 .. k: twice (changed | unchanged input) where the query cache is in use, which takes k <= 32; once, k <= 64
 constexpr uint32_t kMaxBins = 2 * 33;
 constexpr uint32_t kMaxBinGroups = (kMaxBins + 3) / 4;
@@ -272,36 +275,36 @@ struct BucketJob { const uint32_t* in; const uint32_t* count; uint32_t* out; uin
 struct BucketJobs { BucketJob j[STGN_MAX_LAYERS]; };
 // NG: groups of four bins the variant has registers for
 template <uint32_t NG>
-__global__ __launch_bounds__(256) void bucket_rows_kernel(Dev d, BucketJobs jobs) {
-  __shared__ uint16_t s_tot[4][4 * NG];                      // per wave: rows of each bin; then the first place of its rows
+__global__ __launch_bounds__(kBucketThreads) void bucket_rows_kernel(Dev d, BucketJobs jobs) {
+  __shared__ uint16_t s_tot[kBucketWaves][4 * NG];                      // per wave: rows of each bin; then the first place of its rows
   __shared__ uint32_t s_changed[kBucketWindow / 16];
   const BucketJob job = jobs.j[blockIdx.y];
   uint32_t n = job.count_max;
   if (job.count) { const uint32_t c = *job.count; n = c < n ? c : n; }
   const uint32_t w0 = blockIdx.x * kBucketWindow;
   if (w0 >= n) return;
-  const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6, p0 = w0 + t * 16u;
+  const uint32_t t = threadIdx.x, lane = t & 63u, wave = t >> 6, p0 = w0 + t * (uint32_t)kBucketItems;
   const uint32_t nbk = d.k + 1u, nb = job.tile_clean ? 2u * nbk : nbk;
   const uint32_t ng = (nb + 3u) >> 2;                        // <= NG
-  s_changed[t] = 0u;
-  // (loads are unconditional, positions past the end repeat the last row: sixteen requests leave together)
-  uint32_t id[16], bin[16];
+  if (t < kBucketWindow / 16u) s_changed[t] = 0u;
+  // (loads are unconditional, positions past the end repeat the last row: a thread's requests leave together)
+  uint32_t id[kBucketItems], bin[kBucketItems];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
+  for (int i = 0; i < kBucketItems; ++i) {
     const uint32_t p = p0 + i < n ? p0 + i : n - 1u;
     id[i] = job.in ? job.in[p] : p;
   }
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
+  for (int i = 0; i < kBucketItems; ++i) {
     const uint32_t dg = d.deg[id[i]];
     bin[i] = d.k - (dg < d.k ? dg : d.k);                    // bin 0 = full rings: longest rows first
   }
   if (job.tile_clean) {                                      // uniform
 #pragma unroll
-    for (int i = 0; i < 16; ++i) bin[i] += d.flags_kept[id[i]] > job.thr_in ? nbk : 0u;
+    for (int i = 0; i < kBucketItems; ++i) bin[i] += d.flags_kept[id[i]] > job.thr_in ? nbk : 0u;
   }
 #pragma unroll
-  for (int i = 0; i < 16; ++i) bin[i] = p0 + i < n ? bin[i] : 0xFFFFu;   // no row
+  for (int i = 0; i < kBucketItems; ++i) bin[i] = p0 + i < n ? bin[i] : 0xFFFFu;   // no row
   // rows of each bin in front of this thread's within the wave
   uint64_t at[NG];
 #pragma unroll
@@ -310,7 +313,7 @@ __global__ __launch_bounds__(256) void bucket_rows_kernel(Dev d, BucketJobs jobs
     if (g >= ng) continue;                                   // uniform
     uint64_t mine = 0;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) mine += (bin[i] >> 2) == g ? 1ull << (16u * (bin[i] & 3u)) : 0ull;
+    for (int i = 0; i < kBucketItems; ++i) mine += (bin[i] >> 2) == g ? 1ull << (16u * (bin[i] & 3u)) : 0ull;
     uint64_t incl = mine;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
@@ -328,15 +331,14 @@ __global__ __launch_bounds__(256) void bucket_rows_kernel(Dev d, BucketJobs jobs
     uint32_t run = 0;
     for (uint32_t b0 = 0; b0 < nb; b0 += 64u) {              // uniform
       const uint32_t b = b0 + lane;
-      uint32_t c[4] = {0u, 0u, 0u, 0u};
-      if (b < nb)
+      uint32_t c[kBucketWaves], all = 0;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) c[w] = s_tot[w][b];
-      const uint32_t all = c[0] + c[1] + c[2] + c[3], incl = wave_incl_scan(all);
+      for (uint32_t w = 0; w < kBucketWaves; ++w) { c[w] = b < nb ? s_tot[w][b] : 0u; all += c[w]; }
+      const uint32_t incl = wave_incl_scan(all);
       uint32_t o = run + incl - all;
       if (b < nb)
 #pragma unroll
-        for (int w = 0; w < 4; ++w) { s_tot[w][b] = (uint16_t)o; o += c[w]; }
+        for (uint32_t w = 0; w < kBucketWaves; ++w) { s_tot[w][b] = (uint16_t)o; o += c[w]; }
       run += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
     }
   }
@@ -348,7 +350,7 @@ __global__ __launch_bounds__(256) void bucket_rows_kernel(Dev d, BucketJobs jobs
 #pragma unroll
     for (int q = 0; q < 4; ++q) cur += (uint64_t)s_tot[wave][4u * g + q] << (16 * q);
 #pragma unroll
-    for (int i = 0; i < 16; ++i)
+    for (int i = 0; i < kBucketItems; ++i)
       if ((bin[i] >> 2) == g) {
         const uint32_t sh = 16u * (bin[i] & 3u), o = (uint32_t)(cur >> sh) & 0xFFFFu;
         cur += 1ull << sh;
@@ -358,7 +360,7 @@ __global__ __launch_bounds__(256) void bucket_rows_kernel(Dev d, BucketJobs jobs
   }
   if (job.tile_clean) {
     __syncthreads();
-    if (p0 < n) job.tile_clean[p0 >> 4] = s_changed[t] ? 0 : 1;
+    if (t < kBucketWindow / 16u && w0 + 16u * t < n) job.tile_clean[(w0 >> 4) + t] = s_changed[t] ? 0 : 1;
   }
 }
 
@@ -409,9 +411,9 @@ void launch_bucket_rows(const Dev& d, hipStream_t s, bool all_rows) {
   uint32_t halves = 1u;
   for (uint32_t j = 0; j < nj; ++j) if (jobs.j[j].tile_clean) halves = 2u;
   const uint32_t groups = (halves * (d.k + 1u) + 3u) / 4u;
-  if (groups <= 6u) hipLaunchKernelGGL(bucket_rows_kernel<6>, dim3(blocks, nj), dim3(256), 0, s, d, jobs);
-  else if (groups <= 11u) hipLaunchKernelGGL(bucket_rows_kernel<11>, dim3(blocks, nj), dim3(256), 0, s, d, jobs);
-  else hipLaunchKernelGGL(bucket_rows_kernel<kMaxBinGroups>, dim3(blocks, nj), dim3(256), 0, s, d, jobs);
+  if (groups <= 6u) hipLaunchKernelGGL(bucket_rows_kernel<6>, dim3(blocks, nj), dim3(kBucketThreads), 0, s, d, jobs);
+  else if (groups <= 11u) hipLaunchKernelGGL(bucket_rows_kernel<11>, dim3(blocks, nj), dim3(kBucketThreads), 0, s, d, jobs);
+  else hipLaunchKernelGGL(bucket_rows_kernel<kMaxBinGroups>, dim3(blocks, nj), dim3(kBucketThreads), 0, s, d, jobs);
 }
 
 bool compact_in_one(const Dev& d) { return (d.N + kFlagsPerBlock - 1) / kFlagsPerBlock <= kSmallBlocks; }
