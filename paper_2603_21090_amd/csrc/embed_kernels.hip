@@ -18,10 +18,10 @@ using layer_impl::LayerArgs;
 //
 // A copy, bound by HBM for long lists and by the launch for short ones.  A workgroup takes `per` consecutive list
 // positions (and again `per`, a grid further on, when the list outgrows the largest grid) and its threads stride over
-// their pieces of V floats; four pieces per thread are requested before the first is stored, and the (row, piece) pair
-// advances by additions.  One million rows of 100 floats: 184 us = 4.4 TB/s of ids, rows read and rows stored, 4.9 with
-// the padding of the tables' rows to 512 bytes, where a large copy reaches 6.0 (one float per thread and a 64-bit
-// division each: 284 us).
+// their pieces of V floats; eight pieces per thread are requested before the first is stored, and the (row, piece) pair
+// advances by additions.  One million rows of 100 floats: 173 us
+// = 4.6 TB/s of ids, rows read and rows stored, 5.3 with the padding of the tables' rows to 512 bytes, where a large copy
+// reaches 6.0 (four pieces together: 185 us; one float per thread and a 64-bit division each: 284 us).
 // Results are stored past the caches: nothing here reads them again, and the tables keep their place.
 constexpr uint32_t kGatherBlocks = 1u << 16;
 template <int V> struct Piece;
@@ -33,7 +33,7 @@ template <int V>
 __global__ __launch_bounds__(256) void gather_rows_kernel(Table T, uint32_t N, uint32_t width, uint32_t n, uint32_t per,
                                                           const uint32_t* __restrict__ nodes, float* __restrict__ out) {
   using P = typename Piece<V>::type;
-  constexpr int U = 4;
+  constexpr int U = 8;
   const uint32_t q = width / V;                               // pieces per row
   const uint32_t dr = 256u / q, dc = 256u - dr * q;
   for (uint64_t i0 = (uint64_t)blockIdx.x * per; i0 < n; i0 += (uint64_t)gridDim.x * per) {   // (uniform)
