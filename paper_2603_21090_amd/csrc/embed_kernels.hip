@@ -305,6 +305,12 @@ int setup_embed_attributes(const Dev& d) {
     a.set_attr = true;
     go_heads(a);
     if (a.err != hipSuccess) return -1;
+    if (const uint8_t* clean = a.k.tile_clean) {                  // rebuilds run the variant that reads nothing back
+      a.k.tile_clean = nullptr;
+      go_heads(a);
+      if (a.err != hipSuccess) return -1;
+      a.k.tile_clean = clean;
+    }
     if (l + 1 == d.layers) {                                      // the final layer's root rows
       a.roots = true;
       go_heads(a);

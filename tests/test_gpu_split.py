@@ -84,6 +84,7 @@ def test_workgroups_of_several_tiles(binding, kw):
     dict(d_mem=0, d_node=30, d_edge=0, d_time=20, d_emb=100, heads=1),       # one wide head
     dict(d_mem=0, d_node=30, d_edge=9, d_time=70, d_emb=60, heads=4),        # four heads
     dict(d_mem=30, d_edge=9, d_time=70, d_emb=40, heads=1),                  # rows of one slot
+    dict(d_mem=0, d_node=30, d_edge=9, d_time=100, d_emb=128, heads=4, k=20),   # more than 64 KB of LDS, rebuilds included
 ])
 def test_queries_read_back_over_several_tiles(binding, kw):
     """Streamed rows (queries read back from the cache where they did not change) have the bits of rebuilt rows (everything
