@@ -96,8 +96,8 @@ struct LayerLds {
 __host__ __device__ inline LayerLds layer_lds(uint32_t d_in, uint32_t heads, uint32_t ks, uint32_t nz, uint32_t k, bool delta) {
   LayerLds l;
   const uint32_t wx = round_up(d_in, 16u), wo = kSlot * ks;
-  l.ldx = (wx > wo ? wx : wo) + 4;                // the input tile and the head-output tile share storage
-  l.ldq = wo + 4;                                 // q in the padded-head layout, later the output rows h'
+  l.ldx = (wx > wo ? wx : wo) + 4;                // the input tile and the cached part of the head outputs share storage
+  l.ldq = wo + 4;                                 // q in the padded-head layout, later the head outputs
   l.ldz = heads * kSlot * nz + 4;
   l.off_q = kTM * l.ldx;
   l.off_z = l.off_q + kTM * l.ldq;
@@ -232,9 +232,9 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   constexpr uint32_t ntz = Ztp >> 4;                                                                       // tiles of a qt vector
   const uint32_t nzt_t = (a.d_time + 15u) >> 4, nzt = nzt_t + (ES ? (a.d_edge + 15u) >> 4 : 0u);           // ... that hold valid columns
   const LayerLds ll = layer_lds(a.d_in, H, KS, NZ, k, DELTA);
-  float* Xs = lds;                            // input rows (phases 0-1), later the output rows (phases 5-6) ...
-  float* Qs = lds + ll.off_q;                 // q (phases 1-3), then head outputs (phases 3-5) ... or the other way round
-  float* Zs = lds + ll.off_z;                 // qt (phases 2-3), then pb (phases 3-4)
+  float* Xs = lds;                            // input rows, split (phase 1), then the cached-value part of the head outputs (phases 3-4)
+  float* Qs = lds + ll.off_q;                 // q, split (phases 1-3), then the head outputs, split (phases 4-5)
+  float* Zs = lds + ll.off_z;                 // qt (phases 2-3), then pb, split (phases 3-4), then the output rows (phases 5-6)
   RingEntry* Rs = reinterpret_cast<RingEntry*>(__builtin_assume_aligned(lds + ll.off_r, 16));   // [row][j], j = 0 the most recent entry
   using ZBuf = GatherBuf<JC, ES>;
 
