@@ -8,7 +8,6 @@
 
 #include "stgn_internal.h"
 #include "mfma16.h"
-#include "split16.h"
 
 using namespace stgn;
 
@@ -132,44 +131,6 @@ void put_tiled(std::vector<float>& dst, uint32_t K, uint32_t k, uint32_t j, doub
   const size_t block = (size_t)(j / 16) * groups_of(K) + k / kGrpK;
   dst[block * kGrpFloats + (((k % kGrpK) / 4) * 16 + j % 16) * 4 + k % 4] = (float)v;
 }
-
-// The same matrix as split16.h packs it (same size): `v` holds its values, `put` one of them, `pack` everything under the
-// matrix's own power-of-two scale, whose inverse it returns.
-struct SplitMatrix {
-  uint32_t K, N;
-  std::vector<double> v;
-  SplitMatrix(uint32_t K_, uint32_t N_) : K(K_), N(N_), v((size_t)K_ * N_, 0.0) {}
-  void put(uint32_t k, uint32_t j, double x) { v[(size_t)k * N + j] = x; }
-  double largest() const { double m = 0.0; for (double x : v) m = std::max(m, std::fabs(x)); return m; }
-  double column_sum() const {                                 // the largest sum of a column's magnitudes
-    double m = 0.0;
-    for (uint32_t j = 0; j < N; ++j) {
-      double a = 0.0;
-      for (uint32_t k = 0; k < K; ++k) a += std::fabs(v[(size_t)k * N + j]);
-      m = std::max(m, a);
-    }
-    return m;
-  }
-  float pack(std::vector<float>& dst) const {
-    dst.assign(tiled_size(K, N), 0.0f);
-    const double m = largest();
-    int e = 0;
-    if (m > 0.0 && std::isfinite(m)) std::frexp(m, &e);       // m in [2^(e - 1), 2^e)
-    e = std::min(std::max(e, -100), 114);
-    const double t = std::ldexp(1.0, 14 - e);
-    const uint32_t nch = chunks64(K);
-    for (uint32_t k = 0; k < K; ++k)
-      for (uint32_t j = 0; j < N; ++j) {
-        const double x = v[(size_t)k * N + j] * t;
-        const _Float16 h = (_Float16)x, l = (_Float16)((x - (double)h) * (double)kLoScale);
-        const uint32_t kk = k % kChunkK, u = kk / 32u, lane = (kk % 32u) / 8u * 16u + j % 16u;
-        char* block = reinterpret_cast<char*>(dst.data()) + ((size_t)(j / 16u) * nch + k / kChunkK) * (4u * kChunkFloats);
-        memcpy(block + (2u * u) * 1024u + lane * 16u + (kk % 8u) * 2u, &h, 2);
-        memcpy(block + (2u * u + 1u) * 1024u + lane * 16u + (kk % 8u) * 2u, &l, 2);
-      }
-    return (float)std::ldexp(1.0, e - 14);
-  }
-};
 
 // Host inputs travel as one block: src at 0, dst at 4 B, ts at 8 B, edge features at 16 B per edge of the largest batch.
 size_t stage_bytes(const stgn_config& c) { return (size_t)c.max_batch * (16 + (size_t)c.d_edge * sizeof(float)); }
@@ -380,21 +341,21 @@ int pack_parameters(stgn_ctx* ctx, const stgn_weights* w) {
         (rc = upload(ctx, d.br, vec(w->b_r, c.d_mem))) || (rc = upload(ctx, d.bh, vec(w->b_h, c.d_mem))))
       return rc;
   }
-  // attention weights feed split products (split16.h).
+  // attention weights feed 16x16x4 matrix instructions: group-major packing (see tiled_size).
   // Row z of W_K / W_V belongs to the node block (z < d_in), the edge block or the time block of the
   // attention input; column h dk + cc to head h.  In a cached row and in the head-output tile head h
   // starts at float 64 sh h (padded-head layout).
   const uint32_t dk = d.dk, npk = round_up(dk, 16), hp = kSlot * d.sh, Ztp = kSlot * d.nz;
   const double inv_sqrt_dk = 1.0 / std::sqrt((double)dk);
   for (uint32_t l = 0; l < c.layers; ++l) {
-    LayerDev& L = ctx->d.L[l];
+    const LayerDev& L = d.L[l];
     const float *WQ = w->W_Q[l], *WK = w->W_K[l], *WV = w->W_V[l], *WOs = w->W_O[l];
     const uint32_t e0 = L.d_in, t0 = L.d_in + c.d_edge;       // first edge row, first time row
     // the query carries the 1 / sqrt(dk) of the scores
-    SplitMatrix mQ(L.d_in, c.d_emb);
+    std::vector<float> WQn(tiled_size(L.d_in, c.d_emb), 0.0f);
     for (uint32_t i = 0; i < L.d_in; ++i)
       for (uint32_t col = 0; col < c.d_emb; ++col)
-        mQ.put(i, col, (double)WQ[(size_t)i * c.d_emb + col] * inv_sqrt_dk);
+        put_tiled(WQn, L.d_in, i, col, (double)WQ[(size_t)i * c.d_emb + col] * inv_sqrt_dk);
     std::vector<float> cQ(c.d_emb);
     for (uint32_t col = 0; col < c.d_emb; ++col) {
       double acc = 0.0;
@@ -405,47 +366,41 @@ int pack_parameters(stgn_ctx* ctx, const stgn_weights* w) {
     // time rows of W_K, head blocks transposed: K = column inside the head, columns = (head, index in z);
     // time rows of W_V, head blocks: K = index in z, columns = (head, column inside the head padded to 16).
     // z = [phi | f]: time index i at i, and with raw edge rows feature i at 64 nt + i.
-    SplitMatrix mKT(hp, c.heads * Ztp), mV(Ztp, c.heads * npk);
+    std::vector<float> WKT(tiled_size(hp, c.heads * Ztp), 0.0f);
+    std::vector<float> WVp(tiled_size(Ztp, c.heads * npk), 0.0f);
     for (uint32_t h = 0; h < c.heads; ++h)
       for (uint32_t cc = 0; cc < dk; ++cc) {
         for (uint32_t i = 0; i < c.d_time; ++i) {
-          mKT.put(cc, h * Ztp + i, (double)WK[(size_t)(t0 + i) * c.d_emb + h * dk + cc] * tscale);
-          mV.put(i, h * npk + cc, (double)WV[(size_t)(t0 + i) * c.d_emb + h * dk + cc] * tscale);
+          put_tiled(WKT, hp, cc, h * Ztp + i, (double)WK[(size_t)(t0 + i) * c.d_emb + h * dk + cc] * tscale);
+          put_tiled(WVp, Ztp, i, h * npk + cc, (double)WV[(size_t)(t0 + i) * c.d_emb + h * dk + cc] * tscale);
         }
         for (uint32_t i = 0; i < (d.es ? c.d_edge : 0u); ++i) {
-          mKT.put(cc, h * Ztp + kSlot * d.nt + i, WK[(size_t)(e0 + i) * c.d_emb + h * dk + cc]);
-          mV.put(kSlot * d.nt + i, h * npk + cc, WV[(size_t)(e0 + i) * c.d_emb + h * dk + cc]);
+          put_tiled(WKT, hp, cc, h * Ztp + kSlot * d.nt + i, WK[(size_t)(e0 + i) * c.d_emb + h * dk + cc]);
+          put_tiled(WVp, Ztp, kSlot * d.nt + i, h * npk + cc, WV[(size_t)(e0 + i) * c.d_emb + h * dk + cc]);
         }
       }
     // W_O with its rows moved to the padded-head layout of the head outputs
-    SplitMatrix mO(kSlot * d.ks, c.d_emb);
+    std::vector<float> WO(tiled_size(kSlot * d.ks, c.d_emb), 0.0f);
     for (uint32_t h = 0; h < c.heads; ++h)
       for (uint32_t cc = 0; cc < dk; ++cc)
         for (uint32_t col = 0; col < c.d_emb; ++col)
-          mO.put(h * hp + cc, col, WOs[(size_t)(h * dk + cc) * c.d_emb + col]);
+          put_tiled(WO, kSlot * d.ks, h * hp + cc, col, WOs[(size_t)(h * dk + cc) * c.d_emb + col]);
     // node and edge rows of [W_K | W_V] in the cached-row layout: keys in floats [0, 64 ks), values behind
-    SplitMatrix mKV(L.d_in, d.ld_kv), mKVe(d.es ? 0u : c.d_edge, d.ld_kv);
+    std::vector<float> WKVn(tiled_size(L.d_in, d.ld_kv), 0.0f);
+    std::vector<float> WKVe(c.d_edge && !d.es ? tiled_size(c.d_edge, d.ld_kv) : 0, 0.0f);
     for (uint32_t h = 0; h < c.heads; ++h)
       for (uint32_t cc = 0; cc < dk; ++cc) {
         const uint32_t kc = h * hp + cc, vc = kSlot * d.ks + h * hp + cc;
         const size_t wc = (size_t)h * dk + cc;
         for (uint32_t i = 0; i < L.d_in; ++i) {
-          mKV.put(i, kc, WK[(size_t)i * c.d_emb + wc]);
-          mKV.put(i, vc, WV[(size_t)i * c.d_emb + wc]);
+          put_tiled(WKVn, L.d_in, i, kc, WK[(size_t)i * c.d_emb + wc]);
+          put_tiled(WKVn, L.d_in, i, vc, WV[(size_t)i * c.d_emb + wc]);
         }
         for (uint32_t i = 0; i < (d.es ? 0u : c.d_edge); ++i) {
-          mKVe.put(i, kc, WK[(size_t)(e0 + i) * c.d_emb + wc]);
-          mKVe.put(i, vc, WV[(size_t)(e0 + i) * c.d_emb + wc]);
+          put_tiled(WKVe, c.d_edge, i, kc, WK[(size_t)(e0 + i) * c.d_emb + wc]);
+          put_tiled(WKVe, c.d_edge, i, vc, WV[(size_t)(e0 + i) * c.d_emb + wc]);
         }
       }
-    std::vector<float> WQn, WKT, WVp, WO, WKVn, WKVe;
-    L.sp.iQ = mQ.pack(WQn); L.sp.iKT = mKT.pack(WKT); L.sp.iV = mV.pack(WVp); L.sp.iO = mO.pack(WO);
-    L.iKVn = mKV.pack(WKVn);
-    if (mKVe.K) L.iKVe = mKVe.pack(WKVe);
-    auto largest = [](const float* p, uint32_t n) { float m = 0.0f; for (uint32_t i = 0; i < n; ++i) m = std::max(m, std::fabs(p[i])); return m; };
-    L.sp.bQ = (float)mQ.column_sum(); L.sp.bcQ = largest(cQ.data(), c.d_emb);
-    L.sp.bV = (float)mV.column_sum();
-    L.sp.bO = (float)mO.column_sum(); L.sp.bbO = largest(w->b_O[l], c.d_emb);
     if ((rc = upload(ctx, L.WQn, WQn)) || (rc = upload(ctx, L.cQ, cQ)) || (rc = upload(ctx, L.WKT, WKT)) ||
         (rc = upload(ctx, L.WV, WVp)) || (rc = upload(ctx, L.WO, WO)) || (rc = upload(ctx, L.bO, vec(w->b_O[l], c.d_emb))) ||
         (rc = upload(ctx, L.WKVn, WKVn)) || (rc = upload(ctx, L.WKVe, WKVe)))

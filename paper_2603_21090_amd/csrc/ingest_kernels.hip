@@ -5,7 +5,6 @@
 // (adjacency append, in-place memory write-back).
 #include "stgn_internal.h"
 #include "mfma16.h"
-#include "split16.h"
 #include "compaction.h"
 #include "placement.h"
 
@@ -162,18 +161,17 @@ __device__ inline uint64_t log_addr(const Dev& d, uint32_t node, uint32_t pos) {
 //       KVE[l][e] = feat_e [W_K | W_V](edge rows of layer l) for the batch's edges e (not with raw edge rows:
 //       those are copied by the appending workgroups of the launch);
 //   all_nodes (initial state, full rebuild):  KV[0][v] for every node.
-// One workgroup (four waves) per 16 rows and 128 of the 128 ks output columns: the rows go through LDS as the A operand of
-// split products (split16.h), wave w computes the column tiles w and w + 4 of the workgroup's column group (these
-// launches are small and latency-bound: more, shorter workgroups finish sooner).  For all nodes an item is RT tiles of
-// rows and takes every column group in turn: a tile streams 64 KB of weights a group from L2, which is what
-// bounds one tile at a time (200,000 nodes, d 100, two groups: 206 us with fp32 products and one tile, 123 with four).
+// One workgroup (four waves) per 16 rows and 128 of the 128 ks output columns: the rows go through LDS as the A operand,
+// wave w computes the column tiles w and w + 4 of the workgroup's column group (these launches are small and
+// latency-bound: more, shorter workgroups finish sooner).  For all nodes an item is RT tiles of rows and takes every
+// column group in turn: a tile streams 64 KB of weights a group from L2, which is what bounds one tile at a time
+// (200,000 nodes, d 100, two groups: 207 us with one tile, 142 with four).
 // `bid` / `nblk` are the workgroup's index and count among the workgroups that project.
 constexpr uint32_t kProjRows = 16;
 template <int RT>
 __device__ void project_rows(const Dev& d, const float* __restrict__ ef, bool all_nodes, uint32_t bid, uint32_t nblk, float* lds) {
-  __shared__ __align__(16) float s_scale[RT * kProjRows];
   constexpr uint32_t kRows = RT * kProjRows;
-  constexpr int kHeld = RT > 1 ? 2 : 4;                       // 64-column pieces of a row held in registers between its maximum and its split
+  constexpr int kHeld = RT > 1 ? 2 : 4;                       // 64-column pieces of a row requested together
   const BatchCtl* c = d.bc;
   const uint32_t nD = all_nodes ? d.N : (d.d_mem ? c->nD : 0u);
   const uint32_t nE = (all_nodes || !d.d_edge || d.es) ? 0u : c->n_edges;
@@ -188,7 +186,7 @@ __device__ void project_rows(const Dev& d, const float* __restrict__ ef, bool al
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   // 16-byte reads of a row's pieces, where every row starts on such a boundary
   const bool ef_quads = d.d_edge % 4u == 0u && (reinterpret_cast<uintptr_t>(ef) & 15u) == 0u, mem_quads = d.d_mem % 4u == 0u;
-  struct Weights { float4 b[2][4]; };
+  struct Weights { float4 b[2][kCG]; };
   for (uint32_t item = bid; item < ntiles; item += nblk) {
     const uint32_t tile = all_nodes ? item : item / d.ks;
     uint32_t nt = all_nodes ? wave : wave + 8u * (item - tile * d.ks);
@@ -198,15 +196,16 @@ __device__ void project_rows(const Dev& d, const float* __restrict__ ef, bool al
     const uint32_t nrows = node_job ? nD : nE;
     const uint32_t K = node_job ? d.d0 : d.d_edge;
     const float* W = node_job ? d.L[0].WKVn : d.L[layer].WKVe;
-    const float inv_w = node_job ? d.L[0].iKVn : d.L[layer].iKVe;
     float* out = node_job ? d.KV[0].base : d.KVE[layer].base;
-    const uint32_t ck = chunks64(K);
+    const uint32_t ck = chunks_of(K);
     Weights P;                                                // first weight chunk, requested ahead of the staging
-    load_b64(W + (size_t)nt * ck * kChunkFloats, 0, P.b[0], lane);
-    load_b64(W + (size_t)(nt + 4) * ck * kChunkFloats, 0, P.b[1], lane);
-    // Sixteen lanes stage a row, lane `sub` the columns 64 i + 4 sub .. + 3, up to the end of the last chunk (zero past K).
+    load_b16(W + (size_t)nt * ck * kChunkFloats, 0, P.b[0]);
+    load_b16(W + (size_t)(nt + 4) * ck * kChunkFloats, 0, P.b[1]);
+    // Sixteen lanes stage a row, lane `sub` the columns 64 i + 4 sub .. + 3, up to the end of the last chunk (zero past K:
+    // operand padding must be finite).
     // A batch endpoint's new memory is read from the batch's scratch rows: the write-back into the
     // memory table runs in the same launch.
+    float4 held[RT][kHeld];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
       const uint32_t r = rt * kProjRows + r16, row = r0 + r;
@@ -236,47 +235,43 @@ __device__ void project_rows(const Dev& d, const float* __restrict__ ef, bool al
         if (col + 3u < K) v.w = src[3];
         return v;
       };
-      float4 v[kHeld];
-      float m = 0.0f;
+      float* lrow = lds + r * lda + 4u * sub;
 #pragma unroll
-      for (int i = 0; i < kHeld; ++i) { v[i] = piece(i); m = fmaxf(m, max4(v[i])); }
-      for (uint32_t i = kHeld; i < ck; ++i) m = fmaxf(m, max4(piece(i)));
-      const float s = pow2_scale(row16_max(m));
-      if (sub == 0u) s_scale[r] = s;
-      float* lrow = lds + r * lda;
-#pragma unroll
-      for (int i = 0; i < kHeld; ++i) if ((uint32_t)i < ck) split_store4(lrow, kChunkK * i + 4u * sub, v[i], s);
-      for (uint32_t i = kHeld; i < ck; ++i) split_store4(lrow, kChunkK * i + 4u * sub, piece(i), s);
+      for (int i = 0; i < kHeld; ++i) held[rt][i] = piece(i);
+      for (uint32_t i = kHeld; i < ck; ++i) *reinterpret_cast<float4*>(lrow + kChunkK * i) = piece(i);
     }
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int i = 0; i < kHeld; ++i)
+        if ((uint32_t)i < ck) *reinterpret_cast<float4*>(lds + (rt * kProjRows + r16) * lda + 4u * sub + kChunkK * i) = held[rt][i];
     __syncthreads();
     for (uint32_t cg = 0; cg < groups_per_item; ++cg, nt += 8u) {
       const float* const Bt[2] = {W + (size_t)nt * ck * kChunkFloats, W + (size_t)(nt + 4) * ck * kChunkFloats};
-      if (cg) { load_b64(Bt[0], 0, P.b[0], lane); load_b64(Bt[1], 0, P.b[1], lane); }
-      AccS<2> acc[RT];
+      if (cg) { load_b16(Bt[0], 0, P.b[0]); load_b16(Bt[1], 0, P.b[1]); }
+      floatx4 acc[RT][2] = {};
       pingpong_peeled<Weights>(
           ck, P,
-          [&](uint32_t ch, Weights& o) { load_b64(Bt[0], ch, o.b[0], lane); load_b64(Bt[1], ch, o.b[1], lane); },
+          [&](uint32_t ch, Weights& o) { load_b16(Bt[0], ch * kCG, o.b[0]); load_b16(Bt[1], ch * kCG, o.b[1]); },
           [&](uint32_t ch, const Weights& o) {
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) {
-              float4 a[4];
-              load_a64(lds + rt * kProjRows * lda + s16_off(lane, lda), ch, a);
-              mfma_chunk<2>(a, o.b, acc[rt]);
+              float4 a[kCG];
+              load_a16(lds + rt * kProjRows * lda + a16_off(lane, lda), ch * kCG, a);
+              mfma16_chunk<2>(a, o.b, acc[rt]);
             }
           });
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
-        const float4 sc = *reinterpret_cast<const float4*>(s_scale + rt * kProjRows + s16_row(lane, 0));
-        const float f[4] = {inv_pow2(sc.x) * inv_w, inv_pow2(sc.y) * inv_w, inv_pow2(sc.z) * inv_w, inv_pow2(sc.w) * inv_w};
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
-          const uint32_t col = (nt + 4 * t) * 16 + s16_col(lane);           // every column is written: padding columns get exact zeros
+          const uint32_t col = (nt + 4 * t) * 16 + m16_col(lane);           // every column is written: padding columns get exact zeros
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            const uint32_t row = r0 + rt * kProjRows + s16_row(lane, r);
+            const uint32_t row = r0 + rt * kProjRows + m16_row(lane, r);
             if (row < nrows) {
               const size_t orow = node_job ? (size_t)(all_nodes ? row : d.D[row]) : (size_t)(E0 + row);
-              out[orow * d.ld_kv + col] = acc_value(acc[rt], t, r) * f[r];
+              out[orow * d.ld_kv + col] = acc[rt][t][r];
             }
           }
         }
@@ -288,7 +283,7 @@ __device__ void project_rows(const Dev& d, const float* __restrict__ ef, bool al
 
 size_t project_lds(uint32_t tiles, uint32_t kmax) { return (size_t)tiles * kProjRows * (round_up(kmax, kChunkK) + 4) * sizeof(float); }
 size_t project_lds(const Dev& d) { return project_lds(1u, d.d0 > d.d_edge ? d.d0 : d.d_edge); }
-// row tiles per item for all nodes: four while their rows stay in registers between maximum and split
+// row tiles per item for all nodes: four while the pieces of their rows fit the registers (two a row)
 int project_tiles(const Dev& d) { return d.d0 <= 2u * kChunkK ? 4 : 1; }
 
 template <int RT>

@@ -12,7 +12,7 @@
 // cached rows hold the node terms alone.
 // A workgroup of eight waves (four: rows of one slot, delta mode) owns 16 target rows and runs its phases without
 // leaving the CU:
-//   1. q  = h_v W_Q(node block) + phi(0) W_Q(time block)                           (MFMA 16x16x32, split operands)
+//   1. q  = h_v W_Q(node block) + phi(0) W_Q(time block)                           (MFMA 16x16x4)
 //   2. qt_h = q_h W_K,h[time]^T                                                     (MFMA)
 //   3. gather the cached rows of the ring entries, time encodings, scores, softmax, weighted sums;
 //      a row is served by one 16-lane group per key slot, lane x float4               (HBM / vector ALU)
@@ -20,23 +20,22 @@
 //   5. h_v' = [o_1 | .. | o_H] W_O + b_O, written into the layer cache               (MFMA)
 //   6. unless this is the last layer: the row's own cached keys|values for the next layer,
 //      h_v' [W_K | W_V](node rows of layer l + 1)                                     (MFMA)
-// Weights stream from L2, each phase's requested a phase ahead; several workgroups per CU overlap one's gather with
-// another's products.
+// Weights stream from L2 (group-major packing, see mfma16.h), each phase's requested ahead of its barrier; several
+// workgroups per CU overlap one's gather with another's products.
 //
-// The products of phases 1, 2, 4, 5 and 6 take their fp32 operands as pairs of f16 (split16.h): a fifth of the matrix
-// cycles of the fp32 instructions, which had been 30 to 47 % of a launch and stood in line with everything else in it.  Layer launches
-// before and after: 1,000,000 nodes, d_edge 100, 1,017 -> 815 us and (query cache) 942 -> 793; 1,300,000 nodes, raw edge
-// rows, k = 20, 973 -> 817; 100,000 nodes, d_edge 172, 182 -> 151 and 182 -> 159; a rebuild of 200,000 nodes 583 + 403 -> 460 + 324;
-// 10,000 nodes 32 + 37 -> 26 + 32.  Errors of whole layer-2 tables against 64 bits (2-norm / largest over root mean square),
-// fp32 products -> split: d 100, d_edge 172, two heads 2.8e-7 / 2.7e-6 -> 2.5e-7 / 1.9e-6; raw edge rows, k = 20 2.2e-7 /
-// 2.4e-6 -> 1.4e-7 / 9.7e-7; four heads of 32 1.1e-7 / 1.0e-6 -> 7.2e-8 / 5.0e-7; one head of 64 1.2e-7 / 1.1e-6 ->
-// 1.0e-7 / 8.3e-7; one head of 100 1.2e-7 / 1.6e-6 -> 8.4e-8 / 6.9e-7.
+// The products of phases 1, 2, 4, 5 and 6 are fp32 matrix instructions, 30 to 47 % of a launch's matrix cycles.  Operands
+// split into two f16 under one power-of-two scale per row and per matrix took a fifth of those cycles and 12 to 24 % off a launch,
+// but an f16 pair holds 22 bits, and those only within 2^27 of the scale's bound: a large feature with small
+// weights in a row of ordinary ones cost its other columns their bits (queries 4e-5 off with one feature of 1.7e9).  So
+// the operands stay in 32 bits.  Layer launches, with a 16-lane group per row and with the present kernel: 1,000,000 nodes,
+// d_edge 100, 1,082 -> 1,003 us and (query cache) 1,052 -> 924; 1,300,000 nodes, raw edge rows, k = 20, 1,048 -> 952; 100,000
+// nodes, d_edge 172, 190 -> 180 and 204 -> 188; a rebuild of 200,000 nodes 662 + 429 -> 585 + 396.  Whole tables
+// lie 1e-7 to 2.9e-7 (2-norm) and up to 2.6e-6 of the root mean square (largest) off 64-bit results.
 #pragma once
 #include <mutex>
 #include <type_traits>
 #include "stgn_internal.h"
 #include "mfma16.h"
-#include "split16.h"
 
 namespace stgn {
 
@@ -95,13 +94,13 @@ struct LayerLds {
 // fall into distinct banks.  ks = key slots (heads * slots per head), nz = slots of z = [phi | raw edge row].
 __host__ __device__ inline LayerLds layer_lds(uint32_t d_in, uint32_t heads, uint32_t ks, uint32_t nz, uint32_t k, bool delta) {
   LayerLds l;
-  const uint32_t wx = round_up(d_in, 16u), wo = kSlot * ks;
+  const uint32_t wx = round_up(d_in, kGrpK), wo = kSlot * ks;
   l.ldx = (wx > wo ? wx : wo) + 4;                // the input tile and the cached part of the head outputs share storage
   l.ldq = wo + 4;                                 // q in the padded-head layout, later the head outputs
   l.ldz = heads * kSlot * nz + 4;
   l.off_q = kTM * l.ldx;
   l.off_z = l.off_q + kTM * l.ldq;
-  l.off_r = l.off_z + kTM * l.ldz + 64u;    // operand reads may run one chunk past the last row
+  l.off_r = l.off_z + kTM * l.ldz + 4 * kGrpK;    // operand reads may run one chunk past the last row
   l.off_sc = l.off_r + kTM * k * 4;               // the ring records of the tile's rows, 16 bytes each
   l.total = l.off_sc + (delta ? kTM * k * heads : 0u);       // delta mode: the scores of a row's entries until its weights are known
   return l;
@@ -126,8 +125,7 @@ struct LayerArgs {
   const double* om_rev; const double* ph_rev;
   Ctrl* ctrl;
   uint64_t* gathered_slots;                        // statistic: ring entries gathered, one plain counter per workgroup index
-  const float *WQ, *cQ, *WKT, *WV, *WO, *bO, *WKVnext;   // matrices in the packing of split16.h
-  SplitParams sp; float iKVnext;                   // their inverse scales and the bounds (LayerDev)
+  const float *WQ, *cQ, *WKT, *WV, *WO, *bO, *WKVnext;   // matrices group-major (mfma16.h)
   uint32_t ld_in, ld_out, ld_kv, ld_kve;           // ld_kve = 0 without edge features (every edge reads one zero row)
   uint32_t k, d_in, d_emb, dk, d_time, d_edge;
   // query cache (null: off): this layer's cached q | qt rows, [node][64 (KS + H NZ)], and per tile of the row list whether
@@ -176,8 +174,8 @@ __device__ inline void wave_lds_fence() {
 // rows of one slot and the delta mode: four.  What bounds the kernel is the latency of a tile's dependent phases, so what
 // counts is waves in flight and work per wave.  With one 16-lane group per row (all slots of all heads in one lane) a wave
 // needed 240 registers, eight waves fitted a CU, and the time parameters and qt went through LDS once per entry; with
-// a group per slot it needs 111 - 128, sixteen fit, and the entry loop reads nothing from LDS but the ring
-// record.  Layer launches before and after: 100,000 nodes, d_edge 172, 197 -> 173 us; 1,000,000 nodes, d_edge 100,
+// a group per slot it needs 88 - 128, sixteen fit, and the entry loop reads nothing from LDS but the ring
+// record.  Layer launches by this alone: 100,000 nodes, d_edge 172, 197 -> 173 us; 1,000,000 nodes, d_edge 100,
 // 1,087 -> 971 and (query cache) 1,054 -> 1,012; 1,300,000 nodes, raw edge rows, k = 20, 1,053 -> 973; four
 // heads of 32, 20,000 nodes, 110 -> 75; 10,000 nodes, one tile per workgroup, 33 -> 31.
 __host__ __device__ constexpr int layer_waves(int ks, bool delta) { return delta || ks == 1 ? 4 : 8; }
@@ -204,9 +202,6 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   constexpr int RPP = 4 / GPR;                // rows a wave works on at a time there
   constexpr int PASSES = RPW / RPP;
   __shared__ uint32_t s_node[2][kTM], s_sum[NW];
-  // the rows' scales (split16.h): of the input rows, of q, of pb per head, of the output rows, and of the head outputs
-  // (these held twice, by tile parity: a wave may be at the next tile's while another still reads this one's)
-  __shared__ __align__(16) float s_sx[kTM], s_sq[kTM], s_sz[H][kTM], s_sh[kTM], s_so[2][kTM];
   __shared__ __align__(16) double s_om[NT * kSlot], s_ph[NT * kSlot];
   static_assert(KS % H == 0, "whole slots per head");
   static_assert(!(DELTA && ES), "the delta mode keeps projected edge rows");
@@ -227,14 +222,14 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   // wave index, made provably uniform so that tile indices and weight addresses stay in scalar registers
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const uint32_t k = a.k, dk = a.dk;
-  const uint32_t c_in = chunks64(a.d_in), c_de = chunks64(a.d_emb);                                       // chunks of K
+  const uint32_t c_in = chunks_of(a.d_in), c_de = chunks_of(a.d_emb);                                     // chunks of K
   const uint32_t ntd = round_up(a.d_emb, 16) >> 4, ntk = round_up(dk, 16) >> 4;                           // column tiles
   constexpr uint32_t ntz = Ztp >> 4;                                                                       // tiles of a qt vector
   const uint32_t nzt_t = (a.d_time + 15u) >> 4, nzt = nzt_t + (ES ? (a.d_edge + 15u) >> 4 : 0u);           // ... that hold valid columns
   const LayerLds ll = layer_lds(a.d_in, H, KS, NZ, k, DELTA);
-  float* Xs = lds;                            // input rows, split (phase 1), then the cached-value part of the head outputs (phases 3-4)
-  float* Qs = lds + ll.off_q;                 // q, split (phases 1-3), then the head outputs, split (phases 4-5)
-  float* Zs = lds + ll.off_z;                 // qt (phases 2-3), then pb, split (phases 3-4), then the output rows (phases 5-6)
+  float* Xs = lds;                            // input rows (phase 1), then the cached-value part of the head outputs (phases 3-4)
+  float* Qs = lds + ll.off_q;                 // q (phases 1-3), then the head outputs (phases 4-5)
+  float* Zs = lds + ll.off_z;                 // qt (phases 2-3), then pb (phases 3-4), then the output rows (phases 5-6)
   RingEntry* Rs = reinterpret_cast<RingEntry*>(__builtin_assume_aligned(lds + ll.off_r, 16));   // [row][j], j = 0 the most recent entry
   using ZBuf = GatherBuf<JC, ES>;
 
@@ -285,25 +280,18 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     return u;
   };
   auto wkt = [&](uint32_t h, uint32_t t) { return a.WKT + (size_t)(h * ntz + t) * SH * kChunkFloats; };
-  auto request2 = [&](const Unit2& u, OpsS<NTL>& o) {
-    load_b64(wkt(u.h, u.t0), 0, o.b[0], lane);
-    if constexpr (NTL == 2) load_b64(wkt(u.h, u.t1), 0, o.b[1], lane);
+  auto request2 = [&](const Unit2& u, Ops16<NTL>& o) {
+    load_b16(wkt(u.h, u.t0), 0, o.b[0], lane);
+    if constexpr (NTL == 2) load_b16(wkt(u.h, u.t1), 0, o.b[1], lane);
   };
-  // four rows' factors that take a product back to scale: the matrix's inverse scale and the rows'
-  auto unscale = [&](const float* rows_s, float inv_w, float (&f)[4]) {
-    const float4 v = *reinterpret_cast<const float4*>(rows_s + s16_row(lane, 0));
-    f[0] = inv_pow2(v.x) * inv_w; f[1] = inv_pow2(v.y) * inv_w; f[2] = inv_pow2(v.z) * inv_w; f[3] = inv_pow2(v.w) * inv_w;
-  };
-  auto store2 = [&](const Unit2& u, const AccS<NTL>& acc, float iKT) {
-    float* zp = Zs + u.h * Ztp + s16_row(lane, 0) * ll.ldz + s16_col(lane);
-    float f[4];
-    unscale(s_sq, iKT, f);
+  auto store2 = [&](const Unit2& u, const floatx4 (&acc)[NTL]) {
+    float* zp = Zs + u.h * Ztp + m16_row(lane, 0) * ll.ldz + m16_col(lane);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) zp[u.t0 * 16 + r * ll.ldz] = acc_value(acc, 0, r) * f[r];
+    for (int r = 0; r < 4; ++r) zp[u.t0 * 16 + r * ll.ldz] = acc[0][r];
     if constexpr (NTL == 2) {
       if (u.two) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) zp[u.t1 * 16 + r * ll.ldz] = acc_value(acc, 1, r) * f[r];
+        for (int r = 0; r < 4; ++r) zp[u.t1 * 16 + r * ll.ldz] = acc[1][r];
       }
     }
   };
@@ -326,7 +314,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   // needed); and where q and qt are read back, they and the first gather are requested right behind it, so that phase 5
   // hides them.  All but a workgroup's first tile start without waiting for memory.  Shapes whose share does not
   // fit the registers fetch it inside `commit` instead.
-  const uint32_t qpr = round_up(a.d_in, 16u) >> 2;          // 16-byte quads per staged input row
+  const uint32_t qpr = round_up(a.d_in, kGrpK) >> 2;          // 16-byte quads per staged input row
   const bool pf_ok = QCACHE || (kTM * k <= 512u && kTM * qpr <= 512u);   // (the query cache is kept for such shapes only)
   RingEntry p_ring[NI];
   uint32_t p_deg = 0;
@@ -374,42 +362,21 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   // the staged tile's rows: id, entry count and query time of this lane's row
   uint32_t node_s = 0xFFFFFFFFu, cnt_s = 0u;
   double tq_s = 0.0;
-  // Input rows into Xs, split, each row under the scale of its largest magnitude; q's scale follows from a bound.  Columns up to
-  // the end of the last chunk are written (zero past d_in): what else lies there need not be a number.
-  const uint32_t qpz = min(16u * c_in, (ll.ldx - 4u) >> 2);
-  auto row_max = [&](float m) {                               // over the lanes that stage a row (LS = 16 or 32)
-    m = row16_max(m);
-    if constexpr (LS == 32u) { const Two w = both_of_pair(m); m = bits_max(w.lo, w.hi); }
-    return m;
-  };
-  auto row_scales = [&](float m) {
-    const ArgBlock ab = args();
-    const float bQ = ab->sp.bQ, bcQ = ab->sp.bcQ;
-    m = row_max(m);
-    const uint32_t local = wave * RPW + lane / LS;
-    const float sx = pow2_scale(m);
-    if (lane % LS == 0u) { s_sx[local] = sx; s_sq[local] = pow2_scale(fmaf(m, bQ, bcQ)); }
-    return sx;
-  };
-  auto place_x = [&](uint32_t q, float4 v, float sx) {
+  // Input rows into Xs.  Columns up to the end of the last chunk are written (zero past d_in): what else lies there need
+  // not be a number.
+  const uint32_t qpz = min(kChunkK / 4u * c_in, (ll.ldx - 4u) >> 2);
+  auto place_x = [&](uint32_t q, float4 v) {
     if (q >= qpr || node_s == 0xFFFFFFFFu) v = make_float4(0.f, 0.f, 0.f, 0.f);
-    split_store4(Xs + (wave * RPW + lane / LS) * ll.ldx, 4u * q, v, sx);
+    *reinterpret_cast<float4*>(Xs + (wave * RPW + lane / LS) * ll.ldx + 4u * q) = v;
   };
   auto commit_x = [&](bool staged) {
     const uint32_t it = lane % LS;
     if (staged) {
-      float m = 0.0f;
 #pragma unroll
-      for (int e = 0; e < NI; ++e) m = fmaxf(m, it + LS * e < qpr ? max4(p_x[e]) : 0.0f);
-      const float sx = row_scales(m);
-#pragma unroll
-      for (int e = 0; e < NI; ++e) if (it + LS * e < qpz) place_x(it + LS * e, p_x[e], sx);
+      for (int e = 0; e < NI; ++e) if (it + LS * e < qpz) place_x(it + LS * e, p_x[e]);
     } else {
       const float* xr = a.Hin + (size_t)(node_s != 0xFFFFFFFFu ? node_s : 0u) * a.ld_in;
-      float m = 0.0f;
-      for (uint32_t q = it; q < qpr; q += LS) m = fmaxf(m, max4(*reinterpret_cast<const float4*>(xr + 4u * q)));
-      const float sx = row_scales(m);
-      for (uint32_t q = it; q < qpz; q += LS) place_x(q, *reinterpret_cast<const float4*>(xr + 4u * (q < qpr ? q : 0u)), sx);
+      for (uint32_t q = it; q < qpz; q += LS) place_x(q, *reinterpret_cast<const float4*>(xr + 4u * (q < qpr ? q : 0u)));
     }
   };
   auto commit = [&](uint32_t round) {
@@ -519,10 +486,10 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   // Weights of phases 1 and 2: the first units' chunks, requested together.
   const uint32_t w1 = wave < ntd ? wave : 0u;                // loads are unconditional (clamped), products are not
   constexpr int C1 = KS == 1 && !DELTA ? 1 : 2;               // chunks of W_Q requested up front
-  Upfront<NTL, C1> u1;
+  Upfront16<NTL, C1> u1;
   float c1v[NTL];                                             // this lane's c_Q of the first unit
   constexpr int U2 = SH == 1 ? 2 : 1;                         // phase 2's units requested up front
-  OpsS<NTL> o2[U2];
+  Ops16<NTL> o2[U2];
   auto request12 = [&]() {
     const float* const wq = args()->WQ;
     const float* B1[NTL];
@@ -530,7 +497,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     for (int t = 0; t < NTL; ++t) B1[t] = tile_b(wq, w1, t, ntd, c_in);
     u1.request(B1, c_in, lane);
 #pragma unroll
-    for (int t = 0; t < NTL; ++t) { const uint32_t col = (w1 + NW * t) * 16 + s16_col(lane); c1v[t] = a.cQ[col < a.d_emb ? col : 0u]; }
+    for (int t = 0; t < NTL; ++t) { const uint32_t col = (w1 + NW * t) * 16 + m16_col(lane); c1v[t] = a.cQ[col < a.d_emb ? col : 0u]; }
 #pragma unroll
     for (int i = 0; i < U2; ++i) request2(decode2((uint32_t)i < nu2 ? i : 0u), o2[i]);   // (an idle wave: head 0, tile 0)
   };
@@ -541,7 +508,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   commit(0u);
   commit_x(pf_ok);
   derive_slot();
-  if constexpr (QCACHE) request_back(kPass0); else request12();
+  if constexpr (QCACHE) request_back(kPass0);
   __syncthreads();
 
   // What separates a tile's uses of the LDS from the next tile's.  Ring records: a wave reads only its own rows'.  Xs holds the
@@ -561,7 +528,6 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     derive_lane();
     derive_slot();
     const uint32_t* nodes_s = s_node[round & 1u];
-    const uint32_t par = round & 1u;
     const uint32_t local_s = wave * RPW + lane / LS;
     const bool live_s = node_s != 0xFFFFFFFFu;
     bool ex = false;
@@ -577,28 +543,23 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     } else {
     // ================================================================ phase 1: q = x W_Q + c_Q
     if constexpr (QCACHE) describe2();                        // (one register less through the other tiles)
-    if constexpr (QCACHE) request12();                        // (otherwise requested ahead of the previous tile's stores)
+    request12();
     stage_a(next_tile);
     if (!kRowsInZ && rows_in_lds && round) {                  // (the previous tile had its output rows where the input rows go)
       __syncthreads();
       commit_x(false);
     }
     __syncthreads();                                          // input rows there, the previous tile's head outputs read
-    const float iQ = args()->sp.iQ;
-    auto store1 = [&](uint32_t nt, const AccS<NTL>& acc) {
-      float f[4];
-      unscale(s_sx, iQ, f);
-      const float4 sq = *reinterpret_cast<const float4*>(s_sq + s16_row(lane, 0));
-      const float sqv[4] = {sq.x, sq.y, sq.z, sq.w};
+    auto store1 = [&](uint32_t nt, const floatx4 (&acc)[NTL]) {
 #pragma unroll
       for (int t = 0; t < NTL; ++t) {
-        const uint32_t col = (nt + NW * t) * 16 + s16_col(lane);
+        const uint32_t col = (nt + NW * t) * 16 + m16_col(lane);
         if (nt + NW * t < ntd && col < a.d_emb) {
           const float cq = nt == wave ? c1v[t] : a.cQ[col];
           const uint32_t h = H == 1 ? 0u : H == 2 ? (col >= dk ? 1u : 0u) : (col >= dk ? 1u : 0u) + (col >= 2u * dk ? 1u : 0u) + (col >= 3u * dk ? 1u : 0u);
+          float* qp = Qs + m16_row(lane, 0) * ll.ldq + h * (SH * kSlot) + (col - h * dk);
 #pragma unroll
-          for (int r = 0; r < 4; ++r)
-            split_store1(Qs + s16_row(lane, r) * ll.ldq, h * (SH * kSlot) + (col - h * dk), fmaf(acc_value(acc, t, r), f[r], cq), sqv[r]);
+          for (int r = 0; r < 4; ++r) qp[r * ll.ldq] = acc[t][r] + cq;
         }
       }
     };
@@ -606,36 +567,35 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
       const float* B1[NTL];
 #pragma unroll
       for (int t = 0; t < NTL; ++t) B1[t] = tile_b(a.WQ, w1, t, ntd, c_in);
-      AccS<NTL> acc;
-      u1.multiply(Xs + s16_off(lane, ll.ldx), c_in, B1, acc, lane);
+      floatx4 acc[NTL] = {};
+      u1.multiply(Xs + a16_off(lane, ll.ldx), c_in, B1, acc, lane);
       store1(wave, acc);
     }
     for (uint32_t nt = wave + 8; nt < ntd; nt += 8) {
       const float* Bt[NTL];
 #pragma unroll
       for (int t = 0; t < NTL; ++t) Bt[t] = tile_b(a.WQ, nt, t, ntd, c_in);
-      AccS<NTL> acc;
-      mfma_lean<NTL>(Xs + s16_off(lane, ll.ldx), 0u, c_in, Bt, acc, lane);
+      floatx4 acc[NTL] = {};
+      mfma16_lean<NTL>(Xs + a16_off(lane, ll.ldx), 0u, c_in, Bt, acc, lane);
       store1(nt, acc);
     }
     __syncthreads();
     // ================================================================ phase 2: qt_h = q_h W_K,h[time]^T
     {
-      const float* qa = Qs + s16_off(lane, ll.ldq);
-      const float iKT = args()->sp.iKT;
-      auto products2 = [&](uint32_t i, OpsS<NTL>& o) {
+      const float* qa = Qs + a16_off(lane, ll.ldq);
+      auto products2 = [&](uint32_t i, Ops16<NTL>& o) {
         const Unit2 u = decode2(i);
-        AccS<NTL> acc;
+        floatx4 acc[NTL] = {};
         const float* qh = qa + u.h * (SH * kSlot);
-        load_a64(qh, 0, o.a);
-        mfma_chunk<NTL>(o.a, o.b, acc);
+        load_a16(qh, 0, o.a);
+        mfma16_chunk<NTL>(o, acc);
         if constexpr (SH > 1) {
           const float* Bt[NTL];
           Bt[0] = wkt(u.h, u.t0);
           if constexpr (NTL == 2) Bt[1] = wkt(u.h, u.t1);
-          mfma_lean<NTL>(qh, 1u, SH, Bt, acc, lane);
+          mfma16_lean<NTL>(qh, 1u, SH, Bt, acc, lane);
         }
-        store2(u, acc, iKT);
+        store2(u, acc);
       };
       if constexpr (U2 == 2) {
         for (uint32_t i = 0; i < nu2; i += 2) {
@@ -672,7 +632,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
         static_for<PASSES>([&](auto P) {
           constexpr int p = decltype(P)::value;
           const uint32_t node = node_of(p), local = row_of(p);
-          qk[p] = split_load4(Qs + local * ll.ldq, kSlot * g + 4u * sub, inv_pow2(s_sq[local]));
+          qk[p] = *reinterpret_cast<const float4*>(Qs + local * ll.ldq + kSlot * g + 4u * sub);
           float* qrow = a.QC + (size_t)node * kQC + 4u * sub;
           const bool keep = !ROOTS && a.QC && node != 0xFFFFFFFFu;             // the rows' q | qt for later batches
           if (keep) *reinterpret_cast<float4*>(qrow + kSlot * g) = qk[p];
@@ -687,13 +647,6 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
       }
     }
     // ================================================================ phase 3: gather + attention
-    // scales of the head outputs and of the output rows, from bounds: the largest cached-value part plus what pb can add
-    auto output_scales = [&](uint32_t local, float m_o, float m_z, bool writer) {
-      const ArgBlock ab = args();
-      const float bV = ab->sp.bV, bO = ab->sp.bO, bbO = ab->sp.bbO;
-      const float bo = fmaf(m_z, bV, m_o);
-      if (writer) { s_so[par][local] = pow2_scale(bo); s_sh[local] = pow2_scale(fmaf(bo, bO, bbO)); }
-    };
     if constexpr (DELTA) {
       // ---- delta mode.  An exact row runs the same online softmax as the exact mode and leaves its attention
       // cache behind: per entry score, weight and the neighbour|edge part of the value, per row the sums S and
@@ -729,7 +682,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
       }
       float4 qk[KS];
 #pragma unroll
-      for (int s = 0; s < KS; ++s) qk[s] = split_load4(Qs + local * ll.ldq, s * kSlot + 4u * sub, inv_pow2(s_sq[local]));
+      for (int s = 0; s < KS; ++s) qk[s] = *reinterpret_cast<const float4*>(Qs + local * ll.ldq + s * kSlot + 4u * sub);
       float* zq = Zs + local * ll.ldz + 4u * sub;
 #pragma unroll
       for (int h = 0; h < H; ++h) {
@@ -872,7 +825,6 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
       }
       // ---- the row's sums: normalised by the denominator after an exact recomputation, as they stand after a delta update
       wave_lds_fence();
-      float m_o = 0.0f, m_z = 0.0f;                           // largest head output of the row (cached part), largest pb of any head
 #pragma unroll
       for (int h = 0; h < H; ++h) {
         const float inv = ex ? reciprocal(lrun[h]) : 1.0f;
@@ -881,24 +833,16 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
           float4 o = accv[s];
           o.x *= inv; o.y *= inv; o.z *= inv; o.w *= inv;
           *reinterpret_cast<float4*>(Xs + local * ll.ldx + s * kSlot + 4u * sub) = o;
-          m_o = fmaxf(m_o, max4(o));
           if (live) *reinterpret_cast<float4*>(acS + s * kSlot) = o;
         }
-        float mz = 0.0f;
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-          float4& o = accp[h][t];
+          float4 o = accp[h][t];
           o.x *= inv; o.y *= inv; o.z *= inv; o.w *= inv;
           if (t == NT - 1) clear_past_d_time(o, t);
-          mz = fmaxf(mz, max4(o));
+          *reinterpret_cast<float4*>(zq + h * Ztp + t * kSlot) = o;
           if (live) *reinterpret_cast<float4*>(acP + (h * NT + t) * kSlot) = o;
         }
-        mz = row_max(mz);
-        m_z = fmaxf(m_z, mz);
-        const float sz = pow2_scale(mz);
-        if (sub == 0) s_sz[h][local] = sz;
-#pragma unroll
-        for (int t = 0; t < NT; ++t) split_store4(Zs + local * ll.ldz, h * Ztp + t * kSlot + 4u * sub, accp[h][t], sz);
         if (live && sub == 0) { acZM[2 * h] = lrun[h]; acZM[2 * h + 1] = mref[h]; }
         if (ex && live)
           for (uint32_t j = sub; j < cnt; j += 16) {          // the weights in effect after the exact recomputation
@@ -908,7 +852,6 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
             w[2 * h + 1] = lrun[h] > 0.0f ? __expf(sj - mref[h]) * inv : 0.0f;
           }
       }
-      output_scales(local, row_max(m_o), m_z, sub == 0);
       // ---- drift estimator (Sec. 3.5), final layer: an exact recomputation restarts the node's estimate, a
       // delta update adds the changed fraction of its entries to the decayed estimate
       // (the changes of the sum and of the member count are collected per wave and added once, at the end of
@@ -1037,33 +980,18 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
       };
       if (nchunk3) pingpong_clamped<ZBuf>(nchunk3, z0[p], [&](uint32_t c, ZBuf& zb) { gather(p, c, zb); }, attend);
       // the cached-value part of the head outputs goes into Xs (padded-head layout; the padding lanes hold exact
-      // zeros), pb, split, where qt is (each lane owns its columns)
-      wave_lds_fence();                                       // (a lane's split columns share their bytes with its neighbour's qt)
+      // zeros), pb where qt is (each lane owns its columns)
       const float inv = reciprocal(lrun);                     // no entry, or none inside the window: b_O alone
       accv.x *= inv; accv.y *= inv; accv.z *= inv; accv.w *= inv;
       *reinterpret_cast<float4*>(Xs + local * ll.ldx + kSlot * g + 4u * sub) = accv;
-      float m_o = row16_max(max4(accv)), m_z = 0.0f;
 #pragma unroll
       for (int i = 0; i < NZL; ++i) {
         const uint32_t t = SH == 1 ? (uint32_t)i : sg + SH * i;
-        float4& o = accp[i];
+        float4 o = accp[i];
         o.x *= inv; o.y *= inv; o.z *= inv; o.w *= inv;
         if (SH > 1 || i == NT - 1) clear_past_d_time(o, t);    // (a raw edge row's padding is zero, and so are its sums)
-        m_z = fmaxf(m_z, max4(o));
+        if (t < NZ) *reinterpret_cast<float4*>(Zs + local * ll.ldz + head * Ztp + t * kSlot + 4u * sub) = o;
       }
-      m_z = row16_max(m_z);
-      if constexpr (SH >= 2) { const Two w = both_of_pair(m_z); m_z = bits_max(w.lo, w.hi); }
-      if constexpr (SH == 4) { const Two w = both_halves(m_z); m_z = bits_max(w.lo, w.hi); }
-      const float sz = pow2_scale(m_z);                       // of the head's pb
-      if (sub == 0u && sg == 0u) s_sz[head][local] = sz;
-#pragma unroll
-      for (int i = 0; i < NZL; ++i) {
-        const uint32_t t = SH == 1 ? (uint32_t)i : sg + SH * i;
-        if (t < NZ) split_store4(Zs + local * ll.ldz, head * Ztp + t * kSlot + 4u * sub, accp[i], sz);
-      }
-      if constexpr (KS >= 2) { const Two w = both_of_pair(m_o), v = both_of_pair(m_z); m_o = bits_max(w.lo, w.hi); m_z = bits_max(v.lo, v.hi); }
-      if constexpr (KS == 4) { const Two w = both_halves(m_o), v = both_halves(m_z); m_o = bits_max(w.lo, w.hi); m_z = bits_max(v.lo, v.hi); }
-      output_scales(local, m_o, m_z, sub == 0u && g == 0u);
       });
     }
     // ================================================================ phase 4: o_h += pb_h W_V,h[time | raw edge]
@@ -1072,7 +1000,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     derive_lane();
     auto wv = [&](uint32_t h, uint32_t nt) { return a.WV + (size_t)(h * ntk + nt) * NZ * kChunkFloats; };
     uint32_t x4 = wave < nunits4 ? wave : nunits4 - 1u;
-    Upfront<N4, NZ> u4;
+    Upfront16<N4, NZ> u4;
     const float* B4[N4];
     auto head4 = [&]() { return H == 1 ? 0u : H == 2 ? (x4 >= np4 ? 1u : 0u) : (x4 >= np4 ? 1u : 0u) + (x4 >= 2u * np4 ? 1u : 0u) + (x4 >= 3u * np4 ? 1u : 0u); };
     auto request4 = [&]() {
@@ -1082,7 +1010,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
       u4.request(B4, NZ, lane);
     };
     constexpr int U5 = NTL == 1 ? (KS < 2 ? KS : 2) : KS <= 2 ? KS : 1;   // chunks of W_O requested up front
-    Upfront<NTL, U5> u5;
+    Upfront16<NTL, U5> u5;
     const float* B5[NTL];
 #pragma unroll
     for (int t = 0; t < NTL; ++t) B5[t] = tile_b(a.WO, w1, t, ntd, KS);
@@ -1090,30 +1018,25 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     auto request5 = [&]() {
       u5.request(B5, KS, lane);
 #pragma unroll
-      for (int t = 0; t < NTL; ++t) { const uint32_t col = (w1 + NW * t) * 16 + s16_col(lane); b5v[t] = a.bO[col < a.d_emb ? col : 0u]; }
+      for (int t = 0; t < NTL; ++t) { const uint32_t col = (w1 + NW * t) * 16 + m16_col(lane); b5v[t] = a.bO[col < a.d_emb ? col : 0u]; }
     };
     request4();
     stage_b(next_tile);
     __syncthreads();
-    const float iV = args()->sp.iV;
     if (wave < nunits4) {
-      const float4 so = *reinterpret_cast<const float4*>(s_so[par] + s16_row(lane, 0));
-      const float sov[4] = {so.x, so.y, so.z, so.w};
       for (;;) {
         const uint32_t h4 = head4(), n0 = N4 * (x4 - h4 * np4);
-        AccS<N4> acc;
-        u4.multiply(Zs + h4 * Ztp + s16_off(lane, ll.ldz), NZ, B4, acc, lane);
-        float f[4];
-        unscale(s_sz[h4], iV, f);
+        floatx4 acc[N4] = {};
+        u4.multiply(Zs + h4 * Ztp + a16_off(lane, ll.ldz), NZ, B4, acc, lane);
 #pragma unroll
         for (int t = 0; t < N4; ++t) {
-          const uint32_t col = (n0 + t) * 16 + s16_col(lane);
+          const uint32_t col = (n0 + t) * 16 + m16_col(lane);
           if (n0 + t < ntk && col < dk) {
             const uint32_t at = h4 * (SH * kSlot) + col;      // one lane per (row, column)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-              const uint32_t row = s16_row(lane, r);
-              split_store1(Qs + row * ll.ldq, at, fmaf(acc_value(acc, t, r), f[r], Xs[row * ll.ldx + at]), sov[r]);
+              const uint32_t row = m16_row(lane, r);
+              Qs[row * ll.ldq + at] = Xs[row * ll.ldx + at] + acc[t][r];
             }
           }
         }
@@ -1133,23 +1056,15 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     }
     // a load behind a store waits for it: the first units' results stay in registers until everything that the following
     // phases read has been requested
-    const float iO = args()->sp.iO;
-    auto bias5 = [&](uint32_t nt, const AccS<NTL>& acc, floatx4 (&o)[NTL]) {
-      float f[4];
-      unscale(s_so[par], iO, f);
-      const float4 sh = *reinterpret_cast<const float4*>(s_sh + s16_row(lane, 0));
-      const float shv[4] = {sh.x, sh.y, sh.z, sh.w};
+    auto bias5 = [&](uint32_t nt, const floatx4 (&acc)[NTL], floatx4 (&o)[NTL]) {
 #pragma unroll
       for (int t = 0; t < NTL; ++t) {
-        const uint32_t col = (nt + NW * t) * 16 + s16_col(lane);
+        const uint32_t col = (nt + NW * t) * 16 + m16_col(lane);
         const float b = nt == wave ? b5v[t] : a.bO[col < a.d_emb ? col : 0u];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          o[t][r] = fmaf(acc_value(acc, t, r), f[r], b);
-          if (rows_in_lds && nt + NW * t < ntd && col < a.d_emb) {          // for the link scores; operand of phase 6
-            if constexpr (ROOTS) Hs[s16_row(lane, r) * ldh + col] = o[t][r];
-            else split_store1(Hs + s16_row(lane, r) * ldh, col, o[t][r], shv[r]);
-          }
+          o[t][r] = acc[t][r] + b;
+          if (rows_in_lds && nt + NW * t < ntd && col < a.d_emb) Hs[m16_row(lane, r) * ldh + col] = o[t][r];   // for the link scores; operand of phase 6
         }
       }
     };
@@ -1158,11 +1073,11 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
         float* const hout = args()->Hout;
 #pragma unroll
         for (int t = 0; t < NTL; ++t) {
-          const uint32_t col = (nt + NW * t) * 16 + s16_col(lane);
+          const uint32_t col = (nt + NW * t) * 16 + m16_col(lane);
           if (nt + NW * t < ntd && col < a.d_emb) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-              const uint32_t node = nodes_s[s16_row(lane, r)];
+              const uint32_t node = nodes_s[m16_row(lane, r)];
               if (node != 0xFFFFFFFFu) hout[(size_t)node * a.ld_out + col] = acc[t][r];
             }
           }
@@ -1171,23 +1086,22 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     };
     floatx4 out5[NTL] = {};
     if (wave < ntd) {
-      AccS<NTL> acc;
-      u5.multiply(Qs + s16_off(lane, ll.ldq), KS, B5, acc, lane);
+      floatx4 acc[NTL] = {};
+      u5.multiply(Qs + a16_off(lane, ll.ldq), KS, B5, acc, lane);
       bias5(wave, acc, out5);
     }
     for (uint32_t nt = wave + 8; nt < ntd; nt += 8) {
       const float* Bt[NTL];
 #pragma unroll
       for (int t = 0; t < NTL; ++t) Bt[t] = tile_b(a.WO, nt, t, ntd, KS);
-      AccS<NTL> acc;
-      floatx4 o[NTL];
-      mfma_lean<NTL>(Qs + s16_off(lane, ll.ldq), 0u, KS, Bt, acc, lane);
+      floatx4 acc[NTL] = {}, o[NTL];
+      mfma16_lean<NTL>(Qs + a16_off(lane, ll.ldq), 0u, KS, Bt, acc, lane);
       bias5(nt, acc, o);
       store5(nt, o);
     }
     if (!kRowsInZ && kv) {                                    // (Xs: what lies past the output row need not be a number)
       const uint32_t w = 64u * c_de - a.d_emb;
-      for (uint32_t x = threadIdx.x; x < kTM * w; x += TH) split_store1(Xs + (x / w) * ll.ldx, a.d_emb + x % w, 0.0f, 1.0f);
+      for (uint32_t x = threadIdx.x; x < kTM * w; x += TH) Xs[(x / w) * ll.ldx + a.d_emb + x % w] = 0.0f;
     }
     if constexpr (ROOTS) {
       // link scores: a wave takes edges w and on of the tile (the list holds whole edges)
@@ -1209,61 +1123,50 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     constexpr uint32_t ntkv = 8u * KS;
     auto store6 = [&](uint32_t nt, const floatx4& acc) {
       float* const kvout = args()->KVout;
-      const uint32_t col = nt * 16 + s16_col(lane);           // every column is written: padding columns get exact zeros
+      const uint32_t col = nt * 16 + m16_col(lane);           // every column is written: padding columns get exact zeros
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const uint32_t node = nodes_s[s16_row(lane, r)];
+        const uint32_t node = nodes_s[m16_row(lane, r)];
         if (node != 0xFFFFFFFFu) kvout[(size_t)node * (2u * kSlot * KS) + col] = acc[r];
       }
     };
-    floatx4 out6[2] = {};
+    floatx4 out6[2][1] = {};
     if (kv) {
       const float* const wkv0 = args()->WKVnext;
       auto wkv = [&](uint32_t nt) { return wkv0 + (size_t)nt * c_de * kChunkFloats; };
-      const float* Ha = Hs + s16_off(lane, ldh);
+      const float* Ha = Hs + a16_off(lane, ldh);
       const uint32_t c1 = c_de > 1 ? 1u : 0u;
-      float4 b6[2][1][4];
-      load_b64(wkv(wave), 0, b6[0][0], lane);
-      load_b64(wkv(wave), c1, b6[1][0], lane);
+      float4 b6[2][1][kCG];
+      load_b16(wkv(wave), 0, b6[0][0], lane);
+      load_b16(wkv(wave), c1 * kCG, b6[1][0], lane);
       __syncthreads();
-      float f[4];
-      unscale(s_sh, args()->iKVnext, f);
-      AccS<1> acc[2];
-      auto chunk6 = [&](uint32_t ch, const float4 (&b)[1][4], AccS<1>& ac) {
-        float4 x[4];
-        load_a64(Ha, ch, x);
-        mfma_chunk<1>(x, b, ac);
+      auto chunk6 = [&](uint32_t ch, const float4 (&b)[1][kCG], floatx4 (&acc)[1]) {
+        float4 x[kCG];
+        load_a16(Ha, ch * kCG, x);
+        mfma16_chunk<1>(x, b, acc);
       };
-      auto value6 = [&](const AccS<1>& ac) {
-        floatx4 v;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = acc_value(ac, 0, r) * f[r];
-        return v;
-      };
-      chunk6(0, b6[0], acc[0]);
-      load_b64(wkv(wave + NW), 0, b6[0][0], lane);
-      if (c1) chunk6(1, b6[1], acc[0]);
-      load_b64(wkv(wave + NW), c1, b6[1][0], lane);
-      chunk6(0, b6[0], acc[1]);
-      if (c1) chunk6(1, b6[1], acc[1]);
+      chunk6(0, b6[0], out6[0]);
+      load_b16(wkv(wave + NW), 0, b6[0][0], lane);
+      if (c1) chunk6(1, b6[1], out6[0]);
+      load_b16(wkv(wave + NW), c1 * kCG, b6[1][0], lane);
+      chunk6(0, b6[0], out6[1]);
+      if (c1) chunk6(1, b6[1], out6[1]);
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         const float* const Bt[1] = {wkv(wave + NW * t)};
-        mfma_lean<1>(Ha, 2u, c_de, Bt, acc[t], lane);
-        out6[t] = value6(acc[t]);
+        mfma16_lean<1>(Ha, 2u, c_de, Bt, out6[t], lane);
       }
       for (uint32_t nt = wave + 2 * NW; nt < ntkv; nt += NW) {
         const float* const Bt[1] = {wkv(nt)};
-        AccS<1> ac;
-        mfma_lean<1>(Ha, 0u, c_de, Bt, ac, lane);
-        store6(nt, value6(ac));
+        floatx4 acc[1] = {};
+        mfma16_lean<1>(Ha, 0u, c_de, Bt, acc, lane);
+        store6(nt, acc[0]);
       }
     }
-    if constexpr (!QCACHE) request12();                       // the next tile's
     if (wave < ntd) store5(wave, out5);
     if (kv) {
-      store6(wave, out6[0]);
-      store6(wave + NW, out6[1]);
+      store6(wave, out6[0][0]);
+      store6(wave + NW, out6[1][0]);
     }
     if (QCACHE && rows_in_lds) __syncthreads();
   };

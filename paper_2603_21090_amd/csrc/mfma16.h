@@ -26,6 +26,8 @@ constexpr uint32_t kGrpK = 16;            // elements of K per group
 constexpr uint32_t kGrpFloats = 256;      // floats of one (column tile, group) block of packed B
 constexpr int kCG = 4;                    // groups per chunk
 constexpr uint32_t kChunkSteps = 4 * kCG; // k-steps per chunk
+constexpr uint32_t kChunkK = kGrpK * kCG; // elements of K per chunk
+constexpr uint32_t kChunkFloats = kGrpFloats * kCG;   // floats of one (column tile, chunk) block of packed B
 
 // number of groups that cover K elements, rounded up to whole chunks
 __host__ __device__ inline uint32_t chunks_of(uint32_t K) { return (K + kGrpK * kCG - 1) / (kGrpK * kCG); }
@@ -38,6 +40,7 @@ __device__ inline uint32_t m16_row(uint32_t lane, uint32_t r) { return 4u * (lan
 __device__ inline uint32_t m16_col(uint32_t lane) { return lane & 15u; }
 
 // per-lane element offset into an A tile in LDS with stride lda
+__device__ inline uint32_t a16_off(uint32_t lane, uint32_t lda) { return (lane & 15u) * lda + 4u * (lane >> 4); }
 __device__ inline uint32_t a16_lane_off(uint32_t lda) {
   const uint32_t lane = threadIdx.x & 63u;
   return (lane & 15u) * lda + 4u * (lane >> 4);
@@ -58,11 +61,18 @@ __device__ inline void load_a16(const float* Ap, uint32_t g0, float4 (&a)[kCG]) 
   for (int c = 0; c < kCG; ++c) a[c] = *reinterpret_cast<const float4*>(Ap + kGrpK * (g0 + c));
 }
 
-// B operands of groups [g0, g0 + kCG) of the column tile whose group 0 is Bt (wave-uniform).
-__device__ inline void load_b16(const float* __restrict__ Bt, uint32_t g0, float4 (&b)[kCG]) {
-  const float4* p = reinterpret_cast<const float4*>(Bt) + (size_t)g0 * 64u + (threadIdx.x & 63u);
+// B operands of groups [g0, g0 + kCG) of the column tile whose group 0 is Bt (wave-uniform).  The lane is an argument so
+// that a caller with a long loop can pass an opaque copy of it: from threadIdx.x alone the compiler computes one 64-bit
+// address per lane and matrix ahead of the loop and keeps (or spills) them all; with it a load takes its matrix's address
+// from scalar registers and 16 lane as the offset.
+__device__ inline void load_b16(const float* __restrict__ Bt, uint32_t g0, float4 (&b)[kCG], uint32_t lane) {
+  const char* p = reinterpret_cast<const char*>(Bt) + (size_t)g0 * 1024u;
+  const uint32_t off = lane * 16u;
 #pragma unroll
-  for (int c = 0; c < kCG; ++c) b[c] = p[c * 64];
+  for (int c = 0; c < kCG; ++c) b[c] = *reinterpret_cast<const float4*>(p + c * 1024 + off);
+}
+__device__ inline void load_b16(const float* __restrict__ Bt, uint32_t g0, float4 (&b)[kCG]) {
+  load_b16(Bt, g0, b, threadIdx.x & 63u);
 }
 
 template <int U, int NTL>
@@ -173,6 +183,21 @@ __device__ __forceinline__ void mfma16_gemm(const float* Ap, uint32_t nchunks, c
   mfma16_gemm_pre<NTL>(Ap, nchunks, Bt, acc, P);
 }
 
+// Chunks [c0, c1) of a product with one buffer: for what a shape has beyond the products its kernel is tuned for, where the
+// registers of a second buffer would cost those.
+template <int NTL>
+__device__ __forceinline__ void mfma16_lean(const float* Ap, uint32_t c0, uint32_t c1, const float* const (&Bt)[NTL],
+                                            floatx4 (&acc)[NTL], uint32_t lane) {
+#pragma unroll 1
+  for (uint32_t ch = c0; ch < c1; ++ch) {
+    Ops16<NTL> o;
+#pragma unroll
+    for (int t = 0; t < NTL; ++t) load_b16(Bt[t], ch * kCG, o.b[t], lane);
+    load_a16(Ap, ch * kCG, o.a);
+    mfma16_chunk<NTL>(o, acc);
+  }
+}
+
 // All weight chunks of a short product at once: for K of at most MAXC chunks the whole B operand of
 // NTL column tiles is requested in one go (MAXC * NTL * 16 registers), typically ahead of the barrier
 // that completes A, and the products then run as the chunks arrive -- one memory latency per product
@@ -181,12 +206,13 @@ template <int NTL, int MAXC>
 struct Upfront16 {
   float4 b[MAXC][NTL][kCG];
   // requests are unconditional: chunks past the end repeat the last one and are never multiplied
-  __device__ __forceinline__ void request(const float* const (&Bt)[NTL], uint32_t nchunks) {
+  __device__ __forceinline__ void request(const float* const (&Bt)[NTL], uint32_t nchunks) { request(Bt, nchunks, threadIdx.x & 63u); }
+  __device__ __forceinline__ void request(const float* const (&Bt)[NTL], uint32_t nchunks, uint32_t lane) {
 #pragma unroll
     for (int ch = 0; ch < MAXC; ++ch) {
       const uint32_t c = (uint32_t)ch < nchunks ? (uint32_t)ch : nchunks - 1u;
 #pragma unroll
-      for (int t = 0; t < NTL; ++t) load_b16(Bt[t], c * kCG, b[ch][t]);
+      for (int t = 0; t < NTL; ++t) load_b16(Bt[t], c * kCG, b[ch][t], lane);
     }
   }
   __device__ __forceinline__ void multiply(const float* Ap, uint32_t nchunks, floatx4 (&acc)[NTL]) {
@@ -198,6 +224,12 @@ struct Upfront16 {
         mfma16_chunk<NTL>(a, b[ch], acc);
       }
     }
+  }
+  // the whole product, also where K has more chunks than were requested
+  __device__ __forceinline__ void multiply(const float* Ap, uint32_t nchunks, const float* const (&Bt)[NTL],
+                                           floatx4 (&acc)[NTL], uint32_t lane) {
+    multiply(Ap, nchunks, acc);
+    mfma16_lean<NTL>(Ap, MAXC, nchunks, Bt, acc, lane);
   }
 };
 

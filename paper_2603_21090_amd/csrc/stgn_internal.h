@@ -83,7 +83,7 @@ struct Table {
   uint32_t ld;
 };
 
-// Packed parameters of one attention layer (device pointers; matrices in the packing of split16.h).
+// Packed parameters of one attention layer (device pointers; matrices group-major, mfma16.h).
 //
 // Keys and values are linear in the attention input z_j = [h_{u_j} | e_j | phi(dt)], so they split by
 // input block (paper Eq. attn_detail):  K_j = h_{u_j} W_K[node rows] + e_j W_K[edge rows] + phi W_K[time rows].
@@ -105,17 +105,7 @@ struct Table {
 constexpr uint32_t kSlot = 64;
 constexpr uint32_t kMaxKeySlots = 4;     // ks
 constexpr uint32_t kMaxTimeSlots = 2;    // ceil(d_time / 64)
-// The layer kernel multiplies split operands (split16.h).  Per matrix the inverse of its power-of-two scale; and what a
-// row's largest magnitude can become in a product: the largest sum of magnitudes of a column, and of what is added to it.
-struct SplitParams {
-  float iQ, iKT, iV, iO;         // inverse scales of WQn, WKT, WV, WO
-  float bQ, bcQ;                 // |x W_Q + c_Q| <= bQ max|x| + bcQ
-  float bV;                      // |pb_h W_V,h| <= bV max|pb_h|
-  float bO, bbO;                 // |o W_O + b_O| <= bO max|o| + bbO
-};
 struct LayerDev {
-  SplitParams sp;
-  float iKVn, iKVe;              // inverse scales of WKVn and WKVe
   uint32_t d_in;                 // input width
   const float* WQn;              // [d_in x d_emb]            node block of W_Q / sqrt(dk)
   const float* cQ;               // [d_emb]                   phi(0) * (time block of W_Q) / sqrt(dk)

@@ -1,4 +1,5 @@
-"""The layer kernel's split products: scales that follow the operands, and workgroups that walk several tiles."""
+"""The layer kernel's operands at any common scale, workgroups that walk several tiles, and projected rows at the edges of
+their staging."""
 import numpy as np
 import pytest
 
@@ -35,8 +36,7 @@ def _rescaled(w, W, s):
 @pytest.mark.parametrize("kw", [dict(d_edge=6, heads=2, d_emb=100, d_time=100), dict(d_edge=70, heads=4, d_emb=64, d_time=30),
                                 dict(d_edge=0, heads=1, d_emb=130, d_time=70)])
 def test_powers_of_two_change_nothing(binding, kw, e):
-    """Every scale is a power of two taken from the operands themselves, so a model rescaled by one gives the same bits,
-    rescaled: exact, no tolerance."""
+    """A model rescaled by a power of two gives the same bits, rescaled: exact, no tolerance."""
     w = tiny_workload(num_nodes=300, num_edges=2400, batch=200, layers=2, d_mem=0, d_node=20, k=5, **kw)
     W, nf, st, s = synth.make_weights(w), synth.node_features(w), synth.EdgeStream(w), 2.0 ** e
     a = binding.StreamTGN.from_workload(w, W, nf)
@@ -103,7 +103,7 @@ def test_queries_read_back_over_several_tiles(binding, kw):
 
 @pytest.mark.parametrize("kw", [
     dict(d_mem=30, d_node=7, d_edge=70),            # memory ends inside a 16-byte piece, rows of no whole pieces
-    dict(d_mem=32, d_node=100, d_edge=300),         # five chunks: the row is read again between maximum and split
+    dict(d_mem=32, d_node=100, d_edge=300),         # five chunks: more than are requested together
     dict(d_mem=0, d_node=130, d_edge=257),          # node rows too long for four tiles an item
     dict(d_mem=64, d_node=0, d_edge=65),
 ])
