@@ -100,7 +100,7 @@ __host__ __device__ inline LayerLds layer_lds(uint32_t d_in, uint32_t heads, uin
   l.ldz = heads * kSlot * nz + 4;
   l.off_q = kTM * l.ldx;
   l.off_z = l.off_q + kTM * l.ldq;
-  l.off_r = l.off_z + kTM * l.ldz + 4 * kGrpK;    // operand reads may run one chunk past the last row
+  l.off_r = l.off_z + kTM * l.ldz;
   l.off_sc = l.off_r + kTM * k * 4;               // the ring records of the tile's rows, 16 bytes each
   l.total = l.off_sc + (delta ? kTM * k * heads : 0u);       // delta mode: the scores of a row's entries until its weights are known
   return l;
@@ -568,7 +568,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
 #pragma unroll
       for (int t = 0; t < NTL; ++t) B1[t] = tile_b(a.WQ, w1, t, ntd, c_in);
       floatx4 acc[NTL] = {};
-      u1.multiply(Xs + a16_off(lane, ll.ldx), c_in, B1, acc, lane);
+      u1.multiply(Xs + a16_off(lane, ll.ldx), c_in, B1, acc, lane, last_group(ll.ldx));
       store1(wave, acc);
     }
     for (uint32_t nt = wave + 8; nt < ntd; nt += 8) {
@@ -576,7 +576,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
 #pragma unroll
       for (int t = 0; t < NTL; ++t) Bt[t] = tile_b(a.WQ, nt, t, ntd, c_in);
       floatx4 acc[NTL] = {};
-      mfma16_lean<NTL>(Xs + a16_off(lane, ll.ldx), 0u, c_in, Bt, acc, lane);
+      mfma16_lean<NTL>(Xs + a16_off(lane, ll.ldx), 0u, c_in, Bt, acc, lane, last_group(ll.ldx));
       store1(nt, acc);
     }
     __syncthreads();

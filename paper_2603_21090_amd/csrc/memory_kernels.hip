@@ -36,15 +36,19 @@ struct MemLds {
   uint32_t off_m, off_z, off_r, total;
 };
 
-__host__ __device__ inline MemLds memory_lds_layout(uint32_t Kmsg, uint32_t d_msg, uint32_t d_mem) {
+// Operand reads take whole chunks of K and must not leave their row (load_a16).  The short rows of the variant with all
+// weights up front (up) are padded to whole chunks; others, where that could outgrow the LDS, to whole groups, and their reads
+// carry a limit (in the short variant the limit's addresses cost a launch 1.5 of 23 us).
+__host__ __device__ inline MemLds memory_lds_layout(bool up, uint32_t Kmsg, uint32_t d_msg, uint32_t d_mem) {
   MemLds l;
-  l.ldx = round_up(Kmsg, kGrpK) + 4;
-  l.ldm = round_up(d_msg, kGrpK) + 4;
-  l.ldr = round_up(d_mem, kGrpK) + 4;
+  const uint32_t unit = up ? kChunkK : kGrpK;
+  l.ldx = round_up(Kmsg, unit) + 4;
+  l.ldm = round_up(d_msg, unit) + 4;
+  l.ldr = round_up(d_mem, unit) + 4;
   l.off_m = kRows * l.ldx;
   l.off_z = l.off_m + kRows * l.ldm;
   l.off_r = l.off_z + kRows * l.ldr;
-  l.total = l.off_r + kRows * l.ldr + 4 * kGrpK;      // operand reads may run one chunk past the last row
+  l.total = l.off_r + kRows * l.ldr + 4 * kGrpK;      // (room that s_pre takes where the tiles are narrow)
   return l;
 }
 
@@ -75,7 +79,7 @@ __global__ __launch_bounds__(kThreads) void memory_update_kernel(Dev d, const ui
   const uint32_t nD = c->nD;
   const uint32_t ntiles = (nD + kRows - 1) / kRows;
   const uint32_t dm = d.d_mem, dg = d.d_msg, de = d.d_edge, Kmsg = d.Kmsg;
-  const MemLds ll = memory_lds_layout(Kmsg, dg, dm);
+  const MemLds ll = memory_lds_layout(UP, Kmsg, dg, dm);
   float* Xs = lds;                       // [16 x Kmsg]  message input rows; first dm columns = s
   float* Ms = lds + ll.off_m;            // [16 x dg]    messages
   float* Zs = lds + ll.off_z;            // [16 x dm]    update gate
@@ -85,6 +89,7 @@ __global__ __launch_bounds__(kThreads) void memory_update_kernel(Dev d, const ui
   const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const uint32_t c_x = chunks_of(Kmsg), c_g = chunks_of(dg), c_m = chunks_of(dm);
   const uint32_t ntg = round_up(dg, 16) >> 4, ntm = round_up(dm, 16) >> 4;
+  const uint32_t e_x = UP ? kNoLimit : last_group(ll.ldx), e_m = UP ? kNoLimit : last_group(ll.ldm), e_r = UP ? kNoLimit : last_group(ll.ldr);
   const uint32_t a_x = a16_lane_off(ll.ldx), a_m = a16_lane_off(ll.ldm), a_r = a16_lane_off(ll.ldr);
   const uint32_t row0 = m16_row(lane, 0), colL = m16_col(lane);
   const Table H0 = d.H[0];
@@ -247,9 +252,9 @@ __global__ __launch_bounds__(kThreads) void memory_update_kernel(Dev d, const ui
         const float* const Bt[1] = {d.Wmsg + (size_t)nt * kCG * c_x * kGrpFloats};
         floatx4 acc[1] = {{0.f, 0.f, 0.f, 0.f}};
         if constexpr (up_ok) {
-          um.multiply(Xs + a_x, c_x, acc);
+          um.multiply(Xs + a_x, c_x, acc, e_x);
         } else {
-          mfma16_gemm<1>(Xs + a_x, c_x, Bt, acc);
+          mfma16_gemm<1>(Xs + a_x, c_x, Bt, acc, e_x);
         }
         const uint32_t col = nt * 16 + colL;
         if (col < dg) {
@@ -273,11 +278,11 @@ __global__ __launch_bounds__(kThreads) void memory_update_kernel(Dev d, const ui
         const float* const Bu[2] = {d.Uzr + (size_t)nt * kCG * c_m * kGrpFloats, d.Uzr + (size_t)(ntm + nt) * kCG * c_m * kGrpFloats};
         floatx4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
         if constexpr (up_ok) {
-          uw.multiply(Ms + a_m, c_g, acc);
-          uu.multiply(Xs + a_x, c_m, acc);
+          uw.multiply(Ms + a_m, c_g, acc, e_m);
+          uu.multiply(Xs + a_x, c_m, acc, e_x);
         } else {
-          mfma16_gemm<2>(Ms + a_m, c_g, Bw, acc);
-          mfma16_gemm<2>(Xs + a_x, c_m, Bu, acc);
+          mfma16_gemm<2>(Ms + a_m, c_g, Bw, acc, e_m);
+          mfma16_gemm<2>(Xs + a_x, c_m, Bu, acc, e_x);
         }
         const uint32_t col = nt * 16 + colL;
         if (col < dm) {
@@ -305,11 +310,11 @@ __global__ __launch_bounds__(kThreads) void memory_update_kernel(Dev d, const ui
         const float* const Bu[1] = {d.Uh + (size_t)nt * kCG * c_m * kGrpFloats};
         floatx4 acc[1] = {{0.f, 0.f, 0.f, 0.f}};
         if constexpr (up_ok) {
-          uw.multiply(Ms + a_m, c_g, acc);
-          uu.multiply(Rs + a_r, c_m, acc);
+          uw.multiply(Ms + a_m, c_g, acc, e_m);
+          uu.multiply(Rs + a_r, c_m, acc, e_r);
         } else {
-          mfma16_gemm<1>(Ms + a_m, c_g, Bw, acc);
-          mfma16_gemm<1>(Rs + a_r, c_m, Bu, acc);
+          mfma16_gemm<1>(Ms + a_m, c_g, Bw, acc, e_m);
+          mfma16_gemm<1>(Rs + a_r, c_m, Bu, acc, e_r);
         }
         const uint32_t col = nt * 16 + colL;
         if (col < dm) {
@@ -337,7 +342,7 @@ bool memory_upfront(const Dev& d) {
          round_up(d.d_msg, 16) / 16 <= kWaves && round_up(d.d_mem, 16) / 16 <= kWaves;
 }
 
-size_t memory_lds(const Dev& d) { return (size_t)memory_lds_layout(d.Kmsg, d.d_msg, d.d_mem).total * sizeof(float); }
+size_t memory_lds(const Dev& d) { return (size_t)memory_lds_layout(memory_upfront(d), d.Kmsg, d.d_msg, d.d_mem).total * sizeof(float); }
 
 }  // namespace
 

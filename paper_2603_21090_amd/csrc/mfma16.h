@@ -54,12 +54,16 @@ __device__ inline float comp4(const float4& v) {
   else return v.w;
 }
 
-// A operands of groups [g0, g0 + kCG) of the tile row range this lane serves (Ap = tile + lane offset).
-// Reads past the last element of K land in neighbouring (finite) LDS data and meet zero weights.
-__device__ inline void load_a16(const float* Ap, uint32_t g0, float4 (&a)[kCG]) {
+// A operands of groups [g0, g0 + kCG) of the tile row range this lane serves (Ap = tile + lane offset).  Groups past `last`,
+// the last one inside the row, repeat it: they meet zero weights, but the next row's data could hold a NaN, and a
+// NaN times zero is one.  (Rows of whole chunks need no limit.)
+constexpr uint32_t kNoLimit = 0xFFFFFFFFu;
+__device__ inline void load_a16(const float* Ap, uint32_t g0, float4 (&a)[kCG], uint32_t last = kNoLimit) {
 #pragma unroll
-  for (int c = 0; c < kCG; ++c) a[c] = *reinterpret_cast<const float4*>(Ap + kGrpK * (g0 + c));
+  for (int c = 0; c < kCG; ++c) a[c] = *reinterpret_cast<const float4*>(Ap + kGrpK * (g0 + c < last ? g0 + c : last));
 }
+// that group of a row of `ld` floats, 4 of them padding
+__host__ __device__ inline uint32_t last_group(uint32_t ld) { return ld / kGrpK - 1u; }
 
 // B operands of groups [g0, g0 + kCG) of the column tile whose group 0 is Bt (wave-uniform).  The lane is an argument so
 // that a caller with a long loop can pass an opaque copy of it: from threadIdx.x alone the compiler computes one 64-bit
@@ -162,12 +166,12 @@ __device__ __forceinline__ void pingpong_clamped(uint32_t n, Buf& P, LoadF load,
 // already in P.b -- callers request them ahead of the barrier that makes A valid.
 template <int NTL>
 __device__ __forceinline__ void mfma16_gemm_pre(const float* Ap, uint32_t nchunks, const float* const (&Bt)[NTL],
-                                                floatx4 (&acc)[NTL], Ops16<NTL>& P) {
-  load_a16(Ap, 0, P.a);
+                                                floatx4 (&acc)[NTL], Ops16<NTL>& P, uint32_t last) {
+  load_a16(Ap, 0, P.a, last);
   pingpong_peeled<Ops16<NTL>>(
       nchunks, P,
       [&](uint32_t ch, Ops16<NTL>& o) {
-        load_a16(Ap, ch * kCG, o.a);
+        load_a16(Ap, ch * kCG, o.a, last);
 #pragma unroll
         for (int t = 0; t < NTL; ++t) load_b16(Bt[t], ch * kCG, o.b[t]);
       },
@@ -176,24 +180,24 @@ __device__ __forceinline__ void mfma16_gemm_pre(const float* Ap, uint32_t nchunk
 
 template <int NTL>
 __device__ __forceinline__ void mfma16_gemm(const float* Ap, uint32_t nchunks, const float* const (&Bt)[NTL],
-                                            floatx4 (&acc)[NTL]) {
+                                            floatx4 (&acc)[NTL], uint32_t last) {
   Ops16<NTL> P;
 #pragma unroll
   for (int t = 0; t < NTL; ++t) load_b16(Bt[t], 0, P.b[t]);
-  mfma16_gemm_pre<NTL>(Ap, nchunks, Bt, acc, P);
+  mfma16_gemm_pre<NTL>(Ap, nchunks, Bt, acc, P, last);
 }
 
 // Chunks [c0, c1) of a product with one buffer: for what a shape has beyond the products its kernel is tuned for, where the
 // registers of a second buffer would cost those.
 template <int NTL>
 __device__ __forceinline__ void mfma16_lean(const float* Ap, uint32_t c0, uint32_t c1, const float* const (&Bt)[NTL],
-                                            floatx4 (&acc)[NTL], uint32_t lane) {
+                                            floatx4 (&acc)[NTL], uint32_t lane, uint32_t last = kNoLimit) {
 #pragma unroll 1
   for (uint32_t ch = c0; ch < c1; ++ch) {
     Ops16<NTL> o;
 #pragma unroll
     for (int t = 0; t < NTL; ++t) load_b16(Bt[t], ch * kCG, o.b[t], lane);
-    load_a16(Ap, ch * kCG, o.a);
+    load_a16(Ap, ch * kCG, o.a, last);
     mfma16_chunk<NTL>(o, acc);
   }
 }
@@ -215,21 +219,21 @@ struct Upfront16 {
       for (int t = 0; t < NTL; ++t) load_b16(Bt[t], c * kCG, b[ch][t], lane);
     }
   }
-  __device__ __forceinline__ void multiply(const float* Ap, uint32_t nchunks, floatx4 (&acc)[NTL]) {
+  __device__ __forceinline__ void multiply(const float* Ap, uint32_t nchunks, floatx4 (&acc)[NTL], uint32_t last) {
 #pragma unroll
     for (int ch = 0; ch < MAXC; ++ch) {
       if ((uint32_t)ch < nchunks) {                  // wave-uniform; only LDS reads and products inside
         float4 a[kCG];
-        load_a16(Ap, ch * kCG, a);
+        load_a16(Ap, ch * kCG, a, last);
         mfma16_chunk<NTL>(a, b[ch], acc);
       }
     }
   }
   // the whole product, also where K has more chunks than were requested
   __device__ __forceinline__ void multiply(const float* Ap, uint32_t nchunks, const float* const (&Bt)[NTL],
-                                           floatx4 (&acc)[NTL], uint32_t lane) {
-    multiply(Ap, nchunks, acc);
-    mfma16_lean<NTL>(Ap, MAXC, nchunks, Bt, acc, lane);
+                                           floatx4 (&acc)[NTL], uint32_t lane, uint32_t last = kNoLimit) {
+    multiply(Ap, nchunks, acc, last);
+    mfma16_lean<NTL>(Ap, MAXC, nchunks, Bt, acc, lane, last);
   }
 };
 

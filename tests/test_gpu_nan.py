@@ -1,0 +1,66 @@
+"""A NaN among the features reaches the rows that depend on it and no other: what shares a tile, a wave or a zero weight with
+it keeps its bits."""
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+from paper_2603_21090_amd import synth
+from tests.helpers import tiny_workload
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def binding():
+    from paper_2603_21090_amd import binding as b
+    return b
+
+
+def _quiet_node(w, st):
+    """A node of one or two edges whose place in a tile of sixteen is not the first."""
+    deg = np.bincount(np.concatenate([st.src, st.dst]), minlength=w.num_nodes)
+    at = np.nonzero((deg >= 1) & (deg <= 2) & (np.arange(w.num_nodes) % 16 > 3))[0]
+    return int(at[at.size // 2])
+
+
+def _check(binding, w, node=None, edge=None):
+    """Poisons one column of a node's or an edge's features; the oracle says which rows that reaches."""
+    W, nf, st = synth.make_weights(w), synth.node_features(w), synth.EdgeStream(w)
+    bad_nf = None if nf is None else nf.copy()
+    if node is not None:
+        bad_nf[_quiet_node(w, st) if node == "quiet" else node, 0] = np.nan
+    o = orc.Oracle.from_workload(w, W, bad_nf)
+    a, b = binding.StreamTGN.from_workload(w, W, nf), binding.StreamTGN.from_workload(w, W, bad_nf)
+    for i in range(w.num_batches):
+        s, d, t, ef = st.batch(i)
+        bad_ef = ef.copy()
+        if edge is not None and i == w.num_batches - edge:
+            bad_ef[len(s) // 2, 0] = np.nan
+        a.ingest_batch(s, d, t, ef), b.ingest_batch(s, d, t, bad_ef)
+        assert o.ingest(s, d, t, bad_ef)[0] == 0
+    ref, every = o.embed_all(), np.arange(w.num_nodes, dtype=np.uint32)
+    for what in ("streamed", "rebuilt"):
+        for l in range(1, w.layers + 1):
+            reached = np.isnan(ref[l - 1]).any(axis=1)
+            assert 0 < reached.sum() < w.num_nodes // 2
+            x, y = a.get_embeddings(every, layer=l), b.get_embeddings(every, layer=l)
+            assert not np.isnan(x).any() and np.isnan(y[reached]).any(axis=1).all()
+            off = np.nonzero((x != y).any(axis=1) & ~reached)[0]
+            assert off.size == 0, f"{what}, layer {l}: rows {off[:8]} ({off.size} in all) beside the {reached.sum()} reached"
+        a.full_rebuild(), b.full_rebuild()
+    a.close(), b.close()
+
+
+@pytest.mark.parametrize("d_node, heads", [(150, 1), (70, 1), (200, 2)])
+def test_rows_of_a_tile(binding, d_node, heads):
+    """Input rows longer than the head slots and of no whole 64 columns."""
+    _check(binding, tiny_workload(num_nodes=400, num_edges=700, batch=100, zipf_s=0.6, d_mem=0, d_node=d_node, d_edge=0,
+                                  d_emb=40 * heads, heads=heads, d_time=20, k=3), node="quiet")
+
+
+@pytest.mark.parametrize("kw", [dict(d_mem=100, d_msg=100, d_edge=20), dict(d_mem=100, d_msg=100, d_edge=20, aggregator=1),
+                                dict(d_mem=140, d_msg=150, d_edge=20)])
+def test_endpoints_of_a_tile(binding, kw):
+    """Message and memory rows of no whole 64 columns."""
+    _check(binding, tiny_workload(**{**dict(num_nodes=3000, num_edges=1400, batch=200, zipf_s=0.6, d_emb=40, heads=1, d_time=20, k=3),
+                                     **kw}), edge=2)
