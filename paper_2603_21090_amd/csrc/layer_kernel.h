@@ -619,9 +619,11 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     // The time encodings are not masked per entry: a column past d_time has omega = phase = 0 and comes out as
     // cos(0) = 1.  In the scores it meets an exact zero of qt and in phase 4 one of pb: both are cleared there once
     // per row.
+    // A raw edge row's own padding is zero, but qt's there is whatever an earlier tile left (phase 2 writes the tiles that
+    // hold valid columns), and 0 x NaN is NaN: qt is cleared there too.
     // (the last time slot's alone: d_time > 64 (NT - 1))
-    auto clear_past_d_time = [&](float4& o, uint32_t t) {
-      const uint32_t c0 = (NT - 1) * kSlot + 4u * sub, end = t == NT - 1 ? a.d_time : 0xFFFFFFFFu;
+    auto clear_padding = [&](float4& o, uint32_t t) {
+      const uint32_t c0 = 4u * sub, end = t == NT - 1 ? a.d_time - (NT - 1) * kSlot : ES && t == NT ? a.d_edge : kSlot;
       o.x = c0 < end ? o.x : 0.0f;
       o.y = c0 + 1u < end ? o.y : 0.0f;
       o.z = c0 + 2u < end ? o.z : 0.0f;
@@ -640,7 +642,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
           for (int i = 0; i < NZL; ++i) {
             const uint32_t t = SH == 1 ? (uint32_t)i : sg + SH * i, at = head * Ztp + (t < NZ ? t : 0u) * kSlot;
             qt[p][i] = *reinterpret_cast<const float4*>(Zs + local * ll.ldz + at + 4u * sub);
-            if (SH > 1 || i == NT - 1) clear_past_d_time(qt[p][i], t);
+            if (SH > 1 || i >= NT - 1) clear_padding(qt[p][i], t);
             if (keep && t < NZ) *reinterpret_cast<float4*>(qrow + kSlot * KS + at) = qt[p][i];
           }
         });
@@ -688,7 +690,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
       for (int h = 0; h < H; ++h) {
         float4* o = reinterpret_cast<float4*>(zq + h * Ztp + (NT - 1) * kSlot);
         float4 v = *o;
-        clear_past_d_time(v, NT - 1);
+        clear_padding(v, NT - 1);
         *o = v;
       }
       uint32_t nch = 0, nvalid = 0;
@@ -839,7 +841,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
         for (int t = 0; t < NT; ++t) {
           float4 o = accp[h][t];
           o.x *= inv; o.y *= inv; o.z *= inv; o.w *= inv;
-          if (t == NT - 1) clear_past_d_time(o, t);
+          if (t == NT - 1) clear_padding(o, t);
           *reinterpret_cast<float4*>(zq + h * Ztp + t * kSlot) = o;
           if (live) *reinterpret_cast<float4*>(acP + (h * NT + t) * kSlot) = o;
         }
@@ -989,7 +991,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
         const uint32_t t = SH == 1 ? (uint32_t)i : sg + SH * i;
         float4 o = accp[i];
         o.x *= inv; o.y *= inv; o.z *= inv; o.w *= inv;
-        if (SH > 1 || i == NT - 1) clear_past_d_time(o, t);    // (a raw edge row's padding is zero, and so are its sums)
+        if (SH > 1 || i == NT - 1) clear_padding(o, t);    // (a raw edge row's padding is zero, and so are its sums)
         if (t < NZ) *reinterpret_cast<float4*>(Zs + local * ll.ldz + head * Ztp + t * kSlot + 4u * sub) = o;
       }
       });

@@ -64,3 +64,12 @@ def test_endpoints_of_a_tile(binding, kw):
     """Message and memory rows of no whole 64 columns."""
     _check(binding, tiny_workload(**{**dict(num_nodes=3000, num_edges=1400, batch=200, zipf_s=0.6, d_emb=40, heads=1, d_time=20, k=3),
                                      **kw}), edge=2)
+
+
+@pytest.mark.parametrize("kw", [dict(d_edge=9, heads=1, d_emb=40), dict(d_edge=9, heads=2, d_emb=100),
+                                dict(d_edge=35, heads=1, d_emb=100), dict(d_edge=20, heads=4, d_emb=60)])
+def test_tiles_of_a_workgroup(binding, kw):
+    """Raw edge rows: columns of the padded slot that no tile of products writes, over several tiles per workgroup.  (The
+    poisoned rows come early in the lists, so that tiles follow in their place.)"""
+    _check(binding, tiny_workload(**{**dict(num_nodes=40_000, num_edges=60_000, batch=4_000, zipf_s=1.05, d_mem=0, d_node=20,
+                                            d_time=70, k=3), **kw}), edge=1)
