@@ -391,7 +391,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     const uint32_t newest = dg ? (dg - 1u) % k : 0u;
     // the record of adjacency position p sits in ring slot p mod k; with the row's degree known, slot
     // sl holds the j-th most recent entry, j = (newest - sl) mod k; places past the row's entry count
-    // name node 0 / edge 0 (finite cached rows whose weight in every sum is zero)
+    // name node 0 / edge 0, whose cached rows are there to be gathered (they may be NaN: such places are left out of every sum)
     auto place_ring = [&](uint32_t sl, RingEntry e) {
       const uint32_t j = newest >= sl ? newest - sl : newest + k - sl;
       if (j >= cnt_s) { e.nbr = 0u; e.eid = 0u; e.t = 0.0; }
@@ -967,7 +967,8 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
         }
 #pragma unroll
         for (int jc = 0; jc < JC; ++jc) {
-          const float w = vj[jc] ? __expf(sc[jc] - mref) : 0.0f;
+          if (!vj[jc]) continue;                              // (a branch, and not a weight of zero: what does not count may be NaN)
+          const float w = __expf(sc[jc] - mref);
           lrun += w;
           float4 vv = zb.nv[jc];
           if constexpr (!ES) { vv.x += zb.e[jc][1].x; vv.y += zb.e[jc][1].y; vv.z += zb.e[jc][1].z; vv.w += zb.e[jc][1].w; }

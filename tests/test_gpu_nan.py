@@ -28,14 +28,14 @@ def _check(binding, w, node=None, edge=None):
     W, nf, st = synth.make_weights(w), synth.node_features(w), synth.EdgeStream(w)
     bad_nf = None if nf is None else nf.copy()
     if node is not None:
-        bad_nf[_quiet_node(w, st) if node == "quiet" else node, 0] = np.nan
+        bad_nf[{"quiet": _quiet_node, "early": _early_nodes}.get(node, lambda *_: node)(w, st), 0] = np.nan
     o = orc.Oracle.from_workload(w, W, bad_nf)
     a, b = binding.StreamTGN.from_workload(w, W, nf), binding.StreamTGN.from_workload(w, W, bad_nf)
     for i in range(w.num_batches):
         s, d, t, ef = st.batch(i)
         bad_ef = ef.copy()
         if edge is not None and i == w.num_batches - edge:
-            bad_ef[len(s) // 2, 0] = np.nan
+            bad_ef[0 if i == 0 else len(s) // 2, 0] = np.nan
         a.ingest_batch(s, d, t, ef), b.ingest_batch(s, d, t, bad_ef)
         assert o.ingest(s, d, t, bad_ef)[0] == 0
     ref, every = o.embed_all(), np.arange(w.num_nodes, dtype=np.uint32)
@@ -73,3 +73,24 @@ def test_tiles_of_a_workgroup(binding, kw):
     poisoned rows come early in the lists, so that tiles follow in their place.)"""
     _check(binding, tiny_workload(**{**dict(num_nodes=40_000, num_edges=60_000, batch=4_000, zipf_s=1.05, d_mem=0, d_node=20,
                                             d_time=70, k=3), **kw}), edge=1)
+
+
+def _early_nodes(w, st):
+    """Nodes without an edge in the later three quarters of the stream."""
+    late = np.zeros(w.num_nodes, dtype=bool)
+    late[st.src[w.num_edges // 4:]] = late[st.dst[w.num_edges // 4:]] = True
+    return np.nonzero(~late)[0]
+
+
+SHAPES = [dict(d_edge=0, heads=1, d_emb=40), dict(d_edge=9, heads=2, d_emb=100), dict(d_edge=70, heads=2, d_emb=100),
+          dict(d_edge=5, heads=4, d_emb=60), dict(d_edge=0, heads=1, d_emb=200)]
+
+
+@pytest.mark.parametrize("kw, poison", [(kw, p) for kw in SHAPES for p in ("node 0", "edge 0", "outside the window")
+                                        if p != "edge 0" or kw["d_edge"]])
+def test_entries_without_weight(binding, kw, poison):
+    """Places past a row's entries name node 0 and edge 0, and entries outside the temporal window are gathered like the others:
+    neither counts."""
+    w = tiny_workload(**{**dict(num_nodes=900, num_edges=1500, batch=100, zipf_s=0.6, d_mem=0, d_node=20, d_time=20, k=9,
+                                window=40.0 if poison == "outside the window" else 0.0), **kw})
+    _check(binding, w, **{"node 0": dict(node=0), "edge 0": dict(edge=w.num_batches), "outside the window": dict(node="early")}[poison])
