@@ -19,9 +19,9 @@ using layer_impl::LayerArgs;
 // A copy, bound by HBM for long lists and by the launch for short ones.  A workgroup takes `per` consecutive list
 // positions (and again `per`, a grid further on, when the list outgrows the largest grid) and its threads stride over
 // their pieces of V floats; eight pieces per thread are requested before the first is stored, and the (row, piece) pair
-// advances by additions.  One million rows of 100 floats: 173 us
-// = 4.6 TB/s of ids, rows read and rows stored, 5.3 with the padding of the tables' rows to 512 bytes, where a large copy
-// reaches 6.0 (four pieces together: 185 us; one float per thread and a 64-bit division each: 284 us).
+// advances by additions.  One million rows of 100 floats: 173 us = 4.6 TB/s of ids, rows read and rows stored, 5.3 with
+// the padding of the tables' rows to 512 bytes, where a large copy reaches 6.0 (four pieces together: 185 us; one float
+// per thread and a 64-bit division each: 284 us).
 // Results are stored past the caches: nothing here reads them again, and the tables keep their place.
 constexpr uint32_t kGatherBlocks = 1u << 16;
 template <int V> struct Piece;
@@ -161,7 +161,7 @@ void launch_layer(const Dev& d, hipStream_t s, uint32_t layer, const uint32_t* r
 void launch_layer_scores(const Dev& d, hipStream_t s, uint32_t n, const uint32_t* src, const uint32_t* dst, const double* ts,
                          float* scores) {
   LaunchArgs a = make_args(d, d.layers - 1);
-  a.roots = true;                                             // (computed at their own times, from nothing cached)
+  a.roots = true;                                             // (at their own times; q and qt, which do not depend on the time, are read back where a query cache is kept)
   a.k.root_src = src; a.k.root_dst = dst; a.k.root_ts = ts; a.k.nodes = d.N;
   a.k.head = d.pred_w; a.k.scores = scores;
   a.s = s; a.rows = nullptr; a.cp = nullptr; a.cm = 2 * n; a.set_attr = false;
@@ -177,8 +177,8 @@ hipError_t launch_gather_rows(const Dev& d, hipStream_t s, uint32_t layer, uint3
   // 16-byte pieces where the width and the caller's buffer allow (table rows are aligned to 256 bytes), else 8, else 4
   const uintptr_t at = reinterpret_cast<uintptr_t>(out);
   const int v = width % 4 == 0 && at % 16 == 0 ? 4 : width % 2 == 0 && at % 8 == 0 ? 2 : 1;
-  // rows per workgroup: about two rounds of four pieces per thread for long lists, fewer rows while the list would
-  // not fill the chip otherwise
+  // rows per workgroup: one round of eight pieces per thread for long lists, fewer rows while the list would not fill the
+  // chip otherwise
   uint32_t per = 2048u * (uint32_t)v / width;
   const uint32_t fill = n / 2048u;
   if (per > fill) per = fill;

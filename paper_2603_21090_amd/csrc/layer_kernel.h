@@ -117,7 +117,7 @@ struct LayerArgs {
   // row.  The rows are not stored: their tile holds both ends of its eight edges, and the link score
   // y = h_u . head[0 : d) + h_v . head[d : 2d) + head[2d] leaves the kernel in their place (NaN with a dead end).
   // One launch for what took three (roots listed, rows stored, rows read back by the head): 4,000 candidates on
-  // 100,000 nodes 35.1 -> 29.9 us, 28.1 with variants of their own (ROOTS).
+  // 100,000 nodes 35.1 -> 29.9 us, 28.1 with variants of their own (ROOTS), 25.2 with a lane group per key slot.
   const uint32_t *root_src, *root_dst; const double* root_ts; uint32_t nodes;
   const float* head; float* scores;
   double window;                                   // ring entries older than the query time minus this are ignored (+inf: none)
@@ -1259,12 +1259,13 @@ void go(LaunchArgs& a) {
   else go_exact<KS, NT, H, JC, WGS, false>(a);
 }
 
-// Ring entries per chunk and workgroups per CU are bounded by registers: two chunks of JC * 4 KS
-// float4 per lane are in flight beside 2 (KS + H NT) float4 of accumulators and query values.
+// Ring entries per chunk and workgroups per CU are bounded by registers.  Exact mode, a lane per column quad of one key
+// slot: two chunks of JC entries are in flight, 3 (raw edge rows) or 4 float4 each, beside 1 + NZL float4 of sums and as many
+// of q and qt.  One slot: four waves of 168 registers, three workgroups per CU; more: eight of 128, two.  The delta mode, a lane per
+// row's column quad of every slot, holds 4 KS float4 per entry and 2 KS + H NT beside them: four waves of 256 (one slot: 168).
 template <int KS, int NT, int H>
 void go_jc(LaunchArgs& a) {
   if constexpr (KS == 1) go<KS, NT, H, 2, 3>(a);
-  else if constexpr (KS == 2) go<KS, NT, H, 1, 2>(a);
   else go<KS, NT, H, 1, 2>(a);
 }
 

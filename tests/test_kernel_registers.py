@@ -44,11 +44,17 @@ def spills(tmp_path_factory):
 @pytest.mark.parametrize("heads", [1, 2])
 @pytest.mark.parametrize("time_slots", [1, 2])
 def test_streamed_variants_of_two_key_slots(spills, time_slots, heads, raw_edges, qcache):
-    """Rows of up to 128 floats in two slots: nothing spilled, but with two heads, two time slots and the query cache the few
-    registers that variant has always been short of (2 with raw edge rows, 15 without)."""
-    short_of = (15, 2)[raw_edges] if time_slots == 2 and heads == 2 and qcache else 0
+    """Rows of up to 128 floats in two slots: nothing spilled."""
     variant = (2, time_slots, raw_edges, heads, 1, 2, 0, qcache)
-    assert spills[variant + (0,)] <= short_of
+    assert spills[variant + (0,)] == 0
+
+
+def test_streamed_variants_of_one_and_four_key_slots(spills):
+    """Rows of one slot: nothing spilled; of four, whose waves use all 128 registers: four at most."""
+    streamed = {v: n for v, n in spills.items() if not v[6] and not v[8]}
+    assert {v[0] for v in streamed} == {1, 2, 4}
+    for v, n in streamed.items():
+        assert n <= (4 if v[0] == 4 else 0), v
 
 
 def test_link_scores_have_variants_of_their_own(spills):
