@@ -249,8 +249,8 @@ __global__ __launch_bounds__(256) void compact_write_kernel(Dev d) {
 }
 
 // Orders a layer's row list so that rows with equally many recent-neighbour entries sit together.  The
-// attention kernel serves four rows per wave in lockstep and sixteen per workgroup, so a tile costs what
-// its LONGEST row costs: on skewed graphs a tile of sixteen consecutive ids runs to nearly k entries while
+// attention kernel serves the rows that share a wave in lockstep (four, two or one, by key slots) and sixteen per
+// workgroup, so a tile costs what its LONGEST row costs: on skewed graphs a tile of sixteen consecutive ids runs to nearly k entries while
 // the mean row holds a few.  Within every window of 4,096 list positions the rows are regrouped by
 // descending entry count min(deg, k) (a counting sort, stable: ids stay ascending inside a group, and the
 // order is the same on every run); tiles cut from the regrouped list are homogeneous.  With the query cache
@@ -258,10 +258,10 @@ __global__ __launch_bounds__(256) void compact_write_kernel(Dev d) {
 // then the others, and every tile of the window is marked: 1 when none of its rows changed.  A row's result
 // does not depend on which rows share its tile, so only the cost changes.  grid.y = list.
 //
-// A window is one workgroup (25 of them for 100,000 rows): bound by the latency of its chain and by the instructions of its few
-// waves, not by bytes, hence sixteen waves.  A thread owns four consecutive positions (sixteen, in four
-// waves, took 15.3 us for the two lists of 100,000 nodes where this takes 11.1, and 26 for 1,300,000 where this takes 17.7).  The counts of four bins travel in one 64-bit word (a window's largest count
-// takes 13 of a field's 16 bits); a wave scans all groups of four at once, and one exchange of the wave totals
+// A window is one workgroup (25 of them for 100,000 rows): bound by the latency of its chain and by the instructions of
+// its few waves, not by bytes, hence sixteen waves.  A thread owns four consecutive positions (sixteen, in four waves,
+// took 15.3 us for the two lists of 100,000 nodes where this takes 11.1, and 26 for 1,300,000 where this takes 17.7).
+// The counts of four bins travel in one 64-bit word (a window's largest count takes 13 of a field's 16 bits); a wave scans all groups of four at once, and one exchange of the wave totals
 // gives every thread its starting offsets: three barriers in all, where a scan of its own per bin took two barriers
 // per bin and the histogram an LDS atomic per row.
 constexpr uint32_t kBucketWindow = 4096;

@@ -23,11 +23,11 @@
 // Weights stream from L2 (group-major packing, see mfma16.h), each phase's requested ahead of its barrier; several
 // workgroups per CU overlap one's gather with another's products.
 //
-// The products of phases 1, 2, 4, 5 and 6 are fp32 matrix instructions, 30 to 47 % of a launch's matrix cycles.  Operands
-// split into two f16 under one power-of-two scale per row and per matrix took a fifth of those cycles and 12 to 24 % off a launch,
-// but an f16 pair holds 22 bits, and those only within 2^27 of the scale's bound: a large feature with small
-// weights in a row of ordinary ones cost its other columns their bits (queries 4e-5 off with one feature of 1.7e9).  So
-// the operands stay in 32 bits.  Layer launches, with a 16-lane group per row and with the present kernel: 1,000,000 nodes,
+// The products of phases 1, 2, 4, 5 and 6 are fp32 matrix instructions, which keep the matrix pipes busy for 28 to 40 % of
+// a launch.  Operands split into two f16 under one power-of-two scale per row and per matrix took a fifth of those cycles
+// and 12 to 24 % off a launch, but an f16 pair holds 22 bits, and those only within 2^27 of the scale's bound: a large
+// feature with small weights in a row of ordinary ones cost its other columns their bits (queries 4e-5 off with one
+// feature of 1.7e9).  So the operands stay in 32 bits.  Layer launches, with a 16-lane group per row and with the present kernel: 1,000,000 nodes,
 // d_edge 100, 1,082 -> 1,003 us and (query cache) 1,052 -> 924; 1,300,000 nodes, raw edge rows, k = 20, 1,048 -> 952; 100,000
 // nodes, d_edge 172, 190 -> 180 and 204 -> 188; a rebuild of 200,000 nodes 662 + 429 -> 585 + 396.  Whole tables
 // lie 1e-7 to 2.9e-7 (2-norm) and up to 2.6e-6 of the root mean square (largest) off 64-bit results.
