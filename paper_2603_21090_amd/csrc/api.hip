@@ -206,6 +206,7 @@ size_t layout(const stgn_config& c, char* base, Dev* d) {
   for (int i = 0; i < kSets; ++i) d->stripes_set[i] = b.take<uint64_t>((size_t)kStripedCounters * kStripes * kStripeWords);
   d->stripes = d->stripes_set[0];
   d->gathered_slots = b.take<uint64_t>(kStatSlots);
+  d->tile_next = b.take<uint32_t>(c.layers * kStatLine);
   d->items_cap = (uint64_t)N + 2 * c.max_edges / kLogChunk + 1024;
   for (int i = 0; i < kSets; ++i) d->items_set[i] = b.take<uint64_t>(d->items_cap);
   d->items = d->items_set[0];

@@ -289,6 +289,7 @@ int project_tiles(const Dev& d) { return d.d0 <= 2u * kChunkK ? 4 : 1; }
 template <int RT>
 __global__ __launch_bounds__(256) void project_nodes_kernel(Dev d) {
   extern __shared__ __align__(16) float lds[];
+  if (blockIdx.x == 0 && threadIdx.x < d.layers) d.tile_next[threadIdx.x * kStatLine] = 0u;       // for the layer launches behind this one
   project_rows<RT>(d, nullptr, true, blockIdx.x, gridDim.x, lds);
 }
 
@@ -311,6 +312,7 @@ __global__ __launch_bounds__(256) void apply_kernel(Dev d, const uint32_t* __res
   }
   const uint32_t first = proj_blocks + compact_blocks;      // first workgroup of the append group
   const uint32_t tid = (blockIdx.x - first) * blockDim.x + threadIdx.x, nth = (gridDim.x - first) * blockDim.x;
+  if (blockIdx.x == first && threadIdx.x < d.layers) d.tile_next[threadIdx.x * kStatLine] = 0u;   // for the layer launches behind this one
   // Two flag arrays: the other one was last read by the previous batch's compaction and is seeded
   // next by the next batch's placement kernel, which waits for this kernel -- cleared here, skipped batch or not.
   if (blockIdx.x >= proj_blocks && d.mark_other != d.mark) {

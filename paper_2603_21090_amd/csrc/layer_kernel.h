@@ -124,6 +124,7 @@ struct LayerArgs {
   const RingEntry* ring; const uint32_t* deg; const double* t_last;
   const double* om_rev; const double* ph_rev;
   Ctrl* ctrl;
+  uint32_t* tile_next;                             // streamed exact launches: tiles handed out beyond the first one of every workgroup (zero before the launch)
   uint64_t* gathered_slots;                        // statistic: ring entries gathered, one plain counter per workgroup index
   const float *WQ, *cQ, *WKT, *WV, *WO, *bO, *WKVnext;   // matrices group-major (mfma16.h)
   uint32_t ld_in, ld_out, ld_kv, ld_kve;           // ld_kve = 0 without edge features (every edge reads one zero row)
@@ -201,7 +202,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   constexpr int GPR = DELTA ? 1 : KS;         // 16-lane groups per row in phase 3: one per key slot
   constexpr int RPP = 4 / GPR;                // rows a wave works on at a time there
   constexpr int PASSES = RPW / RPP;
-  __shared__ uint32_t s_node[2][kTM], s_sum[NW];
+  __shared__ uint32_t s_node[2][kTM], s_sum[NW], s_next[2];
   __shared__ __align__(16) double s_om[NT * kSlot], s_ph[NT * kSlot];
   static_assert(KS % H == 0, "whole slots per head");
   static_assert(!(DELTA && ES), "the delta mode keeps projected edge rows");
@@ -409,17 +410,33 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     for (int r = 0; r < RPW; ++r) gathered += (uint32_t)__builtin_amdgcn_readlane((int)cnt_s, r * (int)LS);
   };
 
-  // Round i gives workgroup b the tile i G + (b + 37 i) mod G (G workgroups): every round is a permutation of
-  // its G tiles, and a workgroup's position inside the round moves from round to round.  The row list may
-  // be regrouped by entry count in windows of 256 tiles (long rows first), so a fixed position would hand
-  // the same workgroups every long tile.
+  // Tiles of a workgroup.  The first one is that of its index.  On long lists further ones are handed out by a counter, asked a
+  // tile ahead: workgroups that find their place late (the next batch's front part holds CUs when a launch starts) then take
+  // fewer tiles, where with a fixed share they hold up the launch.  On lists of up to four tiles a workgroup a counter only
+  // adds its own latency (10,000 nodes, a tile each: 122 -> 128 us a batch; 20,000 nodes, two or three: 217 -> 221): rounds
+  // go through the workgroups forwards and backwards in turn, since the list may be regrouped by entry count in windows of
+  // 4,096 rows (long rows first) and a fixed position would hand the same workgroups every long tile.  The other modes
+  // give workgroup b the tile i G + (b + 37 i) mod G in round i (G workgroups), to the same end.
+  constexpr bool DYN = !ROOTS && !DELTA;
   const uint32_t G = gridDim.x, step37 = 37u % G;
-  uint32_t tile_base = 0, tile_pos = blockIdx.x, next_tile = blockIdx.x;
-  auto advance = [&]() {                                      // next_tile: this workgroup's tile of the next round
-    tile_base += G;
-    tile_pos += step37;
-    if (tile_pos >= G) tile_pos -= G;
-    next_tile = tile_base + tile_pos;
+  uint32_t tile_base = 0, tile_pos = blockIdx.x, next_tile = blockIdx.x, taken = 0;
+  auto counted = [&]() { return ntiles > 4u * G; };
+  auto take = [&]() {
+    taken = 0u;                                               // (not carried from tile to tile)
+    if (counted() && wave == 0u && lane == 0u)
+      taken = G + __hip_atomic_fetch_add(args()->tile_next, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  auto publish = [&](uint32_t round) { if (counted() && wave == 0u && lane == 0u) s_next[round & 1u] = taken; };
+  auto advance = [&](uint32_t round) {                        // next_tile: this workgroup's tile of the next round
+    if constexpr (DYN) {
+      if (counted()) next_tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_next[round & 1u]);
+      else next_tile = (round + 1u) * G + ((round & 1u) ? blockIdx.x : G - 1u - blockIdx.x);
+    } else {
+      tile_base += G;
+      tile_pos += step37;
+      if (tile_pos >= G) tile_pos -= G;
+      next_tile = tile_base + tile_pos;
+    }
   };
 
   // ---- phase 3's rows: pass p works on rows p RPP .. p RPP + RPP - 1 of the wave's, GPR groups of 16 lanes each,
@@ -503,9 +520,11 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   };
 
   // the first tile
+  if constexpr (DYN) take();
   stage_a(blockIdx.x);
   stage_b(blockIdx.x);
   commit(0u);
+  if constexpr (DYN) publish(0u);
   commit_x(pf_ok);
   derive_slot();
   if constexpr (QCACHE) request_back(kPass0);
@@ -1025,6 +1044,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     };
     request4();
     stage_b(next_tile);
+    if constexpr (DYN) take();                                // (behind what this tile waits for)
     __syncthreads();
     if (wave < nunits4) {
       for (;;) {
@@ -1052,6 +1072,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     derive_lane();
     request5();
     commit(round + 1u);
+    if constexpr (DYN) publish(round + 1u);
     if constexpr (QCACHE) { derive_slot(); request_back(kPass0); }           // (a tile that projects does not use them)
     __syncthreads();
     if (kRowsInZ || !rows_in_lds) {                           // the next tile's input rows, if it projects
@@ -1176,7 +1197,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   for (uint32_t round = 0;; ++round) {
     const uint32_t tile = next_tile;
     if (tile >= ntiles) break;                                // wave-uniform; only in a workgroup's last round
-    advance();
+    advance(round);
     // (set by the staging of a tile ago; uniform)
     if constexpr (QCACHE) {
       if (ROOTS || p_clean != 0u) { work_tile(std::true_type{}, tile, round); continue; }

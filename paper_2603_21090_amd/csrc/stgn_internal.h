@@ -54,6 +54,7 @@ constexpr uint32_t kStripes = 32;
 constexpr uint32_t kStripeWords = 16;                        // uint64 per 128-byte line
 constexpr uint32_t kScannedCounter = STGN_MAX_LAYERS + 1;
 constexpr uint32_t kStripedCounters = STGN_MAX_LAYERS + 2;
+constexpr uint32_t kStatLine = 64;                           // words between counters of their own cache lines
 constexpr uint32_t kStatSlots = 1024;                        // per-workgroup statistic slots of the layer kernel (its grid never exceeds this)
 
 struct Ctrl {
@@ -165,6 +166,7 @@ struct Dev {
   uint8_t* mark_other;               // the array of the other parity (bound batch)
   uint64_t* stripes_set[kSets];          // [kStripedCounters][kStripes] lines of kStripeWords words, per batch parity
   uint64_t* stripes;                 // ... of the bound batch
+  uint32_t* tile_next;               // [layers, a line apart] tiles the layer's launch has handed out; zeroed by the kernel ahead of the launches (apply, projection of all nodes)
   uint64_t* gathered_slots;          // [kStatSlots] ring entries gathered by the layer kernel, one slot per workgroup index
   uint64_t* items;                   // propagation work items (node, chunk)
   uint64_t* items_set[kSets];            // ... held twice, by batch parity: a batch's first hop may run beside the previous batch's last

@@ -1,0 +1,47 @@
+"""Layer launches over lists of every length around what a workgroup's tiles and the tile counter make of them: a
+row that a launch leaves out, or works on from another row's tile, differs from the rebuilt one."""
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+from paper_2603_21090_amd import synth
+from tests.helpers import rows_close, tiny_workload
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("kw", [dict(d_mem=12, d_edge=70, heads=2, d_emb=100, d_time=100, k=5),     # two key slots
+                                dict(d_mem=0, d_node=20, d_edge=9, heads=2, d_emb=20, d_time=30, k=20),    # raw edge rows, query cache at every layer
+                                dict(d_mem=16, d_edge=0, heads=1, d_emb=66, d_time=70, k=10),              # one head of two slots
+                                dict(d_mem=10, d_edge=66, heads=4, d_emb=32, d_time=20, k=3)])             # four
+def test_streamed_rows_equal_a_rebuild_at_every_list_length(kw):
+    """Endpoints drawn evenly over 70,001 nodes: batches of 8 to 8,000 edges list 16 to 70,001 rows per layer, on both sides of
+    one, two and four tiles of 16 or 32 rows for each workgroup, and the rebuild lists them all."""
+    import torch
+    from paper_2603_21090_amd import binding
+    w = tiny_workload(**{**dict(num_nodes=70_001, num_edges=120_000, batch=8_000, layers=2), **kw})
+    W = synth.make_weights(w)
+    nf = synth.node_features(w)
+    g = binding.StreamTGN.from_workload(w, W, nf, max_batch=8_000)
+    o = orc.Oracle.from_workload(w, W, nf)
+    gen = np.random.default_rng(7)
+    every = torch.arange(w.num_nodes, dtype=torch.int32, device="cuda")
+    at, seen = 0.0, set()
+    for b in (8_000, 1_500, 8, 4_000, 300, 8_000, 8_000, 8_000, 700, 8_000, 2_500, 40, 8_000, 8_000, 5_000):
+        src = gen.integers(0, w.num_nodes, b).astype(np.uint32)
+        dst = ((src + gen.integers(1, w.num_nodes, b)) % w.num_nodes).astype(np.uint32)
+        ts = at + np.cumsum(gen.exponential(1.0, b))
+        at = ts[-1]
+        ef = gen.standard_normal((b, w.d_edge), dtype=np.float32)
+        assert o.ingest(src, dst, ts, ef)[0] == 0
+        seen.add(g.ingest_batch(src, dst, ts, ef, stats=True)["n_affected"])
+        rows = [g.get_embeddings(every, layer=l) for l in (1, 2)]
+        g.full_rebuild()
+        for l, x in enumerate(rows, 1):
+            y = g.get_embeddings(every, layer=l)
+            assert torch.equal(x, y), (b, l, int((x != y).any(1).sum()))
+    assert min(seen) < 8_192 and max(seen) > 32_768, sorted(seen)
+    some = np.concatenate([gen.integers(0, w.num_nodes, 200), [0, 1, 65_535, 65_536, w.num_nodes - 1]]).astype(np.uint32)
+    for l in (1, 2):
+        assert rows_close(g.get_embeddings(some, layer=l), o.embed_nodes(some, layer=l)).all()
+    g.close()
