@@ -415,7 +415,8 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   // fewer tiles, where with a fixed share they hold up the launch.  On lists of up to four tiles a workgroup a counter only
   // adds its own latency (10,000 nodes, a tile each: 122 -> 128 us a batch; 20,000 nodes, two or three: 217 -> 221): rounds
   // go through the workgroups forwards and backwards in turn, since the list may be regrouped by entry count in windows of
-  // 4,096 rows (long rows first) and a fixed position would hand the same workgroups every long tile.  The other modes
+  // 4,096 rows (long rows first) and a fixed position would hand the same workgroups every long tile, and the last round
+  // forwards, since the workgroups of low index start first (backwards: 119 -> 128 and 188 -> 208 us).  The other modes
   // give workgroup b the tile i G + (b + 37 i) mod G in round i (G workgroups), to the same end.
   constexpr bool DYN = !ROOTS && !DELTA;
   const uint32_t G = gridDim.x, step37 = 37u % G;
@@ -430,7 +431,10 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   auto advance = [&](uint32_t round) {                        // next_tile: this workgroup's tile of the next round
     if constexpr (DYN) {
       if (counted()) next_tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_next[round & 1u]);
-      else next_tile = (round + 1u) * G + ((round & 1u) ? blockIdx.x : G - 1u - blockIdx.x);
+      else {
+        const uint32_t last = (ntiles >= G) + (ntiles >= 2u * G) + (ntiles >= 3u * G);   // the round that is not full
+        next_tile = (round + 1u) * G + (((last - round) & 1u) ? blockIdx.x : G - 1u - blockIdx.x);
+      }
     } else {
       tile_base += G;
       tile_pos += step37;
