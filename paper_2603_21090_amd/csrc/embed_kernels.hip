@@ -124,7 +124,9 @@ LaunchArgs make_args(const Dev& d, uint32_t layer) {
   a.es = d.es != 0;
   a.ks = d.ks; a.nt = d.nt; a.heads = d.heads;
   a.num_cu = d.num_cu;
-  a.lds = (size_t)layer_impl::layer_lds(L.d_in, d.heads, d.ks, d.nz, d.k, d.delta != 0).total * sizeof(float);
+  a.lds = (size_t)layer_impl::layer_lds(L.d_in, d.d_emb, d.heads, d.ks, d.nz, d.k, d.delta != 0, 16).total * sizeof(float);
+  a.lds32 = (size_t)layer_impl::layer_lds(L.d_in, d.d_emb, d.heads, d.ks, d.nz, d.k, false, 32).total * sizeof(float);
+  a.tall = !d.delta && d.ks >= 2 && a.lds32 + 3072 <= kMaxLds / 2;
   a.err = hipSuccess;
   return a;
 }
@@ -261,7 +263,7 @@ int layer_tiles_fit(const Dev& d, uint32_t nz) {
   go_heads(a);
   if (a.wgs == 0) return 0;
   for (uint32_t l = 0; l < d.layers; ++l) {
-    const size_t lds = (size_t)layer_impl::layer_lds(l ? d.d_emb : d.d0, d.heads, d.ks, nz, d.k, false).total * sizeof(float);
+    const size_t lds = (size_t)layer_impl::layer_lds(l ? d.d_emb : d.d0, d.d_emb, d.heads, d.ks, nz, d.k, false, 16).total * sizeof(float);
     if (lds + 3072 > kMaxLds / a.wgs) return 0;
   }
   return 1;

@@ -10,7 +10,7 @@
 // Edge features of at most one 64-float slot are not cached at all (ES variants): the raw row rides with the
 // time encoding, z_j = [phi_j | e_j] in place of phi_j and W[time | edge] in place of W[time] above, and the
 // cached rows hold the node terms alone.
-// A workgroup of eight waves (four: rows of one slot, delta mode) owns 16 target rows and runs its phases without
+// A workgroup of eight waves (four: rows of one slot, delta mode) owns 16 target rows, or 32 of a long list, and runs its phases without
 // leaving the CU:
 //   1. q  = h_v W_Q(node block) + phi(0) W_Q(time block)                           (MFMA 16x16x4)
 //   2. qt_h = q_h W_K,h[time]^T                                                     (MFMA)
@@ -32,6 +32,7 @@
 // nodes, d_edge 172, 190 -> 180 and 204 -> 188; a rebuild of 200,000 nodes 662 + 429 -> 585 + 396.  Whole tables
 // lie 1e-7 to 2.9e-7 (2-norm) and up to 2.6e-6 of the root mean square (largest) off 64-bit results.
 #pragma once
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 #include "stgn_internal.h"
@@ -41,7 +42,7 @@ namespace stgn {
 
 namespace layer_impl {
 
-constexpr uint32_t kTM = 16;   // target rows per workgroup
+constexpr uint32_t kTM = 16;   // rows of a row tile
 
 template <int CTRL>
 __device__ inline float dpp_mov(float x) {
@@ -86,23 +87,40 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 struct LayerLds {
-  uint32_t ldx, ldq, ldz;        // strides (floats) of the X / O tile, the Q / H' tile and the qt / pb tile
-  uint32_t off_q, off_z, off_r, off_sc, total;
+  uint32_t ldx, ldq, ldz;        // strides (floats) of the input tile, the Q / H' tile and the qt / pb tile
+  uint32_t wx;                   // floats of an input row that are written and read
+  uint32_t off_x, off_q, off_z, off_r, off_sc, total;
 };
 
 // Every stride is 4 (mod 8) floats: rows stay 16-byte aligned and the 16 rows of an operand read
 // fall into distinct banks.  ks = key slots (heads * slots per head), nz = slots of z = [phi | raw edge row].
-__host__ __device__ inline LayerLds layer_lds(uint32_t d_in, uint32_t heads, uint32_t ks, uint32_t nz, uint32_t k, bool delta) {
+//
+// Sixteen rows: the input tile and the cached part of the head outputs share storage.  Thirty-two: both move in with others, so
+// that two workgroups of the widest common shapes fit a CU (two slots, two heads, two time slots, raw edge rows, k = 20: 79 KB,
+// where storage of its own for each makes 94).  The cached part of the head outputs lies where q was and is completed in place,
+// and a row's input lies behind the columns of its output row in the row's share of the qt / pb tile.
+__host__ __device__ inline LayerLds layer_lds(uint32_t d_in, uint32_t d_emb, uint32_t heads, uint32_t ks, uint32_t nz, uint32_t k, bool delta, uint32_t tm) {
   LayerLds l;
-  const uint32_t wx = round_up(d_in, kGrpK), wo = kSlot * ks;
-  l.ldx = (wx > wo ? wx : wo) + 4;                // the input tile and the cached part of the head outputs share storage
+  const uint32_t wx = round_up(d_in, kGrpK), wo = kSlot * ks, wh = round_up(d_emb, kChunkK);
   l.ldq = wo + 4;                                 // q in the padded-head layout, later the head outputs
   l.ldz = heads * kSlot * nz + 4;
-  l.off_q = kTM * l.ldx;
-  l.off_z = l.off_q + kTM * l.ldq;
-  l.off_r = l.off_z + kTM * l.ldz;
-  l.off_sc = l.off_r + kTM * k * 4;               // the ring records of the tile's rows, 16 bytes each
-  l.total = l.off_sc + (delta ? kTM * k * heads : 0u);       // delta mode: the scores of a row's entries until its weights are known
+  if (tm == 16) {
+    l.ldx = (wx > wo ? wx : wo) + 4;
+    l.wx = l.ldx - 4;
+    l.off_x = 0;
+    l.off_q = tm * l.ldx;
+    l.off_z = l.off_q + tm * l.ldq;
+  } else {
+    if (l.ldz < wh + wx + 4) l.ldz = wh + wx + 4;
+    l.ldx = l.ldz;
+    l.wx = wx;
+    l.off_q = 0;
+    l.off_z = tm * l.ldq;
+    l.off_x = l.off_z + wh;
+  }
+  l.off_r = l.off_z + tm * l.ldz;
+  l.off_sc = l.off_r + tm * k * 4;                // the ring records of the tile's rows, 16 bytes each
+  l.total = l.off_sc + (delta ? tm * k * heads : 0u);        // delta mode: the scores of a row's entries until its weights are known
   return l;
 }
 
@@ -181,6 +199,11 @@ __device__ inline void wave_lds_fence() {
 // heads of 32, 20,000 nodes, 110 -> 75; 10,000 nodes, one tile per workgroup, 33 -> 31.
 __host__ __device__ constexpr int layer_waves(int ks, bool delta) { return delta || ks == 1 ? 4 : 8; }
 
+// How a workgroup's tiles are chosen: in a fixed order, by the counter, by the one or the other as the list is short or long, or
+// in a rotating order (see `advance`).  A short list: at most kShortTiles tiles of sixteen rows for every workgroup.
+enum { kFixed, kCounted, kByLength, kRotated };
+constexpr uint32_t kShortTiles = 4;
+
 // KS key slots in total (heads x slots per head), NT time slots; JC ring entries fetched together.
 // ES = 1: raw edge rows.  The vector z_j = [phi(dt_j) | f_j] of NZ = NT + 1 slots takes the place of phi(dt_j)
 // in the re-associated time products (scores: (W_K,h[time | edge] q_h) . z_j; values: (sum_j a_j z_j)
@@ -189,20 +212,22 @@ __host__ __device__ constexpr int layer_waves(int ks, bool delta) { return delta
 // QCACHE: rows may read q and qt back from the query cache.
 // ROOTS: root-node inference (LayerArgs::root_src and on).  A variant of its own and not a test at run time: the
 // places that differ would cost every streamed launch registers.
-template <int KS, int NT, int ES, int H, int JC, int WGS, bool DELTA, bool QCACHE, bool ROOTS>
-__global__ __launch_bounds__(64 * layer_waves(KS, DELTA), WGS * layer_waves(KS, DELTA) / 4)
-void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t* count_ptr, uint32_t count_max) {
+// RT: row tiles of a workgroup.
+template <int KS, int NT, int ES, int H, int JC, bool DELTA, bool QCACHE, bool ROOTS, int RT, int ORDER>
+__device__ __forceinline__
+void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uint32_t n) {
+  constexpr uint32_t TM = kTM * RT;           // rows of a workgroup
   extern __shared__ __align__(16) float lds[];
   constexpr int NW = layer_waves(KS, DELTA);  // waves
   constexpr uint32_t TH = 64u * NW;           // threads
   constexpr int NTL = 8 / NW;                 // column tiles a wave multiplies together in the dense phases
-  constexpr int RPW = (int)kTM / NW;          // rows a wave serves
+  constexpr int RPW = (int)TM / NW;          // rows a wave serves
   constexpr uint32_t LS = 64u / RPW;          // lanes per row while the rows are staged
-  constexpr int NI = NTL;                     // ring slots and input quads per lane that are fetched a tile ahead
+  constexpr int NI = RPW / 2;                 // ring slots and input quads per lane that are fetched a tile ahead
   constexpr int GPR = DELTA ? 1 : KS;         // 16-lane groups per row in phase 3: one per key slot
   constexpr int RPP = 4 / GPR;                // rows a wave works on at a time there
   constexpr int PASSES = RPW / RPP;
-  __shared__ uint32_t s_node[2][kTM], s_sum[NW], s_next[2];
+  __shared__ uint32_t s_node[2][TM], s_sum[NW], s_next[2];
   __shared__ __align__(16) double s_om[NT * kSlot], s_ph[NT * kSlot];
   static_assert(KS % H == 0, "whole slots per head");
   static_assert(!(DELTA && ES), "the delta mode keeps projected edge rows");
@@ -212,9 +237,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   constexpr uint32_t Ztp = NZ * kSlot;        // floats of one head's qt / pb vector
   // (a batch that failed validation leaves every per-layer count at zero: nothing to test here, and the
   // control block's batch fields may already belong to the next batch, whose front part runs concurrently)
-  uint32_t n = count_max;
-  if (count_ptr) { const uint32_t c = *count_ptr; n = c < count_max ? c : count_max; }
-  const uint32_t ntiles = (n + kTM - 1) / kTM;
+  const uint32_t ntiles = (n + TM - 1) / TM;
   if (blockIdx.x >= ntiles) return;           // (a workgroup's first tile is the one of its index)
   // The lane index and everything derived from it are derived anew at the top of every tile and of its phases, from
   // the lane counter and behind the compiler's back: otherwise it hoists dozens of loop-invariant address registers out
@@ -227,9 +250,11 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   const uint32_t ntd = round_up(a.d_emb, 16) >> 4, ntk = round_up(dk, 16) >> 4;                           // column tiles
   constexpr uint32_t ntz = Ztp >> 4;                                                                       // tiles of a qt vector
   const uint32_t nzt_t = (a.d_time + 15u) >> 4, nzt = nzt_t + (ES ? (a.d_edge + 15u) >> 4 : 0u);           // ... that hold valid columns
-  const LayerLds ll = layer_lds(a.d_in, H, KS, NZ, k, DELTA);
-  float* Xs = lds;                            // input rows (phase 1), then the cached-value part of the head outputs (phases 3-4)
+  const LayerLds ll = layer_lds(a.d_in, a.d_emb, H, KS, NZ, k, DELTA, TM);
+  float* Xs = lds + ll.off_x;                 // input rows (phase 1)
   float* Qs = lds + ll.off_q;                 // q (phases 1-3), then the head outputs (phases 4-5)
+  float* As = RT == 1 ? Xs : Qs;              // the cached-value part of the head outputs (phases 3-4)
+  const uint32_t ldas = RT == 1 ? ll.ldx : ll.ldq;
   float* Zs = lds + ll.off_z;                 // qt (phases 2-3), then pb (phases 3-4), then the output rows (phases 5-6)
   RingEntry* Rs = reinterpret_cast<RingEntry*>(__builtin_assume_aligned(lds + ll.off_r, 16));   // [row][j], j = 0 the most recent entry
   using ZBuf = GatherBuf<JC, ES>;
@@ -285,14 +310,17 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     load_b16(wkt(u.h, u.t0), 0, o.b[0], lane);
     if constexpr (NTL == 2) load_b16(wkt(u.h, u.t1), 0, o.b[1], lane);
   };
-  auto store2 = [&](const Unit2& u, const floatx4 (&acc)[NTL]) {
-    float* zp = Zs + u.h * Ztp + m16_row(lane, 0) * ll.ldz + m16_col(lane);
+  auto store2 = [&](const Unit2& u, const floatx4 (&acc)[RT][NTL]) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) zp[u.t0 * 16 + r * ll.ldz] = acc[0][r];
-    if constexpr (NTL == 2) {
-      if (u.two) {
+    for (int rt = 0; rt < RT; ++rt) {
+      float* zp = Zs + u.h * Ztp + (kTM * rt + m16_row(lane, 0)) * ll.ldz + m16_col(lane);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) zp[u.t1 * 16 + r * ll.ldz] = acc[1][r];
+      for (int r = 0; r < 4; ++r) zp[u.t0 * 16 + r * ll.ldz] = acc[rt][0][r];
+      if constexpr (NTL == 2) {
+        if (u.two) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) zp[u.t1 * 16 + r * ll.ldz] = acc[rt][1][r];
+        }
       }
     }
   };
@@ -316,7 +344,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   // hides them.  All but a workgroup's first tile start without waiting for memory.  Shapes whose share does not
   // fit the registers fetch it inside `commit` instead.
   const uint32_t qpr = round_up(a.d_in, kGrpK) >> 2;          // 16-byte quads per staged input row
-  const bool pf_ok = QCACHE || (kTM * k <= 512u && kTM * qpr <= 512u);   // (the query cache is kept for such shapes only)
+  const bool pf_ok = QCACHE || (k <= LS * NI && qpr <= LS * NI);   // (the query cache is kept for such shapes only)
   RingEntry p_ring[NI];
   uint32_t p_deg = 0;
   double p_tl = 0.0;
@@ -325,7 +353,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   uint32_t p_row = 0xFFFFFFFFu, p_clean = 0u;
   double p_tqn = 0.0;
   auto stage_a = [&](uint32_t t) {
-    const uint32_t r = t * kTM + wave * RPW + lane / LS;
+    const uint32_t r = t * TM + wave * RPW + lane / LS;
     const uint32_t rc = r < n ? r : n - 1u;                   // (past the list: its last row, dropped in stage B)
     if constexpr (ROOTS) {
       p_row = ((rc & 1u) ? a.root_dst : a.root_src)[rc >> 1];
@@ -336,7 +364,11 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     if constexpr (QCACHE && !ROOTS) {                         // (a byte of a word that no lane has to hold: scalar)
       const uint32_t tc = t < ntiles ? t : ntiles - 1u;
       typedef const __attribute__((address_space(4))) uint32_t* ScalarWords;
-      p_clean = (((ScalarWords)(uintptr_t)a.tile_clean)[tc >> 2] >> (8u * (tc & 3u))) & 0xFFu;
+      if constexpr (RT == 1) {
+        p_clean = (((ScalarWords)(uintptr_t)a.tile_clean)[tc >> 2] >> (8u * (tc & 3u))) & 0xFFu;
+      } else {                                                // (a byte per 16 rows; one past the list's end may be either)
+        p_clean = ((((ScalarWords)(uintptr_t)a.tile_clean)[tc >> 1] >> (16u * (tc & 1u))) & 0x0101u) == 0x0101u ? 1u : 0u;
+      }
     }
   };
   // (requests without conditions: behind a branch the compiler would wait for more than it needs to)
@@ -344,7 +376,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     const bool cl = QCACHE && (ROOTS || p_clean != 0u);
     const uint32_t it = lane % LS;
     const ArgBlock ab = args();
-    if (t * kTM + wave * RPW + lane / LS >= n || (ROOTS && p_row >= a.nodes)) p_row = 0xFFFFFFFFu;
+    if (t * TM + wave * RPW + lane / LS >= n || (ROOTS && p_row >= a.nodes)) p_row = 0xFFFFFFFFu;
     const size_t nn = p_row != 0xFFFFFFFFu ? p_row : 0u;
     p_deg = ab->deg[nn];
     p_tl = ROOTS ? p_tqn : ab->t_last[nn];
@@ -365,7 +397,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   double tq_s = 0.0;
   // Input rows into Xs.  Columns up to the end of the last chunk are written (zero past d_in): what else lies there need
   // not be a number.
-  const uint32_t qpz = min(kChunkK / 4u * c_in, (ll.ldx - 4u) >> 2);
+  const uint32_t qpz = min(kChunkK / 4u * c_in, ll.wx >> 2);
   auto place_x = [&](uint32_t q, float4 v) {
     if (q >= qpr || node_s == 0xFFFFFFFFu) v = make_float4(0.f, 0.f, 0.f, 0.f);
     *reinterpret_cast<float4*>(Xs + (wave * RPW + lane / LS) * ll.ldx + 4u * q) = v;
@@ -418,18 +450,17 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   // 4,096 rows (long rows first) and a fixed position would hand the same workgroups every long tile, and the last round
   // forwards, since the workgroups of low index start first (backwards: 119 -> 128 and 188 -> 208 us).  The other modes
   // give workgroup b the tile i G + (b + 37 i) mod G in round i (G workgroups), to the same end.
-  constexpr bool DYN = !ROOTS && !DELTA;
   const uint32_t G = gridDim.x, step37 = 37u % G;
   uint32_t tile_base = 0, tile_pos = blockIdx.x, next_tile = blockIdx.x, taken = 0;
-  auto counted = [&]() { return ntiles > 4u * G; };
+  auto counted = [&]() { return ORDER == kCounted || (ORDER == kByLength && ntiles > kShortTiles * G); };
   auto take = [&]() {
     taken = 0u;                                               // (not carried from tile to tile)
-    if (counted() && wave == 0u && lane == 0u)
+    if (ORDER != kRotated && counted() && wave == 0u && lane == 0u)
       taken = G + __hip_atomic_fetch_add(args()->tile_next, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
-  auto publish = [&](uint32_t round) { if (counted() && wave == 0u && lane == 0u) s_next[round & 1u] = taken; };
+  auto publish = [&](uint32_t round) { if (ORDER != kRotated && counted() && wave == 0u && lane == 0u) s_next[round & 1u] = taken; };
   auto advance = [&](uint32_t round) {                        // next_tile: this workgroup's tile of the next round
-    if constexpr (DYN) {
+    if constexpr (ORDER != kRotated) {
       if (counted()) next_tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_next[round & 1u]);
       else {
         const uint32_t last = (ntiles >= G) + (ntiles >= 2u * G) + (ntiles >= 3u * G);   // the round that is not full
@@ -445,17 +476,26 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
 
   // ---- phase 3's rows: pass p works on rows p RPP .. p RPP + RPP - 1 of the wave's, GPR groups of 16 lanes each,
   // group g on key slot g.  With one pass a lane's row is the one it staged, else the pass has one row.
-  static_assert(PASSES == 1 || RPP == 1, "a pass is either all rows of the wave or one of them");
+  constexpr bool LAZY = RT > 1;                               // a pass's query and first gather are requested when the pass before is over
+  static_assert(PASSES == 1 || RPP == 1 || (RPP == 2 && PASSES == 2), "rows of a pass");
   uint32_t g = 0, head = 0, sg = 0;                           // this lane's key slot, its head and its place among the head's slots
   auto derive_slot = [&]() { g = GPR == 1 ? 0u : grp % GPR; head = g / SH; sg = g - head * SH; };
-  auto row_of = [&](int p) { return wave * RPW + (PASSES == 1 ? lane / LS : (uint32_t)p); };
-  auto node_of = [&](int p) { return PASSES == 1 ? node_s : (uint32_t)__builtin_amdgcn_readlane((int)node_s, p * (int)LS); };
-  auto cnt_of = [&](int p) { return PASSES == 1 ? cnt_s : (uint32_t)__builtin_amdgcn_readlane((int)cnt_s, p * (int)LS); };
+  auto row_of = [&](int p) { return wave * RPW + (uint32_t)(p * RPP) + (RPP == 1 ? 0u : grp / GPR); };
+  // the staged value of the row that this lane works on in pass p
+  auto of_pass = [&](uint32_t x, int p) -> uint32_t {
+    if constexpr (PASSES == 1) return x;
+    else if constexpr (RPP == 1) return (uint32_t)__builtin_amdgcn_readlane((int)x, p * (int)LS);
+    else {                                                    // groups {0, 0, 1, 1} in pass 0, {2, 2, 3, 3} in pass 1
+      const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+      const auto q = __builtin_amdgcn_permlane32_swap((uint32_t)r[0], (uint32_t)r[1], false, false);
+      return p ? (uint32_t)q[1] : (uint32_t)q[0];
+    }
+  };
+  auto node_of = [&](int p) { return of_pass(node_s, p); };
+  auto cnt_of = [&](int p) { return of_pass(cnt_s, p); };
   auto tq_of = [&](int p) {
-    if constexpr (PASSES == 1) return tq_s;
     const uint64_t u = __builtin_bit_cast(uint64_t, tq_s);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, p * (int)LS);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), p * (int)LS);
+    const uint32_t lo = of_pass((uint32_t)u, p), hi = of_pass((uint32_t)(u >> 32), p);
     return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
   };
   auto cmax_of = [&](int p) {
@@ -464,8 +504,8 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     for (int r = 1; r < RPP; ++r) m = max(m, (uint32_t)__builtin_amdgcn_readlane((int)cnt_s, (p * RPP + r) * (int)LS));
     return m;
   };
-  auto gather = [&](int p, uint32_t c, ZBuf& zb) {
-    const RingEntry* rrow = Rs + row_of(p) * k;
+  auto gather_row = [&](uint32_t row, uint32_t c, ZBuf& zb) {
+    const RingEntry* rrow = Rs + row * k;
 #pragma unroll
     for (int jc = 0; jc < JC; ++jc) {
       const uint32_t j = c * JC + jc;
@@ -483,25 +523,27 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
       zb.t[jc] = e.t;
     }
   };
+  auto gather = [&](int p, uint32_t c, ZBuf& zb) { gather_row(row_of(p), c, zb); };
   // z slots a lane works with: all of them when a head is one slot (every head needs them all); shared out over the
   // head's slots otherwise, slot t to the lanes of key slot t mod SH
   constexpr int NZL = SH == 1 ? NZ : (NZ + SH - 1) / SH;
-  ZBuf z0[PASSES];                                            // the first gather
-  float4 qk[PASSES], qt[PASSES][NZL];                         // this lane's share of the row's q and qt vectors
-  auto request_first = [&](auto P) { gather(decltype(P)::value, 0, z0[decltype(P)::value]); };
+  constexpr int NP = LAZY ? 1 : PASSES;                       // passes whose first gather and query are held at once
+  ZBuf z0[NP];                                                // the first gather
+  float4 qk[NP], qt[NP][NZL];                                 // this lane's share of the row's q and qt vectors
+  auto request_first = [&](auto P) { gather(decltype(P)::value, 0, z0[decltype(P)::value % NP]); };
   // the pass's q and qt from the query cache, each lane what it needs, and its first gather
-  auto request_back = [&](auto P) {
+  auto request_query = [&](auto P) {
     constexpr int p = decltype(P)::value;
     const uint32_t node = node_of(p);
     const float* qrow = a.QC + (size_t)(node != 0xFFFFFFFFu ? node : 0u) * kQC + 4u * sub;
-    qk[p] = *reinterpret_cast<const float4*>(qrow + kSlot * g);
+    qk[p % NP] = *reinterpret_cast<const float4*>(qrow + kSlot * g);
 #pragma unroll
     for (int i = 0; i < NZL; ++i) {
       const uint32_t t = SH == 1 ? (uint32_t)i : sg + SH * i;
-      qt[p][i] = *reinterpret_cast<const float4*>(qrow + kSlot * KS + head * Ztp + (t < NZ ? t : 0u) * kSlot);
+      qt[p % NP][i] = *reinterpret_cast<const float4*>(qrow + kSlot * KS + head * Ztp + (t < NZ ? t : 0u) * kSlot);
     }
-    request_first(P);
   };
+  auto request_back = [&](auto P) { request_query(P); request_first(P); };
   constexpr std::integral_constant<int, 0> kPass0{};
 
   // Weights of phases 1 and 2: the first units' chunks, requested together.
@@ -524,24 +566,27 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   };
 
   // the first tile
-  if constexpr (DYN) take();
+  take();
   stage_a(blockIdx.x);
   stage_b(blockIdx.x);
   commit(0u);
-  if constexpr (DYN) publish(0u);
+  publish(0u);
   commit_x(pf_ok);
   derive_slot();
   if constexpr (QCACHE) request_back(kPass0);
   __syncthreads();
 
-  // What separates a tile's uses of the LDS from the next tile's.  Ring records: a wave reads only its own rows'.  Xs holds the
+  // (Sixteen rows; for 32 rows see below.)  What separates a tile's uses of the LDS from the next tile's.  Ring records: a wave reads only its own rows'.  Xs holds the
   // input rows (phase 1), then the cached-value part of the head outputs (read in phase 4), and takes the next tile's
   // input rows behind the barrier in front of phase 5.  Qs holds q, then the whole head outputs (phase 5): a projecting tile has a
   // barrier ahead of its phase 1, a tile that reads q back writes Qs behind its first barrier.  Zs holds qt, pb, then the output
   // rows (phase 6, link scores): projecting tiles have two barriers ahead of their qt, and where tiles may read theirs back, a
   // tile that stored output rows there ends with one.
+  // Thirty-two rows (layer_lds): Qs also takes the cached-value part and is completed in place, so every tile of a variant
+  // that may read q back ends with a barrier; input rows lie behind the output row's columns of the same row of Zs, whose
+  // last reader is phase 4, and phase 2 writes there behind the barrier that ends phase 1.
   const bool kv = !ROOTS && a.KVout != nullptr, rows_in_lds = ROOTS || kv;
-  constexpr bool kRowsInZ = H * NZ >= KS;                     // (wide heads of few time slots: Zs is narrower than a row, they take Xs)
+  constexpr bool kRowsInZ = RT > 1 || H * NZ >= KS;                     // (wide heads of few time slots: Zs is narrower than a row, they take Xs)
   float* const Hs = kRowsInZ ? Zs : Xs;                       // output rows
   const uint32_t ldh = kRowsInZ ? ll.ldz : ll.ldx;
   // One tile.  CLEAN: every row of it has its q and qt in the query cache.  Two copies of the body and not tests inside
@@ -561,7 +606,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
       ex = a.force_exact || fl == 1u || (fl != 0u && fl <= a.thr_in);
     }
     if constexpr (clean) {
-      if constexpr (PASSES == 2) request_back(std::integral_constant<int, 1>{});
+      if constexpr (NP == 2) request_back(std::integral_constant<int, 1>{});
       stage_a(next_tile);                          // row ids of this workgroup's next tile
     } else {
     // ================================================================ phase 1: q = x W_Q + c_Q
@@ -573,16 +618,19 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
       commit_x(false);
     }
     __syncthreads();                                          // input rows there, the previous tile's head outputs read
-    auto store1 = [&](uint32_t nt, const floatx4 (&acc)[NTL]) {
+    auto store1 = [&](uint32_t nt, const floatx4 (&acc)[RT][NTL]) {
 #pragma unroll
       for (int t = 0; t < NTL; ++t) {
         const uint32_t col = (nt + NW * t) * 16 + m16_col(lane);
         if (nt + NW * t < ntd && col < a.d_emb) {
           const float cq = nt == wave ? c1v[t] : a.cQ[col];
           const uint32_t h = H == 1 ? 0u : H == 2 ? (col >= dk ? 1u : 0u) : (col >= dk ? 1u : 0u) + (col >= 2u * dk ? 1u : 0u) + (col >= 3u * dk ? 1u : 0u);
-          float* qp = Qs + m16_row(lane, 0) * ll.ldq + h * (SH * kSlot) + (col - h * dk);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) qp[r * ll.ldq] = acc[t][r] + cq;
+          for (int rt = 0; rt < RT; ++rt) {
+            float* qp = Qs + (kTM * rt + m16_row(lane, 0)) * ll.ldq + h * (SH * kSlot) + (col - h * dk);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) qp[r * ll.ldq] = acc[rt][t][r] + cq;
+          }
         }
       }
     };
@@ -590,16 +638,16 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
       const float* B1[NTL];
 #pragma unroll
       for (int t = 0; t < NTL; ++t) B1[t] = tile_b(a.WQ, w1, t, ntd, c_in);
-      floatx4 acc[NTL] = {};
-      u1.multiply(Xs + a16_off(lane, ll.ldx), c_in, B1, acc, lane, last_group(ll.ldx));
+      floatx4 acc[RT][NTL] = {};
+      u1.template multiply_rows<RT>(Xs + a16_off(lane, ll.ldx), kTM * ll.ldx, c_in, B1, acc, lane, ll.wx / kGrpK - 1u);
       store1(wave, acc);
     }
     for (uint32_t nt = wave + 8; nt < ntd; nt += 8) {
       const float* Bt[NTL];
 #pragma unroll
       for (int t = 0; t < NTL; ++t) Bt[t] = tile_b(a.WQ, nt, t, ntd, c_in);
-      floatx4 acc[NTL] = {};
-      mfma16_lean<NTL>(Xs + a16_off(lane, ll.ldx), 0u, c_in, Bt, acc, lane, last_group(ll.ldx));
+      floatx4 acc[RT][NTL] = {};
+      mfma16_lean_rows<RT, NTL>(Xs + a16_off(lane, ll.ldx), kTM * ll.ldx, 0u, c_in, Bt, acc, lane, ll.wx / kGrpK - 1u);
       store1(nt, acc);
     }
     __syncthreads();
@@ -608,15 +656,14 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
       const float* qa = Qs + a16_off(lane, ll.ldq);
       auto products2 = [&](uint32_t i, Ops16<NTL>& o) {
         const Unit2 u = decode2(i);
-        floatx4 acc[NTL] = {};
+        floatx4 acc[RT][NTL] = {};
         const float* qh = qa + u.h * (SH * kSlot);
-        load_a16(qh, 0, o.a);
-        mfma16_chunk<NTL>(o, acc);
+        mfma16_chunk_rows<RT, NTL>(qh, kTM * ll.ldq, 0, o.b, acc);
         if constexpr (SH > 1) {
           const float* Bt[NTL];
           Bt[0] = wkt(u.h, u.t0);
           if constexpr (NTL == 2) Bt[1] = wkt(u.h, u.t1);
-          mfma16_lean<NTL>(qh, 1u, SH, Bt, acc, lane);
+          mfma16_lean_rows<RT, NTL>(qh, kTM * ll.ldq, 1u, SH, Bt, acc, lane);
         }
         store2(u, acc);
       };
@@ -636,7 +683,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
         }
       }
     }
-    if constexpr (!DELTA) static_for<PASSES>(request_first);
+    if constexpr (!DELTA) static_for<NP>(request_first);
     __syncthreads();
     }  // q and qt: read back, or projected
     // The time encodings are not masked per entry: a column past d_time has omega = phase = 0 and comes out as
@@ -652,25 +699,22 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
       o.z = c0 + 2u < end ? o.z : 0.0f;
       o.w = c0 + 3u < end ? o.w : 0.0f;
     };
-    if constexpr (!DELTA) {
-      if constexpr (!clean) {
-        static_for<PASSES>([&](auto P) {
+    auto read_query = [&](auto P) {                           // a projected row's q and qt
           constexpr int p = decltype(P)::value;
           const uint32_t node = node_of(p), local = row_of(p);
-          qk[p] = *reinterpret_cast<const float4*>(Qs + local * ll.ldq + kSlot * g + 4u * sub);
+          qk[p % NP] = *reinterpret_cast<const float4*>(Qs + local * ll.ldq + kSlot * g + 4u * sub);
           float* qrow = a.QC + (size_t)node * kQC + 4u * sub;
           const bool keep = !ROOTS && a.QC && node != 0xFFFFFFFFu;             // the rows' q | qt for later batches
-          if (keep) *reinterpret_cast<float4*>(qrow + kSlot * g) = qk[p];
+          if (keep) *reinterpret_cast<float4*>(qrow + kSlot * g) = qk[p % NP];
 #pragma unroll
           for (int i = 0; i < NZL; ++i) {
             const uint32_t t = SH == 1 ? (uint32_t)i : sg + SH * i, at = head * Ztp + (t < NZ ? t : 0u) * kSlot;
-            qt[p][i] = *reinterpret_cast<const float4*>(Zs + local * ll.ldz + at + 4u * sub);
-            if (SH > 1 || i >= NT - 1) clear_padding(qt[p][i], t);
-            if (keep && t < NZ) *reinterpret_cast<float4*>(qrow + kSlot * KS + at) = qt[p][i];
+            qt[p % NP][i] = *reinterpret_cast<const float4*>(Zs + local * ll.ldz + at + 4u * sub);
+            if (SH > 1 || i >= NT - 1) clear_padding(qt[p % NP][i], t);
+            if (keep && t < NZ) *reinterpret_cast<float4*>(qrow + kSlot * KS + at) = qt[p % NP][i];
           }
-        });
-      }
-    }
+    };
+    if constexpr (!DELTA && !clean) static_for<NP>(read_query);
     // ================================================================ phase 3: gather + attention
     if constexpr (DELTA) {
       // ---- delta mode.  An exact row runs the same online softmax as the exact mode and leaves its attention
@@ -963,9 +1007,9 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
           // score: q . (cached node keys + cached edge keys) + qt . phi  (raw edge rows: q . node keys + qt . z)
           float4 kk = zb.nk[jc];
           if constexpr (!ES) { kk.x += zb.e[jc][0].x; kk.y += zb.e[jc][0].y; kk.z += zb.e[jc][0].z; kk.w += zb.e[jc][0].w; }
-          float s = dot4(qk[p], kk, 0.0f);
+          float s = dot4(qk[p % NP], kk, 0.0f);
 #pragma unroll
-          for (int i = 0; i < NZL; ++i) s = dot4(qt[p][i], zt[jc][i], s);
+          for (int i = 0; i < NZL; ++i) s = dot4(qt[p % NP][i], zt[jc][i], s);
           s = row16_sum(s);
           if constexpr (SH >= 2) { const Two w = both_of_pair(s); s = w.lo + w.hi; }
           if constexpr (SH == 4) { const Two w = both_halves(s); s = w.lo + w.hi; }
@@ -1004,12 +1048,40 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
           }
         }
       };
-      if (nchunk3) pingpong_clamped<ZBuf>(nchunk3, z0[p], [&](uint32_t c, ZBuf& zb) { gather(p, c, zb); }, attend);
+      if constexpr (LAZY && p + 1 < PASSES) {
+        // the next pass's first gather takes the place of the request past this one's end
+        constexpr std::integral_constant<int, p + 1> kNext{};
+        ZBuf& P = z0[0];
+        ZBuf Q;
+        if (nchunk3 == 0u) gather(p + 1, 0, P);
+        for (uint32_t i = 0; i < nchunk3; i += 2) {
+          gather(p, i + 1 < nchunk3 ? i + 1 : nchunk3 - 1, Q);
+          __builtin_amdgcn_sched_barrier(0);
+          attend(i, P);
+          __builtin_amdgcn_sched_barrier(0);
+          gather_row(i + 2 < nchunk3 ? row_of(p) : row_of(p + 1), i + 2 < nchunk3 ? i + 2 : 0u, P);
+          __builtin_amdgcn_sched_barrier(0);
+          if (i + 1 < nchunk3) attend(i + 1, Q);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (clean) request_query(kNext); else read_query(kNext);
+      } else {
+        if (nchunk3) pingpong_clamped<ZBuf>(nchunk3, z0[p % NP], [&](uint32_t c, ZBuf& zb) { gather(p, c, zb); }, attend);
+      }
       // the cached-value part of the head outputs goes into Xs (padded-head layout; the padding lanes hold exact
       // zeros), pb where qt is (each lane owns its columns)
       const float inv = reciprocal(lrun);                     // no entry, or none inside the window: b_O alone
       accv.x *= inv; accv.y *= inv; accv.z *= inv; accv.w *= inv;
-      *reinterpret_cast<float4*>(Xs + local * ll.ldx + kSlot * g + 4u * sub) = accv;
+      if constexpr (RT > 1) {
+        // (the next tile's q comes to lie here, and phase 2 reads its padding columns, against zero weights: they must not
+        // be this row's, whose sums may be NaN)
+        const uint32_t c0 = kSlot * sg + 4u * sub;
+        accv.x = c0 < dk ? accv.x : 0.0f;
+        accv.y = c0 + 1u < dk ? accv.y : 0.0f;
+        accv.z = c0 + 2u < dk ? accv.z : 0.0f;
+        accv.w = c0 + 3u < dk ? accv.w : 0.0f;
+      }
+      *reinterpret_cast<float4*>(As + local * ldas + kSlot * g + 4u * sub) = accv;
 #pragma unroll
       for (int i = 0; i < NZL; ++i) {
         const uint32_t t = SH == 1 ? (uint32_t)i : sg + SH * i;
@@ -1048,23 +1120,25 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     };
     request4();
     stage_b(next_tile);
-    if constexpr (DYN) take();                                // (behind what this tile waits for)
+    take();                                // (behind what this tile waits for)
     __syncthreads();
     if (wave < nunits4) {
       for (;;) {
         const uint32_t h4 = head4(), n0 = N4 * (x4 - h4 * np4);
-        floatx4 acc[N4] = {};
-        u4.multiply(Zs + h4 * Ztp + a16_off(lane, ll.ldz), NZ, B4, acc, lane);
+        floatx4 acc[RT][N4] = {};
+        u4.template multiply_rows<RT>(Zs + h4 * Ztp + a16_off(lane, ll.ldz), kTM * ll.ldz, NZ, B4, acc, lane);
 #pragma unroll
         for (int t = 0; t < N4; ++t) {
           const uint32_t col = (n0 + t) * 16 + m16_col(lane);
           if (n0 + t < ntk && col < dk) {
             const uint32_t at = h4 * (SH * kSlot) + col;      // one lane per (row, column)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const uint32_t row = m16_row(lane, r);
-              Qs[row * ll.ldq + at] = Xs[row * ll.ldx + at] + acc[t][r];
-            }
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) {
+                const uint32_t row = kTM * rt + m16_row(lane, r);
+                Qs[row * ll.ldq + at] = As[row * ldas + at] + acc[rt][t][r];
+              }
           }
         }
         x4 += NW;
@@ -1076,7 +1150,7 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     derive_lane();
     request5();
     commit(round + 1u);
-    if constexpr (DYN) publish(round + 1u);
+    publish(round + 1u);
     if constexpr (QCACHE) { derive_slot(); request_back(kPass0); }           // (a tile that projects does not use them)
     __syncthreads();
     if (kRowsInZ || !rows_in_lds) {                           // the next tile's input rows, if it projects
@@ -1084,19 +1158,21 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     }
     // a load behind a store waits for it: the first units' results stay in registers until everything that the following
     // phases read has been requested
-    auto bias5 = [&](uint32_t nt, const floatx4 (&acc)[NTL], floatx4 (&o)[NTL]) {
+    auto bias5 = [&](uint32_t nt, const floatx4 (&acc)[RT][NTL], floatx4 (&o)[RT][NTL]) {
 #pragma unroll
       for (int t = 0; t < NTL; ++t) {
         const uint32_t col = (nt + NW * t) * 16 + m16_col(lane);
         const float b = nt == wave ? b5v[t] : a.bO[col < a.d_emb ? col : 0u];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          o[t][r] = acc[t][r] + b;
-          if (rows_in_lds && nt + NW * t < ntd && col < a.d_emb) Hs[m16_row(lane, r) * ldh + col] = o[t][r];   // for the link scores; operand of phase 6
-        }
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            o[rt][t][r] = acc[rt][t][r] + b;
+            if (rows_in_lds && nt + NW * t < ntd && col < a.d_emb) Hs[(kTM * rt + m16_row(lane, r)) * ldh + col] = o[rt][t][r];   // for the link scores; operand of phase 6
+          }
       }
     };
-    auto store5 = [&](uint32_t nt, const floatx4 (&acc)[NTL]) {
+    auto store5 = [&](uint32_t nt, const floatx4 (&acc)[RT][NTL]) {
       if constexpr (!ROOTS) {
         float* const hout = args()->Hout;
 #pragma unroll
@@ -1104,38 +1180,40 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
           const uint32_t col = (nt + NW * t) * 16 + m16_col(lane);
           if (nt + NW * t < ntd && col < a.d_emb) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const uint32_t node = nodes_s[m16_row(lane, r)];
-              if (node != 0xFFFFFFFFu) hout[(size_t)node * a.ld_out + col] = acc[t][r];
-            }
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) {
+                const uint32_t node = nodes_s[kTM * rt + m16_row(lane, r)];
+                if (node != 0xFFFFFFFFu) hout[(size_t)node * a.ld_out + col] = acc[rt][t][r];
+              }
           }
         }
       }
     };
-    floatx4 out5[NTL] = {};
+    floatx4 out5[RT][NTL] = {};
     if (wave < ntd) {
-      floatx4 acc[NTL] = {};
-      u5.multiply(Qs + a16_off(lane, ll.ldq), KS, B5, acc, lane);
+      floatx4 acc[RT][NTL] = {};
+      u5.template multiply_rows<RT>(Qs + a16_off(lane, ll.ldq), kTM * ll.ldq, KS, B5, acc, lane);
       bias5(wave, acc, out5);
     }
     for (uint32_t nt = wave + 8; nt < ntd; nt += 8) {
       const float* Bt[NTL];
 #pragma unroll
       for (int t = 0; t < NTL; ++t) Bt[t] = tile_b(a.WO, nt, t, ntd, KS);
-      floatx4 acc[NTL] = {}, o[NTL];
-      mfma16_lean<NTL>(Qs + a16_off(lane, ll.ldq), 0u, KS, Bt, acc, lane);
+      floatx4 acc[RT][NTL] = {}, o[RT][NTL];
+      mfma16_lean_rows<RT, NTL>(Qs + a16_off(lane, ll.ldq), kTM * ll.ldq, 0u, KS, Bt, acc, lane);
       bias5(nt, acc, o);
       store5(nt, o);
     }
     if (!kRowsInZ && kv) {                                    // (Xs: what lies past the output row need not be a number)
       const uint32_t w = 64u * c_de - a.d_emb;
-      for (uint32_t x = threadIdx.x; x < kTM * w; x += TH) Xs[(x / w) * ll.ldx + a.d_emb + x % w] = 0.0f;
+      for (uint32_t x = threadIdx.x; x < TM * w; x += TH) Xs[(x / w) * ll.ldx + a.d_emb + x % w] = 0.0f;
     }
     if constexpr (ROOTS) {
       // link scores: a wave takes edges w and on of the tile (the list holds whole edges)
       __syncthreads();
-      for (uint32_t e = wave; e < kTM / 2; e += NW) {
-        const uint32_t i = tile * (kTM / 2) + e;
+      for (uint32_t e = wave; e < TM / 2; e += NW) {
+        const uint32_t i = tile * (TM / 2) + e;
         const float* hu = Hs + 2u * e * ldh;
         const float* hv = hu + ldh;
         float acc = 0.0f;
@@ -1149,16 +1227,18 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
     // A wave takes column tiles w, w + NW, ... of a cached row.  The second tile's chunks follow the first's into the same
     // registers.
     constexpr uint32_t ntkv = 8u * KS;
-    auto store6 = [&](uint32_t nt, const floatx4& acc) {
+    auto store6 = [&](uint32_t nt, const floatx4 (&acc)[RT][1]) {
       float* const kvout = args()->KVout;
       const uint32_t col = nt * 16 + m16_col(lane);           // every column is written: padding columns get exact zeros
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const uint32_t node = nodes_s[m16_row(lane, r)];
-        if (node != 0xFFFFFFFFu) kvout[(size_t)node * (2u * kSlot * KS) + col] = acc[r];
-      }
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const uint32_t node = nodes_s[kTM * rt + m16_row(lane, r)];
+          if (node != 0xFFFFFFFFu) kvout[(size_t)node * (2u * kSlot * KS) + col] = acc[rt][0][r];
+        }
     };
-    floatx4 out6[2][1] = {};
+    floatx4 out6[2][RT][1] = {};
     if (kv) {
       const float* const wkv0 = args()->WKVnext;
       auto wkv = [&](uint32_t nt) { return wkv0 + (size_t)nt * c_de * kChunkFloats; };
@@ -1168,10 +1248,8 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
       load_b16(wkv(wave), 0, b6[0][0], lane);
       load_b16(wkv(wave), c1 * kCG, b6[1][0], lane);
       __syncthreads();
-      auto chunk6 = [&](uint32_t ch, const float4 (&b)[1][kCG], floatx4 (&acc)[1]) {
-        float4 x[kCG];
-        load_a16(Ha, ch * kCG, x);
-        mfma16_chunk<1>(x, b, acc);
+      auto chunk6 = [&](uint32_t ch, const float4 (&b)[1][kCG], floatx4 (&acc)[RT][1]) {
+        mfma16_chunk_rows<RT, 1>(Ha, kTM * ldh, ch * kCG, b, acc);
       };
       chunk6(0, b6[0], out6[0]);
       load_b16(wkv(wave + NW), 0, b6[0][0], lane);
@@ -1182,21 +1260,21 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         const float* const Bt[1] = {wkv(wave + NW * t)};
-        mfma16_lean<1>(Ha, 2u, c_de, Bt, out6[t], lane);
+        mfma16_lean_rows<RT, 1>(Ha, kTM * ldh, 2u, c_de, Bt, out6[t], lane);
       }
       for (uint32_t nt = wave + 2 * NW; nt < ntkv; nt += NW) {
         const float* const Bt[1] = {wkv(nt)};
-        floatx4 acc[1] = {};
-        mfma16_lean<1>(Ha, 0u, c_de, Bt, acc, lane);
-        store6(nt, acc[0]);
+        floatx4 acc[RT][1] = {};
+        mfma16_lean_rows<RT, 1>(Ha, kTM * ldh, 0u, c_de, Bt, acc, lane);
+        store6(nt, acc);
       }
     }
     if (wave < ntd) store5(wave, out5);
     if (kv) {
-      store6(wave, out6[0][0]);
-      store6(wave + NW, out6[1][0]);
+      store6(wave, out6[0]);
+      store6(wave + NW, out6[1]);
     }
-    if (QCACHE && rows_in_lds) __syncthreads();
+    if (QCACHE && (RT > 1 || rows_in_lds)) __syncthreads();
   };
   for (uint32_t round = 0;; ++round) {
     const uint32_t tile = next_tile;
@@ -1230,6 +1308,32 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
   }
 }
 
+template <int KS, int NT, int ES, int H, int JC, int WGS, bool DELTA, bool QCACHE, bool ROOTS>
+__global__ __launch_bounds__(64 * layer_waves(KS, DELTA), WGS * layer_waves(KS, DELTA) / 4)
+void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t* count_ptr, uint32_t count_max) {
+  uint32_t n = count_max;
+  if (count_ptr) { const uint32_t c = *count_ptr; n = c < count_max ? c : count_max; }
+  layer_body<KS, NT, ES, H, JC, DELTA, QCACHE, ROOTS, 1, DELTA || ROOTS ? kRotated : kByLength>(a, rows, n);
+}
+
+// Launches whose list may be long: tiles of 32 rows if it is, of 16 if not (the list's length is known on the device alone).
+// A tile streams every weight from L2 once whatever its rows (232 KB a tile of two slots, where its sixteen rows gather
+// 190 KB), passes its barriers once and waits once for each phase's requests: 39 K cycles a tile of sixteen rows, half of
+// them such waits.  With two row tiles each weight register meets both, the waits are shared by twice the rows, and a
+// wave serves its four rows in two passes (four slots: four), a pass's first gather in flight through the end of the one before.
+// Layer launches of 1,000,000 nodes (mean of both layers) 922 -> 847 us.  Whole batches: 1,000,000 nodes, d_edge 100, 2,146 ->
+// 2,001 us; 1,300,000 nodes, raw edge rows, k = 20, 1,292 -> 1,220; 200,000 nodes rebuilt 1,152 -> 1,093; 100,000 nodes,
+// five to six tiles a workgroup, 446 -> 444.  Where a workgroup has a tile or two, the longer tile loses more than it
+// shares: 10,000 nodes 113 -> 130 us, 20,000 nodes 188 -> 195, 30,000 nodes 252 -> 248, hence the line at kShortTiles.
+template <int KS, int NT, int ES, int H, bool QCACHE>
+__global__ __launch_bounds__(512, 4)
+void layer32_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t* count_ptr, uint32_t count_max) {
+  uint32_t n = count_max;
+  if (count_ptr) { const uint32_t c = *count_ptr; n = c < count_max ? c : count_max; }
+  if (n > kShortTiles * kTM * gridDim.x) layer_body<KS, NT, ES, H, 1, false, QCACHE, false, 2, kCounted>(a, rows, n);
+  else layer_body<KS, NT, ES, H, 1, false, QCACHE, false, 1, kFixed>(a, rows, n);
+}
+
 // ---- dispatch over (heads, key slots, time slots)
 struct LaunchArgs {
   LayerArgs k;
@@ -1240,6 +1344,7 @@ struct LaunchArgs {
   bool roots;                       // the root-node variant (the exact one also in delta mode)
   uint32_t num_cu;                  // compute units of the device
   bool set_attr; size_t lds; hipError_t err;
+  bool tall; size_t lds32;
   int query_wgs; uint32_t wgs;      // query_wgs: only report the workgroups per CU of the variant in `wgs`
 };
 
@@ -1257,7 +1362,18 @@ void go_k(LaunchArgs& a) {
       a.err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)a.lds);
       if (a.err == hipSuccess) granted = a.lds;
     }
+    if constexpr (!DELTA && !ROOTS && KS >= 2) {
+      if (a.err == hipSuccess && a.tall) a.err = hipFuncSetAttribute((const void*)layer32_kernel<KS, NT, ES, H, QCACHE>, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
+    }
     return;
+  }
+  if constexpr (!DELTA && !ROOTS && KS >= 2) {
+    if (a.tall && a.cm > kShortTiles * kTM * std::min(2u * (a.num_cu ? a.num_cu : 256u), kStatSlots)) {
+      auto kern = layer32_kernel<KS, NT, ES, H, QCACHE>;
+      const uint32_t cap = std::min(2u * (a.num_cu ? a.num_cu : 256u), kStatSlots);
+      hipLaunchKernelGGL(kern, dim3(cap), dim3(512), std::max(a.lds32, a.lds), a.s, a.k, a.rows, a.cp, a.cm);
+      return;
+    }
   }
   uint64_t blocks = ((uint64_t)a.cm + kTM - 1) / kTM;
   uint64_t cap = (uint64_t)WGS * (a.num_cu ? a.num_cu : 256u);         // persistent: each workgroup strides over the tiles,

@@ -100,6 +100,50 @@ __device__ inline void mfma16_chunk(const float4 (&a)[kCG], const float4 (&b)[NT
   }
 }
 
+// The same for RT row tiles (`rs` floats apart in LDS) that share the B operand: every B register meets RT A registers.
+template <int RT, int NTL>
+__device__ inline void mfma16_chunk_rows(const float* Ap, uint32_t rs, uint32_t g0, const float4 (&b)[NTL][kCG],
+                                         floatx4 (&acc)[RT][NTL], uint32_t last = kNoLimit) {
+  auto load = [&](int c, float4 (&a)[RT]) {
+    const uint32_t g = g0 + c < last ? g0 + c : last;
+#pragma unroll
+    for (int r = 0; r < RT; ++r) a[r] = *reinterpret_cast<const float4*>(Ap + r * rs + kGrpK * g);
+  };
+  auto mul = [&](int c, const float4 (&a)[RT]) {
+#pragma unroll
+    for (int r = 0; r < RT; ++r) mfma16_one<0, NTL>(a[r], b, c, acc[r]);
+#pragma unroll
+    for (int r = 0; r < RT; ++r) mfma16_one<1, NTL>(a[r], b, c, acc[r]);
+#pragma unroll
+    for (int r = 0; r < RT; ++r) mfma16_one<2, NTL>(a[r], b, c, acc[r]);
+#pragma unroll
+    for (int r = 0; r < RT; ++r) mfma16_one<3, NTL>(a[r], b, c, acc[r]);
+  };
+  if constexpr (RT == 1) {
+    float4 a[kCG][RT];
+#pragma unroll
+    for (int c = 0; c < kCG; ++c) load(c, a[c]);
+#pragma unroll
+    for (int c = 0; c < kCG; ++c) mul(c, a[c]);
+  } else {
+    static_assert(kCG == 4, "written out for four groups");   // (two groups of A in flight: all four would cost 16 registers more and spill)
+    float4 a0[RT], a1[RT];
+    load(0, a0);
+    load(1, a1);
+    __builtin_amdgcn_sched_barrier(0);
+    mul(0, a0);
+    __builtin_amdgcn_sched_barrier(0);
+    load(2, a0);
+    __builtin_amdgcn_sched_barrier(0);
+    mul(1, a1);
+    __builtin_amdgcn_sched_barrier(0);
+    load(3, a1);
+    __builtin_amdgcn_sched_barrier(0);
+    mul(2, a0);
+    mul(3, a1);
+  }
+}
+
 // Operands of one chunk for NTL column tiles.
 template <int NTL>
 struct Ops16 {
@@ -202,6 +246,19 @@ __device__ __forceinline__ void mfma16_lean(const float* Ap, uint32_t c0, uint32
   }
 }
 
+// ... for RT row tiles
+template <int RT, int NTL>
+__device__ __forceinline__ void mfma16_lean_rows(const float* Ap, uint32_t rs, uint32_t c0, uint32_t c1, const float* const (&Bt)[NTL],
+                                                 floatx4 (&acc)[RT][NTL], uint32_t lane, uint32_t last = kNoLimit) {
+#pragma unroll 1
+  for (uint32_t ch = c0; ch < c1; ++ch) {
+    float4 b[NTL][kCG];
+#pragma unroll
+    for (int t = 0; t < NTL; ++t) load_b16(Bt[t], ch * kCG, b[t], lane);
+    mfma16_chunk_rows<RT, NTL>(Ap, rs, ch * kCG, b, acc, last);
+  }
+}
+
 // All weight chunks of a short product at once: for K of at most MAXC chunks the whole B operand of
 // NTL column tiles is requested in one go (MAXC * NTL * 16 registers), typically ahead of the barrier
 // that completes A, and the products then run as the chunks arrive -- one memory latency per product
@@ -228,6 +285,15 @@ struct Upfront16 {
         mfma16_chunk<NTL>(a, b[ch], acc);
       }
     }
+  }
+  // ... for RT row tiles, also where K has more chunks than were requested
+  template <int RT>
+  __device__ __forceinline__ void multiply_rows(const float* Ap, uint32_t rs, uint32_t nchunks, const float* const (&Bt)[NTL],
+                                                floatx4 (&acc)[RT][NTL], uint32_t lane, uint32_t last = kNoLimit) {
+#pragma unroll
+    for (int ch = 0; ch < MAXC; ++ch)
+      if ((uint32_t)ch < nchunks) mfma16_chunk_rows<RT, NTL>(Ap, rs, ch * kCG, b[ch], acc, last);
+    mfma16_lean_rows<RT, NTL>(Ap, rs, MAXC, nchunks, Bt, acc, lane, last);
   }
   // the whole product, also where K has more chunks than were requested
   __device__ __forceinline__ void multiply(const float* Ap, uint32_t nchunks, const float* const (&Bt)[NTL],

@@ -45,3 +45,14 @@ def test_streamed_rows_equal_a_rebuild_at_every_list_length(kw):
     for l in (1, 2):
         assert rows_close(g.get_embeddings(some, layer=l), o.embed_nodes(some, layer=l)).all()
     g.close()
+
+
+@pytest.mark.parametrize("kw", [dict(d_edge=70, heads=2, d_emb=100), dict(d_edge=0, heads=1, d_emb=100), dict(d_edge=0, heads=4, d_emb=60),
+                                dict(d_edge=66, heads=2, d_emb=140, d_time=20)])
+def test_a_nan_stays_in_the_rows_of_its_tile(kw):
+    """Tiles of 32 rows share storage between their phases: one edge with a NaN among its features (no edge features: among a
+    node's) in a late batch, over several tiles per workgroup, reaches the rows that the oracle says it reaches."""
+    from paper_2603_21090_amd import binding
+    from tests.test_gpu_nan import _check
+    w = tiny_workload(**{**dict(num_nodes=40_000, num_edges=60_000, batch=4_000, zipf_s=1.05, d_mem=0, d_node=20, d_time=70, k=3), **kw})
+    _check(binding, w, **(dict(edge=1) if w.d_edge else dict(node="quiet")))
