@@ -53,10 +53,9 @@ def algorithmic_bytes(w, rows, entries):
 
 
 def cached_row_floats(w):
-    """Floats of one cached key|value row: every head takes whole 64-float slots (1, 2 or 4 of them)."""
-    sh = -(-(w.d_emb // w.heads) // 64)
-    sh = 4 if sh == 3 else sh
-    return 2 * 64 * w.heads * sh
+    """Floats of one cached key|value row: every head takes its floats rounded up to four, a row sixteen."""
+    head = -(-(w.d_emb // w.heads) // 4) * 4
+    return -(-2 * w.heads * head // 16) * 16
 
 
 def raw_edge_rows(w, delta_mode=False):

@@ -175,14 +175,17 @@ size_t layout(const stgn_config& c, char* base, Dev* d) {
   d->es = c.d_edge && c.d_edge <= kSlot && !c.delta_mode ? 1u : 0u;
   if (d->es && !layer_tiles_fit(*d, d->nt + 1)) d->es = 0;   // (shapes whose tiles fill the LDS as they are)
   d->nz = d->nt + d->es;
-  d->ld_kv = 2 * kSlot * d->ks;
+  d->hs = round_up(d->dk, 4u);
+  d->ld_kv = round_up(2u * c.heads * d->hs, 16u);
   float* raw_rows = d->es ? b.take<float>((size_t)c.max_edges * kSlot) : nullptr;
   for (uint32_t l = 0; l < c.layers; ++l) {
     d->KV[l].ld = d->ld_kv;
     d->KV[l].base = b.take<float>((size_t)N * d->ld_kv);
     if (d->es) { d->KVE[l].ld = kSlot; d->KVE[l].base = raw_rows; continue; }
-    d->KVE[l].ld = c.d_edge ? d->ld_kv : 0;                   // without edge features every edge reads one zero row
-    d->KVE[l].base = b.take<float>((size_t)(c.d_edge ? c.max_edges : 1) * d->ld_kv);
+    // a stride of whole slots: an edge's row is gathered once or twice in its life, and starts on a cache line's boundary
+    const uint32_t ld = 2 * kSlot * d->ks;
+    d->KVE[l].ld = c.d_edge ? ld : 0;                         // without edge features every edge reads one zero row
+    d->KVE[l].base = b.take<float>((size_t)(c.d_edge ? c.max_edges : 1) * ld);
   }
   d->ctrl = b.take<Ctrl>(1);
   // staging for host inputs: two blocks (batches alternate), each laid out like the pinned host block
@@ -386,12 +389,12 @@ int pack_parameters(stgn_ctx* ctx, const stgn_weights* w) {
       for (uint32_t cc = 0; cc < dk; ++cc)
         for (uint32_t col = 0; col < c.d_emb; ++col)
           put_tiled(WO, kSlot * d.ks, h * hp + cc, col, WOs[(size_t)(h * dk + cc) * c.d_emb + col]);
-    // node and edge rows of [W_K | W_V] in the cached-row layout: keys in floats [0, 64 ks), values behind
+    // node and edge rows of [W_K | W_V] in the cached-row layout: keys in floats [0, heads hs), values behind
     std::vector<float> WKVn(tiled_size(L.d_in, d.ld_kv), 0.0f);
     std::vector<float> WKVe(c.d_edge && !d.es ? tiled_size(c.d_edge, d.ld_kv) : 0, 0.0f);
     for (uint32_t h = 0; h < c.heads; ++h)
       for (uint32_t cc = 0; cc < dk; ++cc) {
-        const uint32_t kc = h * hp + cc, vc = kSlot * d.ks + h * hp + cc;
+        const uint32_t kc = h * d.hs + cc, vc = c.heads * d.hs + kc;
         const size_t wc = (size_t)h * dk + cc;
         for (uint32_t i = 0; i < L.d_in; ++i) {
           put_tiled(WKVn, L.d_in, i, kc, WK[(size_t)i * c.d_emb + wc]);

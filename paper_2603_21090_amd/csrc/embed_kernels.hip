@@ -106,7 +106,7 @@ LaunchArgs make_args(const Dev& d, uint32_t layer) {
   k.ring = d.ring; k.deg = d.deg; k.t_last = d.t_last;
   k.om_rev = d.om_rev; k.ph_rev = d.ph_rev; k.ctrl = d.ctrl; k.gathered_slots = d.gathered_slots;
   k.WQ = L.WQn; k.cQ = L.cQ; k.WKT = L.WKT; k.WV = L.WV; k.WO = L.WO; k.bO = L.bO;
-  k.ld_in = d.H[layer].ld; k.ld_out = d.H[layer + 1].ld; k.ld_kv = d.ld_kv; k.ld_kve = d.KVE[layer].ld;
+  k.ld_in = d.H[layer].ld; k.ld_out = d.H[layer + 1].ld; k.ld_kv = d.ld_kv; k.hs = d.hs; k.ld_kve = d.KVE[layer].ld;
   k.window = d.window;
   k.tile_next = d.tile_next + layer * kStatLine;
   k.k = d.k; k.d_in = L.d_in; k.d_emb = d.d_emb; k.dk = d.dk; k.d_time = d.d_time; k.d_edge = d.d_edge;

@@ -161,7 +161,7 @@ __device__ inline uint64_t log_addr(const Dev& d, uint32_t node, uint32_t pos) {
 //       KVE[l][e] = feat_e [W_K | W_V](edge rows of layer l) for the batch's edges e (not with raw edge rows:
 //       those are copied by the appending workgroups of the launch);
 //   all_nodes (initial state, full rebuild):  KV[0][v] for every node.
-// One workgroup (four waves) per 16 rows and 128 of the 128 ks output columns: the rows go through LDS as the A operand,
+// One workgroup (four waves) per 16 rows and 128 of the ld_kv output columns: the rows go through LDS as the A operand,
 // wave w computes the column tiles w and w + 4 of the workgroup's column group (these launches are small and
 // latency-bound: more, shorter workgroups finish sooner).  For all nodes an item is RT tiles of rows and takes every
 // column group in turn: a tile streams 64 KB of weights a group from L2, which is what bounds one tile at a time
@@ -178,8 +178,9 @@ __device__ void project_rows(const Dev& d, const float* __restrict__ ef, bool al
   const uint64_t E0 = all_nodes ? 0u : c->E_base;
   const uint32_t tD = (nD + kRows - 1) / kRows, tE = (nE + kRows - 1) / kRows;
   // work items: (row tile, column group); for all nodes one item per row tile
-  const uint32_t groups_per_item = all_nodes ? d.ks : 1u;
-  const uint32_t ntiles = (tD + d.layers * tE) * (all_nodes ? 1u : d.ks);
+  const uint32_t ntkv = d.ld_kv >> 4, ngroups = (ntkv + 7u) >> 3;          // column tiles, and groups of eight
+  const uint32_t groups_per_item = all_nodes ? ngroups : 1u;
+  const uint32_t ntiles = (tD + d.layers * tE) * (all_nodes ? 1u : ngroups);
   const uint32_t kmax = all_nodes || d.d0 > d.d_edge ? d.d0 : d.d_edge;
   const uint32_t lda = round_up(kmax, kChunkK) + 4;
   const uint32_t lane = threadIdx.x & 63u, sub = threadIdx.x & 15u, r16 = threadIdx.x >> 4;
@@ -188,8 +189,8 @@ __device__ void project_rows(const Dev& d, const float* __restrict__ ef, bool al
   const bool ef_quads = d.d_edge % 4u == 0u && (reinterpret_cast<uintptr_t>(ef) & 15u) == 0u, mem_quads = d.d_mem % 4u == 0u;
   struct Weights { float4 b[2][kCG]; };
   for (uint32_t item = bid; item < ntiles; item += nblk) {
-    const uint32_t tile = all_nodes ? item : item / d.ks;
-    uint32_t nt = all_nodes ? wave : wave + 8u * (item - tile * d.ks);
+    const uint32_t tile = all_nodes ? item : item / ngroups;
+    uint32_t nt = all_nodes ? wave : wave + 8u * (item - tile * ngroups);
     const bool node_job = tile < tD;
     const uint32_t layer = node_job ? 0u : (tile - tD) / tE;
     const uint32_t r0 = (node_job ? tile : (tile - tD) - layer * tE) * kRows;
@@ -197,10 +198,12 @@ __device__ void project_rows(const Dev& d, const float* __restrict__ ef, bool al
     const uint32_t K = node_job ? d.d0 : d.d_edge;
     const float* W = node_job ? d.L[0].WKVn : d.L[layer].WKVe;
     float* out = node_job ? d.KV[0].base : d.KVE[layer].base;
+    const uint32_t ld_out = node_job ? d.ld_kv : d.KVE[layer].ld;
     const uint32_t ck = chunks_of(K);
     Weights P;                                                // first weight chunk, requested ahead of the staging
-    load_b16(W + (size_t)nt * ck * kChunkFloats, 0, P.b[0]);
-    load_b16(W + (size_t)(nt + 4) * ck * kChunkFloats, 0, P.b[1]);
+    auto column_tile = [&](uint32_t x) { return W + (size_t)(x < ntkv ? x : ntkv - 1u) * ck * kChunkFloats; };
+    load_b16(column_tile(nt), 0, P.b[0]);
+    load_b16(column_tile(nt + 4), 0, P.b[1]);
     // Sixteen lanes stage a row, lane `sub` the columns 64 i + 4 sub .. + 3, up to the end of the last chunk (zero past K:
     // operand padding must be finite).
     // A batch endpoint's new memory is read from the batch's scratch rows: the write-back into the
@@ -247,7 +250,8 @@ __device__ void project_rows(const Dev& d, const float* __restrict__ ef, bool al
         if ((uint32_t)i < ck) *reinterpret_cast<float4*>(lds + (rt * kProjRows + r16) * lda + 4u * sub + kChunkK * i) = held[rt][i];
     __syncthreads();
     for (uint32_t cg = 0; cg < groups_per_item; ++cg, nt += 8u) {
-      const float* const Bt[2] = {W + (size_t)nt * ck * kChunkFloats, W + (size_t)(nt + 4) * ck * kChunkFloats};
+      if (nt >= ntkv) break;                                  // (uniform per wave; no barrier before the end of the item)
+      const float* const Bt[2] = {column_tile(nt), column_tile(nt + 4)};
       if (cg) { load_b16(Bt[0], 0, P.b[0]); load_b16(Bt[1], 0, P.b[1]); }
       floatx4 acc[RT][2] = {};
       pingpong_peeled<Weights>(
@@ -269,9 +273,9 @@ __device__ void project_rows(const Dev& d, const float* __restrict__ ef, bool al
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             const uint32_t row = r0 + rt * kProjRows + m16_row(lane, r);
-            if (row < nrows) {
+            if (row < nrows && nt + 4 * t < ntkv) {
               const size_t orow = node_job ? (size_t)(all_nodes ? row : d.D[row]) : (size_t)(E0 + row);
-              out[orow * d.ld_kv + col] = acc[rt][t][r];
+              out[orow * ld_out + col] = acc[rt][t][r];
             }
           }
         }
@@ -427,7 +431,7 @@ void launch_apply(const Dev& d, hipStream_t s, const uint32_t* src, const uint32
   if (blocks < 1) blocks = 1;
   // workgroups that project: one per 16-row tile of the largest batch (endpoints, and edges per layer)
   const uint32_t per = (d.max_batch + kProjRows - 1) / kProjRows;
-  uint32_t pblocks = ((d.d_mem ? 2 * per : 0) + (d.d_edge && !d.es ? d.layers * per : 0)) * d.ks;
+  uint32_t pblocks = ((d.d_mem ? 2 * per : 0) + (d.d_edge && !d.es ? d.layers * per : 0)) * (((d.ld_kv >> 4) + 7u) >> 3);
   if (pblocks > 2048) pblocks = 2048;
   const uint32_t cblocks = with_compaction ? compact_blocks_of(d.N) : 0u;
   launch_done(apply_kernel, dim3(blocks + pblocks + cblocks), dim3(256), pblocks ? project_lds(d) : 0, s, done, d, src, dst,

@@ -145,7 +145,7 @@ struct LayerArgs {
   uint32_t* tile_next;                             // streamed exact launches: tiles handed out beyond the first one of every workgroup (zero before the launch)
   uint64_t* gathered_slots;                        // statistic: ring entries gathered, one plain counter per workgroup index
   const float *WQ, *cQ, *WKT, *WV, *WO, *bO, *WKVnext;   // matrices group-major (mfma16.h)
-  uint32_t ld_in, ld_out, ld_kv, ld_kve;           // ld_kve = 0 without edge features (every edge reads one zero row)
+  uint32_t ld_in, ld_out, ld_kv, ld_kve, hs;       // hs: floats of a head's keys in a cached row (values are heads hs further on); ld_kve = 0 without edge features (every edge reads one zero row)
   uint32_t k, d_in, d_emb, dk, d_time, d_edge;
   // query cache (null: off): this layer's cached q | qt rows, [node][64 (KS + H NZ)], and per tile of the row list whether
   // every row's input row is unchanged (then q and qt are read back, not projected); a launch that must recompute everything
@@ -479,7 +479,11 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
   constexpr bool LAZY = RT > 1;                               // a pass's query and first gather are requested when the pass before is over
   static_assert(PASSES == 1 || RPP == 1 || (RPP == 2 && PASSES == 2), "rows of a pass");
   uint32_t g = 0, head = 0, sg = 0;                           // this lane's key slot, its head and its place among the head's slots
-  auto derive_slot = [&]() { g = GPR == 1 ? 0u : grp % GPR; head = g / SH; sg = g - head * SH; };
+  uint32_t kv_at = 0;                                         // ... and the lane's four keys in a cached row
+  auto derive_slot = [&]() {
+    g = GPR == 1 ? 0u : grp % GPR; head = g / SH; sg = g - head * SH;
+    kv_at = head * a.hs + min(kSlot * sg + 4u * sub, a.hs - 4u);   // (past the head's floats: its last four, which count for nothing)
+  };
   auto row_of = [&](int p) { return wave * RPW + (uint32_t)(p * RPP) + (RPP == 1 ? 0u : grp / GPR); };
   // the staged value of the row that this lane works on in pass p
   auto of_pass = [&](uint32_t x, int p) -> uint32_t {
@@ -510,15 +514,16 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
     for (int jc = 0; jc < JC; ++jc) {
       const uint32_t j = c * JC + jc;
       const RingEntry e = rrow[JC == 1 || j < k ? j : k - 1u];   // (a chunk of one never runs past the longest row's entries, but for a wave without any: the record of place 0)
-      const float* nrow = a.KVn + (size_t)e.nbr * (2u * kSlot * KS) + kSlot * g + 4u * sub;
+      // (byte addresses: one multiply-add a row)
+      const float* nrow = reinterpret_cast<const float*>(reinterpret_cast<const char*>(a.KVn + kv_at) + (uint64_t)e.nbr * (4u * a.ld_kv));
       zb.nk[jc] = *reinterpret_cast<const float4*>(nrow);
-      zb.nv[jc] = *reinterpret_cast<const float4*>(nrow + kSlot * KS);
+      zb.nv[jc] = *reinterpret_cast<const float4*>(nrow + H * a.hs);
       if constexpr (ES) {
         zb.e[jc][0] = *reinterpret_cast<const float4*>(a.KVe + (size_t)e.eid * kSlot + 4u * sub);
       } else {
-        const float* erow = a.KVe + (size_t)e.eid * a.ld_kve + kSlot * g + 4u * sub;
+        const float* erow = reinterpret_cast<const float*>(reinterpret_cast<const char*>(a.KVe + kv_at) + (uint64_t)e.eid * (4u * a.ld_kve));
         zb.e[jc][0] = *reinterpret_cast<const float4*>(erow);
-        zb.e[jc][1] = *reinterpret_cast<const float4*>(erow + kSlot * KS);
+        zb.e[jc][1] = *reinterpret_cast<const float4*>(erow + H * a.hs);
       }
       zb.t[jc] = e.t;
     }
@@ -798,12 +803,14 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
           bf.j = j;
           const RingEntry e = rrow[j];
           const bool act = (amask >> (j - jb)) & 1u;
-          const float* nrow = a.KVn + (size_t)(act ? e.nbr : 0u) * a.ld_kv + 4u * sub;
-          const float* erow = a.KVe + (size_t)(act ? e.eid : 0u) * a.ld_kve + 4u * sub;
+          const float* nrow = a.KVn + (size_t)(act ? e.nbr : 0u) * a.ld_kv;
+          const float* erow = a.KVe + (size_t)(act ? e.eid : 0u) * a.ld_kve;
 #pragma unroll
-          for (int s = 0; s < 2 * KS; ++s) {
-            bf.n[s] = *reinterpret_cast<const float4*>(nrow + s * kSlot);
-            bf.e[s] = *reinterpret_cast<const float4*>(erow + s * kSlot);
+          for (int s = 0; s < 2 * KS; ++s) {                  // keys of all heads, then values
+            if (s && s % SH == 0) { nrow += a.hs; erow += a.hs; }
+            const uint32_t at = min(kSlot * (s % SH) + 4u * sub, a.hs - 4u);
+            bf.n[s] = *reinterpret_cast<const float4*>(nrow + at);
+            bf.e[s] = *reinterpret_cast<const float4*>(erow + at);
           }
         };
         auto work = [&](uint32_t, const DBuf& bf) {
@@ -1226,7 +1233,7 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
     // ================================================================ phase 6: next layer's cached keys | values of these rows
     // A wave takes column tiles w, w + NW, ... of a cached row.  The second tile's chunks follow the first's into the same
     // registers.
-    constexpr uint32_t ntkv = 8u * KS;
+    const uint32_t ntkv = args()->ld_kv >> 4;
     auto store6 = [&](uint32_t nt, const floatx4 (&acc)[RT][1]) {
       float* const kvout = args()->KVout;
       const uint32_t col = nt * 16 + m16_col(lane);           // every column is written: padding columns get exact zeros
@@ -1235,13 +1242,14 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const uint32_t node = nodes_s[kTM * rt + m16_row(lane, r)];
-          if (node != 0xFFFFFFFFu) kvout[(size_t)node * (2u * kSlot * KS) + col] = acc[rt][0][r];
+          if (node != 0xFFFFFFFFu) kvout[(size_t)node * (16u * ntkv) + col] = acc[rt][0][r];
         }
     };
     floatx4 out6[2][RT][1] = {};
     if (kv) {
       const float* const wkv0 = args()->WKVnext;
-      auto wkv = [&](uint32_t nt) { return wkv0 + (size_t)nt * c_de * kChunkFloats; };
+      auto wkv = [&](uint32_t nt) { return wkv0 + (size_t)(nt < ntkv ? nt : ntkv - 1u) * c_de * kChunkFloats; };
+      const bool two = wave + NW < ntkv;                      // (uniform)
       const float* Ha = Hs + a16_off(lane, ldh);
       const uint32_t c1 = c_de > 1 ? 1u : 0u;
       float4 b6[2][1][kCG];
@@ -1252,11 +1260,13 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
         mfma16_chunk_rows<RT, 1>(Ha, kTM * ldh, ch * kCG, b, acc);
       };
       chunk6(0, b6[0], out6[0]);
-      load_b16(wkv(wave + NW), 0, b6[0][0], lane);
+      if (two) load_b16(wkv(wave + NW), 0, b6[0][0], lane);
       if (c1) chunk6(1, b6[1], out6[0]);
-      load_b16(wkv(wave + NW), c1 * kCG, b6[1][0], lane);
-      chunk6(0, b6[0], out6[1]);
-      if (c1) chunk6(1, b6[1], out6[1]);
+      if (two) {
+        load_b16(wkv(wave + NW), c1 * kCG, b6[1][0], lane);
+        chunk6(0, b6[0], out6[1]);
+        if (c1) chunk6(1, b6[1], out6[1]);
+      }
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         const float* const Bt[1] = {wkv(wave + NW * t)};
@@ -1271,8 +1281,8 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
     }
     if (wave < ntd) store5(wave, out5);
     if (kv) {
-      store6(wave, out6[0]);
-      store6(wave + NW, out6[1]);
+      if (wave < ntkv) store6(wave, out6[0]);
+      if (wave + NW < ntkv) store6(wave + NW, out6[1]);
     }
     if (QCACHE && (RT > 1 || rows_in_lds)) __syncthreads();
   };

@@ -95,8 +95,11 @@ struct Table {
 // sum_j a_j (phi_j W_V,h) = (sum_j a_j phi_j) W_V,h[time], so every dense product runs over rows, not
 // over (row, neighbour) pairs.
 //
-// A cached row holds [keys | values]; each head occupies whole slots of 64 floats (one slot = 16
-// lanes x float4), columns past dk are exact zeros: ld_kv = 2 * 64 * ks floats, ks = heads * ceil(dk / 64).
+// A cached row holds [keys | values], the heads one behind the other, each in hs = dk rounded up to 4 floats (the padding
+// exact zeros): ld_kv = 2 heads hs floats, rounded up to 16.  In the kernels a head takes whole slots of 64 floats (one slot = 16
+// lanes x float4, ks = heads * ceil(dk / 64) slots); lanes past a head's floats read its last four again, against zeros of
+// the query, and their sums are not used.  Rows are random reads from HBM: two heads of 50 take 832 bytes, 13 of the
+// 16 64-byte pieces that whole slots took, four heads of 32 half of it.
 //
 // Narrow edge features (d_edge <= 64, exact mode) are not projected at all: the raw feature row, padded to
 // one slot, is kept once per edge and rides through the layer kernel as one more slot of the time encoding,
@@ -115,8 +118,8 @@ struct LayerDev {
   const float* WV;               // [64 nz x heads * R16(dk)] time rows of W_V, head block, * sqrt(1/d_t); edge rows in slot nt
   const float* WO;               // [64 ks x d_emb]           rows in the padded-head layout of the head outputs
   const float* bO;               // [d_emb]
-  const float* WKVn;             // [d_in x 128 ks]           node rows of [W_K | W_V] in the cached-row layout
-  const float* WKVe;             // [d_edge x 128 ks]         edge rows of [W_K | W_V] (null without edge features or with raw edge rows)
+  const float* WKVn;             // [d_in x ld_kv]            node rows of [W_K | W_V] in the cached-row layout
+  const float* WKVe;             // [d_edge x ld_kv]          edge rows of [W_K | W_V] (null without edge features or with raw edge rows)
 };
 
 struct Dev {
@@ -138,9 +141,9 @@ struct Dev {
   uint32_t* blk;                     // [N x maxb] block bases in units of kMinBlock entries
   // cached key|value rows (see LayerDev): KV[l] of the rows of H[l], KVE[l] of the edge features
   Table    KV[STGN_MAX_LAYERS];      // [N x ld_kv]
-  Table    KVE[STGN_MAX_LAYERS];     // [max_edges x ld_kv]; one zero row (ld 0) without edge features; with raw edge
+  Table    KVE[STGN_MAX_LAYERS];     // [max_edges x 128 ks], ld_kv floats of each in use; one zero row (ld 0) without edge features; with raw edge
                                      // rows every layer names the one table [max_edges x 64] of padded feature rows
-  uint32_t sh, ks, nt, ld_kv;        // slots per head, key slots, time slots, floats per cached row
+  uint32_t sh, ks, nt, hs, ld_kv;    // slots per head, key slots, time slots, floats of a head's keys (or values) in a cached row, floats per cached row
   uint32_t es, nz;                   // es = 1: raw edge rows; nz = nt + es slots of the vector z = [phi | f]
   // per-batch scratch: two sets, the batches alternate (bind_batch points the plain fields at one of them)
   struct Scratch {

@@ -56,3 +56,25 @@ def test_a_nan_stays_in_the_rows_of_its_tile(kw):
     from tests.test_gpu_nan import _check
     w = tiny_workload(**{**dict(num_nodes=40_000, num_edges=60_000, batch=4_000, zipf_s=1.05, d_mem=0, d_node=20, d_time=70, k=3), **kw})
     _check(binding, w, **(dict(edge=1) if w.d_edge else dict(node="quiet")))
+
+
+@pytest.mark.parametrize("heads, dk", [(1, 1), (1, 4), (1, 63), (1, 64), (1, 65), (1, 129), (1, 200), (2, 3), (2, 5), (2, 16), (2, 50), (2, 64),
+                                       (2, 66), (2, 127), (4, 1), (4, 7), (4, 25), (4, 33), (4, 61)])
+@pytest.mark.parametrize("kw", [dict(d_edge=9), dict(d_edge=70), dict(d_edge=0), dict(d_edge=9, delta_mode=1)])
+def test_cached_rows_of_every_head_width(heads, dk, kw):
+    """A cached row holds its heads' floats one behind the other, each rounded up to four and the row to sixteen: widths around
+    four, a column tile and a slot, against the oracle (the embedding bar of 1e-4 per row)."""
+    from paper_2603_21090_amd import binding
+    delta = kw.get("delta_mode", 0)
+    w = tiny_workload(num_nodes=120, num_edges=900, batch=90, d_emb=heads * dk, heads=heads, d_time=20, d_mem=12, d_edge=kw["d_edge"], k=4)
+    W = synth.make_weights(w)
+    o, g = orc.Oracle.from_workload(w, W), binding.StreamTGN.from_workload(w, W, delta_mode=delta, drift_gamma=0.9 if delta else 0.0)
+    st = synth.EdgeStream(w)
+    for b in range(w.num_batches):
+        assert o.ingest(*st.batch(b))[0] == 0
+        g.ingest_batch(*st.batch(b))
+    if delta:
+        g.full_rebuild()
+    for l, ref in enumerate(o.embed_all(), 1):
+        assert rows_close(g.get_embeddings(np.arange(w.num_nodes, dtype=np.uint32), layer=l), ref).all(), l
+    g.close()
