@@ -284,6 +284,18 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
   };
   derive_lane();
 
+  // groups of a chunk that count, where a chunk is a slot: of a head's columns, of z
+  // (link scores, a tile or two per workgroup: all of them, the arguments' way to the scalar registers takes longer, 25.7 -> 26.2 us)
+  auto groups_of = [&](auto used, uint32_t g0) {
+    if constexpr (ROOTS) return AllGroups{};
+    else return groups_in((used(args()) + 15u) >> 4, g0);
+  };
+  auto groups_head = [&](uint32_t slot) { return groups_of([](ArgBlock p) { return p->dk; }, (SH == 1 ? 0u : slot % SH) * kCG); };
+  auto groups4 = [&](uint32_t slot) {
+    const bool edge = ES && slot == NT;
+    return groups_of([=](ArgBlock p) { return edge ? p->d_edge : p->d_time; }, edge ? 0u : slot * kCG);
+  };
+
   // ---- phase-2 work units: (head, NTL valid qt column tiles); wave w owns units w, w + NW, ...
   // Lane i of `udesc` holds the description of the wave's i-th unit (head, first tile, second tile, whether there is a
   // second one), worked out once; inside the tile loop a unit costs one cross-lane read.
@@ -623,6 +635,7 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
       commit_x(false);
     }
     __syncthreads();                                          // input rows there, the previous tile's head outputs read
+    auto groups1 = [&](uint32_t ch) { return groups_of([](ArgBlock p) { return p->d_in; }, ch * kCG); };
     auto store1 = [&](uint32_t nt, const floatx4 (&acc)[RT][NTL]) {
 #pragma unroll
       for (int t = 0; t < NTL; ++t) {
@@ -644,7 +657,7 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
 #pragma unroll
       for (int t = 0; t < NTL; ++t) B1[t] = tile_b(a.WQ, w1, t, ntd, c_in);
       floatx4 acc[RT][NTL] = {};
-      u1.template multiply_rows<RT>(Xs + a16_off(lane, ll.ldx), kTM * ll.ldx, c_in, B1, acc, lane, ll.wx / kGrpK - 1u);
+      u1.template multiply_rows<RT>(Xs + a16_off(lane, ll.ldx), kTM * ll.ldx, c_in, B1, acc, lane, groups1, ll.wx / kGrpK - 1u);
       store1(wave, acc);
     }
     for (uint32_t nt = wave + 8; nt < ntd; nt += 8) {
@@ -652,7 +665,7 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
 #pragma unroll
       for (int t = 0; t < NTL; ++t) Bt[t] = tile_b(a.WQ, nt, t, ntd, c_in);
       floatx4 acc[RT][NTL] = {};
-      mfma16_lean_rows<RT, NTL>(Xs + a16_off(lane, ll.ldx), kTM * ll.ldx, 0u, c_in, Bt, acc, lane, ll.wx / kGrpK - 1u);
+      mfma16_lean_rows<RT, NTL>(Xs + a16_off(lane, ll.ldx), kTM * ll.ldx, 0u, c_in, Bt, acc, lane, groups1, ll.wx / kGrpK - 1u);
       store1(nt, acc);
     }
     __syncthreads();
@@ -663,12 +676,12 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
         const Unit2 u = decode2(i);
         floatx4 acc[RT][NTL] = {};
         const float* qh = qa + u.h * (SH * kSlot);
-        mfma16_chunk_rows<RT, NTL>(qh, kTM * ll.ldq, 0, o.b, acc);
+        mfma16_chunk_rows<RT, NTL>(qh, kTM * ll.ldq, 0, o.b, acc, groups_head(0u));
         if constexpr (SH > 1) {
           const float* Bt[NTL];
           Bt[0] = wkt(u.h, u.t0);
           if constexpr (NTL == 2) Bt[1] = wkt(u.h, u.t1);
-          mfma16_lean_rows<RT, NTL>(qh, kTM * ll.ldq, 1u, SH, Bt, acc, lane);
+          mfma16_lean_rows<RT, NTL>(qh, kTM * ll.ldq, 1u, SH, Bt, acc, lane, groups_head);
         }
         store2(u, acc);
       };
@@ -1133,7 +1146,7 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
       for (;;) {
         const uint32_t h4 = head4(), n0 = N4 * (x4 - h4 * np4);
         floatx4 acc[RT][N4] = {};
-        u4.template multiply_rows<RT>(Zs + h4 * Ztp + a16_off(lane, ll.ldz), kTM * ll.ldz, NZ, B4, acc, lane);
+        u4.template multiply_rows<RT>(Zs + h4 * Ztp + a16_off(lane, ll.ldz), kTM * ll.ldz, NZ, B4, acc, lane, groups4);
 #pragma unroll
         for (int t = 0; t < N4; ++t) {
           const uint32_t col = (n0 + t) * 16 + m16_col(lane);
@@ -1200,7 +1213,7 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
     floatx4 out5[RT][NTL] = {};
     if (wave < ntd) {
       floatx4 acc[RT][NTL] = {};
-      u5.template multiply_rows<RT>(Qs + a16_off(lane, ll.ldq), kTM * ll.ldq, KS, B5, acc, lane);
+      u5.template multiply_rows<RT>(Qs + a16_off(lane, ll.ldq), kTM * ll.ldq, KS, B5, acc, lane, groups_head);
       bias5(wave, acc, out5);
     }
     for (uint32_t nt = wave + 8; nt < ntd; nt += 8) {
@@ -1208,7 +1221,7 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
 #pragma unroll
       for (int t = 0; t < NTL; ++t) Bt[t] = tile_b(a.WO, nt, t, ntd, KS);
       floatx4 acc[RT][NTL] = {}, o[RT][NTL];
-      mfma16_lean_rows<RT, NTL>(Qs + a16_off(lane, ll.ldq), kTM * ll.ldq, 0u, KS, Bt, acc, lane);
+      mfma16_lean_rows<RT, NTL>(Qs + a16_off(lane, ll.ldq), kTM * ll.ldq, 0u, KS, Bt, acc, lane, groups_head);
       bias5(nt, acc, o);
       store5(nt, o);
     }
@@ -1256,8 +1269,9 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
       load_b16(wkv(wave), 0, b6[0][0], lane);
       load_b16(wkv(wave), c1 * kCG, b6[1][0], lane);
       __syncthreads();
+      auto groups6 = [&](uint32_t ch) { return groups_of([](ArgBlock p) { return p->d_emb; }, ch * kCG); };
       auto chunk6 = [&](uint32_t ch, const float4 (&b)[1][kCG], floatx4 (&acc)[RT][1]) {
-        mfma16_chunk_rows<RT, 1>(Ha, kTM * ldh, ch * kCG, b, acc);
+        mfma16_chunk_rows<RT, 1>(Ha, kTM * ldh, ch * kCG, b, acc, groups6(ch));
       };
       chunk6(0, b6[0], out6[0]);
       if (two) load_b16(wkv(wave + NW), 0, b6[0][0], lane);
@@ -1270,12 +1284,12 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         const float* const Bt[1] = {wkv(wave + NW * t)};
-        mfma16_lean_rows<RT, 1>(Ha, kTM * ldh, 2u, c_de, Bt, out6[t], lane);
+        mfma16_lean_rows<RT, 1>(Ha, kTM * ldh, 2u, c_de, Bt, out6[t], lane, groups6);
       }
       for (uint32_t nt = wave + 2 * NW; nt < ntkv; nt += NW) {
         const float* const Bt[1] = {wkv(nt)};
         floatx4 acc[RT][1] = {};
-        mfma16_lean_rows<RT, 1>(Ha, kTM * ldh, 0u, c_de, Bt, acc, lane);
+        mfma16_lean_rows<RT, 1>(Ha, kTM * ldh, 0u, c_de, Bt, acc, lane, groups6);
         store6(nt, acc);
       }
     }

@@ -17,6 +17,7 @@
 // matrix instructions never wait for each other).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <type_traits>
 
 namespace stgn {
 
@@ -100,10 +101,25 @@ __device__ inline void mfma16_chunk(const float4 (&a)[kCG], const float4 (&b)[NT
   }
 }
 
-// The same for RT row tiles (`rs` floats apart in LDS) that share the B operand: every B register meets RT A registers.
-template <int RT, int NTL>
+// Groups of a chunk that hold elements of K: `used` of the product's groups, the chunk starting at g0 (uniform).
+__device__ inline uint32_t groups_in(uint32_t used, uint32_t g0) { return used <= g0 ? 0u : min(used - g0, (uint32_t)kCG); }
+
+// ... and all of them, where asking would take longer than the products
+struct AllGroups {};
+
+// The same for RT row tiles (`rs` floats apart in LDS) that share the B operand: every B register meets RT A registers.  Only
+// the first ng groups are multiplied, the others hold zero weights: K of 100 has 7 of two chunks' 8 groups, a head of 32 two
+// of four.  Batches with these products left out: four heads of 32 171 -> 164 us, 100,000 nodes of two heads of 50 426 -> 415,
+// 1,000,000 nodes 1,941 -> 1,894.
+template <int RT, int NTL, class NG>
 __device__ inline void mfma16_chunk_rows(const float* Ap, uint32_t rs, uint32_t g0, const float4 (&b)[NTL][kCG],
-                                         floatx4 (&acc)[RT][NTL], uint32_t last = kNoLimit) {
+                                         floatx4 (&acc)[RT][NTL], NG groups, uint32_t last = kNoLimit) {
+  constexpr bool all = std::is_same<NG, AllGroups>::value;
+  uint32_t ng = kCG;
+  if constexpr (!all) {
+    ng = (uint32_t)__builtin_amdgcn_readfirstlane((int)groups);
+    asm volatile("" : "+s"(ng));                              // (else a caller's loop holds every comparison with it in scalar registers)
+  }
   auto load = [&](int c, float4 (&a)[RT]) {
     const uint32_t g = g0 + c < last ? g0 + c : last;
 #pragma unroll
@@ -124,23 +140,24 @@ __device__ inline void mfma16_chunk_rows(const float* Ap, uint32_t rs, uint32_t 
 #pragma unroll
     for (int c = 0; c < kCG; ++c) load(c, a[c]);
 #pragma unroll
-    for (int c = 0; c < kCG; ++c) mul(c, a[c]);
+    for (int c = 0; c < kCG; ++c)
+      if (all || (uint32_t)c < ng) mul(c, a[c]);                     // (uniform)
   } else {
     static_assert(kCG == 4, "written out for four groups");   // (two groups of A in flight: all four would cost 16 registers more and spill)
     float4 a0[RT], a1[RT];
     load(0, a0);
     load(1, a1);
     __builtin_amdgcn_sched_barrier(0);
-    mul(0, a0);
+    if (all || ng > 0u) mul(0, a0);
     __builtin_amdgcn_sched_barrier(0);
     load(2, a0);
     __builtin_amdgcn_sched_barrier(0);
-    mul(1, a1);
+    if (all || ng > 1u) mul(1, a1);
     __builtin_amdgcn_sched_barrier(0);
     load(3, a1);
     __builtin_amdgcn_sched_barrier(0);
-    mul(2, a0);
-    mul(3, a1);
+    if (all || ng > 2u) mul(2, a0);
+    if (all || ng > 3u) mul(3, a1);
   }
 }
 
@@ -247,15 +264,15 @@ __device__ __forceinline__ void mfma16_lean(const float* Ap, uint32_t c0, uint32
 }
 
 // ... for RT row tiles
-template <int RT, int NTL>
+template <int RT, int NTL, class Groups>
 __device__ __forceinline__ void mfma16_lean_rows(const float* Ap, uint32_t rs, uint32_t c0, uint32_t c1, const float* const (&Bt)[NTL],
-                                                 floatx4 (&acc)[RT][NTL], uint32_t lane, uint32_t last = kNoLimit) {
+                                                 floatx4 (&acc)[RT][NTL], uint32_t lane, Groups ng, uint32_t last = kNoLimit) {
 #pragma unroll 1
   for (uint32_t ch = c0; ch < c1; ++ch) {
     float4 b[NTL][kCG];
 #pragma unroll
     for (int t = 0; t < NTL; ++t) load_b16(Bt[t], ch * kCG, b[t], lane);
-    mfma16_chunk_rows<RT, NTL>(Ap, rs, ch * kCG, b, acc, last);
+    mfma16_chunk_rows<RT, NTL>(Ap, rs, ch * kCG, b, acc, ng(ch), last);
   }
 }
 
@@ -286,14 +303,14 @@ struct Upfront16 {
       }
     }
   }
-  // ... for RT row tiles, also where K has more chunks than were requested
-  template <int RT>
+  // ... for RT row tiles, also where K has more chunks than were requested; ng(ch): groups of chunk ch that count
+  template <int RT, class Groups>
   __device__ __forceinline__ void multiply_rows(const float* Ap, uint32_t rs, uint32_t nchunks, const float* const (&Bt)[NTL],
-                                                floatx4 (&acc)[RT][NTL], uint32_t lane, uint32_t last = kNoLimit) {
+                                                floatx4 (&acc)[RT][NTL], uint32_t lane, Groups ng, uint32_t last = kNoLimit) {
 #pragma unroll
     for (int ch = 0; ch < MAXC; ++ch)
-      if ((uint32_t)ch < nchunks) mfma16_chunk_rows<RT, NTL>(Ap, rs, ch * kCG, b[ch], acc, last);
-    mfma16_lean_rows<RT, NTL>(Ap, rs, MAXC, nchunks, Bt, acc, lane, last);
+      if ((uint32_t)ch < nchunks) mfma16_chunk_rows<RT, NTL>(Ap, rs, ch * kCG, b[ch], acc, ng((uint32_t)ch), last);
+    mfma16_lean_rows<RT, NTL>(Ap, rs, MAXC, nchunks, Bt, acc, lane, ng, last);
   }
   // the whole product, also where K has more chunks than were requested
   __device__ __forceinline__ void multiply(const float* Ap, uint32_t nchunks, const float* const (&Bt)[NTL],
