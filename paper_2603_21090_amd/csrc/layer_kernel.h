@@ -494,8 +494,12 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
   uint32_t kv_at = 0;                                         // ... and the lane's four keys in a cached row
   auto derive_slot = [&]() {
     g = GPR == 1 ? 0u : grp % GPR; head = g / SH; sg = g - head * SH;
-    kv_at = head * a.hs + min(kSlot * sg + 4u * sub, a.hs - 4u);   // (past the head's floats: its last four, which count for nothing)
+    kv_at = head * a.hs + min(kSlot * sg + 4u * sub, a.hs - 4u);   // (past the head's floats: its last four; see in_head)
   };
+  // Whether a lane's quad of slot s of its head lies among the head's floats.  Past them the query is zero, but the keys read
+  // there are the head's last four again, not padding: one that has overflowed would make the product a NaN, where the score
+  // is minus infinity and the entry has no weight.
+  auto in_head = [&](uint32_t s) { return kSlot * s + 4u * sub < a.hs; };
   auto row_of = [&](int p) { return wave * RPW + (uint32_t)(p * RPP) + (RPP == 1 ? 0u : grp / GPR); };
   // the staged value of the row that this lane works on in pass p
   auto of_pass = [&](uint32_t x, int p) -> uint32_t {
@@ -852,7 +856,7 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
         for (int h = 0; h < H; ++h) {
           float p = 0.0f;
 #pragma unroll
-          for (int s = h * SH; s < (h + 1) * SH; ++s) p = dot4(qk[s], kk[s], p);
+          for (int s = h * SH; s < (h + 1) * SH; ++s) { const float with = dot4(qk[s], kk[s], p); p = in_head(s - h * SH) ? with : p; }
 #pragma unroll
           for (int t = 0; t < NT; ++t) p = dot4(*reinterpret_cast<const float4*>(zq + h * Ztp + t * kSlot), zt[t], p);
           sc[h] = row16_sum(p);
@@ -1028,6 +1032,7 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
           float4 kk = zb.nk[jc];
           if constexpr (!ES) { kk.x += zb.e[jc][0].x; kk.y += zb.e[jc][0].y; kk.z += zb.e[jc][0].z; kk.w += zb.e[jc][0].w; }
           float s = dot4(qk[p % NP], kk, 0.0f);
+          s = in_head(sg) ? s : 0.0f;
 #pragma unroll
           for (int i = 0; i < NZL; ++i) s = dot4(qt[p % NP][i], zt[jc][i], s);
           s = row16_sum(s);
@@ -1088,8 +1093,8 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
       } else {
         if (nchunk3) pingpong_clamped<ZBuf>(nchunk3, z0[p % NP], [&](uint32_t c, ZBuf& zb) { gather(p, c, zb); }, attend);
       }
-      // the cached-value part of the head outputs goes into Xs (padded-head layout; the padding lanes hold exact
-      // zeros), pb where qt is (each lane owns its columns)
+      // the cached-value part of the head outputs goes into Xs (padded-head layout; what lanes past a head's floats leave in
+      // its padding columns is not read), pb where qt is (each lane owns its columns)
       const float inv = reciprocal(lrun);                     // no entry, or none inside the window: b_O alone
       accv.x *= inv; accv.y *= inv; accv.z *= inv; accv.w *= inv;
       if constexpr (RT > 1) {

@@ -97,8 +97,8 @@ struct Table {
 //
 // A cached row holds [keys | values], the heads one behind the other, each in hs = dk rounded up to 4 floats (the padding
 // exact zeros): ld_kv = 2 heads hs floats, rounded up to 16.  In the kernels a head takes whole slots of 64 floats (one slot = 16
-// lanes x float4, ks = heads * ceil(dk / 64) slots); lanes past a head's floats read its last four again, against zeros of
-// the query, and their sums are not used.  Rows are random reads from HBM: two heads of 50 take 832 bytes, 13 of the
+// lanes x float4, ks = heads * ceil(dk / 64) slots); lanes past a head's floats read its last four again: their share of
+// the scores is left out, and their sums are not used.  Rows are random reads from HBM: two heads of 50 take 832 bytes, 13 of the
 // 16 64-byte pieces that whole slots took, four heads of 32 half of it.
 //
 // Narrow edge features (d_edge <= 64, exact mode) are not projected at all: the raw feature row, padded to

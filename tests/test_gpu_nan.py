@@ -5,7 +5,7 @@ import pytest
 
 from oracle import oracle as orc
 from paper_2603_21090_amd import synth
-from tests.helpers import tiny_workload
+from tests.helpers import rings_matrix, rows_close, tiny_workload
 
 pytestmark = pytest.mark.gpu
 
@@ -94,3 +94,39 @@ def test_entries_without_weight(binding, kw, poison):
     w = tiny_workload(**{**dict(num_nodes=900, num_edges=1500, batch=100, zipf_s=0.6, d_mem=0, d_node=20, d_time=20, k=9,
                                 window=40.0 if poison == "outside the window" else 0.0), **kw})
     _check(binding, w, **{"node 0": dict(node=0), "edge 0": dict(edge=w.num_batches), "outside the window": dict(node="early")}[poison])
+
+
+@pytest.mark.parametrize("kw", [dict(heads=1, d_emb=40), dict(heads=1, d_emb=40, d_edge=70), dict(heads=2, d_emb=100), dict(heads=2, d_emb=100, d_edge=70),
+                                dict(heads=1, d_emb=100), dict(heads=1, d_emb=129, d_edge=70), dict(heads=2, d_emb=190), dict(heads=4, d_emb=128),
+                                dict(heads=4, d_emb=60, d_edge=70), dict(heads=2, d_emb=100, d_edge=70, delta_mode=1),
+                                dict(heads=1, d_emb=100, delta_mode=1), dict(heads=2, d_emb=128)])
+@pytest.mark.parametrize("num_nodes", [900, 40_000])          # (rebuilds of 40,000 rows run tiles of 32)
+def test_an_overflowed_key_takes_no_weight(binding, num_nodes, kw):
+    """The last key column of every head overflows for one node in sixteen, against a query that makes the score minus infinity:
+    such a neighbour has no weight, also where lanes past a head's floats meet its last key again."""
+    delta = kw.get("delta_mode", 0)
+    w = tiny_workload(**{**dict(num_nodes=num_nodes, num_edges=3 * num_nodes, batch=num_nodes // 5, zipf_s=0.3, layers=1, d_mem=0, d_node=20,
+                                d_edge=9, d_time=20, k=5), **{x: v for x, v in kw.items() if x != "delta_mode"}})
+    W, nf, st = synth.make_weights(w), synth.node_features(w), synth.EdgeStream(w)
+    over = np.arange(num_nodes) % 16 == 5
+    nf[:, 0] = np.where(over, 1e4, 0.0)
+    wq, wk, wv = W["W_Q"][0], W["W_K"][0], W["W_V"][0]
+    last = np.arange(1, w.heads + 1) * (w.d_emb // w.heads) - 1
+    wq[0] = wk[0] = wv[0] = 0.0
+    wq[:, last] = wk[:, last] = 0.0
+    wq[w.d_node, last] = -1.0                                 # (the first time column is 1 at a distance of zero)
+    wk[0, last] = 3e38
+    o, g = orc.Oracle.from_workload(w, W, nf), binding.StreamTGN.from_workload(w, W, nf, delta_mode=delta, drift_gamma=0.9 if delta else 0.0)
+    for i in range(w.num_batches):
+        assert o.ingest(*st.batch(i))[0] == 0
+        g.ingest_batch(*st.batch(i))
+    nbr = rings_matrix(st.src, st.dst, w.num_edges, num_nodes, w.k)[0]
+    hit = (nbr >= 0) & over[nbr]
+    some = np.nonzero(~hit[:, :2].any(axis=1))[0]             # (a row's first chunk of entries gives the scores' reference: finite)
+    assert hit[some].any(axis=1).sum() > num_nodes // 20
+    ref = o.embed_all()[0][some]
+    for what in ("streamed", "rebuilt"):
+        close = rows_close(g.get_embeddings(some.astype(np.uint32), layer=1), ref)
+        assert close.all(), f"{what}: {(~close).sum()} of {some.size} rows, {hit[some][~close].any(axis=1).sum()} of them with such a neighbour"
+        g.full_rebuild()
+    g.close()
