@@ -126,7 +126,7 @@ LaunchArgs make_args(const Dev& d, uint32_t layer) {
   a.num_cu = d.num_cu;
   a.lds = (size_t)layer_impl::layer_lds(L.d_in, d.d_emb, d.heads, d.ks, d.nz, d.k, d.delta != 0, 16).total * sizeof(float);
   a.lds32 = (size_t)layer_impl::layer_lds(L.d_in, d.d_emb, d.heads, d.ks, d.nz, d.k, false, 32).total * sizeof(float);
-  a.tall = !d.delta && d.ks >= 2 && a.lds32 + 3072 <= kMaxLds / 2;
+  a.tall = !d.delta && d.ks >= 2 && a.lds32 + layer_impl::kFixedLds <= kMaxLds / 2;
   a.err = hipSuccess;
   return a;
 }
@@ -264,7 +264,7 @@ int layer_tiles_fit(const Dev& d, uint32_t nz) {
   if (a.wgs == 0) return 0;
   for (uint32_t l = 0; l < d.layers; ++l) {
     const size_t lds = (size_t)layer_impl::layer_lds(l ? d.d_emb : d.d0, d.d_emb, d.heads, d.ks, nz, d.k, false, 16).total * sizeof(float);
-    if (lds + 3072 > kMaxLds / a.wgs) return 0;
+    if (lds + layer_impl::kFixedLds > kMaxLds / a.wgs) return 0;
   }
   return 1;
 }
@@ -302,7 +302,7 @@ int setup_embed_attributes(const Dev& d) {
     a.query_wgs = 1;
     go_heads(a);
     if (a.wgs == 0) return -1;                                    // no kernel variant for this shape
-    if (a.lds + 3072 > kMaxLds / a.wgs) return -1;                // that many workgroups per CU, plus the static arrays
+    if (a.lds + layer_impl::kFixedLds > kMaxLds / a.wgs) return -1;   // that many workgroups per CU
     a.query_wgs = 0;
     a.set_attr = true;
     go_heads(a);

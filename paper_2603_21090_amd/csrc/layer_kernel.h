@@ -43,6 +43,7 @@ namespace stgn {
 namespace layer_impl {
 
 constexpr uint32_t kTM = 16;   // rows of a row tile
+constexpr uint32_t kFixedLds = 3072;   // bytes allowed for the kernels' LDS beside the tiles
 
 template <int CTRL>
 __device__ inline float dpp_mov(float x) {
@@ -204,6 +205,14 @@ __host__ __device__ constexpr int layer_waves(int ks, bool delta) { return delta
 enum { kFixed, kCounted, kByLength, kRotated };
 constexpr uint32_t kShortTiles = 4;
 
+// The kernel's own LDS, in front of the tiles: one block, whatever bodies a kernel holds (a body's own arrays would lie there
+// once for every body, the compiler does not overlay them).  kFixedLds is what the launches allow for it.
+template <int NT, int NW, uint32_t TM>
+struct FixedLds {
+  uint32_t node[2][TM], sum[NW], next[2];
+  __attribute__((aligned(16))) double om[NT * kSlot], ph[NT * kSlot];
+};
+
 // KS key slots in total (heads x slots per head), NT time slots; JC ring entries fetched together.
 // ES = 1: raw edge rows.  The vector z_j = [phi(dt_j) | f_j] of NZ = NT + 1 slots takes the place of phi(dt_j)
 // in the re-associated time products (scores: (W_K,h[time | edge] q_h) . z_j; values: (sum_j a_j z_j)
@@ -213,9 +222,9 @@ constexpr uint32_t kShortTiles = 4;
 // ROOTS: root-node inference (LayerArgs::root_src and on).  A variant of its own and not a test at run time: the
 // places that differ would cost every streamed launch registers.
 // RT: row tiles of a workgroup.
-template <int KS, int NT, int ES, int H, int JC, bool DELTA, bool QCACHE, bool ROOTS, int RT, int ORDER>
+template <int KS, int NT, int ES, int H, int JC, bool DELTA, bool QCACHE, bool ROOTS, int RT, int ORDER, class Fixed>
 __device__ __forceinline__
-void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uint32_t n) {
+void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uint32_t n, Fixed& fixed) {
   constexpr uint32_t TM = kTM * RT;           // rows of a workgroup
   extern __shared__ __align__(16) float lds[];
   constexpr int NW = layer_waves(KS, DELTA);  // waves
@@ -227,8 +236,11 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
   constexpr int GPR = DELTA ? 1 : KS;         // 16-lane groups per row in phase 3: one per key slot
   constexpr int RPP = 4 / GPR;                // rows a wave works on at a time there
   constexpr int PASSES = RPW / RPP;
-  __shared__ uint32_t s_node[2][TM], s_sum[NW], s_next[2];
-  __shared__ __align__(16) double s_om[NT * kSlot], s_ph[NT * kSlot];
+  auto& s_node = fixed.node;
+  auto& s_sum = fixed.sum;
+  auto& s_next = fixed.next;
+  auto& s_om = fixed.om;
+  auto& s_ph = fixed.ph;
   static_assert(KS % H == 0, "whole slots per head");
   static_assert(!(DELTA && ES), "the delta mode keeps projected edge rows");
   static_assert(!(DELTA && ROOTS), "root rows are computed exactly");
@@ -1342,7 +1354,9 @@ __global__ __launch_bounds__(64 * layer_waves(KS, DELTA), WGS * layer_waves(KS, 
 void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t* count_ptr, uint32_t count_max) {
   uint32_t n = count_max;
   if (count_ptr) { const uint32_t c = *count_ptr; n = c < count_max ? c : count_max; }
-  layer_body<KS, NT, ES, H, JC, DELTA, QCACHE, ROOTS, 1, DELTA || ROOTS ? kRotated : kByLength>(a, rows, n);
+  __shared__ FixedLds<NT, layer_waves(KS, DELTA), kTM> fixed;
+  static_assert(sizeof(fixed) <= kFixedLds, "the launches allow for it");
+  layer_body<KS, NT, ES, H, JC, DELTA, QCACHE, ROOTS, 1, DELTA || ROOTS ? kRotated : kByLength>(a, rows, n, fixed);
 }
 
 // Launches whose list may be long: tiles of 32 rows if it is, of 16 if not (the list's length is known on the device alone).
@@ -1359,8 +1373,10 @@ __global__ __launch_bounds__(512, 4)
 void layer32_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t* count_ptr, uint32_t count_max) {
   uint32_t n = count_max;
   if (count_ptr) { const uint32_t c = *count_ptr; n = c < count_max ? c : count_max; }
-  if (n > kShortTiles * kTM * gridDim.x) layer_body<KS, NT, ES, H, 1, false, QCACHE, false, 2, kCounted>(a, rows, n);
-  else layer_body<KS, NT, ES, H, 1, false, QCACHE, false, 1, kFixed>(a, rows, n);
+  __shared__ FixedLds<NT, 8, 2 * kTM> fixed;
+  static_assert(sizeof(fixed) <= kFixedLds, "the launches allow for it");
+  if (n > kShortTiles * kTM * gridDim.x) layer_body<KS, NT, ES, H, 1, false, QCACHE, false, 2, kCounted>(a, rows, n, fixed);
+  else layer_body<KS, NT, ES, H, 1, false, QCACHE, false, 1, kFixed>(a, rows, n, fixed);
 }
 
 // ---- dispatch over (heads, key slots, time slots)

@@ -1,4 +1,4 @@
-"""Registers of the layer kernel's variants, from the metadata the compiler wrote into the built library: what only link
+"""Registers and LDS of the layer kernel's variants, from the metadata the compiler wrote into the built library: what only link
 scores need must not crowd the variants that every streamed batch runs."""
 import os
 import re
@@ -15,8 +15,8 @@ VARIANT = re.compile(r"layer_kernelILi(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d)ELb
 
 
 @pytest.fixture(scope="module")
-def spills(tmp_path_factory):
-    """variant -> spilled vector registers"""
+def notes(tmp_path_factory):
+    """name of a layer kernel -> (spilled vector registers, bytes of LDS of its own)"""
     if not os.path.exists(binding.LIB_PATH):
         from paper_2603_21090_amd import build
         build.build_library()
@@ -32,11 +32,18 @@ def spills(tmp_path_factory):
                 continue
             obj = tmp_path_factory.mktemp("objects") / f"{len(out)}.o"
             obj.write_bytes(blob[at + off:at + off + size])
-            notes = subprocess.run([READELF, "--notes", str(obj)], capture_output=True, text=True, check=True).stdout
-            for name, spilled in re.findall(r"\.name:\s+(\S*layer_kernel\S*).*?\.vgpr_spill_count:\s+(\d+)", notes, re.S):
-                out[tuple(int(x or 0) for x in VARIANT.search(name).groups())] = int(spilled)
+            text = subprocess.run([READELF, "--notes", str(obj)], capture_output=True, text=True, check=True).stdout
+            for lds, name, spilled in re.findall(r"\.group_segment_fixed_size:\s+(\d+)(?:(?!\.group_segment).)*?\.name:\s+(\S*layer\w*_kernel\S*)"
+                                                 r".*?\.vgpr_spill_count:\s+(\d+)", text, re.S):
+                out[name] = (int(spilled), int(lds))
         at += len(magic)
     return out
+
+
+@pytest.fixture(scope="module")
+def spills(notes):
+    """variant -> spilled vector registers"""
+    return {tuple(int(x or 0) for x in m.groups()): n for name, (n, _) in notes.items() if (m := VARIANT.search(name))}
 
 
 @pytest.mark.parametrize("qcache", [0, 1])
@@ -60,3 +67,11 @@ def test_streamed_variants_of_one_and_four_key_slots(spills):
 def test_link_scores_have_variants_of_their_own(spills):
     streamed = {v[:8] for v in spills if not v[6] and not v[8]}
     assert streamed and streamed == {v[:8] for v in spills if v[8]}
+
+
+def test_the_launches_allow_for_the_kernels_own_lds(notes):
+    """Launches fit their tiles into what 3,072 bytes leave of a workgroup's share of the LDS (kFixedLds).  A kernel with two bodies
+    once held its arrays twice, 4,560 bytes: rows of 22 to 24 entries then had one workgroup per CU instead of two."""
+    assert any("layer32_kernel" in name for name in notes)
+    for name, (_, lds) in notes.items():
+        assert 0 < lds <= 3072, name
