@@ -297,9 +297,10 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
   derive_lane();
 
   // groups of a chunk that count, where a chunk is a slot: of a head's columns, of z
-  // (link scores, a tile or two per workgroup: all of them, the arguments' way to the scalar registers takes longer, 25.7 -> 26.2 us)
+  // (link scores, a tile or two per workgroup: all of them, the arguments' way to the scalar registers takes longer, 25.7 -> 26.2 us;
+  // delta mode with one slot, whose 168 registers are all in use: all of them, the branches cost sixteen spilled ones)
   auto groups_of = [&](auto used, uint32_t g0) {
-    if constexpr (ROOTS) return AllGroups{};
+    if constexpr (ROOTS || (DELTA && KS == 1)) return AllGroups{};
     else return groups_in((used(args()) + 15u) >> 4, g0);
   };
   auto groups_head = [&](uint32_t slot) { return groups_of([](ArgBlock p) { return p->dk; }, (SH == 1 ? 0u : slot % SH) * kCG); };

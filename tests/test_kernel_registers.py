@@ -75,3 +75,11 @@ def test_the_launches_allow_for_the_kernels_own_lds(notes):
     assert any("layer32_kernel" in name for name in notes)
     for name, (_, lds) in notes.items():
         assert 0 < lds <= 3072, name
+
+
+def test_delta_variants(spills):
+    """One slot (168 registers): one spilled at most; two: none; four, eight in the widest."""
+    delta = {v: n for v, n in spills.items() if v[6]}
+    assert {v[0] for v in delta} == {1, 2, 4}
+    for v, n in delta.items():
+        assert n <= {1: 1, 2: 0, 4: 8}[v[0]], v
