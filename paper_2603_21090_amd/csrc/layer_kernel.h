@@ -743,9 +743,10 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
           if (keep) *reinterpret_cast<float4*>(qrow + kSlot * g) = qk[p % NP];
 #pragma unroll
           for (int i = 0; i < NZL; ++i) {
-            const uint32_t t = SH == 1 ? (uint32_t)i : sg + SH * i, at = head * Ztp + (t < NZ ? t : 0u) * kSlot;
+            // (a lane without a slot of its own reads slot 0 against zeros: that slot's padding is cleared there too)
+            const uint32_t t = SH == 1 ? (uint32_t)i : sg + SH * i, tz = t < NZ ? t : 0u, at = head * Ztp + tz * kSlot;
             qt[p % NP][i] = *reinterpret_cast<const float4*>(Zs + local * ll.ldz + at + 4u * sub);
-            if (SH > 1 || i >= NT - 1) clear_padding(qt[p % NP][i], t);
+            if (SH > 1 || i >= NT - 1) clear_padding(qt[p % NP][i], tz);
             if (keep && t < NZ) *reinterpret_cast<float4*>(qrow + kSlot * KS + at) = qt[p % NP][i];
           }
     };

@@ -58,6 +58,46 @@ def test_a_nan_stays_in_the_rows_of_its_tile(kw):
     _check(binding, w, **(dict(edge=1) if w.d_edge else dict(node="quiet")))
 
 
+@pytest.mark.parametrize("kw", [dict(d_edge=70, heads=2, d_emb=100, d_time=70), dict(d_edge=9, heads=2, d_emb=100, d_time=70), dict(d_edge=66, heads=2, d_emb=140, d_time=20),
+                                dict(d_edge=66, heads=2, d_emb=140, d_time=70), dict(d_edge=0, heads=1, d_emb=100, d_time=20), dict(d_edge=9, heads=1, d_emb=100, d_time=70),
+                                dict(d_edge=9, heads=1, d_emb=200, d_time=20), dict(d_edge=0, heads=1, d_emb=200, d_time=40), dict(d_edge=0, heads=4, d_emb=60, d_time=20),
+                                dict(d_edge=70, heads=2, d_emb=100, d_mem=12, d_node=0, d_time=20)])
+def test_nans_stay_in_their_rows_through_the_tiles_of_a_workgroup(kw):
+    """A NaN in one node of sixty (models with a memory: one edge in a hundred of the last two batches) reaches rows of most tiles, so that
+    tiles follow others that held one in the same place of the LDS.  Lists are long enough for tiles of 32 rows, and batches read the
+    queries of some tiles back and project others; the rows that the oracle says are not reached keep their bits."""
+    import torch
+    from paper_2603_21090_amd import binding
+    w = tiny_workload(**{**dict(num_nodes=42_001, num_edges=64_000, batch=8_000, zipf_s=0.2, layers=2, d_mem=0, d_node=20, k=4), **kw})
+    W, nf, st = synth.make_weights(w), synth.node_features(w), synth.EdgeStream(w)
+    bad_nf = None if nf is None else nf.copy()
+    if nf is not None:
+        bad_nf[7::60, 0] = np.nan
+    o = orc.Oracle.from_workload(w, W, bad_nf)
+    a, b = binding.StreamTGN.from_workload(w, W, nf), binding.StreamTGN.from_workload(w, W, bad_nf)
+    every, long_lists = np.arange(w.num_nodes, dtype=np.uint32), 4 * 16 * 2 * torch.cuda.get_device_properties(0).multi_processor_count
+    for i in range(w.num_batches):
+        s, d, t, ef = st.batch(i)
+        bad_ef = ef.copy()
+        if nf is None and i >= 6:
+            bad_ef[::100, 0] = np.nan
+        listed = a.ingest_batch(s, d, t, ef, stats=True)["n_affected"]
+        b.ingest_batch(s, d, t, bad_ef)
+        assert o.ingest(s, d, t, bad_ef)[0] == 0
+    assert listed > long_lists, listed
+    ref = o.embed_all()
+    for what in ("streamed", "rebuilt"):
+        for l in range(1, w.layers + 1):
+            reached = np.isnan(ref[l - 1]).any(axis=1)
+            assert 0 < reached.sum() < w.num_nodes // 2
+            x, y = a.get_embeddings(every, layer=l), b.get_embeddings(every, layer=l)
+            assert not np.isnan(x).any() and np.isnan(y[reached]).any(axis=1).all()
+            off = np.nonzero((x != y).any(axis=1) & ~reached)[0]
+            assert off.size == 0, f"{what}, layer {l}: rows {off[:8]} ({off.size} in all) beside the {reached.sum()} reached"
+        a.full_rebuild(), b.full_rebuild()
+    a.close(), b.close()
+
+
 @pytest.mark.parametrize("heads, dk", [(1, 1), (1, 4), (1, 63), (1, 64), (1, 65), (1, 129), (1, 200), (2, 3), (2, 5), (2, 16), (2, 50), (2, 64),
                                        (2, 66), (2, 127), (4, 1), (4, 7), (4, 25), (4, 33), (4, 61)])
 @pytest.mark.parametrize("kw", [dict(d_edge=9), dict(d_edge=70), dict(d_edge=0), dict(d_edge=9, delta_mode=1)])
