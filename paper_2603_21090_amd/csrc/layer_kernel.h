@@ -305,8 +305,10 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
   };
   auto groups_head = [&](uint32_t slot) { return groups_of([](ArgBlock p) { return p->dk; }, (SH == 1 ? 0u : slot % SH) * kCG); };
   auto groups4 = [&](uint32_t slot) {
-    const bool edge = ES && slot == NT;
-    return groups_of([=](ArgBlock p) { return edge ? p->d_edge : p->d_time; }, edge ? 0u : slot * kCG);
+    if constexpr (ES) {                                       // (two closures without captures: a captured flag went through scratch memory)
+      if (slot == NT) return groups_of([](ArgBlock p) { return p->d_edge; }, 0u);
+    }
+    return groups_of([](ArgBlock p) { return p->d_time; }, slot * kCG);
   };
 
   // ---- phase-2 work units: (head, NTL valid qt column tiles); wave w owns units w, w + NW, ...

@@ -16,7 +16,7 @@ VARIANT = re.compile(r"layer_kernelILi(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d)ELi(\d)ELb
 
 @pytest.fixture(scope="module")
 def notes(tmp_path_factory):
-    """name of a layer kernel -> (spilled vector registers, bytes of LDS of its own)"""
+    """name of a layer kernel -> (spilled vector registers, bytes of LDS of its own, bytes of scratch memory a lane)"""
     if not os.path.exists(binding.LIB_PATH):
         from paper_2603_21090_amd import build
         build.build_library()
@@ -33,9 +33,10 @@ def notes(tmp_path_factory):
             obj = tmp_path_factory.mktemp("objects") / f"{len(out)}.o"
             obj.write_bytes(blob[at + off:at + off + size])
             text = subprocess.run([READELF, "--notes", str(obj)], capture_output=True, text=True, check=True).stdout
-            for lds, name, spilled in re.findall(r"\.group_segment_fixed_size:\s+(\d+)(?:(?!\.group_segment).)*?\.name:\s+(\S*layer\w*_kernel\S*)"
-                                                 r".*?\.vgpr_spill_count:\s+(\d+)", text, re.S):
-                out[name] = (int(spilled), int(lds))
+            for block in re.split(r"\n  - ", text):            # (a kernel's entry)
+                if (name := re.search(r"\.name:\s+(\S*layer\w*_kernel\S*)", block)):
+                    out[name[1]] = tuple(int(re.search(rf"\.{field}:\s+(\d+)", block)[1])
+                                         for field in ("vgpr_spill_count", "group_segment_fixed_size", "private_segment_fixed_size"))
         at += len(magic)
     return out
 
@@ -43,7 +44,7 @@ def notes(tmp_path_factory):
 @pytest.fixture(scope="module")
 def spills(notes):
     """variant -> spilled vector registers"""
-    return {tuple(int(x or 0) for x in m.groups()): n for name, (n, _) in notes.items() if (m := VARIANT.search(name))}
+    return {tuple(int(x or 0) for x in m.groups()): n for name, (n, _, _) in notes.items() if (m := VARIANT.search(name))}
 
 
 @pytest.mark.parametrize("qcache", [0, 1])
@@ -73,7 +74,7 @@ def test_the_launches_allow_for_the_kernels_own_lds(notes):
     """Launches fit their tiles into what 3,072 bytes leave of a workgroup's share of the LDS (kFixedLds).  A kernel with two bodies
     once held its arrays twice, 4,560 bytes: rows of 22 to 24 entries then had one workgroup per CU instead of two."""
     assert any("layer32_kernel" in name for name in notes)
-    for name, (_, lds) in notes.items():
+    for name, (_, lds, _) in notes.items():
         assert 0 < lds <= 3072, name
 
 
@@ -83,3 +84,10 @@ def test_delta_variants(spills):
     assert {v[0] for v in delta} == {1, 2, 4}
     for v, n in delta.items():
         assert n <= {1: 1, 2: 0, 4: 8}[v[0]], v
+
+
+def test_nothing_but_spilled_registers_lies_in_scratch_memory(notes):
+    """What a kernel keeps in scratch memory of its own will is a store and a load in front of what it is for (a flag of the products'
+    groups was, once per chunk, with raw edge rows)."""
+    for name, (spilled, _, scratch) in notes.items():
+        assert spilled or not scratch, (name, scratch)
