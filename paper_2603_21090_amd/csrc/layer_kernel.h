@@ -100,8 +100,8 @@ struct LayerLds {
 // that two workgroups of the widest common shapes fit a CU (two slots, two heads, two time slots, raw edge rows, k = 20: 79 KB,
 // where storage of its own for each makes 94).  The cached part of the head outputs lies where q was and is completed in place,
 // and a row's input lies behind the columns of its output row in the row's share of the qt / pb tile.
-__host__ __device__ inline LayerLds layer_lds(uint32_t d_in, uint32_t d_emb, uint32_t heads, uint32_t ks, uint32_t nz, uint32_t k, bool delta, uint32_t tm) {
-  LayerLds l;
+__host__ __device__ constexpr LayerLds layer_lds(uint32_t d_in, uint32_t d_emb, uint32_t heads, uint32_t ks, uint32_t nz, uint32_t k, bool delta, uint32_t tm) {
+  LayerLds l{};
   const uint32_t wx = round_up(d_in, kGrpK), wo = kSlot * ks, wh = round_up(d_emb, kChunkK);
   l.ldq = wo + 4;                                 // q in the padded-head layout, later the head outputs
   l.ldz = heads * kSlot * nz + 4;
@@ -299,16 +299,16 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
   // groups of a chunk that count, where a chunk is a slot: of a head's columns, of z
   // (link scores, a tile or two per workgroup: all of them, the arguments' way to the scalar registers takes longer, 25.7 -> 26.2 us;
   // delta mode with one slot, whose 168 registers are all in use: all of them, the branches cost sixteen spilled ones)
-  auto groups_of = [&](auto used, uint32_t g0) {
+  auto groups_used = [&](auto used, uint32_t g0) {
     if constexpr (ROOTS || (DELTA && KS == 1)) return AllGroups{};
     else return groups_in((used(args()) + 15u) >> 4, g0);
   };
-  auto groups_head = [&](uint32_t slot) { return groups_of([](ArgBlock p) { return p->dk; }, (SH == 1 ? 0u : slot % SH) * kCG); };
+  auto groups_head = [&](uint32_t slot) { return groups_used([](ArgBlock p) { return p->dk; }, (SH == 1 ? 0u : slot % SH) * kCG); };
   auto groups4 = [&](uint32_t slot) {
     if constexpr (ES) {                                       // (two closures without captures: a captured flag went through scratch memory)
-      if (slot == NT) return groups_of([](ArgBlock p) { return p->d_edge; }, 0u);
+      if (slot == NT) return groups_used([](ArgBlock p) { return p->d_edge; }, 0u);
     }
-    return groups_of([](ArgBlock p) { return p->d_time; }, slot * kCG);
+    return groups_used([](ArgBlock p) { return p->d_time; }, slot * kCG);
   };
 
   // ---- phase-2 work units: (head, NTL valid qt column tiles); wave w owns units w, w + NW, ...
@@ -333,9 +333,9 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
     return u;
   };
   auto wkt = [&](uint32_t h, uint32_t t) { return a.WKT + (size_t)(h * ntz + t) * SH * kChunkFloats; };
-  auto request2 = [&](const Unit2& u, Ops16<NTL>& o) {
-    load_b16(wkt(u.h, u.t0), 0, o.b[0], lane);
-    if constexpr (NTL == 2) load_b16(wkt(u.h, u.t1), 0, o.b[1], lane);
+  auto request2 = [&](const Unit2& u, float4 (&b)[NTL][kCG]) {
+    load_b16(wkt(u.h, u.t0), 0, b[0], lane);
+    if constexpr (NTL == 2) load_b16(wkt(u.h, u.t1), 0, b[1], lane);
   };
   auto store2 = [&](const Unit2& u, const floatx4 (&acc)[RT][NTL]) {
 #pragma unroll
@@ -588,7 +588,7 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
   Upfront16<NTL, C1> u1;
   float c1v[NTL];                                             // this lane's c_Q of the first unit
   constexpr int U2 = SH == 1 ? 2 : 1;                         // phase 2's units requested up front
-  Ops16<NTL> o2[U2];
+  float4 o2[U2][NTL][kCG];
   auto request12 = [&]() {
     const float* const wq = args()->WQ;
     const float* B1[NTL];
@@ -654,7 +654,7 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
       commit_x(false);
     }
     __syncthreads();                                          // input rows there, the previous tile's head outputs read
-    auto groups1 = [&](uint32_t ch) { return groups_of([](ArgBlock p) { return p->d_in; }, ch * kCG); };
+    auto groups1 = [&](uint32_t ch) { return groups_used([](ArgBlock p) { return p->d_in; }, ch * kCG); };
     auto store1 = [&](uint32_t nt, const floatx4 (&acc)[RT][NTL]) {
 #pragma unroll
       for (int t = 0; t < NTL; ++t) {
@@ -691,11 +691,11 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
     // ================================================================ phase 2: qt_h = q_h W_K,h[time]^T
     {
       const float* qa = Qs + a16_off(lane, ll.ldq);
-      auto products2 = [&](uint32_t i, Ops16<NTL>& o) {
+      auto products2 = [&](uint32_t i, float4 (&b)[NTL][kCG]) {
         const Unit2 u = decode2(i);
         floatx4 acc[RT][NTL] = {};
         const float* qh = qa + u.h * (SH * kSlot);
-        mfma16_chunk_rows<RT, NTL>(qh, kTM * ll.ldq, 0, o.b, acc, groups_head(0u));
+        mfma16_chunk_rows<RT, NTL>(qh, kTM * ll.ldq, 0, b, acc, groups_head(0u));
         if constexpr (SH > 1) {
           const float* Bt[NTL];
           Bt[0] = wkt(u.h, u.t0);
@@ -1290,7 +1290,7 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
       load_b16(wkv(wave), 0, b6[0][0], lane);
       load_b16(wkv(wave), c1 * kCG, b6[1][0], lane);
       __syncthreads();
-      auto groups6 = [&](uint32_t ch) { return groups_of([](ArgBlock p) { return p->d_emb; }, ch * kCG); };
+      auto groups6 = [&](uint32_t ch) { return groups_used([](ArgBlock p) { return p->d_emb; }, ch * kCG); };
       auto chunk6 = [&](uint32_t ch, const float4 (&b)[1][kCG], floatx4 (&acc)[RT][1]) {
         mfma16_chunk_rows<RT, 1>(Ha, kTM * ldh, ch * kCG, b, acc, groups6(ch));
       };
@@ -1383,6 +1383,11 @@ void layer32_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32
   else layer_body<KS, NT, ES, H, 1, false, QCACHE, false, 1, kFixed>(a, rows, n, fixed);
 }
 
+// Whether tiles of 32 rows of the narrowest model of these slots leave room for two workgroups per CU (else there is no such kernel).
+constexpr bool layer32_fits(int ks, int nz, int heads) {
+  return layer_lds(1, heads, heads, ks, nz, 1, false, 32).total * sizeof(float) + kFixedLds <= kMaxLds / 2;
+}
+
 // ---- dispatch over (heads, key slots, time slots)
 struct LaunchArgs {
   LayerArgs k;
@@ -1411,12 +1416,12 @@ void go_k(LaunchArgs& a) {
       a.err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)a.lds);
       if (a.err == hipSuccess) granted = a.lds;
     }
-    if constexpr (!DELTA && !ROOTS && KS >= 2) {
+    if constexpr (!DELTA && !ROOTS && KS >= 2 && layer32_fits(KS, NT + ES, H)) {
       if (a.err == hipSuccess && a.tall) a.err = hipFuncSetAttribute((const void*)layer32_kernel<KS, NT, ES, H, QCACHE>, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
     }
     return;
   }
-  if constexpr (!DELTA && !ROOTS && KS >= 2) {
+  if constexpr (!DELTA && !ROOTS && KS >= 2 && layer32_fits(KS, NT + ES, H)) {
     if (a.tall && a.cm > kShortTiles * kTM * std::min(2u * (a.num_cu ? a.num_cu : 256u), kStatSlots)) {
       auto kern = layer32_kernel<KS, NT, ES, H, QCACHE>;
       const uint32_t cap = std::min(2u * (a.num_cu ? a.num_cu : 256u), kStatSlots);

@@ -87,8 +87,8 @@ __device__ inline void mfma16_one(const float4& a, const float4 (&b)[NTL][kCG], 
     acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(comp4<U>(a), comp4<U>(b[t][c]), acc[t], 0, 0, 0);
 }
 
-// all 16 k-steps of one chunk, for NTL column tiles sharing the A operand.  Straight-line code: K is
-// padded to whole chunks (zero weights, finite A), which costs a few surplus products and buys a
+// all 16 k-steps of one chunk, for NTL column tiles sharing the A operand (memory update, projections).  Straight-line code:
+// K is padded to whole chunks (zero weights, finite A), which costs a few surplus products and buys a
 // loop body without branches that the compiler can schedule around the outstanding loads.
 template <int NTL>
 __device__ inline void mfma16_chunk(const float4 (&a)[kCG], const float4 (&b)[NTL][kCG], floatx4 (&acc)[NTL]) {
@@ -248,22 +248,8 @@ __device__ __forceinline__ void mfma16_gemm(const float* Ap, uint32_t nchunks, c
   mfma16_gemm_pre<NTL>(Ap, nchunks, Bt, acc, P, last);
 }
 
-// Chunks [c0, c1) of a product with one buffer: for what a shape has beyond the products its kernel is tuned for, where the
-// registers of a second buffer would cost those.
-template <int NTL>
-__device__ __forceinline__ void mfma16_lean(const float* Ap, uint32_t c0, uint32_t c1, const float* const (&Bt)[NTL],
-                                            floatx4 (&acc)[NTL], uint32_t lane, uint32_t last = kNoLimit) {
-#pragma unroll 1
-  for (uint32_t ch = c0; ch < c1; ++ch) {
-    Ops16<NTL> o;
-#pragma unroll
-    for (int t = 0; t < NTL; ++t) load_b16(Bt[t], ch * kCG, o.b[t], lane);
-    load_a16(Ap, ch * kCG, o.a, last);
-    mfma16_chunk<NTL>(o, acc);
-  }
-}
-
-// ... for RT row tiles
+// Chunks [c0, c1) of a product for RT row tiles with one buffer: for what a shape has beyond the products its kernel is tuned
+// for, where the registers of a second buffer would cost those.
 template <int RT, int NTL, class Groups>
 __device__ __forceinline__ void mfma16_lean_rows(const float* Ap, uint32_t rs, uint32_t c0, uint32_t c1, const float* const (&Bt)[NTL],
                                                  floatx4 (&acc)[RT][NTL], uint32_t lane, Groups ng, uint32_t last = kNoLimit) {
@@ -311,12 +297,6 @@ struct Upfront16 {
     for (int ch = 0; ch < MAXC; ++ch)
       if ((uint32_t)ch < nchunks) mfma16_chunk_rows<RT, NTL>(Ap, rs, ch * kCG, b[ch], acc, ng((uint32_t)ch), last);
     mfma16_lean_rows<RT, NTL>(Ap, rs, MAXC, nchunks, Bt, acc, lane, ng, last);
-  }
-  // the whole product, also where K has more chunks than were requested
-  __device__ __forceinline__ void multiply(const float* Ap, uint32_t nchunks, const float* const (&Bt)[NTL],
-                                           floatx4 (&acc)[NTL], uint32_t lane, uint32_t last = kNoLimit) {
-    multiply(Ap, nchunks, acc, last);
-    mfma16_lean<NTL>(Ap, MAXC, nchunks, Bt, acc, lane, last);
   }
 };
 

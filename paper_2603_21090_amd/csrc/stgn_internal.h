@@ -228,7 +228,7 @@ struct Dev {
   LayerDev L[STGN_MAX_LAYERS];
 };
 
-inline __host__ __device__ uint32_t round_up(uint32_t x, uint32_t m) { return (x + m - 1) / m * m; }
+constexpr __host__ __device__ uint32_t round_up(uint32_t x, uint32_t m) { return (x + m - 1) / m * m; }
 
 // the device description a batch of the given parity is enqueued with
 // set: which copy of the per-batch state (0 .. kSets - 1); flag_par: which dirty-flag array (0 / 1)
