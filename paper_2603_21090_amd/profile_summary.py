@@ -2,13 +2,13 @@
 
     python -m paper_2603_21090_amd.profile_summary trace  <dir> <bench.json>
     python -m paper_2603_21090_amd.profile_summary traffic <fetch dir> <write dir> <bench.json>
-    python -m paper_2603_21090_amd.profile_summary counters <pmc dir> <kernel name part> <last n dispatches>
+    python -m paper_2603_21090_amd.profile_summary counters <pmc dir> <kernel name, a regular expression> <last n dispatches>
 
 `trace` reads `*_kernel_stats.csv` and `*_kernel_trace.csv` of a `--kernel-trace --stats` run and
 prints the per-kernel table plus, for the layer kernel, the average duration over the launches of
 the batch range in which bench.py took its own event timings (`roofline.batches`).
 
-`counters` prints, for the last n dispatches of the kernels whose name contains the given text, the
+`counters` prints, for the last n dispatches of the kernels whose name matches the given regular expression, the
 average of every counter in a `--pmc` run's `*_counter_collection.csv` and the average duration.
 
 `traffic` reads the `*_counter_collection.csv` of one `--pmc FETCH_SIZE` and one `--pmc WRITE_SIZE`
@@ -23,9 +23,11 @@ import csv
 import glob
 import json
 import os
+import re
 import sys
 
 GIB_KIB = float(1 << 20)
+LAYER = re.compile(r"layer(32)?_kernel")     # tiles of sixteen rows; kernels for long lists, with tiles of 32
 
 
 def _one(dirname, pattern):
@@ -51,7 +53,7 @@ def trace(dirname, bench_json):
               f"{int(r['MaxNs']) / 1e3:>10.2f}")
     rows = list(csv.DictReader(open(_one(dirname, "*kernel_trace.csv"))))
     rows.sort(key=lambda r: int(r["Start_Timestamp"]))
-    lay = [r for r in rows if "layer_kernel" in r["Kernel_Name"]]
+    lay = [r for r in rows if LAYER.search(r["Kernel_Name"])]
     dur = [int(r["End_Timestamp"]) - int(r["Start_Timestamp"]) for r in lay]
     # the first `layers` launches are the rebuild at creation; batch b's launches follow those of batch b - 1
     sel = dur[(b0 + 1) * layers:(b1 + 1) * layers]
@@ -91,7 +93,7 @@ def traffic(fetch_dir, write_dir, bench_json):
     total = 0.0
     for counter, dirname in (("FETCH_SIZE", fetch_dir), ("WRITE_SIZE", write_dir)):
         disp = _counter(dirname, counter)
-        lay = [v for n, v in disp if "layer_kernel" in n][(b0 + 1) * layers:(b1 + 1) * layers]   # (creation launches first)
+        lay = [v for n, v in disp if LAYER.search(n)][(b0 + 1) * layers:(b1 + 1) * layers]   # (creation launches first)
         # (the first copy also pages memory in; the random fills of bench.py's gather yardstick, behind the copies on the
         # workloads that have one, are elementwise kernels of other names)
         cal = [v for n, v in disp if "vectorized_elementwise" in n][-4:]
@@ -106,11 +108,13 @@ def traffic(fetch_dir, write_dir, bench_json):
     print(f"algorithmic bytes per launch (bench.py, same batches): {algo / 1e6:.3f} MB")
     print(f"workload = {bench['config']['workload'].split(':')[0]}")
     print(f"batches = [{b0}, {b1}]")
+    if "cached_row_floats" in bench["roofline"]:
+        print(f"cached_row_floats = {bench['roofline']['cached_row_floats']}")
     print(f"traffic_bytes_per_launch = {total:.0f}")
 
 
 def counters(dirname, name_part, last_n):
-    rows = [r for r in csv.DictReader(open(_one(dirname, "*counter_collection.csv"))) if name_part in r["Kernel_Name"]]
+    rows = [r for r in csv.DictReader(open(_one(dirname, "*counter_collection.csv"))) if re.search(name_part, r["Kernel_Name"])]
     ids = sorted({int(r["Dispatch_Id"]) for r in rows})[-int(last_n):]
     keep = set(ids)
     agg, dur = collections.defaultdict(float), {}
