@@ -19,7 +19,7 @@ FIXED position of the stream, whatever --warmup / --steps say:
   kernels  next batches with one HIP event pair per launch     -> per-kernel average duration,
                                                                   roofline of the dominant kernel
   cpu      the CPU oracle on a bounded sample of the same workload, 1 core
-  copy     a plain 1 GiB copy and a bare gather of the layer launch's own mix of rows, after the
+  copy     a plain 1 GiB copy and a bare gather of as many random rows as a layer launch reads, after the
            library's context is gone                           -> roofline.measured_copy_GBs, roofline.bare_gather
 
 Prints ONE JSON line.
@@ -91,10 +91,11 @@ def projection_flops_per_row(w, layer, delta_mode=False):
     return q, o
 
 
-def stored_traffic(workload, batches):
+def stored_traffic(workload, batches, row_floats=None):
     """HBM bytes per layer-kernel launch from the hardware counters.  Counters cannot be read from
     inside this process; the figure comes from the two counter runs of this same command whose
-    summary is kept as text under profiles/, and applies only to the same workload and batch range."""
+    summary is kept as text under profiles/, and applies only to the same workload and batch range, and to
+    cached rows of the same width (where `row_floats` is given)."""
     path = os.path.join(ROOT, "profiles", f"layer_kernel_{workload}_hbm_traffic.txt")
     try:
         text = open(path).read()
@@ -103,6 +104,9 @@ def stored_traffic(workload, batches):
     m = re.search(r"^traffic_bytes_per_launch\s*=\s*([0-9.eE+]+)", text, re.M)
     r = re.search(r"^batches\s*=\s*\[(\d+),\s*(\d+)\]", text, re.M)
     if not m or not r or [int(r.group(1)), int(r.group(2))] != list(batches):
+        return None
+    c = re.search(r"^cached_row_floats\s*=\s*(\d+)", text, re.M)
+    if row_floats is not None and (not c or int(c.group(1)) != row_floats):
         return None
     return float(m.group(1))
 
@@ -431,7 +435,8 @@ def main():
         roofline["avg_launch_us"] = kernels[roofline["kernel"]]["avg_us"]
         roofline["event_overhead_us"] = overhead_us
         roofline["batches"] = kernel_pass
-        roofline["traffic"] = stored_traffic(w.name, kernel_pass)
+        roofline["cached_row_floats"] = cached_row_floats(w)
+        roofline["traffic"] = stored_traffic(w.name, kernel_pass, cached_row_floats(w))
 
     # delta mode: how far the cached rows have moved from what an exact recomputation of the same state gives
     delta = None
@@ -556,9 +561,10 @@ def main():
     torch.cuda.synchronize()
     copy_gbs = 4 * 2 * (1 << 30) / (e0.elapsed_time(e1) * 1e-3) / 1e9
     del a_, b_
-    # a bare gather with the layer launch's own mix (rows recomputed, entries per row, a 1 KiB cached row and
-    # a 256-byte or 1 KiB edge row per entry, uniformly random rows of tables of the workload's sizes): what the
-    # memory system delivers to the kernel's access pattern when nothing else is asked of the chip
+    # a bare gather of as many entries as a layer launch has (rows recomputed, entries per row, a 1 KiB row of a table of the
+    # nodes and a 256-byte or 1 KiB edge row per entry, uniformly random): the rate at which the memory system delivers random
+    # rows when nothing else is asked of the chip.  The launch's own node rows are `cached_row_floats` wide (the probe takes rows
+    # of 64 or 256 floats), so the two times are not to be divided by each other.
     gather = None
     if out["roofline"] is not None and w.num_nodes >= 32768:
         rows_l = max(int(out["roofline"]["rows_per_launch"]), 1)
@@ -587,8 +593,7 @@ def main():
         g_us = e0.elapsed_time(e1) * 1e3 / 4
         g_bytes = rows_l * per * 4 * (256 + edge_floats)
         gather = {"us": g_us, "GBs": g_bytes / g_us / 1e3, "groups": rows_l, "entries_per_group": per,
-                  "bytes_per_entry": 4 * (256 + edge_floats),
-                  "layer_launch_over_bare_gather": out["roofline"]["avg_launch_us"] / g_us}
+                  "bytes_per_entry": 4 * (256 + edge_floats), "node_row_bytes": 1024, "edge_row_bytes": 4 * edge_floats}
         del tn, te, i_n, i_e, o_
     if out["roofline"] is not None:
         out["roofline"]["bare_gather"] = gather

@@ -40,3 +40,16 @@ def test_kernels_of_long_lists_are_layer_launches_too(tmp_path, capsys):
     profile_summary.traffic(str(tmp_path / "FETCH_SIZE"), str(tmp_path / "WRITE_SIZE"), str(tmp_path / "bench.json"))
     out = capsys.readouterr().out
     assert "4 launches: mean 35.0 units" in out and "cached_row_floats = 208" in out
+
+
+def test_counter_traffic_of_another_row_width_is_not_reported(tmp_path, monkeypatch):
+    import bench
+    (tmp_path / "profiles").mkdir()
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    path = tmp_path / "profiles" / "layer_kernel_C5_hbm_traffic.txt"
+    path.write_text("batches = [3, 5]\ntraffic_bytes_per_launch = 100\n")
+    assert bench.stored_traffic("C5", [3, 5], 208) is None                 # (a file that does not say)
+    path.write_text("batches = [3, 5]\ncached_row_floats = 256\ntraffic_bytes_per_launch = 100\n")
+    assert bench.stored_traffic("C5", [3, 5], 208) is None
+    path.write_text("batches = [3, 5]\ncached_row_floats = 208\ntraffic_bytes_per_launch = 100\n")
+    assert bench.stored_traffic("C5", [3, 5], 208) == 100.0 and bench.stored_traffic("C5", [3, 6], 208) is None
