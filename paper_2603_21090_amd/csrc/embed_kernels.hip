@@ -109,7 +109,7 @@ LaunchArgs make_args(const Dev& d, uint32_t layer) {
   k.ld_in = d.H[layer].ld; k.ld_out = d.H[layer + 1].ld; k.ld_kv = d.ld_kv; k.hs = d.hs; k.ld_kve = d.KVE[layer].ld;
   k.window = d.window;
   k.tile_next = d.tile_next + layer * kStatLine;
-  k.k = d.k; k.d_in = L.d_in; k.d_emb = d.d_emb; k.dk = d.dk; k.d_time = d.d_time; k.d_edge = d.d_edge;
+  k.k = d.k; k.k_inv = 0xFFFFFFFFu / d.k; k.d_in = L.d_in; k.d_emb = d.d_emb; k.dk = d.dk; k.d_time = d.d_time; k.d_edge = d.d_edge;
   if (d.delta) {
     k.flags = d.flags_kept;
     k.thr_in = d.d_mem ? layer + 1u : layer;                  // flags at or below: the owner's input row of this layer changed

@@ -148,6 +148,7 @@ struct LayerArgs {
   const float *WQ, *cQ, *WKT, *WV, *WO, *bO, *WKVnext;   // matrices group-major (mfma16.h)
   uint32_t ld_in, ld_out, ld_kv, ld_kve, hs;       // hs: floats of a head's keys in a cached row (values are heads hs further on); ld_kve = 0 without edge features (every edge reads one zero row)
   uint32_t k, d_in, d_emb, dk, d_time, d_edge;
+  uint32_t k_inv;                                  // (2^32 - 1) / k
   // query cache (null: off): this layer's cached q | qt rows, [node][64 (KS + H NZ)], and per tile of the row list whether
   // every row's input row is unchanged (then q and qt are read back, not projected); a launch that must recompute everything
   // takes the variant without the cache, which still refreshes QC.  Link scores read every root's row back: nothing changed.
@@ -313,7 +314,8 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
 
   // ---- phase-2 work units: (head, NTL valid qt column tiles); wave w owns units w, w + NW, ...
   // Lane i of `udesc` holds the description of the wave's i-th unit (head, first tile, second tile, whether there is a
-  // second one), worked out once; inside the tile loop a unit costs one cross-lane read.
+  // second one), worked out once; inside the tile loop a unit costs one cross-lane read.  Lanes past the last unit describe the
+  // first again (an idle wave's: head 0, tile 0).
   const uint32_t npr = (nzt + NTL - 1u) / NTL, nunits2 = H * npr;
   const uint32_t nu2 = wave < nunits2 ? (nunits2 - wave + (NW - 1u)) / NW : 0u;     // units of this wave
   struct Unit2 { uint32_t h, t0, t1; bool two; };
@@ -321,7 +323,8 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
   auto describe2 = [&]() {
     // the i-th valid tile: time tiles first, then (raw edge rows) the tiles of slot NT
     auto vt = [&](uint32_t i) { return i < nzt_t ? i : 4u * NT + (i - nzt_t); };
-    const uint32_t x = wave + NW * (lane < nu2 ? lane : 0u), h = x / npr, i0 = NTL * (x - h * npr);
+    const uint32_t x = wave + NW * (lane < nu2 ? lane : 0u);
+    const uint32_t h = (H > 1 && x >= npr ? 1u : 0u) + (H > 2 && x >= 2u * npr ? 1u : 0u) + (H > 2 && x >= 3u * npr ? 1u : 0u), i0 = NTL * (x - h * npr);
     const uint32_t two = NTL == 2 && i0 + 1u < nzt ? 1u : 0u;
     udesc = nu2 ? h | (vt(i0) << 8) | (vt(i0 + two) << 16) | (two << 24) : 0u;
   };
@@ -448,7 +451,11 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
     tq_s = pf_ok || ROOTS ? p_tl : a.t_last[nn];
     const uint32_t dg = live ? dg0 : 0u;
     cnt_s = dg < k ? dg : k;
-    const uint32_t newest = dg ? (dg - 1u) % k : 0u;
+    // (dg - 1) mod k.  A division here, like one anywhere in the tile loop, is a reciprocal that the compiler keeps in a vector
+    // register through the whole loop and spills; its reload then waited for every request in flight.
+    uint32_t newest = dg ? dg - 1u : 0u;
+    newest -= __umulhi(newest, args()->k_inv) * k;            // (the quotient is exact or one short)
+    newest = newest >= k ? newest - k : newest;
     // the record of adjacency position p sits in ring slot p mod k; with the row's degree known, slot
     // sl holds the j-th most recent entry, j = (newest - sl) mod k; places past the row's entry count
     // name node 0 / edge 0, whose cached rows are there to be gathered (they may be NaN: such places are left out of every sum)
@@ -598,7 +605,7 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
 #pragma unroll
     for (int t = 0; t < NTL; ++t) { const uint32_t col = (w1 + NW * t) * 16 + m16_col(lane); c1v[t] = a.cQ[col < a.d_emb ? col : 0u]; }
 #pragma unroll
-    for (int i = 0; i < U2; ++i) request2(decode2((uint32_t)i < nu2 ? i : 0u), o2[i]);   // (an idle wave: head 0, tile 0)
+    for (int i = 0; i < U2; ++i) request2(decode2((uint32_t)i), o2[i]);
   };
 
   // the first tile
@@ -1343,7 +1350,7 @@ void layer_body(const LayerArgs& a, const uint32_t* __restrict__ rows, const uin
   if constexpr (!ROOTS) {
     if (lane == 0) s_sum[wave] = gathered;
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (wave == 0u && lane == 0u) {                           // (threadIdx.x would be held, or spilled, through the tile loop)
       uint32_t tot = 0;
 #pragma unroll
       for (int w = 0; w < NW; ++w) tot += s_sum[w];

@@ -118,3 +118,22 @@ def test_cached_rows_of_every_head_width(heads, dk, kw):
     for l, ref in enumerate(o.embed_all(), 1):
         assert rows_close(g.get_embeddings(np.arange(w.num_nodes, dtype=np.uint32), layer=l), ref).all(), l
     g.close()
+
+
+@pytest.mark.parametrize("k", [1, 2, 7, 31, 33, 64, 100])
+def test_rings_of_every_length_wrap(k):
+    """Rows whose degrees run from nothing to many times k: a ring's newest slot is the degree's remainder."""
+    from paper_2603_21090_amd import binding
+    w = tiny_workload(num_nodes=90, num_edges=120 * max(k, 10), batch=60 * max(k, 10), zipf_s=1.2, d_edge=9, d_time=20, d_emb=20, k=k)
+    W, st = synth.make_weights(w), synth.EdgeStream(w)
+    o, g = orc.Oracle.from_workload(w, W, None), binding.StreamTGN.from_workload(w, W, None)
+    degree = np.bincount(np.concatenate([st.src[:w.num_edges], st.dst[:w.num_edges]]), minlength=w.num_nodes)
+    assert (degree > 7 * k).any() and (degree % k != 0).any() or k == 1
+    for i in range(w.num_batches):
+        assert o.ingest(*st.batch(i))[0] == 0
+        g.ingest_batch(*st.batch(i))
+    ref = o.embed_all()
+    for l in range(1, w.layers + 1):
+        close = rows_close(g.get_embeddings(np.arange(w.num_nodes, dtype=np.uint32), layer=l), ref[l - 1])
+        assert close.all(), f"layer {l}: rows {np.nonzero(~close)[0][:8]}"
+    g.close()

@@ -91,3 +91,15 @@ def test_nothing_but_spilled_registers_lies_in_scratch_memory(notes):
     groups was, once per chunk, with raw edge rows)."""
     for name, (spilled, _, scratch) in notes.items():
         assert spilled or not scratch, (name, scratch)
+
+
+def test_variants_of_long_lists(notes):
+    """Kernels of 32-row tiles: nothing spilled without the query cache.  With it, where a tile holds the next one's rows through its last
+    two phases, a pair of registers in the widest models of two slots and up to four registers with four slots, reloaded once a tile;
+    none of them a constant of a division, whose reload waited for the weights requested ahead of it."""
+    name = re.compile(r"layer32_kernelILi(\d)ELi(\d)ELi(\d)ELi(\d)ELb(\d)E")
+    tall = {tuple(map(int, m.groups())): n for key, (n, _, _) in notes.items() if (m := name.search(key))}
+    assert {(v[0], v[4]) for v in tall} == {(2, 0), (2, 1), (4, 0), (4, 1)}
+    for v, n in tall.items():
+        assert n <= (0 if not v[4] else 2 if v[0] == 2 else 4), v
+    assert tall[2, 2, 0, 2, 1] == 0                            # (heads of 33 to 64 floats, wide edge features: the common shape)
