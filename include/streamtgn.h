@@ -270,8 +270,8 @@ int stgn_kernel_times(stgn_ctx *ctx, int enable, int reset, uint32_t cap,
 
 /* Diagnostic, no context: one launch of a bare gather on hip_stream, for pricing the layer kernel's
  * gathers against what the memory system delivers to that access pattern alone.  table: device,
- * n_rows rows of row_bytes (256 or 1024: a raw edge row, a cached key|value row of two slots per
- * half) each, 256-byte aligned; idx: device, n_groups * per_group row numbers < n_rows (not
+ * n_rows rows of row_bytes (256 or 1024: a raw edge row, the stride of an edge's cached key|value
+ * row of two slots per half) each, 256-byte aligned; idx: device, n_groups * per_group row numbers < n_rows (not
  * checked: the caller's); every group of 16 lanes sums its per_group rows, one row in flight, and
  * writes 16 floats to out (device, n_groups * 16 floats).  Asynchronous; the caller times it.
  * STGN_E_INVALID_ARG for a NULL pointer, another row size or an empty launch. */

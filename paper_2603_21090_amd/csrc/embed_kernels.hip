@@ -141,7 +141,7 @@ void go_heads(LaunchArgs& a) {
 
 }  // namespace
 
-// heads in {1, 2, 4}; every head takes whole 64-float slots of a cached row, at most four in total;
+// heads in {1, 2, 4}; every head takes whole slots of 64 floats in the kernels, at most four in total;
 // the time encoding takes at most two
 int attn_supported(uint32_t d_emb, uint32_t d_time, uint32_t heads) {
   if (!(heads == 1 || heads == 2 || heads == 4) || d_emb == 0 || d_emb % heads) return 0;

@@ -23,14 +23,15 @@
 // Weights stream from L2 (group-major packing, see mfma16.h), each phase's requested ahead of its barrier; several
 // workgroups per CU overlap one's gather with another's products.
 //
-// The products of phases 1, 2, 4, 5 and 6 are fp32 matrix instructions, which keep the matrix pipes busy for 28 to 40 % of
+// The products of phases 1, 2, 4, 5 and 6 are fp32 matrix instructions, which keep the matrix pipes busy for 26 to 43 % of
 // a launch.  Operands split into two f16 under one power-of-two scale per row and per matrix took a fifth of those cycles
 // and 12 to 24 % off a launch, but an f16 pair holds 22 bits, and those only within 2^27 of the scale's bound: a large
 // feature with small weights in a row of ordinary ones cost its other columns their bits (queries 4e-5 off with one
-// feature of 1.7e9).  So the operands stay in 32 bits.  Layer launches, with a 16-lane group per row and with the present kernel: 1,000,000 nodes,
-// d_edge 100, 1,082 -> 1,003 us and (query cache) 1,052 -> 924; 1,300,000 nodes, raw edge rows, k = 20, 1,048 -> 952; 100,000
-// nodes, d_edge 172, 190 -> 180 and 204 -> 188; a rebuild of 200,000 nodes 662 + 429 -> 585 + 396.  Whole tables
-// lie 1e-7 to 2.9e-7 (2-norm) and up to 2.6e-6 of the root mean square (largest) off 64-bit results.
+// feature of 1.7e9).  So the operands stay in 32 bits.  Layer launches, with a 16-lane group per row and with one per key
+// slot (tiles of sixteen rows; for tiles of 32 see layer32_kernel): 1,000,000 nodes, d_edge 100, 1,082 -> 1,003 us and (query
+// cache) 1,052 -> 924; 1,300,000 nodes, raw edge rows, k = 20, 1,048 -> 952; 100,000 nodes, d_edge 172, 190 -> 180 and 204 ->
+// 188; a rebuild of 200,000 nodes 662 + 429 -> 585 + 396.  Whole tables lie 1e-7 to 2.9e-7 (2-norm) and up to 2.6e-6 of the
+// root mean square (largest) off 64-bit results.
 #pragma once
 #include <algorithm>
 #include <mutex>
@@ -1375,7 +1376,8 @@ void layer_kernel(LayerArgs a, const uint32_t* __restrict__ rows, const uint32_t
 // 190 KB), passes its barriers once and waits once for each phase's requests: 39 K cycles a tile of sixteen rows, half of
 // them such waits.  With two row tiles each weight register meets both, the waits are shared by twice the rows, and a
 // wave serves its four rows in two passes (four slots: four), a pass's first gather in flight through the end of the one before.
-// Layer launches of 1,000,000 nodes (mean of both layers) 922 -> 847 us.  Whole batches: 1,000,000 nodes, d_edge 100, 2,146 ->
+// Layer launches of 1,000,000 nodes (mean of both layers) 922 -> 847 us (794 with compact cached rows and without the products
+// of zero weights; first layer, last layer, of 200,000 rebuilt nodes 585, 396 -> 481, 332).  Whole batches: 1,000,000 nodes, d_edge 100, 2,146 ->
 // 2,001 us; 1,300,000 nodes, raw edge rows, k = 20, 1,292 -> 1,220; 200,000 nodes rebuilt 1,152 -> 1,093; 100,000 nodes,
 // five to six tiles a workgroup, 446 -> 444.  Where a workgroup has a tile or two, the longer tile loses more than it
 // shares: 10,000 nodes 113 -> 130 us, 20,000 nodes 188 -> 195, 30,000 nodes 252 -> 248, hence the line at kShortTiles.
